@@ -90,13 +90,14 @@ parle_status parle_k_conv_backward_data(void *hip_stream, const parle_conv_desc 
                ? PARLE_OK
                : PARLE_EHIP;
   }
-  if (launch_weight_transpose(st, desc->dtype, desc->n, c.Cout, c.R * c.R, c.Cin, w, wsize, wt_scratch, wsize) !=
-      hipSuccess)
-    return PARLE_EHIP;
   const ConvGeom g = conv_bwd_geom(c);
   GemmIO io{};
+  io.w_kn = fc_f32_applicable(desc->dtype, desc->n, g);
+  if (!io.w_kn && launch_weight_transpose(st, desc->dtype, desc->n, c.Cout, c.R * c.R, c.Cin, w, wsize, wt_scratch, wsize) !=
+                      hipSuccess)
+    return PARLE_EHIP;
   io.in = dy, io.in_rs = (long long)c.B * c.Ho() * c.Wo() * c.Cout;
-  io.w = wt_scratch, io.w_rs = wsize;
+  io.w = io.w_kn ? w : wt_scratch, io.w_rs = wsize;
   io.out = dx, io.out_rs = (long long)g.M * g.N, io.ldc = g.N;
   io.mask = relu_mask, io.mask_rs = io.out_rs;
   io.accumulate = accumulate;

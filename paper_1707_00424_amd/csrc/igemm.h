@@ -59,6 +59,7 @@ struct GemmIO {
   const void *mask;   // [M][ldc]: result multiplied by (mask > 0), or NULL
   long long mask_rs;
   int relu, accumulate;
+  int w_kn;           // `w` lies as [K][N] (a layer's weights read for its input gradient); only launch_fc_f32 takes it
   int vecA, vecB;     // 16-byte loads allowed for the gathered operand / the weight matrix
   long long in_bytes; // bytes of one replica's gathered tensor (range of the buffer loads)
   // The gathered tensor lies in memory as fp32 although the layer computes in bf16 (the caller's images in front of a
@@ -151,9 +152,14 @@ hipError_t launch_wgrad_smallk(hipStream_t st, int replicas, const ConvGeom &g, 
 bool wgrad9_applicable(int dtype, const ConvGeom &g);
 int wgrad9_plan(int replicas, const ConvGeom &g, int *chunk_out);
 hipError_t launch_wgrad9(hipStream_t st, int replicas, const ConvGeom &g, const WgradIO &io);
-// Plain products with few output tiles: the contraction split over the wavefronts of a workgroup (igemm_ksplit.hip).
+// bf16 plain products with few output tiles: the contraction split over the wavefronts of a workgroup (igemm_ksplit.hip).
 bool gemm_ksplit_applicable(int dtype, int replicas, const ConvGeom &g, const GemmIO &io);
 hipError_t launch_gemm_ksplit(hipStream_t st, int dtype, bool out_f32, int replicas, const ConvGeom &g, const GemmIO &io);
+// The same in fp32, all three products of a layer, weights read as they lie (igemm_fc.hip).
+bool fc_f32_applicable(int dtype, int replicas, const ConvGeom &g);
+hipError_t launch_fc_f32(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io);
+bool wgrad_fc_f32_applicable(int dtype, const ConvGeom &g);
+hipError_t launch_wgrad_fc_f32(hipStream_t st, int replicas, const ConvGeom &g, const WgradIO &io);
 // fp32 backward-weight with at most 32 output channels and a window of at most 32 values (igemm_ksplit.hip).
 bool wgrad_small_f32_applicable(int dtype, const ConvGeom &g);
 // True when launch_wgrad would run a kernel that honours WgradIO::with_bias for this layer and these operands

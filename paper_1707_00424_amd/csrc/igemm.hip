@@ -406,6 +406,8 @@ hipError_t launch_igemm(hipStream_t st, int dtype, bool out_f32, int replicas, c
                         int *stat_splits) {
   if (g.M < 1 || g.N < 1 || g.K < 1 || replicas < 1 || replicas > 65535) return hipErrorInvalidValue;
   if (stat_splits) *stat_splits = 0;
+  if (io_in.w_kn && !fc_f32_applicable(dtype, replicas, g)) return hipErrorInvalidValue;
+  if (fc_f32_applicable(dtype, replicas, g)) return launch_fc_f32(st, replicas, g, io_in);
   if (io_in.stat && stat_splits) {
     // the same order of choices as below, for the kernels whose epilogue can take the sums
     int S = 0;
@@ -447,6 +449,7 @@ hipError_t launch_wgrad(hipStream_t st, int dtype, int replicas, const ConvGeom 
   if (wgrad_smallk_applicable(dtype, g) && aligned_to(io.dy, 16)) return launch_wgrad_smallk(st, replicas, g, io);
   if (io.x_f32) return hipErrorInvalidValue;  // only the kernel above reads fp32 memory for a bf16 layer
   if (wgrad_small_f32_applicable(dtype, g)) return launch_wgrad_small_f32(st, replicas, g, io);
+  if (wgrad_fc_f32_applicable(dtype, g)) return launch_wgrad_fc_f32(st, replicas, g, io);
   if (wgrad_window_applicable(dtype, g)) return launch_wgrad_window(st, replicas, g, io);
   if (wgrad9_applicable(dtype, g) && io.pairA && io.pairB) return launch_wgrad9(st, replicas, g, io);
   if (wgrad_fast_applicable(dtype, g) && io.pairA && io.pairB) return launch_wgrad_fast(st, replicas, g, io);
@@ -464,7 +467,7 @@ bool wgrad_takes_bias(int dtype, const ConvGeom &g, const WgradIO &io) {
   if (wgrad_smallk_applicable(dtype, g) && aligned_to(io.dy, 16)) return g.K < 32;
   if (wgrad_small_f32_applicable(dtype, g)) return g.K < 32;
   if (wgrad_window_applicable(dtype, g)) return false;
-  if (dtype == 0) return true;  // the generic fp32 kernel
+  if (dtype == 0) return true;  // the fully connected and the generic fp32 kernel
   return (wgrad9_applicable(dtype, g) || wgrad_fast_applicable(dtype, g)) && io.pairA && io.pairB;
 }
 
@@ -472,6 +475,10 @@ int wgrad_plan(int dtype, int replicas, const ConvGeom &g, int *chunk_out) {
   if (wgrad9_applicable(dtype, g)) return wgrad9_plan(replicas, g, chunk_out);
   if (!wgrad_smallk_applicable(dtype, g) && !wgrad_small_f32_applicable(dtype, g) && wgrad_window_applicable(dtype, g))
     return wgrad_window_plan(replicas, g, chunk_out);
+  if (!wgrad_small_f32_applicable(dtype, g) && wgrad_fc_f32_applicable(dtype, g)) {
+    if (chunk_out) *chunk_out = (g.M + 31) / 32 * 32;
+    return 1;
+  }
   int bm, bn;
   if (wgrad_smallk_applicable(dtype, g)) {
     bm = 128, bn = 32;

@@ -44,6 +44,7 @@ struct Op {
   int dx_after = -1;       // index of the shortcut op whose input gradient this op's accumulates onto
   int64_t wt_off = -1;     // transposed weights (bytes)
   int64_t col_off = -1;    // per-tap products of the two-pass backward-data (bytes), -1 = direct kernel
+  bool w_as_is = false;    // backward-data by the fully connected kernel, which reads the weights as they lie
   bool win = false;        // backward-data through per-tap products held in LDS, one image per workgroup
   // pool
   bool pool_relu_mask = false;
@@ -351,7 +352,9 @@ bool build_plan(Net &N, std::string &err) {
       const int64_t wsize = (int64_t)op.Cout * op.R * op.R * op.Cin;
       if (op.need_dx) {
         N.want_grad(op.in);
-        if (!op.head) op.wt_off = N.alloc((int64_t)N.n * wsize * N.esize);  // the head kernel reads the weights as they lie
+        op.w_as_is = fc_f32_applicable(
+            N.dtype, N.n, conv_bwd_geom(ConvShape{N.B, op.Hin, op.Win, op.Cin, op.Cout, op.R, op.stride, op.pad}));
+        if (!op.head && !op.w_as_is) op.wt_off = N.alloc((int64_t)N.n * wsize * N.esize);  // the head kernel reads the weights as they lie
         // few input channels under a wide window (LeNet's second convolution: 20 channels, 25 taps): as a
         // direct implicit GEMM the pass has 20 output columns on 32-wide fp32 MFMA tiles and a contraction
         // of 1250; as dy x W (500 columns, contraction 50) plus a gather over the window it is a fraction
@@ -405,7 +408,7 @@ bool build_plan(Net &N, std::string &err) {
   for (int vec = 1; vec >= 0; --vec) {
     bool open = false;
     for (const Op &op : N.ops) {
-      if (op.type != OP_CONV || !op.need_dx || op.head || op.win) continue;  // these read the weights as they lie
+      if (op.type != OP_CONV || !op.need_dx || op.head || op.win || op.w_as_is) continue;  // these read the weights as they lie
       if ((int)transpose_vector_ok(N.dtype, op.Cout, op.Cin, N.segs[op.wseg].offset) != vec) continue;
       if (!open || N.transposes.back().count == TransposeTable::kMax) {
         N.transposes.emplace_back();
@@ -611,6 +614,7 @@ hipError_t backward(const Run &r, float *grad) {
     GemmIO io{};
     io.in = dy, io.in_rs = dy_rs;
     io.w = r.ws + op.wt_off, io.w_rs = wsize;  // transposed once per step, all layers in one launch
+    if (op.w_as_is) io.w = r.wptr(op.wseg), io.w_rs = r.p_rs, io.w_kn = 1;
     io.out = r.gptr(op.in), io.out_rs = r.trs(op.in), io.ldc = op.Cin;
     io.mask = op.mask_in ? r.tptr(op.in) : nullptr, io.mask_rs = r.trs(op.in);
     io.accumulate = op.dx_accumulate;
