@@ -842,6 +842,11 @@ Net *net_create(const parle_config &cfg, const Arch &a, const std::vector<Segmen
     delete N;
     return nullptr;
   }
+  // A network whose whole forward pass is less than half a GFLOP is bound by the host's launches: a second stream hides
+  // a few microseconds of kernels and costs ten event calls per step.  One stream against two, us per step: MLP with
+  // three replicas (0.08 GFLOP) 33 / 74, LeNet with one replica of 16 (0.07) 140 / 155, of 64 (0.28) 153 / 155, of 128
+  // (0.56) 175 / 170, six of 128 (3.4) 376 / 344.
+  N->overlap = net_forward_flops_per_image(N) * N->n * N->B >= 500000000LL;
   if (const char *e = getenv("PARLE_OVERLAP_WGRAD")) N->overlap = atoi(e) != 0;
   return N;
 }
