@@ -128,7 +128,7 @@ parle_status backward_weight(void *hip_stream, const parle_conv_desc *desc, cons
   io.splits = S, io.chunk = chunk;
   io.pairA = (c.Cout % 2 == 0);
   io.pairB = (c.Cin % 2 == 0);
-  io.with_bias = took_bias_host && wgrad_takes_bias(desc->dtype, g, io);
+  io.with_bias = took_bias_host && wgrad_takes_bias(desc->dtype, desc->n, g, io, false);
   if (took_bias_host) *took_bias_host = io.with_bias;
   // values a kernel writes per (replica, split), and the caller's row: the bias slots exist in dw whenever the caller
   // asked for this form, and are written only by a kernel that takes the bias along

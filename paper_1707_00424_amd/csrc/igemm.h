@@ -155,7 +155,14 @@ hipError_t launch_wgrad9(hipStream_t st, int replicas, const ConvGeom &g, const 
 // bf16 plain products with few output tiles: the contraction split over the wavefronts of a workgroup (igemm_ksplit.hip).
 bool gemm_ksplit_applicable(int dtype, int replicas, const ConvGeom &g, const GemmIO &io);
 hipError_t launch_gemm_ksplit(hipStream_t st, int dtype, bool out_f32, int replicas, const ConvGeom &g, const GemmIO &io);
-// The same in fp32, all three products of a layer, weights read as they lie (igemm_fc.hip).
+// fp32 convolutions as six products of bf16 parts, at fp32 accuracy (igemm_f32.hip).
+bool conv_f32x3_applicable(int dtype, int replicas, const ConvGeom &g, const GemmIO &io);
+hipError_t launch_conv_f32x3(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io);
+// ... and their weight gradients, window 3 x 3 or larger (igemm_f32_wgrad.hip).
+bool wgrad_f32x3_applicable(int dtype, int replicas, const ConvGeom &g);
+int wgrad_f32x3_plan(int replicas, const ConvGeom &g, int *chunk_out);
+hipError_t launch_wgrad_f32x3(hipStream_t st, int replicas, const ConvGeom &g, const WgradIO &io);
+// fp32 plain products with few output tiles, all three products of a layer, weights read as they lie (igemm_fc.hip).
 bool fc_f32_applicable(int dtype, int replicas, const ConvGeom &g);
 hipError_t launch_fc_f32(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io);
 bool wgrad_fc_f32_applicable(int dtype, const ConvGeom &g);
@@ -165,7 +172,9 @@ bool wgrad_small_f32_applicable(int dtype, const ConvGeom &g);
 // True when launch_wgrad would run a kernel that honours WgradIO::with_bias for this layer and these operands
 // (io.dy, io.pairA, io.pairB set): the small-window kernels when the window leaves one of their 32 contraction
 // columns unused, the stride-1 3x3 kernel, the transpose-read kernel and the generic fp32 kernel.
-bool wgrad_takes_bias(int dtype, const ConvGeom &g, const WgradIO &io);
+// `per_image`: layers whose images the per-image LDS kernel could take (few channels under a wide window) leave the bias
+// to the caller at the entry point, whatever kernel runs them; the networks pass true and have it taken along.
+bool wgrad_takes_bias(int dtype, int replicas, const ConvGeom &g, const WgradIO &io, bool per_image);
 hipError_t launch_wgrad_small_f32(hipStream_t st, int replicas, const ConvGeom &g, const WgradIO &io);
 // Backward-data of stride-2 3x3 pad-1 layers, four parity classes per workgroup (igemm_dgrad2.hip).
 bool dgrad_s2_applicable(int dtype, const ConvGeom &g, const GemmIO &io, bool out_f32);

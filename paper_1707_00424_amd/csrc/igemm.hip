@@ -413,7 +413,7 @@ hipError_t launch_igemm(hipStream_t st, int dtype, bool out_f32, int replicas, c
     int S = 0;
     const bool smallk = conv_smallk_applicable(dtype, g, io_in);
     const bool halo = !smallk && conv_halo_applicable(dtype, g, io_in, out_f32);
-    const bool fast = !smallk && !halo && !dgrad_s2_applicable(dtype, g, io_in, out_f32) &&
+    const bool fast = !smallk && !halo && !conv_f32x3_applicable(dtype, replicas, g, io_in) && !dgrad_s2_applicable(dtype, g, io_in, out_f32) &&
                       !gemm_ksplit_applicable(dtype, replicas, g, io_in) && igemm_fast_applicable(dtype, g, io_in);
     if (smallk) S = conv_smallk_stat_splits(g, out_f32);
     if (halo) S = conv_halo_stat_splits(g, replicas);
@@ -430,6 +430,7 @@ hipError_t launch_igemm(hipStream_t st, int dtype, bool out_f32, int replicas, c
   if (io.in_f32 && !(dtype == 1 && !out_f32 && conv_smallk_applicable(dtype, g, io))) return hipErrorInvalidValue;
   if (conv_smallk_applicable(dtype, g, io)) return launch_conv_smallk(st, dtype, out_f32, replicas, g, io);
   if (conv_halo_applicable(dtype, g, io, out_f32)) return launch_conv_halo(st, replicas, g, io);
+  if (conv_f32x3_applicable(dtype, replicas, g, io)) return launch_conv_f32x3(st, replicas, g, io);
   if (dgrad_s2_applicable(dtype, g, io, out_f32)) return launch_dgrad_s2(st, replicas, g, io);
   if (gemm_ksplit_applicable(dtype, replicas, g, io)) return launch_gemm_ksplit(st, dtype, out_f32, replicas, g, io);
   if (igemm_fast_applicable(dtype, g, io)) return launch_igemm_fast(st, dtype, out_f32, replicas, g, io);
@@ -450,6 +451,7 @@ hipError_t launch_wgrad(hipStream_t st, int dtype, int replicas, const ConvGeom 
   if (io.x_f32) return hipErrorInvalidValue;  // only the kernel above reads fp32 memory for a bf16 layer
   if (wgrad_small_f32_applicable(dtype, g)) return launch_wgrad_small_f32(st, replicas, g, io);
   if (wgrad_fc_f32_applicable(dtype, g)) return launch_wgrad_fc_f32(st, replicas, g, io);
+  if (wgrad_f32x3_applicable(dtype, replicas, g)) return launch_wgrad_f32x3(st, replicas, g, io);
   if (wgrad_window_applicable(dtype, g)) return launch_wgrad_window(st, replicas, g, io);
   if (wgrad9_applicable(dtype, g) && io.pairA && io.pairB) return launch_wgrad9(st, replicas, g, io);
   if (wgrad_fast_applicable(dtype, g) && io.pairA && io.pairB) return launch_wgrad_fast(st, replicas, g, io);
@@ -463,16 +465,18 @@ hipError_t launch_wgrad(hipStream_t st, int dtype, int replicas, const ConvGeom 
 }
 
 // mirrors the order of launch_wgrad
-bool wgrad_takes_bias(int dtype, const ConvGeom &g, const WgradIO &io) {
+bool wgrad_takes_bias(int dtype, int replicas, const ConvGeom &g, const WgradIO &io, bool per_image) {
   if (wgrad_smallk_applicable(dtype, g) && aligned_to(io.dy, 16)) return g.K < 32;
   if (wgrad_small_f32_applicable(dtype, g)) return g.K < 32;
-  if (wgrad_window_applicable(dtype, g)) return false;
+  if (wgrad_window_applicable(dtype, g)) return per_image && wgrad_f32x3_applicable(dtype, replicas, g);
   if (dtype == 0) return true;  // the fully connected and the generic fp32 kernel
   return (wgrad9_applicable(dtype, g) || wgrad_fast_applicable(dtype, g)) && io.pairA && io.pairB;
 }
 
 int wgrad_plan(int dtype, int replicas, const ConvGeom &g, int *chunk_out) {
   if (wgrad9_applicable(dtype, g)) return wgrad9_plan(replicas, g, chunk_out);
+  if (!wgrad_small_f32_applicable(dtype, g) && wgrad_f32x3_applicable(dtype, replicas, g))
+    return wgrad_f32x3_plan(replicas, g, chunk_out);
   if (!wgrad_smallk_applicable(dtype, g) && !wgrad_small_f32_applicable(dtype, g) && wgrad_window_applicable(dtype, g))
     return wgrad_window_plan(replicas, g, chunk_out);
   if (!wgrad_small_f32_applicable(dtype, g) && wgrad_fc_f32_applicable(dtype, g)) {

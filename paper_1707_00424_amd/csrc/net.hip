@@ -692,7 +692,7 @@ hipError_t backward(const Run &r, float *grad) {
         io.pairA = (op.Cout % 2 == 0) && aligned_to(dy, 4);
         io.pairB = (op.Cin % 2 == 0) && aligned_to(io.x, 4);
         io.x_f32 = r.images_direct && op.in == N.t_images;
-        const bool bias_in_wgrad = op.bseg >= 0 && N.bias_in_wgrad && wgrad_takes_bias(N.dtype, gf, io) &&
+        const bool bias_in_wgrad = op.bseg >= 0 && N.bias_in_wgrad && wgrad_takes_bias(N.dtype, r.n, gf, io, true) &&
                                    N.segs[op.bseg].offset == N.segs[op.wseg].offset + N.segs[op.wseg].size;
         if (op.bseg >= 0 && !bias_in_wgrad) {
           hipStream_t bst = lst;
