@@ -766,7 +766,11 @@ __global__ __launch_bounds__(kThreads) void k_gap_bwd_vec(long long total, int H
   }
 }
 
-template <typename T>
+// The two element-wise passes of a batch-norm on 16-byte vectors.  Bound by memory; the per-channel values are 4 (6 in the
+// backward pass) floats per element against 2 to 8 bytes of data, so loaded per vector they are most of what passes
+// through L1.  The grid's stride is a multiple of the row (see bn_grid): a thread keeps its channels, their values stay in
+// registers, and two vectors are in flight.  RUNNING: `saved` holds running means and variances (evaluation).
+template <typename T, bool RUNNING>
 __global__ __launch_bounds__(kThreads) void k_bn_apply_relu_vec(int M, int C, const T *__restrict__ x, long long x_rs,
                                                                 const float *__restrict__ gamma,
                                                                 const float *__restrict__ beta, long long p_rs,
@@ -775,21 +779,35 @@ __global__ __launch_bounds__(kThreads) void k_bn_apply_relu_vec(int M, int C, co
   constexpr int VW = 16 / sizeof(T);
   const int rep = blockIdx.y;
   const int CV = C / VW;
-  const long long total = (long long)M * CV;
+  const long long total = (long long)M * CV, stride = (long long)gridDim.x * kThreads;
+  const long long first = (long long)blockIdx.x * kThreads + threadIdx.x;
+  if (first >= total) return;
   const T *xp = x + rep * x_rs;
   T *op = out + rep * out_rs;
-  const float *mean = saved + (long long)rep * 2 * C, *rstd = mean + C;
-  const float *gm = gamma + rep * p_rs, *bt = beta + rep * p_rs;
-  for (long long i = (long long)blockIdx.x * kThreads + threadIdx.x; i < total; i += (long long)gridDim.x * kThreads) {
-    const int c0 = (int)(i % CV) * VW;
+  const int c0 = (int)(first % CV) * VW;
+  const float *mean = saved + (long long)rep * 2 * C + c0, *var = mean + C;
+  const float *gm = gamma + rep * p_rs + c0, *bt = beta + rep * p_rs + c0;
+  float mu[VW], rs[VW], g[VW], b[VW];
+#pragma unroll
+  for (int e = 0; e < VW; ++e) {
+    mu[e] = mean[e], g[e] = gm[e], b[e] = bt[e];
+    rs[e] = RUNNING ? 1.0f / sqrtf(var[e] + kBnEps) : var[e];
+  }
+  auto apply = [&](const u4e &v, long long i) {
     float xv[VW], ov[VW];
-    unpack16<T>(*(const u4e *)(xp + i * VW), xv);
+    unpack16<T>(v, xv);
 #pragma unroll
     for (int e = 0; e < VW; ++e) {
-      const float v = (xv[e] - mean[c0 + e]) * rstd[c0 + e] * gm[c0 + e] + bt[c0 + e];
-      ov[e] = v > 0.f ? v : 0.f;
+      const float t = (xv[e] - mu[e]) * rs[e] * g[e] + b[e];
+      ov[e] = t > 0.f ? t : 0.f;
     }
     *(u4e *)(op + i * VW) = pack16<T>(ov);
+  };
+  for (long long i = first; i < total; i += 2 * stride) {
+    const bool two = i + stride < total;
+    const u4e v0 = *(const u4e *)(xp + i * VW), v1 = *(const u4e *)(xp + (two ? i + stride : i) * VW);
+    apply(v0, i);
+    if (two) apply(v1, i + stride);
   }
 }
 
@@ -804,31 +822,45 @@ __global__ __launch_bounds__(kThreads) void k_bn_bwd_apply_vec(int M, int C, con
   constexpr int VW = 16 / sizeof(T);
   const int rep = blockIdx.y;
   const int CV = C / VW;
-  const long long total = (long long)M * CV;
+  const long long total = (long long)M * CV, stride = (long long)gridDim.x * kThreads;
+  const long long first = (long long)blockIdx.x * kThreads + threadIdx.x;
+  if (first >= total) return;
   const T *xp = x + rep * x_rs;
   const T *dp = dout + rep * dout_rs;
   const T *ap = add ? add + rep * add_rs : nullptr;
   T *op = dx + rep * dx_rs;
-  const float *mean = saved + (long long)rep * 2 * C, *rstd = mean + C;
-  const float *s1 = sums + (long long)rep * 2 * C, *s2 = s1 + C;
-  const float *gm = gamma + rep * p_rs, *bt = beta + rep * p_rs;
+  const int c0 = (int)(first % CV) * VW;
+  const float *mean = saved + (long long)rep * 2 * C + c0, *rstd = mean + C;
+  const float *s1 = sums + (long long)rep * 2 * C + c0, *s2 = s1 + C;
+  const float *gm = gamma + rep * p_rs + c0, *bt = beta + rep * p_rs + c0;
   const float invM = 1.0f / (float)M;
-  for (long long i = (long long)blockIdx.x * kThreads + threadIdx.x; i < total; i += (long long)gridDim.x * kThreads) {
-    const int c0 = (int)(i % CV) * VW;
+  float mu[VW], rs[VW], g[VW], b[VW], m1[VW], m2[VW];
+#pragma unroll
+  for (int e = 0; e < VW; ++e) mu[e] = mean[e], rs[e] = rstd[e], g[e] = gm[e], b[e] = bt[e], m1[e] = s1[e] * invM, m2[e] = s2[e];
+  auto apply = [&](const u4e &x4, const u4e &d4, const u4e &a4, long long i) {
     float xv[VW], dv[VW], av[VW], ov[VW];
-    unpack16<T>(*(const u4e *)(xp + i * VW), xv);
-    unpack16<T>(*(const u4e *)(dp + i * VW), dv);
-    if (ap) unpack16<T>(*(const u4e *)(ap + i * VW), av);
+    unpack16<T>(x4, xv);
+    unpack16<T>(d4, dv);
+    if (ap) unpack16<T>(a4, av);
 #pragma unroll
     for (int e = 0; e < VW; ++e) {
-      const int c = c0 + e;
-      const float xh = (xv[e] - mean[c]) * rstd[c];
-      const float d = (xh * gm[c] + bt[c]) > 0.f ? dv[e] : 0.f;
-      float v = gm[c] * rstd[c] * (d - s1[c] * invM - xh * s2[c] * invM);
+      const float xh = (xv[e] - mu[e]) * rs[e];
+      const float d = (xh * g[e] + b[e]) > 0.f ? dv[e] : 0.f;
+      float v = g[e] * rs[e] * (d - m1[e] - xh * m2[e] * invM);
       if (ap) v += av[e];
       ov[e] = v;
     }
     *(u4e *)(op + i * VW) = pack16<T>(ov);
+  };
+  for (long long i = first; i < total; i += 2 * stride) {
+    const bool two = i + stride < total;
+    const long long i1 = two ? i + stride : i;
+    const u4e x0 = *(const u4e *)(xp + i * VW), x1 = *(const u4e *)(xp + i1 * VW);
+    const u4e d0 = *(const u4e *)(dp + i * VW), d1 = *(const u4e *)(dp + i1 * VW);
+    u4e a0 = {0, 0, 0, 0}, a1 = a0;
+    if (ap) a0 = *(const u4e *)(ap + i * VW), a1 = *(const u4e *)(ap + i1 * VW);
+    apply(x0, d0, a0, i);
+    if (two) apply(x1, d1, a1, i1);
   }
 }
 
@@ -878,8 +910,17 @@ __global__ __launch_bounds__(kThreads) void k_reduce_partials(int S, long long l
                                                               float *__restrict__ out, long long out_rs) {
   const int rep = blockIdx.y;
   for (long long i = (long long)blockIdx.x * kThreads + threadIdx.x; i < len; i += (long long)gridDim.x * kThreads) {
+    const float *src = partial + (long long)rep * S * len + i;
     float s = 0.f;
-    for (int sp = 0; sp < S; ++sp) s += partial[((long long)rep * S + sp) * len + i];
+    int sp = 0;
+    for (; sp + 8 <= S; sp += 8) {  // eight loads in flight, added in order
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = __builtin_nontemporal_load(src + (long long)(sp + u) * len);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) s += v[u];
+    }
+    for (; sp < S; ++sp) s += __builtin_nontemporal_load(src + (long long)sp * len);
     out[rep * out_rs + i] = s;
   }
 }
@@ -1343,6 +1384,22 @@ hipError_t launch_reduce_partials(hipStream_t st, int n, int S, long long len, c
   return hipGetLastError();
 }
 
+// Grid of the vector passes: a multiple of the row length in threads, so that a thread keeps its channels; up to four
+// vectors per thread where that leaves eight workgroups per compute unit.
+static dim3 bn_grid(int n, int M, int cv) {
+  const long long vectors = (long long)M * cv;
+  int per = 4;
+  while (per > 1 && vectors * n / per / kThreads < 8 * 256) per >>= 1;
+  int a = cv, b = kThreads;
+  while (b) {
+    const int t = a % b;
+    a = b, b = t;
+  }
+  const int unit = cv / a;  // workgroups after which the channels repeat
+  const int blocks = blocks_for((vectors + per - 1) / per, 8192);
+  return dim3((blocks + unit - 1) / unit * unit, n);
+}
+
 hipError_t launch_bn_train_fwd(hipStream_t st, int dtype, int n, int M, int C, const void *x, long long x_rs,
                                const float *gamma, const float *beta, long long p_rs, double *partial, int pre_splits,
                                float *saved, float *running, long long run_rs, void *out, long long out_rs) {
@@ -1361,11 +1418,11 @@ hipError_t launch_bn_train_fwd(hipStream_t st, int dtype, int n, int M, int C, c
                      run_rs);
   const int vw = dtype ? 8 : 4;
   if (C % vw == 0 && x_rs % vw == 0 && out_rs % vw == 0 && aligned_to(x, 16) && aligned_to(out, 16)) {
-    dim3 vgrid(blocks_for((long long)M * (C / vw), 8192), n);
+    const dim3 vgrid = bn_grid(n, M, C / vw);
     DISPATCH_T(dtype,
-               hipLaunchKernelGGL(k_bn_apply_relu_vec<float>, vgrid, dim3(kThreads), 0, st, M, C, (const float *)x, x_rs,
-                                  gamma, beta, p_rs, saved, (float *)out, out_rs),
-               hipLaunchKernelGGL(k_bn_apply_relu_vec<bf16_t>, vgrid, dim3(kThreads), 0, st, M, C, (const bf16_t *)x,
+               hipLaunchKernelGGL((k_bn_apply_relu_vec<float, false>), vgrid, dim3(kThreads), 0, st, M, C, (const float *)x,
+                                  x_rs, gamma, beta, p_rs, saved, (float *)out, out_rs),
+               hipLaunchKernelGGL((k_bn_apply_relu_vec<bf16_t, false>), vgrid, dim3(kThreads), 0, st, M, C, (const bf16_t *)x,
                                   x_rs, gamma, beta, p_rs, saved, (bf16_t *)out, out_rs));
     return hipGetLastError();
   }
@@ -1380,6 +1437,16 @@ hipError_t launch_bn_train_fwd(hipStream_t st, int dtype, int n, int M, int C, c
 
 hipError_t launch_bn_eval_fwd(hipStream_t st, int dtype, int M, int C, const void *x, const float *gamma,
                               const float *beta, const float *running_row, float *saved, void *out) {
+  const int vw = dtype ? 8 : 4;
+  if (C % vw == 0 && aligned_to(x, 16) && aligned_to(out, 16)) {
+    const dim3 vgrid = bn_grid(1, M, C / vw);
+    DISPATCH_T(dtype,
+               hipLaunchKernelGGL((k_bn_apply_relu_vec<float, true>), vgrid, dim3(kThreads), 0, st, M, C, (const float *)x,
+                                  0LL, gamma, beta, 0LL, running_row, (float *)out, 0LL),
+               hipLaunchKernelGGL((k_bn_apply_relu_vec<bf16_t, true>), vgrid, dim3(kThreads), 0, st, M, C,
+                                  (const bf16_t *)x, 0LL, gamma, beta, 0LL, running_row, (bf16_t *)out, 0LL));
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_bn_eval_prepare, dim3((C + kThreads - 1) / kThreads), dim3(kThreads), 0, st, C, running_row,
                      saved);
   dim3 agrid(blocks_for((long long)M * C, 4096), 1);
@@ -1406,7 +1473,7 @@ hipError_t launch_bn_bwd(hipStream_t st, int dtype, int n, int M, int C, const v
   const int vw = dtype ? 8 : 4;
   if (C % vw == 0 && x_rs % vw == 0 && dout_rs % vw == 0 && dx_rs % vw == 0 && add_rs % vw == 0 && aligned_to(x, 16) &&
       aligned_to(dout, 16) && aligned_to(dx, 16) && aligned_to(add, 16)) {
-    dim3 vgrid(blocks_for((long long)M * (C / vw), 8192), n);
+    const dim3 vgrid = bn_grid(n, M, C / vw);
     DISPATCH_T(dtype,
                hipLaunchKernelGGL(k_bn_bwd_apply_vec<float>, vgrid, dim3(kThreads), 0, st, M, C, (const float *)x, x_rs,
                                   (const float *)dout, dout_rs, gamma, beta, p_rs, saved, sums, (const float *)add,
