@@ -1,10 +1,10 @@
-// Stride-1 "same" convolutions (forward, and backward-data of such a layer) with the input patch
+// Stride-1 convolutions (forward, and backward-data of such a layer) with the input patch
 // staged ONCE in LDS and reused by every window tap.
 //
 // Why: the vector memory path of a CU delivers 64 bytes per clock; an implicit GEMM that fetches a
 // fresh 256 x 32 operand tile from L1/L2 for each of the R*S taps moves (BM + BN) * 64 bytes per
 // contraction step through that path, which caps the MFMA units near half of their rate for
-// BN <= 128.  Here a workgroup owns 256 consecutive output pixels (whole image rows), loads the
+// BN <= 128.  Here a workgroup owns up to 256 consecutive output pixels (whole image rows), loads the
 // (rows + R - 1) x (width + S - 1) halo patch of 32 input channels once per channel chunk, and the
 // MFMA fragments of all R*S taps are read from that patch at a tap-dependent LDS offset.  Global
 // traffic per step drops to the weight tile plus 1/(R*S) of the patch.
@@ -27,16 +27,20 @@ using namespace igemm_dev;
 
 constexpr uint32_t kOob = 0x80000000u;
 constexpr int kHaloSlots = 400;    // LDS patch capacity in pixels (32 KB at 32 channels + padding)
+constexpr int kHaloSlotsHalf = 304;  // 128 output pixels at stride 1, 24 KB
 constexpr int kHaloSlotsS2 = 592;  // stride 2: 17 x 33 (16 output columns) or 2 x 17 x 17 (two 8 x 8 outputs), 47 KB
 
+// A tile is a number of whole output rows, counted through all images (row b*P + p), as many as BM pixels hold: 8 rows of
+// 32, four images of 8 x 8, 9 rows of 28.  An image that ends inside a tile adds its own halo rows to the patch.
 struct HaloGeom {
-  int TH;          // output rows of one image inside a tile
-  int nimg;        // images per tile (> 1 when an image has fewer than 256 pixels)
-  int HR, HC;      // patch rows / columns per image = TH + R - 1, Q + S - 1
-  int slots;       // nimg * HR * HC
-  int omin_h, omin_w;  // smallest tap offset (input row = output row + offset)
-  FastDiv dImg, dHC, dRows;  // by HR*HC, HC and TH*Q (no integer division on the device)
-  int tiles, nb, bn;  // pixel tiles, column blocks and their width in channels (set with the grid)
+  int TH;              // output rows per tile
+  int HC;              // patch columns = sp*(Q - 1) + S
+  int PRI;             // patch rows of a whole image = sp*(P - 1) + R
+  int slots;           // pixels of the largest patch
+  int rows;            // output rows of all images
+  int omin_h, omin_w;  // smallest tap offset (input row = sp * output row + offset)
+  FastDiv dP, dHC, dPRI;  // no integer division on the device
+  int tiles, nb, bn;   // pixel tiles, column blocks and their width in channels (set with the grid)
 };
 
 // LDS of a workgroup with TN column tiles: patch + a ring of three weight tiles; the epilogue reuses the same
@@ -64,9 +68,8 @@ __device__ __forceinline__ void conv_halo_body(const ConvGeom &g, const GemmIO &
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int rep = blockIdx.z;
-  const int m0 = tile * BM, n0 = col * hg.bn;
+  const int row0 = tile * hg.TH, m0 = row0 * g.Q, n0 = col * hg.bn;
   const int lrow = tid >> 2, lkv = tid & 3;
-  const int PQ = g.P * g.Q;
   const int RS = g.R * g.S;
   const __amdgpu_buffer_rsrc_t a_rsrc = __builtin_amdgcn_make_buffer_rsrc(
       (void *)((const T *)io.in + rep * io.in_rs), 0, (int)(io.in_bytes), 0x00020000);
@@ -74,17 +77,22 @@ __device__ __forceinline__ void conv_halo_body(const ConvGeom &g, const GemmIO &
       (void *)((const T *)io.w + rep * io.w_rs), 0, (int)((long long)g.N * g.K * sizeof(T)), 0x00020000);
 
   // patch loader: vector v = it*256 + tid covers patch pixel v/4, channels 8*(v%4) .. +7 of the chunk
-  const int b0 = (int)fdiv((uint32_t)m0, g.dPQ), p0 = (int)fdiv((uint32_t)(m0 - b0 * PQ), g.dQ);
+  const int b0 = (int)fdiv((uint32_t)row0, hg.dP), p0 = row0 - b0 * g.P;
+  const int first_rows = SP * (g.P - 1 - p0) + g.R;  // patch rows of the first image, should the tile go beyond it
   uint32_t h_off[H_IT];
 #pragma unroll
   for (int it = 0; it < H_IT; ++it) {
     const int v = it * kThreads + tid, slot = v >> 2;
     uint32_t off = kOob;
     if (slot < hg.slots) {
-      const int img = (int)fdiv((uint32_t)slot, hg.dImg), rem = slot - img * hg.HR * hg.HC;
-      const int hh = (int)fdiv((uint32_t)rem, hg.dHC), ww = rem - hh * hg.HC;
-      const int b = b0 + img, ih = SP * p0 + hh + hg.omin_h, iw = ww + hg.omin_w;
-      if ((b * PQ < g.M) && ih >= 0 && ih < g.Hin && iw >= 0 && iw < g.Win)
+      const int pr = (int)fdiv((uint32_t)slot, hg.dHC), pc = slot - pr * hg.HC;
+      int b = b0, ih = SP * p0 + pr + hg.omin_h;
+      if (pr >= first_rows) {
+        const int rest = pr - first_rows, img = (int)fdiv((uint32_t)rest, hg.dPRI);
+        b = b0 + 1 + img, ih = rest - img * hg.PRI + hg.omin_h;
+      }
+      const int iw = pc + hg.omin_w;
+      if ((b * g.P < hg.rows) && ih >= 0 && ih < g.Hin && iw >= 0 && iw < g.Win)
         off = (uint32_t)((((b * g.Hin + ih) * g.Win + iw) * g.Cc + (v & 3) * VW) * (int)sizeof(T));
     }
     h_off[it] = off;
@@ -100,9 +108,12 @@ __device__ __forceinline__ void conv_halo_body(const ConvGeom &g, const GemmIO &
 #pragma unroll
   for (int tm = 0; tm < TM; ++tm) {
     const int ml = wave * (TM * 32) + tm * 32 + (lane & 31);
-    const int img = (int)fdiv((uint32_t)ml, hg.dRows), rem = ml - img * hg.TH * g.Q;
-    const int ph = (int)fdiv((uint32_t)rem, g.dQ), pw = rem - ph * g.Q;
-    a_lds[tm] = (((img * hg.HR + SP * ph) * hg.HC + SP * pw) * LK + (lane >> 5) * VW);
+    int i = (int)fdiv((uint32_t)ml, g.dQ);
+    const int q = ml - i * g.Q;
+    i = i < hg.TH ? i : 0;  // rows beyond the tile are dropped by the epilogue
+    const int b = (int)fdiv((uint32_t)(row0 + i), hg.dP), p = row0 + i - b * g.P;
+    const int pr = b == b0 ? SP * (p - p0) : first_rows + (b - b0 - 1) * hg.PRI + SP * p;
+    a_lds[tm] = (pr * hg.HC + SP * q) * LK + (lane >> 5) * VW;
   }
   const int b_lds = (lane & 31) * LK + (lane >> 5) * VW;
 
@@ -248,7 +259,9 @@ __device__ __forceinline__ void conv_halo_body(const ConvGeom &g, const GemmIO &
     if (kt + i < KT) step(kt + i, rq[i]);
   // the barrier that ends the last step: patch and weight tiles are dead, their LDS becomes the staging strips
   float *wsums = reinterpret_cast<float *>(smem) + 4 * kStageFloats<TN>;
-  store_tile_lds<T, TM, TN, false, STAT>(g, io, rep, m0 + wave * TM * 32, n0, lane, acc,
+  ConvGeom gt = g;
+  gt.M = min(g.M, m0 + hg.TH * g.Q);  // rows beyond the tile belong to the next one
+  store_tile_lds<T, TM, TN, false, STAT>(gt, io, rep, m0 + wave * TM * 32, n0, lane, acc,
                                          reinterpret_cast<float *>(smem) + wave * kStageFloats<TN>, wsums + wave * 2 * BN);
   // the workgroup's rows: one partial row per pixel tile
   if (STAT) write_tile_sums<BN, 4>(g, io, rep, hg.tiles, tile, n0, tid, wsums);
@@ -302,41 +315,60 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     conv_halo_body<TN, STAT, 1, kHaloSlotsS2, 2>(g, io, hg, smem, tile, col);
 }
 
+// Stride 1 on 128 output pixels, for launches that 256-pixel tiles leave below two workgroups per compute unit.
+template <int TN, bool STAT>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TN == 3 ? 3 : 2))) void k_conv_halo_half(
+    const ConvGeom g, const GemmIO io, const HaloGeom hg) {
+  __shared__ __attribute__((aligned(16))) char smem[halo_lds_bytes<TN, STAT, kHaloSlotsHalf>()];
+  int tile, col;
+  if (!halo_block(hg, tile, col)) return;
+  conv_halo_body<TN, STAT, 1, kHaloSlotsHalf>(g, io, hg, smem, tile, col);
+}
+
 // grid of `tiles` pixel tiles x `nb` column blocks of `bn` channels (the last may be narrower), laid out in
 // groups of 8 tiles (see halo_block)
 dim3 halo_grid(const ConvGeom &g, int bn, int replicas, HaloGeom &hg) {
-  const int bm = g.sp == 2 ? 128 : 256;
-  hg.tiles = (g.M + bm - 1) / bm;
+  hg.tiles = (hg.rows + hg.TH - 1) / hg.TH;
   hg.bn = bn;
   hg.nb = (g.N + bn - 1) / bn;
   return dim3((hg.tiles + 7) / 8 * 8 * hg.nb, 1, replicas);
 }
 
+// the instance with column sums where the variant has one and io.stat asks for them
+#define HALO_LAUNCH(KERNEL, STAT_OK, ...)                                                              \
+  do {                                                                                                 \
+    if (STAT_OK && io.stat)                                                                            \
+      hipLaunchKernelGGL((KERNEL<__VA_ARGS__ STAT_OK>), grid, dim3(kThreads), 0, st, g, io, hg);       \
+    else                                                                                               \
+      hipLaunchKernelGGL((KERNEL<__VA_ARGS__ false>), grid, dim3(kThreads), 0, st, g, io, hg);         \
+  } while (0)
+
 template <int TN, int TL>
 hipError_t run_halo_s2(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io, HaloGeom hg) {
   const dim3 grid = halo_grid(g, TN * 32, replicas, hg);
-  if (TN != 3 && io.stat)
-    hipLaunchKernelGGL((k_conv_halo_s2<TN, TL, TN != 3>), grid, dim3(kThreads), 0, st, g, io, hg);
-  else
-    hipLaunchKernelGGL((k_conv_halo_s2<TN, TL, false>), grid, dim3(kThreads), 0, st, g, io, hg);
+  HALO_LAUNCH(k_conv_halo_s2, TN != 3, TN, TL, );
+  return hipGetLastError();
+}
+
+template <int TN>
+hipError_t run_halo_half(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io, HaloGeom hg) {
+  const dim3 grid = halo_grid(g, TN * 32, replicas, hg);
+  HALO_LAUNCH(k_conv_halo_half, TN == 4, TN, );
   return hipGetLastError();
 }
 
 template <int TN, int TL>
 hipError_t run_halo(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io, HaloGeom hg) {
   const dim3 grid = halo_grid(g, TN * 32, replicas, hg);
-  if (TN == 4 && io.stat)
-    hipLaunchKernelGGL((k_conv_halo<TN, TL, TN == 4>), grid, dim3(kThreads), 0, st, g, io, hg);
-  else
-    hipLaunchKernelGGL((k_conv_halo<TN, TL, false>), grid, dim3(kThreads), 0, st, g, io, hg);
+  HALO_LAUNCH(k_conv_halo, TN == 4, TN, TL, );
   return hipGetLastError();
 }
 
-bool make_halo_geom(const ConvGeom &g, HaloGeom &hg) {
+bool make_halo_geom(const ConvGeom &g, HaloGeom &hg, bool half = false) {
   const bool s2 = g.sp == 2;
-  const int BM = s2 ? 128 : 256;
-  if (g.dshift != 0) return false;
-  if (s2) {  // forward 3x3, padding 1, even image
+  const int BM = s2 || half ? 128 : 256;
+  if (g.dshift != 0 || g.R < g.sp || g.S < g.sp) return false;
+  if (s2) {  // forward 3x3
     // with few input channels a workgroup is mostly prologue and epilogue, and the kernel that gathers per tap, at
     // three workgroups per compute unit instead of two, is as fast or faster (96 channels: 38 against 44 us)
     static const int min_c = [] {
@@ -344,27 +376,25 @@ bool make_halo_geom(const ConvGeom &g, HaloGeom &hg) {
       return e ? atoi(e) : 128;
     }();
     if (g.Cc < min_c) return false;
-    if (g.R != 3 || g.S != 3 || g.off != -1 || g.sr != 1 || 2 * g.P != g.Hin || 2 * g.Q != g.Win) return false;
-  } else if (g.sp != 1 || g.P != g.Hin || g.Q != g.Win) {
+    if (g.R != 3 || g.S != 3 || g.sr != 1) return false;
+  } else if (g.sp != 1) {
     return false;
   }
-  if (BM % g.Q != 0) return false;
-  const int PQ = g.P * g.Q;
-  if (PQ >= BM) {
-    if (PQ % BM != 0) return false;
-    hg.TH = BM / g.Q, hg.nimg = 1;
-  } else {
-    if (BM % PQ != 0) return false;
-    hg.TH = g.P, hg.nimg = BM / PQ;
+  hg.HC = g.sp * (g.Q - 1) + g.S, hg.PRI = g.sp * (g.P - 1) + g.R;
+  for (hg.TH = BM / g.Q; hg.TH > 0; --hg.TH) {
+    // images a tile can touch: tiles start at multiples of TH rows
+    const int images = g.P % hg.TH == 0 ? 1 : hg.TH % g.P == 0 ? hg.TH / g.P : (hg.TH + g.P - 2) / g.P + 1;
+    const long long slots = (long long)(g.sp * (hg.TH - images) + g.R * images) * hg.HC;
+    hg.slots = (int)slots;
+    if (slots <= (s2 ? kHaloSlotsS2 : half ? kHaloSlotsHalf : kHaloSlots)) break;
   }
-  hg.HR = g.sp * (hg.TH - 1) + g.R, hg.HC = g.sp * (g.Q - 1) + g.S;
-  hg.slots = hg.nimg * hg.HR * hg.HC;
-  hg.dImg = make_fastdiv(hg.HR * hg.HC), hg.dHC = make_fastdiv(hg.HC), hg.dRows = make_fastdiv(hg.TH * g.Q);
-  const int o_first = g.off, o_last = g.off + (g.R - 1) * g.sr;
-  hg.omin_h = o_first < o_last ? o_first : o_last;
-  const int w_first = g.off, w_last = g.off + (g.S - 1) * g.sr;
-  hg.omin_w = w_first < w_last ? w_first : w_last;
-  return hg.slots <= (s2 ? kHaloSlotsS2 : kHaloSlots);
+  // a tile less than three quarters full gives away what the patch gains
+  if (hg.TH * g.Q * 4 < BM * 3) return false;
+  hg.rows = g.M / g.Q;
+  hg.dP = make_fastdiv(g.P), hg.dHC = make_fastdiv(hg.HC), hg.dPRI = make_fastdiv(hg.PRI);
+  const int o_last = g.off + (g.R - 1) * g.sr, w_last = g.off + (g.S - 1) * g.sr;
+  hg.omin_h = g.off < o_last ? g.off : o_last, hg.omin_w = g.off < w_last ? g.off : w_last;
+  return true;
 }
 
 }  // namespace
@@ -384,20 +414,27 @@ namespace {
 // 16 x 16 images, three replicas of 128: -8 %).  With fewer narrow workgroups than that the wide ones are as fast
 // or faster.  Otherwise 96- or 128-wide column blocks, whichever pads the output channels least (ties go to the
 // wider tile); a last block of at most 64 channels runs two tiles wide.
-enum HaloVariant { kHalo64, kHalo96, kHalo128 };
-HaloVariant halo_variant(const ConvGeom &g, int replicas) {
+enum HaloVariant { kHalo64, kHalo96, kHalo128, kHaloHalf96, kHaloHalf128 };
+HaloVariant halo_variant(const ConvGeom &g, const HaloGeom &hg, int replicas) {
   constexpr int kCus = 256;
   const int n = g.N;
   if (g.sp == 2) {  // 128-pixel tiles: one width rule
     if (n <= 64) return kHalo64;
     return (n + 95) / 96 * 96 < (n + 127) / 128 * 128 ? kHalo96 : kHalo128;
   }
-  const long long tiles = (g.M + 255) / 256, wide = tiles * ((n + 127) / 128) * replicas,
+  const long long tiles = (hg.rows + hg.TH - 1) / hg.TH, wide = tiles * ((n + 127) / 128) * replicas,
                   narrow_wgs = tiles * (n / 64) * replicas;
   const bool narrow = n % 64 == 0 && wide < 2 * kCus && narrow_wgs > 2 * kCus && narrow_wgs <= 3 * kCus;
   if (n <= 64 || narrow) return kHalo64;
   const int pad3 = (n + 95) / 96 * 96, pad4 = (n + 127) / 128 * 128;
-  return pad3 < pad4 ? kHalo96 : kHalo128;
+  const bool by96 = pad3 < pad4;
+  // at most one workgroup for every second compute unit: 128-pixel tiles, twice as many (us per layer pass: 256 channels
+  // on 7 x 7, 78 workgroups, 126 -> 108; 192 on 16 x 16, 128 workgroups, 95 -> 84; but 256 on 8 x 8, 192 workgroups,
+  // 148 -> 155)
+  HaloGeom half;
+  if (2 * tiles * (by96 ? pad3 / 96 : pad4 / 128) * replicas <= kCus && make_halo_geom(g, half, true))
+    return by96 ? kHaloHalf96 : kHaloHalf128;
+  return by96 ? kHalo96 : kHalo128;
 }
 
 }  // namespace
@@ -407,8 +444,12 @@ HaloVariant halo_variant(const ConvGeom &g, int replicas) {
 // sums cost more than the reduction pass they replace (160 channels on 32 x 32 images: +0.5 % per step against
 // -0.7 % for the other layers of the same network).
 int conv_halo_stat_splits(const ConvGeom &g, int replicas) {
-  const int bm = g.sp == 2 ? 128 : 256;
-  return halo_variant(g, replicas) == kHalo96 ? 0 : (g.M + bm - 1) / bm;
+  HaloGeom hg;
+  if (!make_halo_geom(g, hg)) return 0;
+  const HaloVariant v = halo_variant(g, hg, replicas);
+  if (v == kHalo96 || v == kHaloHalf96) return 0;
+  if (v == kHaloHalf128) make_halo_geom(g, hg, true);
+  return (hg.rows + hg.TH - 1) / hg.TH;
 }
 
 hipError_t launch_conv_halo(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io) {
@@ -416,7 +457,7 @@ hipError_t launch_conv_halo(hipStream_t st, int replicas, const ConvGeom &g, con
   if (!make_halo_geom(g, hg)) return hipErrorInvalidValue;
   const int n = g.N;
   if (g.sp == 2) {
-    switch (halo_variant(g, replicas)) {
+    switch (halo_variant(g, hg, replicas)) {
       case kHalo64: return run_halo_s2<2, 2>(st, replicas, g, io, hg);
       case kHalo96: {
         if (io.stat) return hipErrorInvalidValue;
@@ -429,15 +470,19 @@ hipError_t launch_conv_halo(hipStream_t st, int replicas, const ConvGeom &g, con
       }
     }
   }
-  switch (halo_variant(g, replicas)) {
+  switch (halo_variant(g, hg, replicas)) {
     case kHalo64: {
       const dim3 grid = halo_grid(g, 64, replicas, hg);
-      if (io.stat)
-        hipLaunchKernelGGL(k_conv_halo_n64<true>, grid, dim3(kThreads), 0, st, g, io, hg);
-      else
-        hipLaunchKernelGGL(k_conv_halo_n64<false>, grid, dim3(kThreads), 0, st, g, io, hg);
+      HALO_LAUNCH(k_conv_halo_n64, true, );
       return hipGetLastError();
     }
+    case kHaloHalf96:
+      if (io.stat) return hipErrorInvalidValue;  // see conv_halo_stat_splits
+      make_halo_geom(g, hg, true);
+      return run_halo_half<3>(st, replicas, g, io, hg);
+    case kHaloHalf128:
+      make_halo_geom(g, hg, true);
+      return run_halo_half<4>(st, replicas, g, io, hg);
     case kHalo96: {
       if (io.stat) return hipErrorInvalidValue;  // see conv_halo_stat_splits
       const int last = n - ((n + 95) / 96 * 96 - 96);
