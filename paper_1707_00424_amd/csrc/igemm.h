@@ -128,7 +128,7 @@ int igemm_fast_stat_splits(int dtype, bool out_f32, const ConvGeom &g, const Gem
 // Stride-1 'same' convolutions with the input patch staged once in LDS (igemm_halo.hip).
 bool conv_halo_applicable(int dtype, const ConvGeom &g, const GemmIO &io, bool out_f32);
 hipError_t launch_conv_halo(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io);
-int conv_halo_stat_splits(const ConvGeom &g, int replicas);
+int conv_halo_stat_splits(const ConvGeom &g, const GemmIO &io, int replicas);
 // fp32 backward-data of a stride-1 layer with few input channels under a wide window, the per-tap products of one
 // image held in LDS (igemm_dgrad_win.hip).  w: the layer's weights as they lie, [Cout][R][R][Cin].
 // ... and its backward-weight pass with the window gather in LDS (splits over images; partial sums per split).
@@ -152,6 +152,10 @@ hipError_t launch_wgrad_smallk(hipStream_t st, int replicas, const ConvGeom &g, 
 bool wgrad9_applicable(int dtype, const ConvGeom &g);
 int wgrad9_plan(int replicas, const ConvGeom &g, int *chunk_out);
 hipError_t launch_wgrad9(hipStream_t st, int replicas, const ConvGeom &g, const WgradIO &io);
+// bf16 backward-weight of windows of 3 x 3 and larger with channel counts no vector kernel takes (igemm_strips.hip).
+bool wgrad_strips_applicable(int dtype, int replicas, const ConvGeom &g);
+int wgrad_strips_plan(int replicas, const ConvGeom &g, int *chunk_out);
+hipError_t launch_wgrad_strips(hipStream_t st, int replicas, const ConvGeom &g, const WgradIO &io);
 // bf16 plain products with few output tiles: the contraction split over the wavefronts of a workgroup (igemm_ksplit.hip).
 bool gemm_ksplit_applicable(int dtype, int replicas, const ConvGeom &g, const GemmIO &io);
 hipError_t launch_gemm_ksplit(hipStream_t st, int dtype, bool out_f32, int replicas, const ConvGeom &g, const GemmIO &io);

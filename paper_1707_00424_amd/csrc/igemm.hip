@@ -416,7 +416,7 @@ hipError_t launch_igemm(hipStream_t st, int dtype, bool out_f32, int replicas, c
     const bool fast = !smallk && !halo && !conv_f32x3_applicable(dtype, replicas, g, io_in) && !dgrad_s2_applicable(dtype, g, io_in, out_f32) &&
                       !gemm_ksplit_applicable(dtype, replicas, g, io_in) && igemm_fast_applicable(dtype, g, io_in);
     if (smallk) S = conv_smallk_stat_splits(g, out_f32);
-    if (halo) S = conv_halo_stat_splits(g, replicas);
+    if (halo) S = conv_halo_stat_splits(g, io_in, replicas);
     if (fast) S = igemm_fast_stat_splits(dtype, out_f32, g, io_in);
     if (S > 0 && S <= io_in.stat_capacity) {
       *stat_splits = S;
@@ -455,6 +455,7 @@ hipError_t launch_wgrad(hipStream_t st, int dtype, int replicas, const ConvGeom 
   if (wgrad_window_applicable(dtype, g)) return launch_wgrad_window(st, replicas, g, io);
   if (wgrad9_applicable(dtype, g) && io.pairA && io.pairB) return launch_wgrad9(st, replicas, g, io);
   if (wgrad_fast_applicable(dtype, g) && io.pairA && io.pairB) return launch_wgrad_fast(st, replicas, g, io);
+  if (wgrad_strips_applicable(dtype, replicas, g)) return launch_wgrad_strips(st, replicas, g, io);
   if (dtype == 0) return run_wgrad<float, 2, 2, 1, 1>(st, replicas, g, io);
   switch (bf16_ntile(g.N)) {
     case 32: return run_wgrad<bf16_t, 1, 4, 1, 1>(st, replicas, g, io);
@@ -474,6 +475,9 @@ bool wgrad_takes_bias(int dtype, int replicas, const ConvGeom &g, const WgradIO 
 }
 
 int wgrad_plan(int dtype, int replicas, const ConvGeom &g, int *chunk_out) {
+  if (!wgrad_smallk_applicable(dtype, g) && !wgrad9_applicable(dtype, g) && !wgrad_fast_applicable(dtype, g) &&
+      wgrad_strips_applicable(dtype, replicas, g))
+    return wgrad_strips_plan(replicas, g, chunk_out);
   if (wgrad9_applicable(dtype, g)) return wgrad9_plan(replicas, g, chunk_out);
   if (!wgrad_small_f32_applicable(dtype, g) && wgrad_f32x3_applicable(dtype, replicas, g))
     return wgrad_f32x3_plan(replicas, g, chunk_out);

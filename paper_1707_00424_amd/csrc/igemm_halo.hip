@@ -55,7 +55,9 @@ constexpr int halo_lds_bytes() {
 
 // `tile`, `col`: pixel tile and column block of this workgroup; column blocks before it are hg.bn wide.
 // TM: 32-pixel tiles per wavefront (the workgroup's tile is TM * 128 output pixels); SLOTS: patch capacity; SP: stride.
-template <int TN, bool STAT, int TM = 2, int SLOTS = kHaloSlots, int SP = 1>
+// VL: channels per load (8; 2 or 1 where the channel count is no multiple of 8); ROWS: epilogue through LDS in whole rows
+// (output channels a multiple of 4), else straight from the accumulators.
+template <int TN, bool STAT, int TM = 2, int SLOTS = kHaloSlots, int SP = 1, int VL = 8, bool ROWS = true>
 __device__ __forceinline__ void conv_halo_body(const ConvGeom &g, const GemmIO &io, const HaloGeom &hg, char *smem,
                                                int tile, int col) {
   typedef bf16_t T;
@@ -117,14 +119,37 @@ __device__ __forceinline__ void conv_halo_body(const ConvGeom &g, const GemmIO &
   }
   const int b_lds = (lane & 31) * LK + (lane >> 5) * VW;
 
+  // a vector of eight channels from channel c on, c + 7 maybe beyond the layer's: those are zero
+  auto load_narrow = [&](__amdgpu_buffer_rsrc_t rsrc, uint32_t off, int c) -> u4 {
+    u4 r;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (VL == 2) {
+        r[e] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, off != kOob && c + 2 * e < g.Cc ? off + 4u * e : kOob, 0, 0);
+      } else {
+        const uint32_t lo = (unsigned short)__builtin_amdgcn_raw_buffer_load_b16(
+            rsrc, off != kOob && c + 2 * e < g.Cc ? off + 4u * e : kOob, 0, 0);
+        const uint32_t hi = (unsigned short)__builtin_amdgcn_raw_buffer_load_b16(
+            rsrc, off != kOob && c + 2 * e + 1 < g.Cc ? off + 4u * e + 2u : kOob, 0, 0);
+        r[e] = lo | hi << 16;
+      }
+    }
+    return r;
+  };
   u4 hreg[H_IT];
   auto load_halo = [&](int chunk) {
     const uint32_t cb = (uint32_t)(chunk * BK * (int)sizeof(T));
     // channel counts that are no multiple of 32: the vectors of the last chunk beyond the row are zeros
     const bool live = chunk * BK + (tid & 3) * VW < g.Cc;
+    if constexpr (VL == 8) {
 #pragma unroll
-    for (int it = 0; it < H_IT; ++it)
-      hreg[it] = __builtin_amdgcn_raw_buffer_load_b128(a_rsrc, (live && h_off[it] != kOob) ? h_off[it] + cb : kOob, 0, 0);
+      for (int it = 0; it < H_IT; ++it)
+        hreg[it] = __builtin_amdgcn_raw_buffer_load_b128(a_rsrc, (live && h_off[it] != kOob) ? h_off[it] + cb : kOob, 0, 0);
+    } else {
+#pragma unroll
+      for (int it = 0; it < H_IT; ++it)
+        hreg[it] = load_narrow(a_rsrc, (live && h_off[it] != kOob) ? h_off[it] + cb : kOob, chunk * BK + (tid & 3) * VW);
+    }
   };
   auto store_halo = [&]() {
 #pragma unroll
@@ -139,9 +164,15 @@ __device__ __forceinline__ void conv_halo_body(const ConvGeom &g, const GemmIO &
   auto load_b = [&](u4 (&breg)[B_IT]) {
     const uint32_t kb = (uint32_t)((ld_tap * g.Cc + ld_chunk * BK) * (int)sizeof(T));
     const bool live = ld_t < KT && ld_chunk * BK + lkv * VW < g.Cc;  // not into the next tap's weights
+    if constexpr (VL == 8) {
 #pragma unroll
-    for (int i = 0; i < B_IT; ++i)
-      breg[i] = __builtin_amdgcn_raw_buffer_load_b128(b_rsrc, (live && b_off[i] != kOob) ? b_off[i] + kb : kOob, 0, 0);
+      for (int i = 0; i < B_IT; ++i)
+        breg[i] = __builtin_amdgcn_raw_buffer_load_b128(b_rsrc, (live && b_off[i] != kOob) ? b_off[i] + kb : kOob, 0, 0);
+    } else {
+#pragma unroll
+      for (int i = 0; i < B_IT; ++i)
+        breg[i] = load_narrow(b_rsrc, (live && b_off[i] != kOob) ? b_off[i] + kb : kOob, ld_chunk * BK + lkv * VW);
+    }
     ++ld_t;
     if (++ld_tap == RS) {
       ld_tap = 0;
@@ -190,7 +221,12 @@ __device__ __forceinline__ void conv_halo_body(const ConvGeom &g, const GemmIO &
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
-      for (int tn = 0; tn < TN; ++tn) mma<T>(bf[tn], af[tm], acc[tm][tn]);
+      for (int tn = 0; tn < TN; ++tn) {
+        if (ROWS)
+          mma<T>(bf[tn], af[tm], acc[tm][tn]);
+        else
+          mma<T>(af[tm], bf[tn], acc[tm][tn]);
+      }
   };
 
   constexpr int D = TN >= 4 ? 2 : 4;  // weight tiles in flight from global memory (registers permitting)
@@ -261,8 +297,11 @@ __device__ __forceinline__ void conv_halo_body(const ConvGeom &g, const GemmIO &
   float *wsums = reinterpret_cast<float *>(smem) + 4 * kStageFloats<TN>;
   ConvGeom gt = g;
   gt.M = min(g.M, m0 + hg.TH * g.Q);  // rows beyond the tile belong to the next one
-  store_tile_lds<T, TM, TN, false, STAT>(gt, io, rep, m0 + wave * TM * 32, n0, lane, acc,
-                                         reinterpret_cast<float *>(smem) + wave * kStageFloats<TN>, wsums + wave * 2 * BN);
+  if constexpr (ROWS)
+    store_tile_lds<T, TM, TN, false, STAT>(gt, io, rep, m0 + wave * TM * 32, n0, lane, acc,
+                                           reinterpret_cast<float *>(smem) + wave * kStageFloats<TN>, wsums + wave * 2 * BN);
+  else
+    store_tile<T, TM, TN, false>(gt, io, rep, m0 + wave * TM * 32, n0, lane, acc);
   // the workgroup's rows: one partial row per pixel tile
   if (STAT) write_tile_sums<BN, 4>(g, io, rep, hg.tiles, tile, n0, tid, wsums);
 }
@@ -315,6 +354,17 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     conv_halo_body<TN, STAT, 1, kHaloSlotsS2, 2>(g, io, hg, smem, tile, col);
 }
 
+// Channel counts that are no multiple of 8 (input) or 4 (output).
+template <int TN, int VL, bool ROWS>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_conv_halo_narrow(const ConvGeom g,
+                                                                                                      const GemmIO io,
+                                                                                                      const HaloGeom hg) {
+  __shared__ __attribute__((aligned(16))) char smem[halo_lds_bytes<TN>()];
+  int tile, col;
+  if (!halo_block(hg, tile, col)) return;
+  conv_halo_body<TN, false, 2, kHaloSlots, 1, VL, ROWS>(g, io, hg, smem, tile, col);
+}
+
 // Stride 1 on 128 output pixels, for launches that 256-pixel tiles leave below two workgroups per compute unit.
 template <int TN, bool STAT>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TN == 3 ? 3 : 2))) void k_conv_halo_half(
@@ -333,6 +383,10 @@ dim3 halo_grid(const ConvGeom &g, int bn, int replicas, HaloGeom &hg) {
   hg.nb = (g.N + bn - 1) / bn;
   return dim3((hg.tiles + 7) / 8 * 8 * hg.nb, 1, replicas);
 }
+
+// 16-byte loads of the input and the weights allowed; whole-row epilogue as well
+bool halo_wide(const ConvGeom &g, const GemmIO &io) { return io.vecA && io.vecB && g.Cc % 8 == 0; }
+bool halo_vector(const ConvGeom &g, const GemmIO &io) { return halo_wide(g, io) && g.N % 4 == 0 && io.ldc % 4 == 0; }
 
 // the instance with column sums where the variant has one and io.stat asks for them
 #define HALO_LAUNCH(KERNEL, STAT_OK, ...)                                                              \
@@ -354,6 +408,26 @@ template <int TN>
 hipError_t run_halo_half(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io, HaloGeom hg) {
   const dim3 grid = halo_grid(g, TN * 32, replicas, hg);
   HALO_LAUNCH(k_conv_halo_half, TN == 4, TN, );
+  return hipGetLastError();
+}
+
+template <int TN>
+hipError_t run_halo_narrow(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io, HaloGeom hg) {
+  const dim3 grid = halo_grid(g, TN * 32, replicas, hg);
+#define NARROW_LAUNCH(VLV)                                                                                        \
+  do {                                                                                                            \
+    if (g.N % 4 == 0 && io.ldc % 4 == 0)                                                                          \
+      hipLaunchKernelGGL((k_conv_halo_narrow<TN, VLV, true>), grid, dim3(kThreads), 0, st, g, io, hg);            \
+    else                                                                                                          \
+      hipLaunchKernelGGL((k_conv_halo_narrow<TN, VLV, false>), grid, dim3(kThreads), 0, st, g, io, hg);           \
+  } while (0)
+  if (halo_wide(g, io))
+    NARROW_LAUNCH(8);
+  else if (g.Cc % 2 == 0)
+    NARROW_LAUNCH(2);
+  else
+    NARROW_LAUNCH(1);
+#undef NARROW_LAUNCH
   return hipGetLastError();
 }
 
@@ -401,9 +475,11 @@ bool make_halo_geom(const ConvGeom &g, HaloGeom &hg, bool half = false) {
 
 bool conv_halo_applicable(int dtype, const ConvGeom &g, const GemmIO &io, bool out_f32) {
   HaloGeom hg;
-  return dtype == 1 && !out_f32 && io.vecA && io.vecB && g.R * g.S > 1 && g.Cc % 8 == 0 && g.Cc >= 16 && g.N % 4 == 0 &&
-         io.ldc % 4 == 0 && io.in_bytes > 0 && io.in_bytes < (1LL << 31) && (long long)g.M * io.ldc * 4 < (1LL << 31) && (long long)g.N * g.K * 2 < (1LL << 31) &&
-         g.M >= 256 && make_halo_geom(g, hg);
+  if (dtype != 1 || out_f32 || g.R * g.S < 2 || g.Cc < 16 || g.M < 256 || !make_halo_geom(g, hg)) return false;
+  // rows of an even number of channels start on a dword wherever the tensors do
+  const bool narrow_ok = g.sp == 1 && (g.Cc % 2 == 1 || (aligned_to(io.in, 4) && aligned_to(io.w, 4) && io.in_rs % 2 == 0 && io.w_rs % 2 == 0));
+  return (halo_vector(g, io) || narrow_ok) && io.in_bytes > 0 && io.in_bytes < (1LL << 31) &&
+         (long long)g.M * io.ldc * 4 < (1LL << 31) && (long long)g.N * g.K * 2 < (1LL << 31);
 }
 
 namespace {
@@ -443,9 +519,9 @@ HaloVariant halo_variant(const ConvGeom &g, const HaloGeom &hg, int replicas) {
 // the layer does not take them: in the 96-wide epilogue, whose walk visits three channel groups per lane, the
 // sums cost more than the reduction pass they replace (160 channels on 32 x 32 images: +0.5 % per step against
 // -0.7 % for the other layers of the same network).
-int conv_halo_stat_splits(const ConvGeom &g, int replicas) {
+int conv_halo_stat_splits(const ConvGeom &g, const GemmIO &io, int replicas) {
   HaloGeom hg;
-  if (!make_halo_geom(g, hg)) return 0;
+  if (!halo_vector(g, io) || !make_halo_geom(g, hg)) return 0;
   const HaloVariant v = halo_variant(g, hg, replicas);
   if (v == kHalo96 || v == kHaloHalf96) return 0;
   if (v == kHaloHalf128) make_halo_geom(g, hg, true);
@@ -456,6 +532,11 @@ hipError_t launch_conv_halo(hipStream_t st, int replicas, const ConvGeom &g, con
   HaloGeom hg;
   if (!make_halo_geom(g, hg)) return hipErrorInvalidValue;
   const int n = g.N;
+  if (!halo_vector(g, io)) {
+    if (io.stat) return hipErrorInvalidValue;
+    return n <= 64 || (n + 63) / 64 * 64 < (n + 127) / 128 * 128 ? run_halo_narrow<2>(st, replicas, g, io, hg)
+                                                                  : run_halo_narrow<4>(st, replicas, g, io, hg);
+  }
   if (g.sp == 2) {
     switch (halo_variant(g, hg, replicas)) {
       case kHalo64: return run_halo_s2<2, 2>(st, replicas, g, io, hg);

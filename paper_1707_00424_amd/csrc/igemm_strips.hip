@@ -1,0 +1,148 @@
+// bf16 weight gradients without LDS: the operands go from memory into MFMA fragments in registers.
+//
+//   dW[n][r][s][c] = sum over pixels (b, p, q) of dy[b, p, q, n] * x[b, sp*p + r - pad, sp*q + s - pad, c]
+//
+// The contraction runs over pixels, the slow index of both operands in memory, and an MFMA fragment wants eight of them in
+// one lane.  A lane loads a pair of channels (one dword; 32 lanes on 128 consecutive bytes) of eight neighbouring pixels,
+// and one v_perm per two pixels and channel makes the fragments: lane l of the even (odd) fragment holds channel 2l
+// (2l + 1) of a tile of 64.  A wavefront owns such a tile of dy, one of x and three taps of one row of the window: twelve
+// accumulators, 26 permutes and 18 loads per 12 MFMAs (384 cycles).  The fragments of the three taps are the same loaded
+// values paired one pixel further on.  No LDS, no barrier, no halo, any image size; a few rows of loads in flight cover
+// the latency with one wavefront per SIMD.
+// What bounds it is the number of load instructions, sixteen cycles each for a compute unit whatever their width: 320 -> 320
+// channels on 16 x 16 take 380 us against 207 us in the kernel that stages blocks in LDS (k_wgrad9), 96 -> 96 on 32 x 32
+// 235 against 97.  It runs the layers no vector kernel takes, channel counts that are no multiple of 8, where the
+// generic kernel gathers element by element: 50 -> 64 channels on 16 x 16, batch 6 x 50, layer pass 187 -> 149 us; 20 -> 50
+// on 28 x 28, 2 x 100, 265 -> 220 us.
+// P: channels per lane, 1 where a count is odd.
+#include "igemm_dev.h"
+#include "igemm_strips.h"
+
+namespace {
+
+using namespace igemm_dev;
+
+template <int P, int S, int SP>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(P == 2 ? 1 : 2))) void k_wgrad_strips(const ConvGeom g,
+                                                                                                       const WgradIO io,
+                                                                                                       const StripGeom wg) {
+  typedef StripWalk<S, SP, 2> Walk;
+  constexpr int NX = Walk::NX, L0 = Walk::L0;
+  const StripUnit un = strip_unit(wg, S);
+  if (!un.live) return;
+  const int rep = blockIdx.z;
+  const int lane = threadIdx.x, ch = lane & 31, h = lane >> 5;
+  const int n = (un.ntile * 32 + ch) * P, c = (un.ctile * 32 + ch) * P;
+  Walk walk(g, wg, io, rep, un, h, c, n);
+
+  f16v acc[P][P][S];
+#pragma unroll
+  for (int i = 0; i < P; ++i)
+#pragma unroll
+    for (int j = 0; j < P; ++j)
+#pragma unroll
+      for (int s = 0; s < S; ++s)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[i][j][s][v] = 0.f;
+
+  // channel `par` of values a (low half of the result) and b
+  auto pair = [](uint32_t a, uint32_t b, int par) {
+    return __builtin_amdgcn_perm(b, a, par ? 0x07060302u : 0x05040100u);
+  };
+  auto multiply = [&](const uint32_t (&xv)[NX], const uint32_t (&dv)[8]) {
+    u4 a[P], b[P][S];
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        a[i][e] = pair(dv[2 * e], dv[2 * e + 1], i);
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+          const int v = (s % SP ? L0 : 0) + s / SP + 2 * e;
+          b[i][s][e] = pair(xv[v], xv[v + 1], i);
+        }
+      }
+    }
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+      for (int i = 0; i < P; ++i)
+#pragma unroll
+        for (int j = 0; j < P; ++j) mma<bf16_t>(a[i], b[j][s], acc[i][j][s]);
+  };
+  constexpr int D = 3;  // rows in flight
+  uint32_t xr[D][NX], dr[D][8];
+#pragma unroll
+  for (int i = 0; i < D; ++i) walk.template load<2 * P, 2 * P>(xr[i], dr[i]);
+  const int rows = walk.rows();
+  for (int t = 0; t < rows; t += D) {  // rows beyond the last are zeros
+#pragma unroll
+    for (int i = 0; i < D; ++i) {
+      multiply(xr[i], dr[i]);
+      walk.template load<2 * P, 2 * P>(xr[i], dr[i]);
+    }
+  }
+
+  // register v of a lane: row 8*(v/4) + 4*h + v%4 of the tile of dy, column `ch` of the tile of x
+  float *out = io.out + rep * io.out_rs + un.split * io.split_stride;
+  typedef float f2u __attribute__((ext_vector_type(2), aligned(4)));
+#pragma unroll
+  for (int i = 0; i < P; ++i)
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int nn = (un.ntile * 32 + 8 * (v >> 2) + 4 * h + (v & 3)) * P + i;
+        if (nn < g.N && c < g.Cc && un.s0 + s < g.S) {
+          float *dst = out + (long long)nn * g.K + (un.r * g.S + un.s0 + s) * g.Cc + c;
+          if constexpr (P == 2)
+            *(f2u *)dst = f2u{acc[i][0][s][v], acc[i][1][s][v]};
+          else
+            *dst = acc[i][0][s][v];
+        }
+      }
+}
+
+// channels per lane
+int strips_pair(const ConvGeom &g) { return g.N % 2 == 0 && g.Cc % 2 == 0 ? 2 : 1; }
+
+bool make_strips(const ConvGeom &g, int replicas, StripGeom &wg) {
+  const int p = strips_pair(g);
+  return plan_strips(g, replicas, 2, 32 * p, 32 * p, 3, p == 2 ? 1024 : 2048, p == 2 ? 260 : 200, wg);
+}
+
+}  // namespace
+
+bool wgrad_strips_applicable(int dtype, int replicas, const ConvGeom &g) {
+  StripGeom wg;
+  return dtype == 1 && g.Cc >= 16 && g.N >= 16 && make_strips(g, replicas, wg);
+}
+
+int wgrad_strips_plan(int replicas, const ConvGeom &g, int *chunk_out) {
+  StripGeom wg;
+  make_strips(g, replicas, wg);
+  if (chunk_out) *chunk_out = wg.pps * 32;
+  return wg.splits;
+}
+
+hipError_t launch_wgrad_strips(hipStream_t st, int replicas, const ConvGeom &g, const WgradIO &io) {
+  StripGeom wg;
+  if (io.with_bias || !make_strips(g, replicas, wg)) return hipErrorInvalidValue;
+  wg.pps = io.chunk / 32, wg.splits = io.splits;
+  if (wg.pps < 1 || (long long)wg.pps * wg.splits < wg.pairs) return hipErrorInvalidValue;
+  const dim3 grid((wg.splits + 7) / 8 * 8 * wg.units, 1, replicas);
+#define STRIPS_LAUNCH(PV, SPV) hipLaunchKernelGGL((k_wgrad_strips<PV, 3, SPV>), grid, dim3(64), 0, st, g, io, wg)
+  if (strips_pair(g) == 2) {
+    if (g.sp == 2)
+      STRIPS_LAUNCH(2, 2);
+    else
+      STRIPS_LAUNCH(2, 1);
+  } else {
+    if (g.sp == 2)
+      STRIPS_LAUNCH(1, 2);
+    else
+      STRIPS_LAUNCH(1, 1);
+  }
+#undef STRIPS_LAUNCH
+  return hipGetLastError();
+}

@@ -20,6 +20,15 @@ CASES = [
     (1, 2, 20, 40, 64, 64, 3, 1, 1),     # rows of 40: six per tile
     (1, 2, 9, 100, 32, 32, 3, 1, 1),     # two rows of 100: a patch too wide for LDS, the gather kernels
     (3, 3, 16, 8, 96, 192, 3, 1, 1),     # not square
+    (2, 3, 16, 16, 50, 64, 3, 1, 1),     # even channel counts that are no multiple of 8: dword loads, pairs of channels
+    (1, 4, 12, 12, 33, 47, 3, 1, 1),     # odd counts: 16-bit loads, results straight from the accumulators
+    (1, 2, 14, 14, 160, 50, 3, 1, 1),    # 50 outputs of whole-vector input, two 64-wide blocks back
+    (1, 3, 15, 15, 16, 19, 3, 1, 1),     # one tile of channels in the weight gradient, mostly padding
+    (2, 2, 12, 12, 17, 300, 3, 1, 1),    # 300 outputs: three wide blocks; backward over a ragged last chunk of 300
+    (1, 2, 10, 10, 18, 130, 5, 1, 2),    # 5 x 5: two groups of taps per window row in the weight gradient
+    (1, 2, 9, 9, 17, 20, 7, 1, 3),       # 7 x 7, odd count
+    (1, 3, 16, 16, 50, 94, 3, 2, 1),     # stride 2: even and odd columns of the input in the weight gradient
+    (1, 3, 11, 13, 21, 23, 3, 2, 1),     # same, odd everything
 ]
 
 
