@@ -4,14 +4,22 @@
 //   col[m][(r, s, ci)] = sum_n dy[m][n] * w[n][r][s][ci]          a plain matrix product over the output channels
 //   dx[h][w][ci]       = sum_{r, s} col[(h + pad - r, w + pad - s)][(r, s, ci)]
 //
-// As a direct implicit GEMM the pass has Cin = 20 of 32 MFMA columns in use and a contraction of R*S*Cout; as two
-// kernels (the product, then the gather over the window) every entry of col travels to memory and back, 100 MB
-// for the layer above.  Here col of ONE image stays in LDS (P*Q x R*S*Cin floats: 125 KB for that layer): the
-// workgroup multiplies its image's dy tile, held in LDS, with the weights read straight from memory into MFMA
-// fragments - as they lie, [Cout][R*S*Cin], they are the [K][N] operand, so the 32 lanes of a fragment half read 32
-// consecutive floats - parks the product in LDS and gathers from there.  One workgroup per compute unit (LDS),
-// eight wavefronts.
+// As a direct implicit GEMM the pass has Cin = 20 of 32 MFMA columns in use and a contraction of R*S*Cout (the row
+// kernel of igemm_f32.hip: LeNet's step 365 us against 314 here); as two kernels (the product, then the gather over the
+// window) every entry of col travels to memory and back, 100 MB for the layer above.  Here col of ONE image never
+// leaves LDS, 128 columns at a time: four pairs of wavefronts multiply 32 columns each (a row tile per wavefront) with
+// the weights read straight from memory into MFMA fragments - as they lie, [Cout][R*S*Cin], they are the [K][N]
+// operand, so the 32 lanes of a fragment half read 32 consecutive floats - park the product in LDS, and every thread
+// adds the taps that lie in those columns to its elements of dx, which stay in LDS until the last columns are through.
+// A chunk's weights travel while the one before is gathered.  With 34 KB for the columns and dx beside them (11 KB for
+// that layer) two workgroups share a compute unit, one's products over the other's gather.  The product is the six
+// products of bf16 parts of igemm_f32.hip; dy is split once, into registers, and serves every column.
+// Bound by the vector work of the gather and of the splits, and by an image's chain of phases.  The layer above, against
+// the whole of col at once in 125 KB, one workgroup per compute unit, fp32 MFMA: 128 / 384 / 768 images 17.7 / 35.7 /
+// 56.7 -> 17.3 / 26.7 / 42.2 us, error against 64 bits 1.5e-7 -> 0.9e-7.  Four wavefronts with both row tiles each
+// split the weights once instead of twice, but an image then takes longer: 1 us more at 128 and at 768 images.
 #include "igemm_dev.h"
+#include "igemm_split.h"
 
 namespace {
 
@@ -21,157 +29,170 @@ constexpr int kWinThreads = 512;
 constexpr int kWinMaxPix = 64;    // output pixels of an image: two 32-row MFMA tiles
 constexpr int kWinMaxCout = 64;   // contraction length
 constexpr int kWinLdsBytes = 160 * 1024;
+constexpr int kDxCols = 128;              // columns of col in LDS: 32 per wavefront
+constexpr int kDxPitch = kDxCols + 4;     // floats; the spare four of row 0 hold zeros for taps outside the image
+constexpr int kDxDyPitch = kWinMaxCout + 4;  // of the dy tile, which lies there first
 
 struct WinGeom {
   int B, H, W, Cin, Cout, R, pad, P, Q;  // dx [B][H][W][Cin], dy [B][P][Q][Cout]
   int NC;                                // R*R*Cin: columns of col
-  int KG;                                // contraction groups of 8
-  int lda, ldc;                          // LDS row pitches (floats) of the dy tile and of col
-  FastDiv dCin, dW, dCout, dCv;          // no integer division on the device
   int vec;                               // Cin % 4 == 0: the gather runs on 16-byte vectors
+  FastDiv dCin, dW, dCv, dR;             // no integer division on the device (dCv: vectors of a pixel)
 };
 
-// LDS pitches: the dy tile is read as 16-byte fragments by 32 rows x 2 halves (pitch = 4 mod 32 banks keeps the
-// eight 16-byte accesses of a quarter-wavefront apart); col is written 32 consecutive columns at a time and read
-// along Cin, so any pitch does
-__host__ __device__ inline int win_lda(int Cout) { return (Cout + 7) / 8 * 8 + 4; }
-
-__global__ __launch_bounds__(kWinThreads) void k_dgrad_window(const WinGeom g, const float *__restrict__ dy,
-                                                              long long dy_rs, const float *__restrict__ w,
-                                                              long long w_rs, const float *__restrict__ mask,
-                                                              long long mask_rs, int accumulate, float *__restrict__ dx,
-                                                              long long dx_rs) {
+// V: consecutive channels a thread gathers at a time (4 or 1)
+template <int V>
+__global__ __launch_bounds__(kWinThreads, 4) void k_dgrad_window(const WinGeom g, const float *__restrict__ dy, long long dy_rs,
+                                                             const float *__restrict__ w, long long w_rs,
+                                                             const float *__restrict__ mask, long long mask_rs,
+                                                             int accumulate, float *__restrict__ dx, long long dx_rs) {
+  typedef float fv __attribute__((ext_vector_type(V)));
+  constexpr int KS = kWinMaxCout / 16, NW = kWinThreads / 64, DI = kWinMaxPix / NW;
   extern __shared__ __attribute__((aligned(16))) float win_lds[];
-  float *dyS = win_lds;                       // [64][lda], rows beyond P*Q and columns beyond Cout are zero
-  float *colS = win_lds + kWinMaxPix * g.lda;  // [P*Q][ldc]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  float *colS = win_lds;                        // [64][kDxPitch]; the dy tile before that
+  float *dxS = win_lds + kWinMaxPix * kDxPitch;  // [H*W*Cin]
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wc = wave & 3;
   const int b = blockIdx.x, rep = blockIdx.y;
-  const int PQ = g.P * g.Q;
+  const int PQ = g.P * g.Q, ks_n = (g.Cout + 15) / 16;
+  const int row0 = wave >> 2 << 5;  // this wavefront's rows of col; none of them may be in use
+  const bool rows = row0 < PQ;
+  const int r32 = lane & 31, h = lane >> 5;
   const float *dyp = dy + rep * dy_rs + (long long)b * PQ * g.Cout;
-  const float *wp = w + rep * w_rs;
+  const __amdgpu_buffer_rsrc_t w_rsrc =
+      __builtin_amdgcn_make_buffer_rsrc((void *)(w + rep * w_rs), 0, g.Cout * g.NC * 4, 0x00020000);
 
-  // dy tile -> LDS (zero padded)
-  for (int i = tid; i < kWinMaxPix * g.lda; i += kWinThreads) dyS[i] = 0.f;
-  __syncthreads();
-  for (int i = tid; i < PQ * g.Cout; i += kWinThreads) {   // the tile is contiguous in memory
-    const int m = (int)fdiv((uint32_t)i, g.dCout), k = i - m * g.Cout;
-    dyS[m * g.lda + k] = dyp[i];
+  // weights of one chunk: rows (output channels) 16 ks + 8 h + j of column c0 + 32 wc + r32; zero beyond either end
+  float wraw[KS][8];
+  auto load_w = [&](int c0) {
+    const int col = c0 + wc * 32 + r32;
+    const uint32_t first = col < g.NC ? (uint32_t)((8 * h * g.NC + col) * 4) : kOobOffset;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+      if (ks < ks_n) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j)  // a row beyond Cout lies beyond the buffer
+          wraw[ks][j] = __uint_as_float(
+              __builtin_amdgcn_raw_buffer_load_b32(w_rsrc, first + (uint32_t)((16 * ks + j) * g.NC * 4), 0, 0));
+      }
+  };
+  {
+    float t[DI];
+#pragma unroll
+    for (int i = 0; i < DI; ++i) {
+      const int m = wave + NW * i;
+      t[i] = lane < g.Cout && m < PQ ? dyp[m * g.Cout + lane] : 0.f;
+    }
+    load_w(0);
+#pragma unroll
+    for (int i = 0; i < DI; ++i) colS[(wave + NW * i) * kDxDyPitch + lane] = t[i];
   }
   __syncthreads();
-
-  // col = dy x w: column tile tn (32 columns of col) per wavefront and trip, both row tiles at once so that a
-  // weight fragment serves two MFMAs.  Fragment of half h, element j of group q: contraction index 8q + 4h + j.
-  const int r = lane & 31, h = lane >> 5;
-  const int n_tiles = (g.NC + 31) / 32;
-  for (int tn = wave; tn < n_tiles; tn += kWinThreads / 64) {
-    const int col = tn * 32 + r;
-    const bool col_ok = col < g.NC;
-    const float *wcol = wp + col;   // element (k, col) at wcol[k * NC]
-    f16v acc0, acc1;
+  u4 a[KS][3];  // dy's parts: row row0 + r32, output channels 16 ks + 8 h ..
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc0[v] = 0.f, acc1[v] = 0.f;
-    // four groups = 32 contraction values per trip; the fragments of the next trip travel while this one multiplies
-    auto load_b = [&](int q0, u4 (&bf)[4]) {
+  for (int ks = 0; ks < KS; ++ks)
+    if (ks < ks_n) {
+      const float *src = colS + (row0 + r32) * kDxDyPitch + 16 * ks + 8 * h;
+      const f4 v0 = *(const f4 *)src, v1 = *(const f4 *)(src + 4);
+      const float v[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+      uint32_t p[3][4];
+      split_words<8>(v, p);
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int k = 8 * (q0 + u) + 4 * h;
-        float t[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) t[j] = (col_ok && k + j < g.Cout) ? wcol[(long long)(k + j) * g.NC] : 0.f;
-        bf[u] = u4{__float_as_uint(t[0]), __float_as_uint(t[1]), __float_as_uint(t[2]), __float_as_uint(t[3])};
-      }
-    };
-    u4 cur[4], nxt[4];
-    load_b(0, cur);
-    for (int q0 = 0; q0 < g.KG; q0 += 4) {
-      if (q0 + 4 < g.KG) load_b(q0 + 4, nxt);
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        if (q0 + u < g.KG) {
-          const int k = 8 * (q0 + u) + 4 * h;
-          const u4 a0 = *(const u4 *)&dyS[r * g.lda + k], a1 = *(const u4 *)&dyS[(32 + r) * g.lda + k];
-          mma<float>(a0, cur[u], acc0);
-          mma<float>(a1, cur[u], acc1);
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) cur[u] = nxt[u];
+      for (int q = 0; q < 3; ++q) a[ks][q] = u4{p[q][0], p[q][1], p[q][2], p[q][3]};
     }
-    // accumulator v of a lane: row 8*(v/4) + 4*h + v%4 of its row tile, column r of the column tile
-    if (col_ok) {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int m = 8 * (v >> 2) + 4 * h + (v & 3);
-        if (m < PQ) colS[m * g.ldc + col] = acc0[v];
-        if (32 + m < PQ) colS[(32 + m) * g.ldc + col] = acc1[v];
-      }
-    }
-  }
-  __syncthreads();
+  __syncthreads();  // the dy tile is dead
+  if (tid < 4) colS[kDxCols + tid] = 0.f;
 
-  // gather over the window, taps in order (the order the two-kernel path adds them in)
   const int total = g.H * g.W * g.Cin;
   const long long img = (long long)b * total;
   const float *mp = mask ? mask + rep * mask_rs + img : nullptr;
   float *op = dx + rep * dx_rs + img;
-  if (g.vec) {
-    // four consecutive channels per thread: 16-byte LDS reads (pitch and tap offsets are multiples of four floats)
-    const int cv = g.Cin >> 2, total4 = g.H * g.W * cv;
-    for (int i = tid; i < total4; i += kWinThreads) {
-      const int pix = (int)fdiv((uint32_t)i, g.dCv), c4 = (i - pix * cv) * 4;
-      const int hh = (int)fdiv((uint32_t)pix, g.dW), w = pix - hh * g.W;
-      f4 sum = {0.f, 0.f, 0.f, 0.f};
-      for (int rr = 0; rr < g.R; ++rr) {
-        const int p = hh + g.pad - rr;
-        if (p < 0 || p >= g.P) continue;
-        for (int ss = 0; ss < g.R; ++ss) {
-          const int q = w + g.pad - ss;
-          if (q < 0 || q >= g.Q) continue;
-          sum += *(const f4 *)&colS[(p * g.Q + q) * g.ldc + (rr * g.R + ss) * g.Cin + c4];
+  const int taps = g.R * g.R;
+  for (int c0 = 0; c0 < g.NC; c0 += kDxCols) {
+    if (rows) {
+      f16v hi, lo;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) hi[v] = 0.f, lo[v] = 0.f;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+        if (ks < ks_n) {
+          uint32_t p[3][4];
+          split_words<8>(wraw[ks], p);
+          u4 bw[3];
+#pragma unroll
+          for (int q = 0; q < 3; ++q) bw[q] = u4{p[q][0], p[q][1], p[q][2], p[q][3]};
+          mma<bf16_t>(a[ks][0], bw[2], lo);
+          mma<bf16_t>(a[ks][2], bw[0], lo);
+          mma<bf16_t>(a[ks][1], bw[1], lo);
+          mma<bf16_t>(a[ks][0], bw[1], lo);
+          mma<bf16_t>(a[ks][1], bw[0], lo);
+          mma<bf16_t>(a[ks][0], bw[0], hi);
         }
+      // accumulator v of a lane: row 8*(v/4) + 4*h + v%4 of its row tile, column r32 of the wavefront's columns
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const float t = hi[v] + lo[v];
+        colS[(row0 + 8 * (v >> 2) + 4 * h + (v & 3)) * kDxPitch + wc * 32 + r32] = t == t ? t : hi[v];
       }
-      const int o = pix * g.Cin + c4;
+    }
+    __syncthreads();
+    const bool last = c0 + kDxCols >= g.NC;
+    if (!last) load_w(c0 + kDxCols);
+
+    // gather over the taps of these columns, in order
+    for (int i = tid; i < total / V; i += kWinThreads) {
+      const int pix = (int)fdiv((uint32_t)i, V == 4 ? g.dCv : g.dCin), c = i * V - pix * g.Cin;
+      const int hh = (int)fdiv((uint32_t)pix, g.dW), ww = pix - hh * g.W;
+      const int t0 = (int)fdiv((uint32_t)max(c0 - c + g.Cin - 1, 0), g.dCin);
+      const int t1 = min(taps, (int)fdiv((uint32_t)max(c0 + kDxCols - c + g.Cin - 1, 0), g.dCin));
+      int p = (int)fdiv((uint32_t)t0, g.dR), q = t0 - p * g.R;
+      p = hh + g.pad - p, q = ww + g.pad - q;
+      const int q_lo = ww + g.pad - g.R;  // where a window row's taps end
+      int col = t0 * g.Cin + c - c0;
+      fv sum = {};
+      if (c0) sum = *(const fv *)&dxS[i * V];
+      for (int t = t0; t < t1; t += 4) {
+        fv part[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const bool ok = t + u < t1 && (unsigned)p < (unsigned)g.P && (unsigned)q < (unsigned)g.Q;
+          part[u] = *(const fv *)&colS[ok ? (p * g.Q + q) * kDxPitch + col : kDxCols];
+          col += g.Cin;
+          if (--q == q_lo) q += g.R, --p;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) sum += part[u];
+      }
+      if (!last) {
+        *(fv *)&dxS[i * V] = sum;
+        continue;
+      }
       if (mp) {
-        const f4 m = *(const f4 *)&mp[o];
-        sum.x = m.x > 0.f ? sum.x : 0.f, sum.y = m.y > 0.f ? sum.y : 0.f;
-        sum.z = m.z > 0.f ? sum.z : 0.f, sum.w = m.w > 0.f ? sum.w : 0.f;
+        const fv mv = *(const fv *)&mp[i * V];
+#pragma unroll
+        for (int e = 0; e < V; ++e) sum[e] = mv[e] > 0.f ? sum[e] : 0.f;
       }
-      if (accumulate) sum += *(const f4 *)&op[o];
-      *(f4 *)&op[o] = sum;
+      if (accumulate) sum += *(const fv *)&op[i * V];
+      *(fv *)&op[i * V] = sum;
     }
-    return;
-  }
-  for (int i = tid; i < total; i += kWinThreads) {
-    const int pix = (int)fdiv((uint32_t)i, g.dCin), ci = i - pix * g.Cin;
-    const int hh = (int)fdiv((uint32_t)pix, g.dW), w = pix - hh * g.W;
-    float sum = 0.f;
-    for (int rr = 0; rr < g.R; ++rr) {
-      const int p = hh + g.pad - rr;
-      if (p < 0 || p >= g.P) continue;
-      for (int ss = 0; ss < g.R; ++ss) {
-        const int q = w + g.pad - ss;
-        if (q < 0 || q >= g.Q) continue;
-        sum += colS[(p * g.Q + q) * g.ldc + (rr * g.R + ss) * g.Cin + ci];
-      }
-    }
-    if (mp && !(mp[i] > 0.f)) sum = 0.f;
-    op[i] = accumulate ? op[i] + sum : sum;
+    if (!last) __syncthreads();  // the next columns replace these
   }
 }
 
+size_t dx_lds_bytes(const WinGeom &g) { return ((size_t)kWinMaxPix * kDxPitch + (size_t)g.H * g.W * g.Cin) * sizeof(float); }
+
+// an image of at most 64 output pixels and 64 output channels, whose col would fit LDS (beyond, the window is so wide or the
+// channels so many that a direct contraction has full columns to work on) and whose dx fits beside a chunk
 bool make_win_geom(int B, int H, int W, int Cin, int Cout, int R, int pad, WinGeom &g) {
   g.B = B, g.H = H, g.W = W, g.Cin = Cin, g.Cout = Cout, g.R = R, g.pad = pad;
   g.P = H + 2 * pad - R + 1, g.Q = W + 2 * pad - R + 1;
   if (g.P < 1 || g.Q < 1 || g.P * g.Q > kWinMaxPix || Cout > kWinMaxCout || Cout < 1) return false;
+  if ((long long)B * H * W * Cin >= (1LL << 31) || (long long)R * R * Cin > kWinLdsBytes / 4) return false;
   g.NC = R * R * Cin;
-  g.KG = (Cout + 7) / 8;
-  g.lda = win_lda(Cout);
   g.vec = Cin % 4 == 0;
-  g.ldc = g.vec ? g.NC + 4 : g.NC + 1;
-  g.dCin = make_fastdiv(Cin), g.dW = make_fastdiv(W), g.dCout = make_fastdiv(Cout);
+  g.dCin = make_fastdiv(Cin), g.dW = make_fastdiv(W), g.dR = make_fastdiv(R);
   g.dCv = make_fastdiv(g.vec ? Cin / 4 : 1);
-  const long long lds = ((long long)kWinMaxPix * g.lda + (long long)g.P * g.Q * g.ldc) * 4;
-  return lds <= kWinLdsBytes && (long long)B * H * W * Cin < (1LL << 31);
+  const long long col = ((long long)kWinMaxPix * ((Cout + 7) / 8 * 8 + 4) + (long long)g.P * g.Q * (g.NC + (g.vec ? 4 : 1))) * 4;
+  return col <= kWinLdsBytes && dx_lds_bytes(g) <= kWinLdsBytes;
 }
 
 }  // namespace
@@ -187,15 +208,21 @@ hipError_t launch_dgrad_window(hipStream_t st, int n, int B, int H, int W, int C
   WinGeom g;
   if (!make_win_geom(B, H, W, Cin, Cout, R, pad, g) || n < 1 || n > 65535 || B > 65535) return hipErrorInvalidValue;
   if (!aligned_to(dy, 16)) return hipErrorInvalidValue;
-  const size_t lds = ((size_t)kWinMaxPix * g.lda + (size_t)g.P * g.Q * g.ldc) * sizeof(float);
+  const size_t lds = dx_lds_bytes(g);
   static bool raised = false;   // more than 64 KB of dynamic LDS has to be asked for once
   if (!raised) {
-    hipError_t e = hipFuncSetAttribute((const void *)k_dgrad_window, hipFuncAttributeMaxDynamicSharedMemorySize, kWinLdsBytes);
-    if (e != hipSuccess) return e;
+    for (const void *f : {(const void *)k_dgrad_window<4>, (const void *)k_dgrad_window<1>}) {
+      const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kWinLdsBytes);
+      if (e != hipSuccess) return e;
+    }
     raised = true;
   }
-  hipLaunchKernelGGL(k_dgrad_window, dim3(B, n), dim3(kWinThreads), lds, st, g, dy, dy_rs, w, w_rs, mask,
-                     mask_rs, accumulate, dx, dx_rs);
+  if (g.vec)
+    hipLaunchKernelGGL(k_dgrad_window<4>, dim3(B, n), dim3(kWinThreads), lds, st, g, dy, dy_rs, w, w_rs, mask, mask_rs,
+                       accumulate, dx, dx_rs);
+  else
+    hipLaunchKernelGGL(k_dgrad_window<1>, dim3(B, n), dim3(kWinThreads), lds, st, g, dy, dy_rs, w, w_rs, mask, mask_rs,
+                       accumulate, dx, dx_rs);
   return hipGetLastError();
 }
 

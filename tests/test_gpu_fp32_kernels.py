@@ -54,6 +54,26 @@ def test_split_convolutions_match_oracle(gpu, case):
     tk.test_conv_kernels_match_oracle(gpu, case, 0)
 
 
+WINDOW_CASES = [
+    # n, B, H, W, Cin, Cout, k, stride, pad: backward-data with an image per workgroup, 128 columns of products at a time
+    (1, 1, 2, 2, 1, 1, 2, 1, 0),         # one output pixel, one channel
+    (2, 3, 9, 9, 32, 64, 2, 1, 0),       # 128 columns exactly, all 64 pixels and contraction values
+    (1, 2, 6, 6, 33, 17, 2, 1, 0),       # 132 columns: a second chunk of four
+    (1, 2, 5, 12, 132, 16, 2, 1, 0),     # a tap wider than a chunk
+    (1, 2, 6, 6, 131, 33, 2, 1, 0),      # the same, odd
+    (2, 2, 7, 7, 28, 48, 3, 1, 1),       # two chunks, the second nearly full, taps across the seam
+    (1, 3, 4, 8, 15, 63, 3, 1, 1),       # 32 output pixels: one row tile
+    (1, 3, 3, 11, 15, 20, 3, 1, 1),      # 33
+    (3, 2, 10, 10, 7, 50, 7, 1, 2),      # 7 x 7
+    (1, 1, 12, 12, 4, 3, 5, 1, 0),       # a single vector per pixel
+]
+
+
+@pytest.mark.parametrize("case", WINDOW_CASES)
+def test_window_products_match_oracle(gpu, case):
+    tk.test_conv_kernels_match_oracle(gpu, case, 0)
+
+
 @pytest.mark.parametrize("case", [(1, 3, 8, 8, 32, 96, 3, 1, 1), (1, 2, 12, 12, 20, 50, 5, 1, 0), (1, 3, 16, 16, 16, 32, 3, 2, 1)])
 def test_split_convolutions_keep_infinities_and_nan(gpu, case):
     """An infinite or NaN operand reaches the results it reaches in plain arithmetic, with the same sign, and no others:
