@@ -158,7 +158,7 @@ int wgrad_strips_plan(int replicas, const ConvGeom &g, int *chunk_out);
 hipError_t launch_wgrad_strips(hipStream_t st, int replicas, const ConvGeom &g, const WgradIO &io);
 // bf16 plain products with few output tiles: the contraction split over the wavefronts of a workgroup (igemm_ksplit.hip).
 bool gemm_ksplit_applicable(int dtype, int replicas, const ConvGeom &g, const GemmIO &io);
-hipError_t launch_gemm_ksplit(hipStream_t st, int dtype, bool out_f32, int replicas, const ConvGeom &g, const GemmIO &io);
+hipError_t launch_gemm_ksplit(hipStream_t st, bool out_f32, int replicas, const ConvGeom &g, const GemmIO &io);
 // fp32 convolutions as six products of bf16 parts, at fp32 accuracy (igemm_f32.hip).
 bool conv_f32x3_applicable(int dtype, int replicas, const ConvGeom &g, const GemmIO &io);
 hipError_t launch_conv_f32x3(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io);

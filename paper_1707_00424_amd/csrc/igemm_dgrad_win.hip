@@ -227,12 +227,13 @@ hipError_t launch_dgrad_window(hipStream_t st, int n, int B, int H, int W, int C
 }
 
 // ---------------------------------------------------------------------------------------------
-// Backward-weight of the same kind of layer (fp32, stride 1, images of at most 64 output pixels), the window
-// gather done in LDS:   dW[n][(r, s, ci)] = sum over images and output pixels m of dy[m][n] * x[m + (r, s)][ci].
-// A workgroup takes a few images one after the other; per image the input patch (12 x 12 x 20 floats for LeNet's
-// second convolution) and the dy tile lie in LDS, and both MFMA operands are read from there element by element:
-// the (tap, channel) column of a lane is a fixed offset into the patch, the pixel a wavefront-uniform base.  In the
-// generic kernel the same gather runs against global memory, 25 times per input element.  Eight wavefronts own
+// Backward-weight of the same kind of layer (fp32, stride 1, images of at most 64 output pixels) with fewer than 12 input
+// channels (with more, the register kernel of igemm_f32_wgrad.hip takes it), the window gather done in LDS:
+//   dW[n][(r, s, ci)] = sum over images and output pixels m of dy[m][n] * x[m + (r, s)][ci].
+// A workgroup takes a few images one after the other; per image the input patch (12 x 12 x 8 floats, say) and the dy
+// tile lie in LDS, and both MFMA operands are read from there element by element: the (tap, channel) column of a lane
+// is a fixed offset into the patch, the pixel a wavefront-uniform base.  In the generic kernel the same gather runs
+// against global memory, once per tap and input element.  Eight wavefronts own
 // the 2 x 16 tiles of 32 x 32 outputs (two column tiles and both row tiles each); the partial sums of the
 // workgroups are added by the fixed-order reduction every split backward-weight kernel uses.
 // ---------------------------------------------------------------------------------------------

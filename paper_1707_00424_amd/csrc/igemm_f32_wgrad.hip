@@ -9,12 +9,14 @@
 // instruction.  The fragments of the S horizontal taps are the same packed words shifted by one value each, so a row of x
 // is loaded and split once for all of them.  No LDS, no barrier: a wavefront owns 32 output channels, 32 input channels
 // and up to three taps of one row of the window (an accumulator pair each), and walks down strips eight output columns
-// wide and about eight rows high, one strip per lane half, so that images of any size fill the 16-deep contraction; the
-// loads of the next two rows are in flight while one is multiplied.
+// wide and as high as the image (lower where that would leave wavefront slots without strips), one strip per lane half,
+// so that images of any size fill the 16-deep contraction; the loads of the next two rows are in flight while one is
+// multiplied.
 // 3 x 3, 96 -> 96 channels, 32 x 32, batch 3 x 128: 1680 us in the generic kernel (39 TFLOP/s, bound by its per-element
-// gather), 375 us here (174 TFLOP/s; matrix units busy half of the time, the conversions the other half: an in-register
-// split of one row serves 18 MFMAs.  Keeping three rows for all nine taps, 54 MFMAs per split, needs 450 registers, which
-// the compiler spilled: 1600 us).  LeNet's 5 x 5 layer, six replicas: 62 -> 43 us.
+// gather), 375 us here (174 TFLOP/s; matrix units busy half of the time).  Bound by its load instructions: a load takes
+// 16 cycles of the compute unit whatever its width, and the 18 that a wavefront issues for every two rows make 2304 of
+// the 2314 cycles that eight wavefronts take for them.  Keeping three rows for all nine taps, 54 MFMAs per split, needs 450 registers, which
+// the compiler spilled: 1600 us.  LeNet's 5 x 5 layer, six replicas: 62 -> 43 us.
 // BIAS: the wavefronts of the first input-channel tile and window row also add up dy.
 #include "igemm_dev.h"
 #include "igemm_split.h"

@@ -99,8 +99,7 @@ bool gemm_ksplit_applicable(int dtype, int replicas, const ConvGeom &g, const Ge
   return tiles64 <= 256;
 }
 
-hipError_t launch_gemm_ksplit(hipStream_t st, int dtype, bool out_f32, int replicas, const ConvGeom &g, const GemmIO &io) {
-  (void)dtype;
+hipError_t launch_gemm_ksplit(hipStream_t st, bool out_f32, int replicas, const ConvGeom &g, const GemmIO &io) {
   return run_ksplit<bf16_t>(st, out_f32, replicas, g, io);
 }
 

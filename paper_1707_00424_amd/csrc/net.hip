@@ -355,9 +355,9 @@ bool build_plan(Net &N, std::string &err) {
         op.w_as_is = fc_f32_applicable(
             N.dtype, N.n, conv_bwd_geom(ConvShape{N.B, op.Hin, op.Win, op.Cin, op.Cout, op.R, op.stride, op.pad}));
         if (!op.head && !op.w_as_is) op.wt_off = N.alloc((int64_t)N.n * wsize * N.esize);  // the head kernel reads the weights as they lie
-        // few input channels under a wide window (LeNet's second convolution: 20 channels, 25 taps): as a
-        // direct implicit GEMM the pass has 20 output columns on 32-wide fp32 MFMA tiles and a contraction
-        // of 1250; as dy x W (500 columns, contraction 50) plus a gather over the window it is a fraction
+        // few input channels under a wide window (LeNet's second convolution: 20 channels, 25 taps): the direct kernel
+        // fills 20 of 32 output columns and visits every input pixel; as dy x W (500 columns, contraction 50) plus a
+        // gather over the window the pass has no such padding and visits the output pixels only
         if (N.dtype == 0 && op.stride == 1 && op.R > 1 && op.Cin <= 32 && op.R * op.R * op.Cin >= 128 &&
             (int64_t)N.B * op.Ho * op.Wo * op.Cin * op.R * op.R < (1LL << 31)) {
           // the products of one image fit in LDS: one kernel, nothing through memory
@@ -365,9 +365,19 @@ bool build_plan(Net &N, std::string &err) {
             const char *e = getenv("PARLE_DGRAD_WINDOW");
             return !(e && atoi(e) == 0);
           }();
+          // Else two kernels with the products in memory between them, on fp32 matrix instructions, or the direct kernel:
+          // 32 columns per input pixel at 6/16 of that cost against Cin per output pixel and the trip through memory.
+          // Step times, two kernels / direct: 3 x 3 padded, 3 x 128 images of 32 channels 1155 / 758 us, 2 x 64 of 16
+          // channels 388 / 332; unpadded 4 x 4 of 20 channels (the product is 1.1 times the other side of the rule)
+          // 391 / 372, 5 x 5 of 28 (1.2) 206 / 217, of 32 (1.4) 188 / 177, of 20 (0.9) 194 / 214.
+          GemmIO dio{};
+          dio.in_bytes = (int64_t)N.B * op.Ho * op.Wo * op.Cout * 4, dio.ldc = op.Cin;
+          const ConvGeom gb = conv_bwd_geom(ConvShape{N.B, op.Hin, op.Win, op.Cin, op.Cout, op.R, op.stride, op.pad});
+          const bool direct = conv_f32x3_applicable(N.dtype, N.n, gb, dio) &&
+                              (int64_t)op.Hin * op.Win * 10 <= (int64_t)op.Ho * op.Wo * op.Cin;
           if (window_kernel && dgrad_window_applicable(N.dtype, N.B, op.Hin, op.Win, op.Cin, op.Cout, op.R, op.stride, op.pad))
             op.win = true;
-          else
+          else if (!direct)
             col_bytes = std::max(col_bytes, (int64_t)N.n * N.B * op.Ho * op.Wo * op.Cin * op.R * op.R * 4), op.col_off = 0;
         }
       }

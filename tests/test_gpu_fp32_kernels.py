@@ -108,3 +108,14 @@ def test_split_convolutions_keep_infinities_and_nan(gpu, case):
         assert (got[inf] == ref[inf]).all(), name
         assert np.isnan(got[np.isnan(ref)]).all(), name
         tk.assert_near(name, got[fin], ref[fin], 1e-6, 2e-5 * np.abs(ref[fin]).max())
+
+
+@pytest.mark.parametrize("arch", [
+    dict(kind="lenet", H=28, W=28, C=1, c1=20, c2=72, k=5, fc=40, classes=10),   # products through memory
+    dict(kind="lenet", H=28, W=28, C=1, c1=30, c2=72, k=5, fc=40, classes=10),   # directly
+    dict(kind="allcnn", H=12, W=12, C=3, ca=16, cb=32, classes=10),              # directly, padded
+])
+def test_networks_choose_between_two_input_gradient_routes(gpu, monkeypatch, arch):
+    import test_gpu_nets as tn
+    monkeypatch.setitem(tn.SMALL, "route", tn.onets.arch(arch["kind"], **{k: v for k, v in arch.items() if k != "kind"}))
+    tn.test_one_step_loss_and_gradient(gpu, "route", 0)
