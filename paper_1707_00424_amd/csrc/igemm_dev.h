@@ -50,6 +50,13 @@ __device__ __forceinline__ void mma<bf16_t>(const u4 &a, const u4 &b, f16v &acc)
   acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, a), __builtin_bit_cast(bf8, b), acc, 0, 0, 0);
 }
 
+// Notes among a wavefront's results any that is infinite or NaN.
+struct NonFinite {
+  uint32_t most = 0;  // twice the largest magnitude
+  __device__ __forceinline__ void add(float v) { most = max(most, __float_as_uint(v) << 1); }
+  __device__ __forceinline__ bool any() const { return __any(most >= 0xff000000u); }
+};
+
 template <typename T, int VW>
 __device__ __forceinline__ u4 pack_vec(const T *tmp) {
   u4 r;

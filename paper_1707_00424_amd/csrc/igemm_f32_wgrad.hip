@@ -18,6 +18,11 @@
 // the 2314 cycles that eight wavefronts take for them.  Keeping three rows for all nine taps, 54 MFMAs per split, needs 450 registers, which
 // the compiler spilled: 1600 us.  LeNet's 5 x 5 layer, six replicas: 62 -> 43 us.
 // BIAS: the wavefronts of the first input-channel tile and window row also add up dy.
+// A wavefront with a result that is not finite walks its strips a second time in plain fp32.  Such results come from
+// infinities and NaN, whose corrections are NaN, and from operands beyond the
+// largest bf16 value (3.39e38), whose x0 is infinite.  Where the width is no multiple of 8 there is a third source: the last columns of a strip lie beyond the row,
+// their dy is zero, and the x values beside them belong to other taps; an infinity there would make 0 * inf of it.  The
+// second walk sets them to zero, which the first need not do: 0 * x adds nothing while x is finite.
 #include "igemm_dev.h"
 #include "igemm_split.h"
 #include "igemm_strips.h"
@@ -124,6 +129,29 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(OCC))) void 
       row_product(dw, xw);
     }
   }
+  NonFinite odd;
+#pragma unroll
+  for (int s = 0; s < S; ++s)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) hi[s][v] += lo[s][v], odd.add(hi[s][v]);
+  if (odd.any()) {  // see above: the same sums on fp32 matrix instructions, a pixel of either strip at a time
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) hi[s][v] = 0.f;
+    walk.restart();
+    for (int t = 0; t < rows; ++t) {
+      const int live = walk.live_columns();
+      walk.template load<4, 4>(xr[0], dr[0]);
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+          const float xv = __uint_as_float(xr[0][(s % SP == 0 ? 0 : L0) + s / SP + e]);
+          hi[s] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(dr[0][e]), e < live ? xv : 0.f, hi[s], 0, 0, 0);
+        }
+    }
+  }
 
   // register v of a lane: output channel 8*(v/4) + 4*h + v%4 of the tile, input channel `ch`
   float *out = io.out + rep * io.out_rs + un.split * io.split_stride;
@@ -132,8 +160,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(OCC))) void 
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int nn = un.ntile * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
-      const float hv = hi[s][v], t = hv + lo[s][v];
-      if (nn < g.N && c < g.Cc && s0 + s < g.S) out[(long long)nn * g.K + (r * g.S + s0 + s) * g.Cc + c] = t == t ? t : hv;
+      if (nn < g.N && c < g.Cc && s0 + s < g.S) out[(long long)nn * g.K + (r * g.S + s0 + s) * g.Cc + c] = hi[s][v];
     }
   if (tally) {
     bsum += __shfl_xor(bsum, 32, 64);

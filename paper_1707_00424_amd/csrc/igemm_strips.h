@@ -59,12 +59,23 @@ struct StripWalk {
   __device__ __forceinline__ StripWalk(const ConvGeom &g_, const StripGeom &wg_, const WgradIO &io, int rep, const StripUnit &u,
                                        int h_, int c_, int n_)
       : g(g_), wg(wg_), r(u.r), s0(u.s0), h(h_), c(c_), n(n_) {
-    first = u.split * wg.pps, last = min(wg.pairs, first + wg.pps), pair = first;
+    first = u.split * wg.pps, last = min(wg.pairs, first + wg.pps);
     x_ptr = (void *)((const char *)io.x + rep * io.x_rs * ES);
     x_bytes = (int)((long long)wg.images * g.Hin * g.Win * g.Cc * ES);
     d_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)((const char *)io.dy + rep * io.dy_rs * ES), 0,
                                                (int)((long long)g.M * g.N * ES), 0x00020000);
+    restart();
+  }
+  __device__ __forceinline__ void restart() {
+    pair = first;
     set_strip();
+  }
+  // output columns of this lane's strip, which is loaded next, inside the image row: where it is less than 8, dy is zero
+  // for the others, but the x values beside them may belong to other taps of the row
+  __device__ __forceinline__ int live_columns() const {
+    const int in_group = pair - (int)fdiv((uint32_t)pair, wg.dPpg) * wg.ppg;
+    const int strip = 2 * (in_group - (int)fdiv((uint32_t)in_group, wg.dPph) * wg.pph) + h;
+    return g.Q - (strip - (int)fdiv((uint32_t)strip, wg.dSegs) * wg.segs) * 8;
   }
   __device__ __forceinline__ void set_strip() {
     const int group = (int)fdiv((uint32_t)pair, wg.dPpg), in_group = pair - group * wg.ppg;

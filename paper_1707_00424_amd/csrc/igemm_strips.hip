@@ -15,6 +15,9 @@
 // generic kernel gathers element by element: 50 -> 64 channels on 16 x 16, batch 6 x 50, layer pass 187 -> 149 us; 20 -> 50
 // on 28 x 28, 2 x 100, 265 -> 220 us.
 // P: channels per lane, 1 where a count is odd.
+// Where the width is no multiple of 8, the last columns of a strip lie beyond the row: dy is zero there, and the x values
+// beside it belong to other taps.  0 * x adds nothing while x is finite; a wavefront with a result that is not finite
+// walks its strips a second time with those values set to zero.
 #include "igemm_dev.h"
 #include "igemm_strips.h"
 
@@ -36,20 +39,28 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(P == 2 ? 1 :
   Walk walk(g, wg, io, rep, un, h, c, n);
 
   f16v acc[P][P][S];
+  auto each_acc = [&](auto f) {
 #pragma unroll
-  for (int i = 0; i < P; ++i)
+    for (int i = 0; i < P; ++i)
 #pragma unroll
-    for (int j = 0; j < P; ++j)
+      for (int j = 0; j < P; ++j)
 #pragma unroll
-      for (int s = 0; s < S; ++s)
+        for (int s = 0; s < S; ++s)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[i][j][s][v] = 0.f;
+          for (int v = 0; v < 16; ++v) {
+            float a = acc[i][j][s][v];
+            f(a);
+            acc[i][j][s][v] = a;
+          }
+  };
+  each_acc([](float &a) { a = 0.f; });
 
   // channel `par` of values a (low half of the result) and b
   auto pair = [](uint32_t a, uint32_t b, int par) {
     return __builtin_amdgcn_perm(b, a, par ? 0x07060302u : 0x05040100u);
   };
-  auto multiply = [&](const uint32_t (&xv)[NX], const uint32_t (&dv)[8]) {
+  // MASKED: only the first `live` columns of x
+  auto multiply = [&](auto masked, int live, const uint32_t (&xv)[NX], const uint32_t (&dv)[8]) {
     u4 a[P], b[P][S];
 #pragma unroll
     for (int i = 0; i < P; ++i) {
@@ -60,6 +71,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(P == 2 ? 1 :
         for (int s = 0; s < S; ++s) {
           const int v = (s % SP ? L0 : 0) + s / SP + 2 * e;
           b[i][s][e] = pair(xv[v], xv[v + 1], i);
+          if (decltype(masked)::value) b[i][s][e] &= live > 2 * e + 1 ? ~0u : live > 2 * e ? 0xffffu : 0u;
         }
       }
     }
@@ -78,8 +90,21 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(P == 2 ? 1 :
   for (int t = 0; t < rows; t += D) {  // rows beyond the last are zeros
 #pragma unroll
     for (int i = 0; i < D; ++i) {
-      multiply(xr[i], dr[i]);
+      multiply(std::false_type{}, 8, xr[i], dr[i]);
       walk.template load<2 * P, 2 * P>(xr[i], dr[i]);
+    }
+  }
+  if (g.Q % 8 != 0) {
+    NonFinite odd;
+    each_acc([&](float &a) { odd.add(a); });
+    if (odd.any()) {
+      each_acc([](float &a) { a = 0.f; });
+      walk.restart();
+      for (int t = 0; t < rows; ++t) {
+        const int live = walk.live_columns();
+        walk.template load<2 * P, 2 * P>(xr[0], dr[0]);
+        multiply(std::true_type{}, live, xr[0], dr[0]);
+      }
     }
   }
 

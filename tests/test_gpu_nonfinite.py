@@ -1,0 +1,70 @@
+"""Operands at and beyond the ends of the number format, through the convolution kernels: infinities and NaN reach the
+results they reach in plain arithmetic and no others."""
+import numpy as np
+import pytest
+
+import test_gpu_kernels as tk
+
+pytestmark = pytest.mark.gpu
+gpu = tk.gpu
+
+
+def shapes(case):
+    n, B, H, W, Cin, Cout, k, stride, pad = case
+    Ho, Wo = (H + 2 * pad - k) // stride + 1, (W + 2 * pad - k) // stride + 1
+    return (n, B, H, W, Cin), (n, Cout, k, k, Cin), (n, B, Ho, Wo, Cout)
+
+
+def weight_and_bias_gradient(torch, pb, case, dtype, x, dy):
+    """Replica 0's weight gradient, and its bias gradient where the kernel takes it along (else None)."""
+    _, ws, _ = shapes(case)
+    desc = pb.parle_conv_desc(dtype, *case)
+    dx_, ddy = tk.upload(torch, x, dtype), tk.upload(torch, dy, dtype)
+    wsize, cout = int(np.prod(ws[1:])), ws[1]
+    scratch = torch.zeros(max(pb.parle_k_conv_scratch_bytes(desc) // 4, 4), dtype=torch.float32, device="cuda")
+    gw = torch.zeros((ws[0], wsize + cout), dtype=torch.float32, device="cuda")
+    took = pb.parle_k_conv_backward_weight_bias(desc, ddy, dx_, scratch, gw)
+    torch.cuda.synchronize()
+    gw = tk.download(gw[0])
+    return gw[:wsize].reshape(ws[1:]), (gw[wsize:] if took else None)
+
+
+def assert_same_kind(name, got, ref):
+    """Finite where the reference is and near it, the same infinities, NaN where it has them."""
+    fin = np.isfinite(ref)
+    assert (np.isfinite(got) == fin).all(), f"{name}: {np.sum(np.isfinite(got) != fin)} of {ref.size} differ in kind"
+    inf = np.isinf(ref)
+    assert (got[inf] == ref[inf]).all(), name
+    assert np.isnan(got[np.isnan(ref)]).all(), name
+    if fin.any():
+        tk.assert_near(name, got[fin], ref[fin], 1e-6, 2e-5 * np.abs(ref[fin]).max())
+
+
+RAGGED = [
+    # dtype, (n, B, H, W, Cin, Cout, k, stride, pad): output rows that are no multiple of eight columns
+    (0, (1, 3, 7, 7, 24, 36, 3, 1, 1)),
+    (0, (1, 2, 12, 12, 20, 50, 5, 1, 2)),    # four dead columns under a 5 x 5 window
+    (0, (1, 2, 9, 28, 16, 32, 3, 1, 1)),
+    (0, (1, 2, 9, 28, 16, 32, 3, 2, 1)),     # stride 2: even and odd columns
+    (0, (1, 2, 16, 15, 13, 40, 7, 1, 3)),    # three groups of taps per window row
+    (1, (1, 3, 7, 7, 20, 36, 3, 1, 1)),      # bf16, two channels per lane
+    (1, (1, 2, 9, 28, 17, 33, 3, 1, 1)),     # one channel per lane
+    (1, (1, 2, 9, 28, 18, 34, 3, 2, 1)),
+]
+
+
+@pytest.mark.parametrize("dtype,case", RAGGED)
+def test_infinity_in_the_last_column_stays_in_its_taps(gpu, dtype, case):
+    """The last column of x reaches the taps that some output column reads it through, and no tap beyond the row."""
+    torch, pb = gpu
+    stride, pad = case[7:]
+    xs, ws, ys = shapes(case)
+    rng = np.random.default_rng(3)
+    q = tk.to_bf16_grid if dtype else (lambda a: np.asarray(a, np.float32))
+    x, dy = q(rng.standard_normal(xs)), q(rng.standard_normal(ys))
+    x[0, 0, 3, -1, 1], x[0, 1, 4, -1, 2], x[0, 1, 5, -2, 12] = np.inf, np.nan, -np.inf
+    with np.errstate(invalid="ignore"):
+        _, _, ref = tk.oracle_conv(x[0], np.zeros(ws[1:]), None, None, False, stride, pad, dy[0])
+    assert np.isfinite(ref[..., 1]).any(), "the case has a tap that the infinity does not reach"
+    got, _ = weight_and_bias_gradient(torch, pb, case, dtype, x, dy)
+    assert_same_kind("weight gradient", got, ref)
