@@ -19,7 +19,7 @@
 // the compiler spilled: 1600 us.  LeNet's 5 x 5 layer, six replicas: 62 -> 43 us.
 // BIAS: the wavefronts of the first input-channel tile and window row also add up dy.
 // A wavefront with a result that is not finite walks its strips a second time in plain fp32.  Such results come from
-// infinities and NaN, whose corrections are NaN, and from operands beyond the
+// infinities and NaN, whose corrections are NaN (as is the compensation of the sum of dy), and from operands beyond the
 // largest bf16 value (3.39e38), whose x0 is infinite.  Where the width is no multiple of 8 there is a third source: the last columns of a strip lie beyond the row,
 // their dy is zero, and the x values beside them belong to other taps; an infinity there would make 0 * inf of it.  The
 // second walk sets them to zero, which the first need not do: 0 * x adds nothing while x is finite.
@@ -130,11 +130,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(OCC))) void 
     }
   }
   NonFinite odd;
+  odd.add(bsum);
 #pragma unroll
   for (int s = 0; s < S; ++s)
 #pragma unroll
     for (int v = 0; v < 16; ++v) hi[s][v] += lo[s][v], odd.add(hi[s][v]);
   if (odd.any()) {  // see above: the same sums on fp32 matrix instructions, a pixel of either strip at a time
+    bsum = 0.f;
 #pragma unroll
     for (int s = 0; s < S; ++s)
 #pragma unroll
@@ -144,12 +146,15 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(OCC))) void 
       const int live = walk.live_columns();
       walk.template load<4, 4>(xr[0], dr[0]);
 #pragma unroll
-      for (int e = 0; e < 8; ++e)
+      for (int e = 0; e < 8; ++e) {
+        const float dv = __uint_as_float(dr[0][e]);
+        bsum += dv;
 #pragma unroll
         for (int s = 0; s < S; ++s) {
           const float xv = __uint_as_float(xr[0][(s % SP == 0 ? 0 : L0) + s / SP + e]);
-          hi[s] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(dr[0][e]), e < live ? xv : 0.f, hi[s], 0, 0, 0);
+          hi[s] = __builtin_amdgcn_mfma_f32_32x32x2f32(dv, e < live ? xv : 0.f, hi[s], 0, 0, 0);
         }
+      }
     }
   }
 

@@ -68,3 +68,19 @@ def test_infinity_in_the_last_column_stays_in_its_taps(gpu, dtype, case):
     assert np.isfinite(ref[..., 1]).any(), "the case has a tap that the infinity does not reach"
     got, _ = weight_and_bias_gradient(torch, pb, case, dtype, x, dy)
     assert_same_kind("weight gradient", got, ref)
+
+
+@pytest.mark.parametrize("case", [(1, 3, 7, 7, 24, 36, 3, 1, 1), (1, 2, 16, 16, 16, 32, 3, 1, 1)])
+def test_infinite_gradient_leaves_an_infinite_bias_gradient(gpu, case):
+    torch, pb = gpu
+    xs, ws, ys = shapes(case)
+    rng = np.random.default_rng(4)
+    x, dy = (rng.standard_normal(s).astype(np.float32) for s in (xs, ys))
+    dy[0, 0, 2, 3, 5], dy[0, 1, 1, 1, 6], dy[0, 1, 2, 2, 7] = np.inf, -np.inf, np.nan
+    got, bias = weight_and_bias_gradient(torch, pb, case, 0, x, dy)
+    assert bias is not None
+    with np.errstate(invalid="ignore"):
+        ref = dy[0].astype(np.float64).sum(axis=(0, 1, 2))
+        _, _, rdw = tk.oracle_conv(x[0], np.zeros(ws[1:]), None, None, False, *case[7:], dy[0])
+    assert_same_kind("bias gradient", bias, ref)
+    assert_same_kind("weight gradient", got, rdw)
