@@ -40,6 +40,21 @@ struct WinGeom {
   FastDiv dCin, dW, dCv, dR;             // no integer division on the device (dCv: vectors of a pixel)
 };
 
+// One element of dx in plain fp32, a tap's products added up first as in the kernel: for elements the split products leave
+// without a finite value, because an operand is not finite itself or has an infinite first part (igemm_f32.hip).
+__device__ float plain_dx(const WinGeom &g, const float *dy, const float *w, int hh, int ww, int c) {
+  float sum = 0.f;
+  for (int r = 0; r < g.R; ++r)
+    for (int s = 0; s < g.R; ++s) {
+      const int p = hh + g.pad - r, q = ww + g.pad - s;
+      if ((unsigned)p >= (unsigned)g.P || (unsigned)q >= (unsigned)g.Q) continue;
+      float tap = 0.f;
+      for (int n = 0; n < g.Cout; ++n) tap = fmaf(dy[(p * g.Q + q) * g.Cout + n], w[(long long)n * g.NC + (r * g.R + s) * g.Cin + c], tap);
+      sum += tap;
+    }
+  return sum;
+}
+
 // V: consecutive channels a thread gathers at a time (4 or 1)
 template <int V>
 __global__ __launch_bounds__(kWinThreads, 4) void k_dgrad_window(const WinGeom g, const float *__restrict__ dy, long long dy_rs,
@@ -129,10 +144,8 @@ __global__ __launch_bounds__(kWinThreads, 4) void k_dgrad_window(const WinGeom g
         }
       // accumulator v of a lane: row 8*(v/4) + 4*h + v%4 of its row tile, column r32 of the wavefront's columns
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const float t = hi[v] + lo[v];
-        colS[(row0 + 8 * (v >> 2) + 4 * h + (v & 3)) * kDxPitch + wc * 32 + r32] = t == t ? t : hi[v];
-      }
+      for (int v = 0; v < 16; ++v)
+        colS[(row0 + 8 * (v >> 2) + 4 * h + (v & 3)) * kDxPitch + wc * 32 + r32] = hi[v] + lo[v];
     }
     __syncthreads();
     const bool last = c0 + kDxCols >= g.NC;
@@ -166,6 +179,9 @@ __global__ __launch_bounds__(kWinThreads, 4) void k_dgrad_window(const WinGeom g
         *(fv *)&dxS[i * V] = sum;
         continue;
       }
+#pragma unroll
+      for (int e = 0; e < V; ++e)
+        if (__builtin_expect(not_finite(sum[e]), 0)) sum[e] = plain_dx(g, dyp, w + rep * w_rs, hh, ww, c + e);
       if (mp) {
         const fv mv = *(const fv *)&mp[i * V];
 #pragma unroll

@@ -10,8 +10,9 @@
 // at the end.  Relative error against 64 bits on random operands, contraction 64 / 864 / 2880 / 32768: fp32 MFMA
 // 1.0e-7 / 3.7e-7 / 6.7e-7 / 2.3e-6, this 0.41e-7 / 1.3e-7 / 2.6e-7 / 1.1e-6 (16 products are added per rounding instead
 // of 2); with one accumulator for all six it would be 1.1e-7 / 4.2e-7 / 7.8e-7 / 2.8e-6.
-// An infinite or NaN operand makes the corrections NaN (inf - inf); the result is then the x0*y0 sum alone, which is
-// what fp32 arithmetic gives: inf, or NaN where infinities of both signs or an infinity and a zero meet.
+// Where an operand is infinite or NaN the corrections are NaN (inf - inf), and an operand beyond the largest bf16 value
+// (3.39e38; the largest float is 3.40e38) has an infinite x0.  A workgroup that finds a result that is not finite runs its
+// contraction a second time with fp32 MFMA on the values as they are, so such operands give what plain fp32 gives.
 //
 // The input patch of a workgroup's output pixels is staged once per 16 channels, split as it is stored to LDS (5.5 vector
 // instructions per value), and serves all taps.  A tile is a number of whole output rows, counted through all images
@@ -57,6 +58,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
   constexpr int BN = TN * 32;
   constexpr int H_IT = (SLOTS * 4 + kThreads - 1) / kThreads, B_IT = (BN * 4 + kThreads - 1) / kThreads;
   __shared__ __attribute__((aligned(16))) char smem[f32_lds_bytes<TN, SLOTS>()];
+  __shared__ int again;  // whether the tile takes the second pass
   char *const Hs = smem, *const Bs = smem + SLOTS * kSlotBytes;  // patch; two weight tiles
 
   // column blocks of one pixel tile differ by 8 in the workgroup id: the same XCD, whose L2 then holds the patch for all
@@ -134,18 +136,23 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
 #pragma unroll
     for (int it = 0; it < H_IT; ++it) hreg[it] = load_piece(a_rsrc, h_off[it], (uint32_t)chunk * kChunk * 4u, chunk * kChunk + (tid & 3) * 4);
   };
-  auto store_piece = [&](char *dst, const u4 &v) {
-    const float f[4] = {__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w)};
-    uint32_t p[3][2];
-    split_words<4>(f, p);
+  // PLAIN: the values as they are, 16 channels in 64 bytes, for the second pass
+  auto store_piece = [&](auto plain, char *slot, int quarter, const u4 &v) {
+    if constexpr (decltype(plain)::value) {
+      *(u4 *)(slot + quarter * 16) = v;
+    } else {
+      const float f[4] = {__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w)};
+      uint32_t p[3][2];
+      split_words<4>(f, p);
 #pragma unroll
-    for (int s = 0; s < 3; ++s) *(u2 *)(dst + s * kPlane) = u2{p[s][0], p[s][1]};
+      for (int s = 0; s < 3; ++s) *(u2 *)(slot + quarter * 8 + s * kPlane) = u2{p[s][0], p[s][1]};
+    }
   };
-  auto store_halo = [&]() {
+  auto store_halo = [&](auto plain) {
 #pragma unroll
     for (int it = 0; it < H_IT; ++it) {
       const int piece = it * kThreads + tid;
-      if (SLOTS * 4 % kThreads == 0 || piece < SLOTS * 4) store_piece(Hs + (piece >> 2) * kSlotBytes + (piece & 3) * 8, hreg[it]);
+      if (SLOTS * 4 % kThreads == 0 || piece < SLOTS * 4) store_piece(plain, Hs + (piece >> 2) * kSlotBytes, piece & 3, hreg[it]);
     }
   };
   // weight tile of step t: channels of chunk t / RS at tap t % RS
@@ -158,12 +165,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     for (int i = 0; i < B_IT; ++i) breg[i] = load_piece(b_rsrc, b_off[i], kb, c);
     if (++ld_tap == RS) ld_tap = 0, ++ld_chunk;
   };
-  auto store_b = [&](int buf, const u4 (&breg)[B_IT]) {
+  auto store_b = [&](auto plain, int buf, const u4 (&breg)[B_IT]) {
 #pragma unroll
     for (int i = 0; i < B_IT; ++i) {
       const int piece = i * kThreads + tid;
       if (BN * 4 % kThreads == 0 || piece < BN * 4)
-        store_piece(Bs + (buf * BN + (piece >> 2)) * kSlotBytes + (piece & 3) * 8, breg[i]);
+        store_piece(plain, Bs + (buf * BN + (piece >> 2)) * kSlotBytes, piece & 3, breg[i]);
     }
   };
   auto shift_of = [&](int r, int c) {
@@ -172,88 +179,107 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
   };
 
   f16v hi[TM][TN], lo[TM][TN];
-#pragma unroll
-  for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-    for (int tn = 0; tn < TN; ++tn)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) hi[tm][tn][v] = 0.f, lo[tm][tn][v] = 0.f;
   // D = A x B with the pixel index in the registers (rows) for the direct epilogue, in the lanes for the one through LDS
-  auto product = [&](const u4 (&a)[TM], const u4 (&b)[TN], f16v (&acc)[TM][TN]) {
+  auto product = [&](auto type, const u4 (&a)[TM], const u4 (&b)[TN], f16v (&acc)[TM][TN]) {
+    typedef decltype(type) T;
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
       for (int tn = 0; tn < TN; ++tn) {
         if (ROWS)
-          mma<bf16_t>(b[tn], a[tm], acc[tm][tn]);
+          mma<T>(b[tn], a[tm], acc[tm][tn]);
         else
-          mma<bf16_t>(a[tm], b[tn], acc[tm][tn]);
+          mma<T>(a[tm], b[tn], acc[tm][tn]);
       }
   };
-
-  u4 rq[2][B_IT];  // weight tiles in flight: the tile stored in step t was requested in step t - 1
-  load_halo(0);
-  load_b(rq[0]);
-  load_b(rq[1]);
-  store_halo();
-  load_halo(1);
-  store_b(0, rq[0]);
-  load_b(rq[0]);
-  __syncthreads();
-  int chunk = 0, tap_r = 0, tap_s = 0;
-  auto step = [&](int t, u4 (&ra)[B_IT]) {  // `ra` holds tile t + 1 and then receives tile t + 3
-    const int shift = shift_of(tap_r, tap_s);
-    const char *bt = Bs + (t & 1) * BN * kSlotBytes + b_lds;
-    u4 a[3][TM], b[3][TN];
+  auto contract = [&](auto plain) {
+    constexpr bool PLAIN = decltype(plain)::value;
 #pragma unroll
-    for (int s = 0; s < 3; ++s) {
+    for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
-      for (int tm = 0; tm < TM; ++tm) a[s][tm] = *(const u4 *)(Hs + a_lds[tm] + shift + s * kPlane);
+      for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
-      for (int tn = 0; tn < TN; ++tn) b[s][tn] = *(const u4 *)(bt + tn * 32 * kSlotBytes + s * kPlane);
-    }
-    product(a[0], b[0], hi);
-    product(a[0], b[1], lo);
-    product(a[1], b[0], lo);
-    product(a[1], b[1], lo);
-    product(a[0], b[2], lo);
-    product(a[2], b[0], lo);
-    if (++tap_s == g.S) {
-      tap_s = 0;
-      if (++tap_r == g.R) tap_r = 0;
-    }
-    if (t + 1 < KT) {
-      store_b((t + 1) & 1, ra);
-      load_b(ra);
-      if (tap_r == 0 && tap_s == 0) {
-        __syncthreads();  // every wavefront has its fragments of the old patch
-        ++chunk;
-        store_halo();
-        load_halo(chunk + 1);
+        for (int v = 0; v < 16; ++v) hi[tm][tn][v] = 0.f, lo[tm][tn][v] = 0.f;
+    u4 rq[2][B_IT];  // weight tiles in flight: the tile stored in step t was requested in step t - 1
+    ld_chunk = 0, ld_tap = 0;
+    load_halo(0);
+    load_b(rq[0]);
+    load_b(rq[1]);
+    store_halo(plain);
+    load_halo(1);
+    store_b(plain, 0, rq[0]);
+    load_b(rq[0]);
+    __syncthreads();
+    int chunk = 0, tap_r = 0, tap_s = 0;
+    auto step = [&](int t, u4 (&ra)[B_IT]) {  // `ra` holds tile t + 1 and then receives tile t + 3
+      const int shift = shift_of(tap_r, tap_s);
+      const char *bt = Bs + (t & 1) * BN * kSlotBytes + b_lds;
+      constexpr int PARTS = PLAIN ? 2 : 3;  // three parts of 16 channels, or two times eight channels
+      u4 a[PARTS][TM], b[PARTS][TN];
+#pragma unroll
+      for (int s = 0; s < PARTS; ++s) {
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm) a[s][tm] = *(const u4 *)(Hs + a_lds[tm] + shift + s * kPlane);
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn) b[s][tn] = *(const u4 *)(bt + tn * 32 * kSlotBytes + s * kPlane);
       }
-      __syncthreads();
+      if constexpr (PLAIN) {
+        product(float{}, a[0], b[0], hi);
+        product(float{}, a[1], b[1], hi);
+      } else {
+        product(bf16_t{}, a[0], b[0], hi);
+        product(bf16_t{}, a[0], b[1], lo);
+        product(bf16_t{}, a[1], b[0], lo);
+        product(bf16_t{}, a[1], b[1], lo);
+        product(bf16_t{}, a[0], b[2], lo);
+        product(bf16_t{}, a[2], b[0], lo);
+      }
+      if (++tap_s == g.S) {
+        tap_s = 0;
+        if (++tap_r == g.R) tap_r = 0;
+      }
+      if (t + 1 < KT) {
+        store_b(plain, (t + 1) & 1, ra);
+        load_b(ra);
+        if (tap_r == 0 && tap_s == 0) {
+          __syncthreads();  // every wavefront has its fragments of the old patch
+          ++chunk;
+          store_halo(plain);
+          load_halo(chunk + 1);
+        }
+        __syncthreads();
+      }
+    };
+    int t = 0;
+    for (; t + 1 < KT; t += 2) {
+      step(t, rq[1]);
+      step(t + 1, rq[0]);
     }
+    if (t < KT) step(t, rq[1]);
   };
-  int t = 0;
-  for (; t + 1 < KT; t += 2) {
-    step(t, rq[1]);
-    step(t + 1, rq[0]);
-  }
-  if (t < KT) step(t, rq[1]);
-
+  if (tid == 0) again = 0;
+  contract(std::false_type{});
+  NonFinite odd;
 #pragma unroll
   for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
     for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const float h = hi[tm][tn][v], r = h + lo[tm][tn][v];
-        hi[tm][tn][v] = r == r ? r : h;
-      }
+      for (int v = 0; v < 16; ++v) hi[tm][tn][v] += lo[tm][tn][v], odd.add(hi[tm][tn][v]);
+  if (odd.any()) again = 1;
+  __syncthreads();  // patch and weight tiles are dead
+  if (__builtin_expect(again, 0)) {
+    // the pass works its addresses out anew: kept through the first pass, they would cost it registers
+#pragma unroll
+    for (int it = 0; it < H_IT; ++it) asm volatile("" : "+v"(h_off[it]));
+#pragma unroll
+    for (int i = 0; i < B_IT; ++i) asm volatile("" : "+v"(b_off[i]));
+    contract(std::true_type{});
+    __syncthreads();
+  }
   ConvGeom gt = g;
   gt.M = min(g.M, m0 + fg.TH * g.Q);  // rows beyond the tile belong to the next one
-  if (ROWS) {
-    __syncthreads();  // patch and weight tiles are dead, their LDS becomes the staging strips
+  if (ROWS) {  // the LDS of patch and weight tiles becomes the staging strips
     store_tile_lds<float, TM, TN, false>(gt, io, rep, m0 + wave * TM * 32, n0, lane, hi,
                                          reinterpret_cast<float *>(smem) + wave * kStageFloats<TN>);
   } else {

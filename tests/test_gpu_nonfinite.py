@@ -84,3 +84,54 @@ def test_infinite_gradient_leaves_an_infinite_bias_gradient(gpu, case):
         _, _, rdw = tk.oracle_conv(x[0], np.zeros(ws[1:]), None, None, False, *case[7:], dy[0])
     assert_same_kind("bias gradient", bias, ref)
     assert_same_kind("weight gradient", got, rdw)
+
+
+SPLIT = [
+    # n, B, H, W, Cin, Cout, k, stride, pad: every form of the kernels that split fp32 values into bf16 parts
+    (1, 3, 16, 16, 32, 64, 3, 1, 1),     # results in whole rows
+    (1, 3, 15, 15, 33, 47, 3, 1, 1),     # odd counts, results straight from the accumulators
+    (1, 2, 14, 14, 50, 20, 3, 2, 1),     # stride 2
+    (1, 2, 12, 12, 20, 50, 5, 1, 0),     # input gradient with an image per workgroup
+    (1, 2, 7, 7, 28, 48, 3, 1, 1),
+]
+
+
+def three_products(torch, pb, case, x, w, dy):
+    """Replica 0's forward result, input gradient and weight gradient in fp32."""
+    xs, ws, ys = shapes(case)
+    desc = pb.parle_conv_desc(0, *case)
+    dx_, dw_, ddy = (tk.upload(torch, a, 0) for a in (x, w, dy))
+    y, gx, gw = (torch.zeros(s, dtype=torch.float32, device="cuda") for s in (ys, xs, ws))
+    scratch = torch.zeros(max(pb.parle_k_conv_scratch_bytes(desc) // 4, 4), dtype=torch.float32, device="cuda")
+    pb.parle_k_conv_forward(desc, dx_, dw_, None, None, 0, y)
+    pb.parle_k_conv_backward_data(desc, ddy, dw_, None, 0, torch.zeros_like(dw_), gx)
+    pb.parle_k_conv_backward_weight(desc, ddy, dx_, scratch, gw)
+    torch.cuda.synchronize()
+    return [tk.download(t[0]) for t in (y, gx, gw)]
+
+
+def assert_within_fp32(case, got, x, w, dy):
+    """Every result within the bound of a plain fp32 sum: a rounding of 2^-24 per product, of the sum of their magnitudes."""
+    stride, pad = case[7:]
+    refs = tk.oracle_conv(x[0], w[0], None, None, False, stride, pad, dy[0])
+    sizes = tk.oracle_conv(np.abs(x[0]), np.abs(w[0]), None, None, False, stride, pad, np.abs(dy[0]))
+    _, (_, co, k, _, ci), (_, B, Ho, Wo, _) = shapes(case)
+    for name, g, ref, size, terms in zip(("forward", "input gradient", "weight gradient"), got, refs, sizes,
+                                         (k * k * ci, k * k * co, B * Ho * Wo)):
+        outside = ~(np.abs(g - ref) <= terms * 2.0 ** -24 * size)  # NaN counts
+        assert not outside.any(), f"{name}: {outside.sum()} of {ref.size} outside"
+
+
+@pytest.mark.parametrize("case", SPLIT)
+def test_operands_beyond_the_largest_bf16_value(gpu, case):
+    """Floats from 3.396e38 up round to an infinite bf16 value; their products with small numbers are finite."""
+    torch, pb = gpu
+    xs, ws, ys = shapes(case)
+    big = np.finfo(np.float32).max
+    places = [((0, 0, 3, 4, 1), (0, 1, 5, 2, 3)), ((0, 2, 1, 1, 4), (0, 5, 0, 1, 2)), ((0, 0, 2, 2, 5), (0, 1, 1, 3, 0))]
+    for turn in range(3):  # x, w, dy in turn
+        rng = np.random.default_rng(6)
+        operands = [1e-3 * rng.standard_normal(s).astype(np.float32) for s in (xs, ws, ys)]
+        first, second = places[turn]
+        operands[turn][first], operands[turn][second] = big, -np.float32(3.3962e38)
+        assert_within_fp32(case, three_products(torch, pb, case, *operands), *operands)
