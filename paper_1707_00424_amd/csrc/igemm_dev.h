@@ -50,8 +50,6 @@ __device__ __forceinline__ void mma<bf16_t>(const u4 &a, const u4 &b, f16v &acc)
   acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, a), __builtin_bit_cast(bf8, b), acc, 0, 0, 0);
 }
 
-__device__ __forceinline__ bool not_finite(float v) { return (__float_as_uint(v) << 1) >= 0xff000000u; }
-
 // Notes among a wavefront's results any that is infinite or NaN.
 struct NonFinite {
   uint32_t most = 0;  // twice the largest magnitude

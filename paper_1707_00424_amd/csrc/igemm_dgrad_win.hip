@@ -40,19 +40,27 @@ struct WinGeom {
   FastDiv dCin, dW, dCv, dR;             // no integer division on the device (dCv: vectors of a pixel)
 };
 
-// One element of dx in plain fp32, a tap's products added up first as in the kernel: for elements the split products leave
-// without a finite value, because an operand is not finite itself or has an infinite first part (igemm_f32.hip).
-__device__ float plain_dx(const WinGeom &g, const float *dy, const float *w, int hh, int ww, int c) {
-  float sum = 0.f;
+// V elements of dx in plain fp32, a tap's products added up first as in the kernel: for results that split products do not
+// give (see igemm_split.h).
+template <int V>
+__device__ __forceinline__ void plain_dx(const WinGeom &g, const float *dy, const float *w, int hh, int ww, int c, float (&sum)[V]) {
+  typedef float fu __attribute__((ext_vector_type(V), aligned(4)));
   for (int r = 0; r < g.R; ++r)
     for (int s = 0; s < g.R; ++s) {
       const int p = hh + g.pad - r, q = ww + g.pad - s;
       if ((unsigned)p >= (unsigned)g.P || (unsigned)q >= (unsigned)g.Q) continue;
-      float tap = 0.f;
-      for (int n = 0; n < g.Cout; ++n) tap = fmaf(dy[(p * g.Q + q) * g.Cout + n], w[(long long)n * g.NC + (r * g.R + s) * g.Cin + c], tap);
-      sum += tap;
+      const float *wt = w + (r * g.R + s) * g.Cin + c, *dt = dy + (p * g.Q + q) * g.Cout;
+      float tap[V] = {};
+#pragma unroll 8
+      for (int n = 0; n < g.Cout; ++n) {
+        const fu wv = *(const fu *)(wt + n * g.NC);  // Cout * NC < 2^22
+        const float d = dt[n];
+#pragma unroll
+        for (int e = 0; e < V; ++e) tap[e] = fmaf(d, wv[e], tap[e]);
+      }
+#pragma unroll
+      for (int e = 0; e < V; ++e) sum[e] += tap[e];
     }
-  return sum;
 }
 
 // V: consecutive channels a thread gathers at a time (4 or 1)
@@ -121,6 +129,16 @@ __global__ __launch_bounds__(kWinThreads, 4) void k_dgrad_window(const WinGeom g
   const long long img = (long long)b * total;
   const float *mp = mask ? mask + rep * mask_rs + img : nullptr;
   float *op = dx + rep * dx_rs + img;
+  auto finish = [&](int i, fv sum) {
+    if (mp) {
+      const fv mv = *(const fv *)&mp[i * V];
+#pragma unroll
+      for (int e = 0; e < V; ++e) sum[e] = mv[e] > 0.f ? sum[e] : 0.f;
+    }
+    if (accumulate) sum += *(const fv *)&op[i * V];
+    *(fv *)&op[i * V] = sum;
+  };
+  bool left = false;
   const int taps = g.R * g.R;
   for (int c0 = 0; c0 < g.NC; c0 += kDxCols) {
     if (rows) {
@@ -179,18 +197,25 @@ __global__ __launch_bounds__(kWinThreads, 4) void k_dgrad_window(const WinGeom g
         *(fv *)&dxS[i * V] = sum;
         continue;
       }
+      bool odd = false;
 #pragma unroll
-      for (int e = 0; e < V; ++e)
-        if (__builtin_expect(not_finite(sum[e]), 0)) sum[e] = plain_dx(g, dyp, w + rep * w_rs, hh, ww, c + e);
-      if (mp) {
-        const fv mv = *(const fv *)&mp[i * V];
-#pragma unroll
-        for (int e = 0; e < V; ++e) sum[e] = mv[e] > 0.f ? sum[e] : 0.f;
-      }
-      if (accumulate) sum += *(const fv *)&op[i * V];
-      *(fv *)&op[i * V] = sum;
+      for (int e = 0; e < V; ++e) odd |= out_of_split_range(sum[e]);
+      dxS[i * V] = odd ? 1.f : 0.f;  // left for plain fp32, after the loop: here it would cost the loop registers
+      left |= odd;
+      if (!odd) finish(i, sum);
     }
     if (!last) __syncthreads();  // the next columns replace these
+  }
+  if (__builtin_expect(!left, 1)) return;
+  for (int i = tid; i < total / V; i += kWinThreads) {
+    if (dxS[i * V] == 0.f) continue;
+    const int pix = i * V / g.Cin, c = i * V - pix * g.Cin, hh = pix / g.W, ww = pix - hh * g.W;
+    float sum[V] = {};
+    plain_dx<V>(g, dyp, w + rep * w_rs, hh, ww, c, sum);
+    fv out;
+#pragma unroll
+    for (int e = 0; e < V; ++e) out[e] = sum[e];
+    finish(i, out);
   }
 }
 

@@ -3,16 +3,17 @@
 //
 // What bounds such a layer is the fp32 MFMA rate (157 TFLOP/s dense against 2.5 PFLOP/s in bf16).  An fp32 value is the
 // sum of three bf16 values, x = x0 + x1 + x2 with x0 = bf16(x), x1 = bf16(x - x0), x2 = x - x0 - x1 (8 + 8 + 8 bits of
-// significand and two signs: nothing is lost while x2 is no denormal), so a product is
+// significand and two signs: nothing is lost while x2 is no denormal, from 2^-110 up), so a product is
 //   x*y = x0*y0 + (x0*y1 + x1*y0 + x1*y1 + x0*y2 + x2*y0) + terms below 2^-24 |x*y|
 // and six v_mfma_f32_32x32x16_bf16 (192 cycles) do what eight v_mfma_f32_32x32x2_f32 (512 cycles) did.  The products are
 // exact in fp32; x0*y0 has an accumulator of its own, the five corrections share a second one, and the two are added once
 // at the end.  Relative error against 64 bits on random operands, contraction 64 / 864 / 2880 / 32768: fp32 MFMA
 // 1.0e-7 / 3.7e-7 / 6.7e-7 / 2.3e-6, this 0.41e-7 / 1.3e-7 / 2.6e-7 / 1.1e-6 (16 products are added per rounding instead
 // of 2); with one accumulator for all six it would be 1.1e-7 / 4.2e-7 / 7.8e-7 / 2.8e-6.
-// Where an operand is infinite or NaN the corrections are NaN (inf - inf), and an operand beyond the largest bf16 value
-// (3.39e38; the largest float is 3.40e38) has an infinite x0.  A workgroup that finds a result that is not finite runs its
-// contraction a second time with fp32 MFMA on the values as they are, so such operands give what plain fp32 gives.
+// Where an operand is infinite or NaN the corrections are NaN (inf - inf), an operand beyond the largest bf16 value
+// (3.39e38; the largest float is 3.40e38) has an infinite x0, and operands below 2^-110 lose bits.  A workgroup that finds
+// a result that is not finite, or too small to be sure of (igemm_split.h), runs its contraction a second time with fp32
+// MFMA on the values as they are, so such operands give what plain fp32 gives.
 //
 // The input patch of a workgroup's output pixels is staged once per 16 channels, split as it is stored to LDS (5.5 vector
 // instructions per value), and serves all taps.  A tile is a number of whole output rows, counted through all images
@@ -259,14 +260,23 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
   };
   if (tid == 0) again = 0;
   contract(std::false_type{});
-  NonFinite odd;
+  SplitRange range;
 #pragma unroll
   for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
     for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) hi[tm][tn][v] += lo[tm][tn][v], odd.add(hi[tm][tn][v]);
-  if (odd.any()) again = 1;
+      for (int v = 0; v < 16; ++v) hi[tm][tn][v] += lo[tm][tn][v], range.add(hi[tm][tn][v]);
+  if (range.in_doubt()) {
+    bool left = false;
+#pragma unroll
+    for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+      for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) left |= out_of_split_range(hi[tm][tn][v]);
+    if (__any(left)) again = 1;
+  }
   __syncthreads();  // patch and weight tiles are dead
   if (__builtin_expect(again, 0)) {
     // the pass works its addresses out anew: kept through the first pass, they would cost it registers

@@ -18,11 +18,12 @@
 // the 2314 cycles that eight wavefronts take for them.  Keeping three rows for all nine taps, 54 MFMAs per split, needs 450 registers, which
 // the compiler spilled: 1600 us.  LeNet's 5 x 5 layer, six replicas: 62 -> 43 us.
 // BIAS: the wavefronts of the first input-channel tile and window row also add up dy.
-// A wavefront with a result that is not finite walks its strips a second time in plain fp32.  Such results come from
-// infinities and NaN, whose corrections are NaN (as is the compensation of the sum of dy), and from operands beyond the
-// largest bf16 value (3.39e38), whose x0 is infinite.  Where the width is no multiple of 8 there is a third source: the last columns of a strip lie beyond the row,
-// their dy is zero, and the x values beside them belong to other taps; an infinity there would make 0 * inf of it.  The
-// second walk sets them to zero, which the first need not do: 0 * x adds nothing while x is finite.
+// A wavefront with a result that is not finite, or too small to be sure of (igemm_split.h), walks its strips a second time
+// in plain fp32.  Infinities and NaN leave NaN in the corrections (and in the compensation of the sum of dy), and operands
+// beyond the largest bf16 value (3.39e38) have an infinite x0.  Where the width is no multiple of 8 there is a third
+// source: the last columns of a strip lie beyond the row, their dy is zero, and the x values beside them belong to other
+// taps; an infinity there would make 0 * inf of it.  The second walk sets them to zero, which the first need not do: 0 * x
+// adds nothing while x is finite.
 #include "igemm_dev.h"
 #include "igemm_split.h"
 #include "igemm_strips.h"
@@ -129,13 +130,21 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(OCC))) void 
       row_product(dw, xw);
     }
   }
-  NonFinite odd;
-  odd.add(bsum);
+  SplitRange range;
+  range.add(bsum);
 #pragma unroll
   for (int s = 0; s < S; ++s)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) hi[s][v] += lo[s][v], odd.add(hi[s][v]);
-  if (odd.any()) {  // see above: the same sums on fp32 matrix instructions, a pixel of either strip at a time
+    for (int v = 0; v < 16; ++v) hi[s][v] += lo[s][v], range.add(hi[s][v]);
+  bool left = false;
+  if (range.in_doubt()) {
+    left = out_of_split_range(bsum);
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) left |= out_of_split_range(hi[s][v]);
+  }
+  if (__builtin_expect(__any(left), 0)) {  // see above: the same sums on fp32 matrix instructions, a pixel of either strip at a time
     bsum = 0.f;
 #pragma unroll
     for (int s = 0; s < S; ++s)

@@ -18,4 +18,20 @@ __device__ __forceinline__ void split_words(const float *v, uint32_t (&p)[3][(V 
   }
 }
 
+// Results of split products that plain fp32 has to give instead: infinite and NaN ones, and nonzero ones below 2^-64.  A part
+// that would lie below bf16's smallest denormal is lost, up to 2^-134 of either operand: of a sum of 4096 products with
+// values below 2^33, less than 2^-88, which is within an fp32 rounding of any result from 2^-64 up.  A result of exactly
+// zero is kept (rows of zeros are common): its products all underflow in fp32 as well.
+constexpr uint32_t kLeastTwice = 0x3f000000u;  // the bits of 2^-64, without the sign, times two
+__device__ __forceinline__ bool out_of_split_range(float v) {
+  const uint32_t u = __float_as_uint(v) << 1;
+  return u >= 0xff000000u || u - 1 < kLeastTwice - 1;
+}
+// A quick look at many results: one and a half instructions each, and it also stops at zeros.
+struct SplitRange {
+  uint32_t least = ~0u;
+  __device__ __forceinline__ void add(float v) { least = min(least, (__float_as_uint(v) << 1) + 0x01000000u); }
+  __device__ __forceinline__ bool in_doubt() const { return __builtin_expect(__any(least < kLeastTwice + 0x01000000u), 0); }
+};
+
 }  // namespace igemm_dev
