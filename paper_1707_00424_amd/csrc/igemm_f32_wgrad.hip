@@ -182,10 +182,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(OCC))) void 
   }
 }
 
+// the 5 x 5 kernel takes all five taps of a window row: one wavefront per SIMD
+bool five_taps(const ConvGeom &g) { return g.sp == 1 && g.S == 5; }
+int wgf32_slots(const ConvGeom &g) { return five_taps(g) ? 1024 : 2048; }
+
 bool make_wgf32(const ConvGeom &g, int replicas, StripGeom &wg) {
-  if (g.Cc < 12) return false;
-  const bool five = g.sp == 1 && g.S == 5;  // all five taps: one wavefront per SIMD
-  return plan_strips(g, replicas, 4, 32, 32, five ? 5 : 3, five ? 1024 : 2048, 900, wg);
+  return g.Cc >= 12 && strip_geom(g, replicas, 4, 32, 32, five_taps(g) ? 5 : 3, wgf32_slots(g), wg);
 }
 
 }  // namespace
@@ -198,6 +200,7 @@ bool wgrad_f32x3_applicable(int dtype, int replicas, const ConvGeom &g) {
 int wgrad_f32x3_plan(int replicas, const ConvGeom &g, int *chunk_out) {
   StripGeom wg;
   make_wgf32(g, replicas, wg);
+  split_strips(g, replicas, wgf32_slots(g), 900, wg);
   if (chunk_out) *chunk_out = wg.pps * 32;
   return wg.splits;
 }
@@ -217,7 +220,7 @@ hipError_t launch_wgrad_f32x3(hipStream_t st, int replicas, const ConvGeom &g, c
   } while (0)
   if (g.sp == 2)
     WGF32_LAUNCH(3, 2, 2);
-  else if (g.S == 5)
+  else if (five_taps(g))
     WGF32_LAUNCH(5, 1, 1);  // ten accumulators: one wavefront per SIMD
   else
     WGF32_LAUNCH(3, 1, 2);

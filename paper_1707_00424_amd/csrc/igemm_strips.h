@@ -132,9 +132,9 @@ struct StripWalk {
   }
 };
 
-// Splits a layer: tiles of `tn` x `tc` channels and `taps` taps of a window row per wavefront, `slots` wavefronts on the
-// chip, about `row_ns` nanoseconds per row with a full chip.
-inline bool plan_strips(const ConvGeom &g, int replicas, int es, int tn, int tc, int taps, int slots, int row_ns, StripGeom &wg) {
+// The walk of a layer: tiles of `tn` x `tc` channels and `taps` taps of a window row per wavefront, `slots` wavefronts on the
+// chip.  False where the layer is none for these kernels.
+inline bool strip_geom(const ConvGeom &g, int replicas, int es, int tn, int tc, int taps, int slots, StripGeom &wg) {
   if (g.dshift != 0 || g.sr != 1 || g.R != g.S || g.S < 3 || (g.sp != 1 && g.sp != 2) || g.M % (g.P * g.Q) != 0) return false;
   const int images = g.M / (g.P * g.Q);
   const long long lim = 1LL << 31;
@@ -152,17 +152,24 @@ inline bool plan_strips(const ConvGeom &g, int replicas, int es, int tn, int tc,
   if ((long long)(images + 1) * wg.ppg >= lim) return false;
   wg.pairs = (images + wg.gi - 1) / wg.gi * wg.ppg;
   wg.dSegs = make_fastdiv(wg.segs), wg.dPph = make_fastdiv(wg.pph), wg.dPpg = make_fastdiv(wg.ppg);
-  // splits, by estimated time in ns: rows on the busiest slot, writing and reading the partial sums (3 TB/s), adding them up
+  return true;
+}
+
+// Splits the pairs by estimated time in ns: rows on the busiest slot (about `row_ns` with a full chip), writing and reading
+// the partial sums (3 TB/s), adding them up.  Split counts that leave the same number of pairs to a split are one plan; the
+// search visits each plan once (a few tens, under a microsecond).
+inline void split_strips(const ConvGeom &g, int replicas, int slots, int row_ns, StripGeom &wg) {
   const long long per_split = (long long)wg.units * replicas;
   long long best = -1;
   const int max_splits = (int)std::min<long long>(std::min<long long>(wg.pairs, 65535 / replicas), slots / per_split + 1);
-  for (int s = 1; s <= max_splits; ++s) {
+  for (int s = 1; s <= max_splits;) {
     const int pps = (wg.pairs + s - 1) / s, real = (wg.pairs + pps - 1) / pps;
     const long long rounds = (per_split * real + slots - 1) / slots;
     const long long cost = rounds * pps * wg.PC * row_ns + real * 60 + (long long)real * replicas * g.N * g.K * 4 / 3000;
     if (best < 0 || cost < best) best = cost, wg.pps = pps, wg.splits = real;
+    if (pps == 1) break;
+    s = (wg.pairs + pps - 2) / (pps - 1);  // the first with fewer pairs to a split
   }
-  return true;
 }
 
 }  // namespace igemm_dev

@@ -131,9 +131,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(P == 2 ? 1 :
 // channels per lane
 int strips_pair(const ConvGeom &g) { return g.N % 2 == 0 && g.Cc % 2 == 0 ? 2 : 1; }
 
+int strips_slots(const ConvGeom &g) { return strips_pair(g) == 2 ? 1024 : 2048; }
+
 bool make_strips(const ConvGeom &g, int replicas, StripGeom &wg) {
   const int p = strips_pair(g);
-  return plan_strips(g, replicas, 2, 32 * p, 32 * p, 3, p == 2 ? 1024 : 2048, p == 2 ? 260 : 200, wg);
+  return strip_geom(g, replicas, 2, 32 * p, 32 * p, 3, strips_slots(g), wg);
 }
 
 }  // namespace
@@ -146,6 +148,7 @@ bool wgrad_strips_applicable(int dtype, int replicas, const ConvGeom &g) {
 int wgrad_strips_plan(int replicas, const ConvGeom &g, int *chunk_out) {
   StripGeom wg;
   make_strips(g, replicas, wg);
+  split_strips(g, replicas, strips_slots(g), strips_pair(g) == 2 ? 260 : 200, wg);
   if (chunk_out) *chunk_out = wg.pps * 32;
   return wg.splits;
 }
