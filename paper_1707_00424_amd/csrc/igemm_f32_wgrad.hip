@@ -210,7 +210,7 @@ hipError_t launch_wgrad_f32x3(hipStream_t st, int replicas, const ConvGeom &g, c
   if (!make_wgf32(g, replicas, wg)) return hipErrorInvalidValue;
   wg.pps = io.chunk / 32, wg.splits = io.splits;
   if (wg.pps < 1 || (long long)wg.pps * wg.splits < wg.pairs) return hipErrorInvalidValue;
-  const dim3 grid((wg.splits + 7) / 8 * 8 * wg.units, 1, replicas);
+  const dim3 grid(strip_blocks(wg), 1, replicas);
 #define WGF32_LAUNCH(SV, SPV, OCCV)                                                                       \
   do {                                                                                                    \
     if (io.with_bias)                                                                                     \

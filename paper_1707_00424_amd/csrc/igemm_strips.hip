@@ -158,7 +158,7 @@ hipError_t launch_wgrad_strips(hipStream_t st, int replicas, const ConvGeom &g, 
   if (io.with_bias || !make_strips(g, replicas, wg)) return hipErrorInvalidValue;
   wg.pps = io.chunk / 32, wg.splits = io.splits;
   if (wg.pps < 1 || (long long)wg.pps * wg.splits < wg.pairs) return hipErrorInvalidValue;
-  const dim3 grid((wg.splits + 7) / 8 * 8 * wg.units, 1, replicas);
+  const dim3 grid(strip_blocks(wg), 1, replicas);
 #define STRIPS_LAUNCH(PV, SPV) hipLaunchKernelGGL((k_wgrad_strips<PV, 3, SPV>), grid, dim3(64), 0, st, g, io, wg)
   if (strips_pair(g) == 2) {
     if (g.sp == 2)
