@@ -169,7 +169,7 @@ hipError_t launch_wgrad_f32x3(hipStream_t st, int replicas, const ConvGeom &g, c
 // fp32 plain products with few output tiles, all three products of a layer, weights read as they lie (igemm_fc.hip).
 bool fc_f32_applicable(int dtype, int replicas, const ConvGeom &g);
 hipError_t launch_fc_f32(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io);
-bool wgrad_fc_f32_applicable(int dtype, const ConvGeom &g);
+bool wgrad_fc_f32_applicable(int dtype, int replicas, const ConvGeom &g);
 hipError_t launch_wgrad_fc_f32(hipStream_t st, int replicas, const ConvGeom &g, const WgradIO &io);
 // fp32 backward-weight with at most 32 output channels and a window of at most 32 values (igemm_ksplit.hip).
 bool wgrad_small_f32_applicable(int dtype, const ConvGeom &g);

@@ -450,7 +450,7 @@ hipError_t launch_wgrad(hipStream_t st, int dtype, int replicas, const ConvGeom 
   if (wgrad_smallk_applicable(dtype, g) && aligned_to(io.dy, 16)) return launch_wgrad_smallk(st, replicas, g, io);
   if (io.x_f32) return hipErrorInvalidValue;  // only the kernel above reads fp32 memory for a bf16 layer
   if (wgrad_small_f32_applicable(dtype, g)) return launch_wgrad_small_f32(st, replicas, g, io);
-  if (wgrad_fc_f32_applicable(dtype, g)) return launch_wgrad_fc_f32(st, replicas, g, io);
+  if (wgrad_fc_f32_applicable(dtype, replicas, g)) return launch_wgrad_fc_f32(st, replicas, g, io);
   if (wgrad_f32x3_applicable(dtype, replicas, g)) return launch_wgrad_f32x3(st, replicas, g, io);
   if (wgrad_window_applicable(dtype, g)) return launch_wgrad_window(st, replicas, g, io);
   if (wgrad9_applicable(dtype, g) && io.pairA && io.pairB) return launch_wgrad9(st, replicas, g, io);
@@ -483,7 +483,7 @@ int wgrad_plan(int dtype, int replicas, const ConvGeom &g, int *chunk_out) {
     return wgrad_f32x3_plan(replicas, g, chunk_out);
   if (!wgrad_smallk_applicable(dtype, g) && !wgrad_small_f32_applicable(dtype, g) && wgrad_window_applicable(dtype, g))
     return wgrad_window_plan(replicas, g, chunk_out);
-  if (!wgrad_small_f32_applicable(dtype, g) && wgrad_fc_f32_applicable(dtype, g)) {
+  if (!wgrad_small_f32_applicable(dtype, g) && wgrad_fc_f32_applicable(dtype, replicas, g)) {
     if (chunk_out) *chunk_out = (g.M + 31) / 32 * 32;
     return 1;
   }

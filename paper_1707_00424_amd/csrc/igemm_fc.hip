@@ -253,9 +253,12 @@ hipError_t choose_fc(hipStream_t st, int replicas, FcArgs &g) {
   // 32 x 32): <32, 4, 1> 13.5 / 18.4 / 14.7, <32, 2, 2> 17.4 / 17.3 / 13.9, <16, 4, 1> 14.1 / 17.7 / 18.8; three of
   // 128 x 784 x 128 (48 / 300 / 300 tiles): <32, 4, 1> 9.5 / 4.5 / 4.6, <16, 8, 1> 4.6 / 6.4 / 6.6.  So: small tiles while
   // large ones leave compute units empty, more wavefronts per tile the longer the contraction, and from two large tiles
-  // per compute unit on fewer wavefronts per tile, each with more of the contraction.
+  // per compute unit on fewer wavefronts per tile, each with more of the contraction.  Eight wavefronts to a small tile fill
+  // the chip earlier than four: <16, 8, 1> / <32, 4, 1> at 160 large tiles (4 x 128 x 500 x 320 forward, 5 x 64 x 800 x 500
+  // input gradient) 8.9 / 8.2 and 14.7 / 8.4, at 192 (3 x 128 x 500 x 500) 9.5 / 8.4, at 128 (8 x 32 x 1024 x 512) 7.8 / 7.9;
+  // <16, 4, 1> / <32, 4, 1> at 192 (3 x 128 x 256 x 500) 4.9 / 5.5.
   const long long t32 = fc_tiles(g.I, g.J, 32) * replicas;
-  if (t32 < kCus) {
+  if (t32 < (g.K > 256 ? 144 : kCus)) {
     if (g.K > 256) return run_fc<16, A_SLOW, B_SLOW, 8, 1>(st, replicas, g);
     return run_fc<16, A_SLOW, B_SLOW, 4, 1>(st, replicas, g);
   }
@@ -294,12 +297,17 @@ hipError_t launch_fc_f32(hipStream_t st, int replicas, const ConvGeom &g, const 
   return io.w_kn ? choose_fc<false, true>(st, replicas, f) : choose_fc<false, false>(st, replicas, f);
 }
 
-// Weight gradient of such a layer (g: forward geometry).
-bool wgrad_fc_f32_applicable(int dtype, const ConvGeom &g) {
-  if (dtype != 0 || !plain_product(g)) return false;
+// Weight gradient of such a layer (g: forward geometry).  A tile costs this kernel about 2.5 us of a workgroup beside its
+// contraction (staging, partial tiles, the strided result), the generic kernel less, but that takes 1.8 us per 32 rows of
+// the batch.  us, generic / this, at 256, 1024, 2400, 4096 and 16384 tiles of 32 x 32: 16 rows 3.6 / 4.2, 4.1 / 5.1,
+// 6.4 / 11.9, 7.9 / 16.5, 16 / 53; 64 rows 6.4 / 4.3, 7.0 / 5.7, 11.5 / 12.5, 14.0 / 17.7, 39 / 59; 128 rows 10.1 / 4.4,
+// 10.8 / 7.5, 18.2 / 17.3, 22.3 / 23.6, 68 / 83; 256 rows 13.4 / 5.4, 19.7 / 10.8, 30.8 / 28.6, 39.3 / 37.4, 127 / 132; at
+// 512 rows this one leads at every size (245 / 233).  So the number of tiles it takes grows with the rows.
+bool wgrad_fc_f32_applicable(int dtype, int replicas, const ConvGeom &g) {
+  if (dtype != 0 || !plain_product(g) || g.M > 1024 || (g.N + 15) / 16 > 65535) return false;
   const long long lim = 1LL << 31;
-  return (long long)g.M * g.K * 4 < lim && (long long)g.M * g.N * 4 < lim && (long long)g.N * g.K * 4 < lim &&
-         g.M <= 1024 && (g.N + 15) / 16 <= 65535;
+  if ((long long)g.M * g.K * 4 >= lim || (long long)g.M * g.N * 4 >= lim || (long long)g.N * g.K * 4 >= lim) return false;
+  return g.M >= 512 || fc_tiles(g.N, g.K, 32) * replicas <= (g.M > 16 ? 24LL * (g.M - 8) : 192LL);
 }
 
 hipError_t launch_wgrad_fc_f32(hipStream_t st, int replicas, const ConvGeom &g, const WgradIO &io) {

@@ -48,8 +48,10 @@ CASES = [
     (3, 40, 16, 16, 32, 256, 3, 1, 1),    # ... and with the chip full
     (1, 3, 15, 15, 33, 47, 3, 1, 1),      # odd counts: dword loads, results straight from the accumulators
     (1, 3, 14, 14, 50, 70, 3, 1, 1),      # even counts: 8-byte loads
-    (1, 5, 16, 16, 36, 64, 3, 2, 1),      # stride 2
-    (1, 4, 14, 14, 34, 33, 3, 2, 1),
+    (8, 20, 32, 32, 36, 64, 3, 2, 1),     # stride 2, which takes 160 workgroups
+    (16, 30, 14, 14, 34, 33, 3, 2, 1),    # ... even counts, seven columns, an odd number of outputs
+    (16, 30, 15, 13, 35, 36, 3, 2, 1),    # ... odd ones
+    (8, 10, 28, 28, 12, 96, 5, 2, 2),     # ... under a 5 x 5 window
     (2, 3, 12, 12, 20, 50, 5, 1, 0),      # input gradient with an image per workgroup, five taps per wavefront
     (1, 3, 7, 9, 6, 13, 3, 1, 1),         # the same, a channel at a time
     (1, 2, 10, 11, 16, 64, 5, 1, 2),

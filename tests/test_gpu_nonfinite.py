@@ -90,7 +90,7 @@ SPLIT = [
     # n, B, H, W, Cin, Cout, k, stride, pad: every form of the kernels that split fp32 values into bf16 parts
     (1, 3, 16, 16, 32, 64, 3, 1, 1),     # results in whole rows
     (1, 3, 15, 15, 33, 47, 3, 1, 1),     # odd counts, results straight from the accumulators
-    (1, 2, 14, 14, 50, 20, 3, 2, 1),     # stride 2
+    (16, 24, 14, 14, 50, 20, 3, 2, 1),   # stride 2, which takes 160 workgroups
     (1, 2, 12, 12, 20, 50, 5, 1, 0),     # input gradient with an image per workgroup
     (1, 2, 7, 7, 28, 48, 3, 1, 1),
 ]
