@@ -342,6 +342,11 @@ bool plan_f32(const ConvGeom &g, int replicas, F32Plan &best) {
   }
   if (best_cost < 0) return false;
   F32Geom &fg = best.fg;
+  // Stride 2 has the one tile of 128 x 64, and a workgroup alone on its compute unit is bound by its chain of steps, where
+  // the gather kernel with twice as many workgroups is shorter.  us, gather kernel / here: 64 -> 128 channels on 32 x 32, 128
+  // workgroups 20.1 / 23.4, 256 29.7 / 25.5; 128 -> 256 on 16 x 16, 128 34.1 / 42.4, 256 51.9 / 45.0; 96 -> 96 on 28 x 28, 100
+  // 26.0 / 33.2, 200 38.7 / 34.4; 32 -> 32 on 32 x 32, 128 12.3 / 13.8, 256 17.9 / 15.1.
+  if (g.sp == 2 && (long long)fg.tiles * fg.nb * replicas < 160) return false;
   fg.PRI = g.sp * (g.P - 1) + g.R;
   const int last_h = g.off + (g.R - 1) * g.sr, last_w = g.off + (g.S - 1) * g.sr;
   fg.omin_h = g.off < last_h ? g.off : last_h, fg.omin_w = g.off < last_w ? g.off : last_w;
