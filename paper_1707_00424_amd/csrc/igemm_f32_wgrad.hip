@@ -190,11 +190,25 @@ bool make_wgf32(const ConvGeom &g, int replicas, StripGeom &wg) {
   return g.Cc >= 12 && strip_geom(g, replicas, 4, 32, 32, five_taps(g) ? 5 : 3, wgf32_slots(g), wg);
 }
 
+// Layers of few pixels whose channels fill the generic kernel's tiles of 64: that kernel has no dead columns (half of a strip
+// at a width of 4) and fewer partial sums to write, which is most of the time here.  Both by estimate, in ns: the generic
+// kernel takes 2.5 us and per step of 32 rows 1.6, or 2.5 where two workgroups share a compute unit; splits cost either
+// 4.5 us and their partial sums.  us, estimates in parentheses, generic / here: 256 -> 256 channels, 16 images of 4 x 4
+// 16.7 (18.6) / 21.9 (21.2), of 6 x 6 23.5 (24.4) / 23.7 (23.0), three replicas of 16 images of 4 x 4 24.7 (22.5) / 28.6
+// (29.6), one of 128 61 (64) / 45 (45); 128 -> 128, three of 128 images of 3 x 3 30.5 (31.9) / 36.7 (34.1).
+bool generic_is_faster(const ConvGeom &g, int replicas, StripGeom &wg) {
+  if (g.M > 2048 || g.N < 64 || g.Cc < 64) return false;
+  const GenericSplit s = generic_split(g, replicas, 64, 64);
+  const long long partial = (long long)replicas * g.N * g.K * 4 / 3000;
+  const long long strips = split_strips(g, replicas, wgf32_slots(g), 900, wg) + 4500 + wg.splits * partial;
+  return 2500 + s.steps * (s.groups > 256 ? 2500 : 1600) + (s.splits > 1 ? 4500 + s.splits * partial : 0) < strips;
+}
+
 }  // namespace
 
 bool wgrad_f32x3_applicable(int dtype, int replicas, const ConvGeom &g) {
   StripGeom wg;
-  return dtype == 0 && make_wgf32(g, replicas, wg);
+  return dtype == 0 && make_wgf32(g, replicas, wg) && !generic_is_faster(g, replicas, wg);
 }
 
 int wgrad_f32x3_plan(int replicas, const ConvGeom &g, int *chunk_out) {

@@ -162,8 +162,8 @@ inline bool strip_geom(const ConvGeom &g, int replicas, int es, int tn, int tc, 
 
 // Splits the pairs by estimated time in ns: rows on the busiest slot (about `row_ns` with a full chip), writing and reading
 // the partial sums (3 TB/s), adding them up.  Split counts that leave the same number of pairs to a split are one plan; the
-// search visits each plan once (a few tens, under a microsecond).
-inline void split_strips(const ConvGeom &g, int replicas, int slots, int row_ns, StripGeom &wg) {
+// search visits each plan once (a few tens, under a microsecond).  Returns the estimate.
+inline long long split_strips(const ConvGeom &g, int replicas, int slots, int row_ns, StripGeom &wg) {
   const long long per_split = (long long)wg.units * replicas;
   long long best = -1;
   const int max_splits = (int)std::min<long long>(std::min<long long>(wg.pairs, 65535 / replicas), slots / per_split + 1);
@@ -175,6 +175,22 @@ inline void split_strips(const ConvGeom &g, int replicas, int slots, int row_ns,
     if (pps == 1) break;
     s = (wg.pairs + pps - 2) / (pps - 1);  // the first with fewer pairs to a split
   }
+  return best;
+}
+
+// The generic weight gradient's plan for tiles of tn x tk outputs: rows in steps of 32 to a workgroup, and workgroups.
+struct GenericSplit {
+  long long tiles, groups;
+  int steps, splits;
+};
+inline GenericSplit generic_split(const ConvGeom &g, int replicas, int tn, int tk) {
+  GenericSplit s;
+  s.tiles = (long long)((g.K + tk - 1) / tk) * ((g.N + tn - 1) / tn) * replicas;
+  const int all = (g.M + 31) / 32;
+  const int want = (int)std::max<long long>(1, std::min<long long>(512 / s.tiles, all / 4));
+  s.steps = (all + want - 1) / want, s.splits = (all + s.steps - 1) / s.steps;
+  s.groups = s.tiles * s.splits;
+  return s;
 }
 
 }  // namespace igemm_dev
