@@ -140,9 +140,24 @@ bool make_strips(const ConvGeom &g, int replicas, StripGeom &wg) {
 
 }  // namespace
 
+// Layers with so little to do that the generic kernel is at its shortest (four or five steps to a workgroup, 17 to 20 us with
+// the sums of its splits), and a wavefront here walks eight rows or more, at half a microsecond each with nothing beside it
+// to cover the loads.  Even channel counts only: odd ones cost the generic kernel 1.6 times as much.  us, generic / here, 20
+// -> 20 channels, 128 images: 7 x 7 19.1 / 20.2, 10 x 10 19.7 / 22.2, 20 x 20 with stride 2 19.8 / 24.0; 4 x 32 images, 50 -> 50,
+// 7 x 7 with stride 2 17.6 / 20.4; but 16 images of 20 channels, 7 x 7, seven rows 19.2 / 16.0, and more workgroups, 64 images
+// of 7 x 7, 250 -> 130, 52.3 / 33.6.
+bool generic_is_shorter(const ConvGeom &g, int replicas, StripGeom &wg) {
+  if (strips_pair(g) != 2) return false;
+  const int tn = g.N <= 32 ? 32 : g.N <= 64 ? 64 : g.N % 96 == 0 || g.N <= 96 ? 96 : 128;
+  const GenericSplit s = generic_split(g, replicas, tn, 128);
+  if (s.steps > 5 || s.groups > (tn == 32 ? 512 : 256)) return false;
+  split_strips(g, replicas, strips_slots(g), 260, wg);
+  return wg.pps * wg.PC >= 8;
+}
+
 bool wgrad_strips_applicable(int dtype, int replicas, const ConvGeom &g) {
   StripGeom wg;
-  return dtype == 1 && g.Cc >= 16 && g.N >= 16 && make_strips(g, replicas, wg);
+  return dtype == 1 && g.Cc >= 16 && g.N >= 16 && make_strips(g, replicas, wg) && !generic_is_shorter(g, replicas, wg);
 }
 
 int wgrad_strips_plan(int replicas, const ConvGeom &g, int *chunk_out) {
