@@ -126,7 +126,7 @@ bool igemm_fast_applicable(int dtype, const ConvGeom &g, const GemmIO &io);
 hipError_t launch_igemm_fast(hipStream_t st, int dtype, bool out_f32, int replicas, const ConvGeom &g, const GemmIO &io);
 int igemm_fast_stat_splits(int dtype, bool out_f32, const ConvGeom &g, const GemmIO &io);
 // Stride-1 'same' convolutions with the input patch staged once in LDS (igemm_halo.hip).
-bool conv_halo_applicable(int dtype, const ConvGeom &g, const GemmIO &io, bool out_f32);
+bool conv_halo_applicable(int dtype, int replicas, const ConvGeom &g, const GemmIO &io, bool out_f32);
 hipError_t launch_conv_halo(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io);
 int conv_halo_stat_splits(const ConvGeom &g, const GemmIO &io, int replicas);
 // fp32 backward-data of a stride-1 layer with few input channels under a wide window, the per-tap products of one

@@ -412,7 +412,7 @@ hipError_t launch_igemm(hipStream_t st, int dtype, bool out_f32, int replicas, c
     // the same order of choices as below, for the kernels whose epilogue can take the sums
     int S = 0;
     const bool smallk = conv_smallk_applicable(dtype, g, io_in);
-    const bool halo = !smallk && conv_halo_applicable(dtype, g, io_in, out_f32);
+    const bool halo = !smallk && conv_halo_applicable(dtype, replicas, g, io_in, out_f32);
     const bool fast = !smallk && !halo && !conv_f32x3_applicable(dtype, replicas, g, io_in) && !dgrad_s2_applicable(dtype, g, io_in, out_f32) &&
                       !gemm_ksplit_applicable(dtype, replicas, g, io_in) && igemm_fast_applicable(dtype, g, io_in);
     if (smallk) S = conv_smallk_stat_splits(g, out_f32);
@@ -429,7 +429,7 @@ hipError_t launch_igemm(hipStream_t st, int dtype, bool out_f32, int replicas, c
   io.stat = nullptr;
   if (io.in_f32 && !(dtype == 1 && !out_f32 && conv_smallk_applicable(dtype, g, io))) return hipErrorInvalidValue;
   if (conv_smallk_applicable(dtype, g, io)) return launch_conv_smallk(st, dtype, out_f32, replicas, g, io);
-  if (conv_halo_applicable(dtype, g, io, out_f32)) return launch_conv_halo(st, replicas, g, io);
+  if (conv_halo_applicable(dtype, replicas, g, io, out_f32)) return launch_conv_halo(st, replicas, g, io);
   if (conv_f32x3_applicable(dtype, replicas, g, io)) return launch_conv_f32x3(st, replicas, g, io);
   if (dgrad_s2_applicable(dtype, g, io, out_f32)) return launch_dgrad_s2(st, replicas, g, io);
   if (gemm_ksplit_applicable(dtype, replicas, g, io)) return launch_gemm_ksplit(st, out_f32, replicas, g, io);

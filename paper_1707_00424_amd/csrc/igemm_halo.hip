@@ -473,9 +473,27 @@ bool make_halo_geom(const ConvGeom &g, HaloGeom &hg, bool half = false) {
 
 }  // namespace
 
-bool conv_halo_applicable(int dtype, const ConvGeom &g, const GemmIO &io, bool out_f32) {
+namespace {
+// Layers of whole-vector input whose output channels are no multiple of 4: the kernel that gathers per tap loads vectors as
+// well, pads a contraction only at its end and not in every tap, and starts sooner; the patch kernel is ahead in a long
+// contraction and in a large launch.  Measured 3 x 3, patch / gather time at 13 to 130 pixel tiles, 200, 400 and 1200 or
+// more, by input channels: 10 to 30 outputs, 16 channels 1.45, 1.36, 1.28, 1.2; 32: 1.18, 1.09, 0.98, 0.94; 64: 0.98, 0.88,
+// 0.82, 0.8.  34 to 62 outputs, 16: 1.5, 1.38, 1.28, 0.7; 32: 1.3, 1.16, 1.04, 0.6; 64: 1.1, 0.97, 0.88, 0.6; 96: 0.99, 0.89,
+// 0.81.  90 outputs, 16: 1.66, 1.52, 1.0, 0.98; 64: 1.2, 1.12, 0.76, 0.8; 128: 1.04, 1.0, 0.68; 160: 1.0, 0.94, 0.63.  From
+// 130 outputs up it is ahead everywhere (16 channels 0.74).  5 x 5 goes by the same contraction lengths.
+bool short_contraction(const ConvGeom &g, const HaloGeom &hg, int replicas) {
+  const long long tiles = (long long)((hg.rows + hg.TH - 1) / hg.TH) * replicas;
+  if (g.N > 128) return false;
+  if (g.N > 64) return tiles < 384 && g.K < 1400;
+  if (tiles >= 384) return g.K < 288 && (g.N <= 32 || tiles < 768);
+  return g.K < (g.N > 32 ? 780 : 560);
+}
+}  // namespace
+
+bool conv_halo_applicable(int dtype, int replicas, const ConvGeom &g, const GemmIO &io, bool out_f32) {
   HaloGeom hg;
   if (dtype != 1 || out_f32 || g.R * g.S < 2 || g.Cc < 16 || g.M < 256 || !make_halo_geom(g, hg)) return false;
+  if (halo_wide(g, io) && !halo_vector(g, io) && short_contraction(g, hg, replicas)) return false;
   // rows of an even number of channels start on a dword wherever the tensors do
   const bool narrow_ok = g.sp == 1 && (g.Cc % 2 == 1 || (aligned_to(io.in, 4) && aligned_to(io.w, 4) && io.in_rs % 2 == 0 && io.w_rs % 2 == 0));
   return (halo_vector(g, io) || narrow_ok) && io.in_bytes > 0 && io.in_bytes < (1LL << 31) &&
