@@ -1,5 +1,6 @@
 """Split counts of the weight gradients on strips (host code: the scratch query plans as the launch does): the search that
-visits each plan once finds what a search over every count finds, and costs a fraction of it."""
+visits each plan once finds what a search over every count finds, layers go to the kernel the comments of the dispatch say,
+and a plan costs a fraction of a search."""
 import ctypes
 import random
 import time
@@ -9,19 +10,20 @@ import pytest
 from paper_1707_00424_amd import binding as pb
 
 
+def up(a, b):
+    return -(-a // b)
+
+
 def exhaustive(dtype, n, B, H, W, cin, cout, k, stride, pad):
-    """Splits by trying every count: the cost model of igemm_strips.h."""
+    """Splits by trying every count: the cost model of igemm_strips.h, and what the dispatch between these kernels and the
+    generic one makes of it."""
     P, Q = (H + 2 * pad - k) // stride + 1, (W + 2 * pad - k) // stride + 1
+    pair = cin % 2 == 0 and cout % 2 == 0
     if dtype == 0:
         five = stride == 1 and k == 5
         tile, taps, slots, row_ns = 32, 5 if five else 3, 1024 if five else 2048, 900
     else:
-        pair = cin % 2 == 0 and cout % 2 == 0
         tile, taps, slots, row_ns = (64, 3, 1024, 260) if pair else (32, 3, 2048, 200)
-
-    def up(a, b):
-        return -(-a // b)
-
     segs = up(Q, 8)
     gi = 1 if segs % 2 == 0 else 2
     units = up(cout, tile) * up(cin, tile) * up(k, taps) * k
@@ -37,8 +39,23 @@ def exhaustive(dtype, n, B, H, W, cin, cout, k, stride, pad):
         real = up(pairs, pps)
         cost = up(per_split * real, slots) * pps * rows * row_ns + real * 60 + real * n * cout * k * k * cin * 4 // 3000
         if best is None or cost < best[0]:
-            best = (cost, real)
-    return best[1]
+            best = (cost, real, pps)
+    cost, splits, pps = best
+
+    # the generic kernel: steps of 32 rows, tiles of tn x tk outputs
+    tn, tk = (64, 64) if dtype == 0 else (32 if cout <= 32 else 64 if cout <= 64 else 96 if cout % 96 == 0 or cout <= 96 else 128, 128)
+    tiles, steps = up(k * k * cin, tk) * up(cout, tn) * n, up(B * P * Q, 32)
+    chunk = up(steps, max(1, min(512 // tiles, steps // 4)))
+    generic = up(steps, chunk)
+    if dtype == 0:
+        partial = n * cout * k * k * cin * 4 // 3000
+        if B * P * Q <= 2048 and cout >= 64 and cin >= 64:
+            other = 2500 + chunk * (2500 if tiles * generic > 256 else 1600) + (4500 + generic * partial if generic > 1 else 0)
+            if other < cost + 4500 + splits * partial:
+                return generic
+    elif pair and chunk <= 5 and tiles * generic <= (512 if tn == 32 else 256) and pps * rows >= 8:
+        return generic
+    return splits
 
 
 def cases(count):
