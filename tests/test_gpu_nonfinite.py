@@ -50,6 +50,8 @@ RAGGED = [
     (1, (1, 3, 7, 7, 20, 36, 3, 1, 1)),      # bf16, two channels per lane
     (1, (1, 2, 9, 28, 17, 33, 3, 1, 1)),     # one channel per lane
     (1, (1, 2, 9, 28, 18, 34, 3, 2, 1)),
+    (1, (1, 2, 9, 11, 18, 34, 5, 1, 0)),     # two groups of taps, whose values beyond the row are pixels of the image
+    (0, (1, 2, 9, 11, 18, 34, 7, 1, 0)),
 ]
 
 
