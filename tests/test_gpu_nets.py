@@ -616,6 +616,15 @@ def test_inner_block_graph_replays_equal_step_by_step(gpu, name, bf16, alg):
     assert Pg.parle_get_state()[0] == blocks * L + 2
 
 
+@pytest.mark.parametrize("overlap", ["0", "1"])
+@pytest.mark.parametrize("name,bf16,alg", [("lenet_vec", 0, 0), ("wrn_vec", 1, 0), ("mlp_vec", 0, 1)])
+def test_graph_replays_on_one_and_two_streams(gpu, name, bf16, alg, overlap, monkeypatch):
+    """The same whichever way the networks' size would decide: with a second stream the fork and the join become edges of
+    the recorded graph, without it the graph is a chain."""
+    monkeypatch.setenv("PARLE_OVERLAP_WGRAD", overlap)      # read when the context is created
+    test_inner_block_graph_replays_equal_step_by_step(gpu, name, bf16, alg)
+
+
 def test_wrn_28_10_one_step_reduced_batch(gpu):
     """WRN-28-10 (Section 4.3, 36.5 million weights) as arch = (16, 10, 4): one inner step and the outer step for one
     replica on a batch of 4 (the oracle needs seconds), bf16 compute with fp32 master weights."""
@@ -764,7 +773,7 @@ def test_split_data_between_replicas(gpu, n, fraction, alg):
         check("x", got["x_ref"], O.st.x, 1e-5)
 
 
-@pytest.mark.parametrize("name,bf16", [("allcnn_vec", 1), ("wrn_vec", 0)])
+@pytest.mark.parametrize("name,bf16", [("allcnn_vec", 1), ("wrn_vec", 0), ("lenet_vec", 0), ("mlp_vec", 0)])
 def test_second_stream_changes_nothing(gpu, name, bf16, monkeypatch):
     """Weight and bias gradients run on a second stream beside the input-gradient chain; switching that off
     (one stream) must give the same bits: same kernels, same fixed-order reductions, only their timing differs."""
