@@ -443,6 +443,12 @@ hipError_t launch_igemm(hipStream_t st, int dtype, bool out_f32, int replicas, c
   }
 }
 
+// bf16 layers the strips take: none that a vector kernel takes, also where its operands turn out not to lie in pairs (the
+// generic kernel then reads them value by value, on the vector kernel's plan)
+static bool wgrad_on_strips(int dtype, int replicas, const ConvGeom &g) {
+  return !wgrad9_applicable(dtype, g) && !wgrad_fast_applicable(dtype, g) && wgrad_strips_applicable(dtype, replicas, g);
+}
+
 hipError_t launch_wgrad(hipStream_t st, int dtype, int replicas, const ConvGeom &g, const WgradIO &io) {
   if (g.M < 1 || g.N < 1 || g.K < 1 || replicas < 1 || io.splits < 1 || (long long)replicas * io.splits > 65535 ||
       io.chunk < 32 || (io.chunk & 31))
@@ -455,7 +461,7 @@ hipError_t launch_wgrad(hipStream_t st, int dtype, int replicas, const ConvGeom 
   if (wgrad_window_applicable(dtype, g)) return launch_wgrad_window(st, replicas, g, io);
   if (wgrad9_applicable(dtype, g) && io.pairA && io.pairB) return launch_wgrad9(st, replicas, g, io);
   if (wgrad_fast_applicable(dtype, g) && io.pairA && io.pairB) return launch_wgrad_fast(st, replicas, g, io);
-  if (wgrad_strips_applicable(dtype, replicas, g)) return launch_wgrad_strips(st, replicas, g, io);
+  if (wgrad_on_strips(dtype, replicas, g)) return launch_wgrad_strips(st, replicas, g, io);
   if (dtype == 0) return run_wgrad<float, 2, 2, 1, 1>(st, replicas, g, io);
   switch (bf16_ntile(g.N)) {
     case 32: return run_wgrad<bf16_t, 1, 4, 1, 1>(st, replicas, g, io);
@@ -475,8 +481,7 @@ bool wgrad_takes_bias(int dtype, int replicas, const ConvGeom &g, const WgradIO 
 }
 
 int wgrad_plan(int dtype, int replicas, const ConvGeom &g, int *chunk_out) {
-  if (!wgrad_smallk_applicable(dtype, g) && !wgrad9_applicable(dtype, g) && !wgrad_fast_applicable(dtype, g) &&
-      wgrad_strips_applicable(dtype, replicas, g))
+  if (!wgrad_smallk_applicable(dtype, g) && wgrad_on_strips(dtype, replicas, g))
     return wgrad_strips_plan(replicas, g, chunk_out);
   if (wgrad9_applicable(dtype, g)) return wgrad9_plan(replicas, g, chunk_out);
   if (!wgrad_small_f32_applicable(dtype, g) && wgrad_f32x3_applicable(dtype, replicas, g))

@@ -62,7 +62,7 @@ __device__ __forceinline__ void conv_halo_body(const ConvGeom &g, const GemmIO &
                                                int tile, int col) {
   typedef bf16_t T;
   constexpr int VW = 8, BK = 32, LK = BK + VW;
-  constexpr int BM = TM * 128, BN = TN * 32;  // four wavefronts stacked along the pixel axis
+  constexpr int BN = TN * 32;  // TM * 128 pixels: four wavefronts stacked along the pixel axis
   constexpr int B_IT = (BN + 63) / 64;
   constexpr int H_IT = (SLOTS * 4 + kThreads - 1) / kThreads;
   T *Hs = reinterpret_cast<T *>(smem);

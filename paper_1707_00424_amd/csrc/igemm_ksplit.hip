@@ -16,9 +16,10 @@ using namespace igemm_dev;
 
 constexpr uint32_t kOob = 0x80000000u;
 
-template <typename T, bool OUT_F32>
+template <bool OUT_F32>
 __global__ __launch_bounds__(kThreads) void k_gemm_ksplit(const ConvGeom g, const GemmIO io) {
-  constexpr int VW = 16 / sizeof(T);  // elements per fragment: lane half h holds k = 2*VW*s + VW*h .. +VW-1 of sub-step s
+  typedef bf16_t T;
+  constexpr int VW = 8;               // elements per fragment: lane half h holds k = 2*VW*s + VW*h .. +VW-1 of sub-step s
   constexpr int KS = 2 * VW;          // contraction elements per sub-step
   constexpr int U = 4;                // sub-steps in flight
   __shared__ __attribute__((aligned(16))) float part[3][64 * 16];
@@ -75,16 +76,6 @@ __global__ __launch_bounds__(kThreads) void k_gemm_ksplit(const ConvGeom g, cons
   store_tile<T, 1, 1, OUT_F32>(g, io, rep, m0, n0, lane, tile);
 }
 
-template <typename T>
-hipError_t run_ksplit(hipStream_t st, bool out_f32, int replicas, const ConvGeom &g, const GemmIO &io) {
-  dim3 grid((g.M + 31) / 32, (g.N + 31) / 32, replicas);
-  if (out_f32)
-    hipLaunchKernelGGL((k_gemm_ksplit<T, true>), grid, dim3(kThreads), 0, st, g, io);
-  else
-    hipLaunchKernelGGL((k_gemm_ksplit<T, false>), grid, dim3(kThreads), 0, st, g, io);
-  return hipGetLastError();
-}
-
 }  // namespace
 
 // A plain product (1 x 1 window, stride 1, no padding: row m of the product reads row m of `in`) whose 64 x 64
@@ -100,7 +91,12 @@ bool gemm_ksplit_applicable(int dtype, int replicas, const ConvGeom &g, const Ge
 }
 
 hipError_t launch_gemm_ksplit(hipStream_t st, bool out_f32, int replicas, const ConvGeom &g, const GemmIO &io) {
-  return run_ksplit<bf16_t>(st, out_f32, replicas, g, io);
+  const dim3 grid((g.M + 31) / 32, (g.N + 31) / 32, replicas);
+  if (out_f32)
+    hipLaunchKernelGGL(k_gemm_ksplit<true>, grid, dim3(kThreads), 0, st, g, io);
+  else
+    hipLaunchKernelGGL(k_gemm_ksplit<false>, grid, dim3(kThreads), 0, st, g, io);
+  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------------------------

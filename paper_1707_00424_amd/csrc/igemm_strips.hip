@@ -171,6 +171,7 @@ int wgrad_strips_plan(int replicas, const ConvGeom &g, int *chunk_out) {
 hipError_t launch_wgrad_strips(hipStream_t st, int replicas, const ConvGeom &g, const WgradIO &io) {
   StripGeom wg;
   if (io.with_bias || !make_strips(g, replicas, wg)) return hipErrorInvalidValue;
+  if (strips_pair(g) == 2 && !(io.pairA && io.pairB)) return hipErrorInvalidValue;  // loads pairs of channels
   wg.pps = io.chunk / 32, wg.splits = io.splits;
   if (wg.pps < 1 || (long long)wg.pps * wg.splits < wg.pairs) return hipErrorInvalidValue;
   const dim3 grid(strip_blocks(wg), 1, replicas);
