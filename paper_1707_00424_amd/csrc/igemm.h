@@ -115,7 +115,8 @@ inline ConvGeom conv_bwd_geom(const ConvShape &c) {
   return g;
 }
 
-// dtype: 0 = fp32 (v_mfma_f32_32x32x2_f32), 1 = bf16 (v_mfma_f32_32x32x16_bf16), fp32 accumulation.
+// dtype: 0 = fp32 (v_mfma_f32_32x32x2_f32, or six v_mfma_f32_32x32x16_bf16 on the values' bf16 parts: igemm_f32.hip),
+// 1 = bf16 (v_mfma_f32_32x32x16_bf16); fp32 accumulation.
 // `stat_splits`: with io.stat set, receives the number S of partial rows of column sums the kernel writes
 // (0: the kernel that runs this layer does not produce them; the caller takes them in a pass of its own).
 hipError_t launch_igemm(hipStream_t st, int dtype, bool out_f32, int replicas, const ConvGeom &g, const GemmIO &io,
@@ -175,9 +176,11 @@ hipError_t launch_wgrad_fc_f32(hipStream_t st, int replicas, const ConvGeom &g, 
 bool wgrad_small_f32_applicable(int dtype, const ConvGeom &g);
 // True when launch_wgrad would run a kernel that honours WgradIO::with_bias for this layer and these operands
 // (io.dy, io.pairA, io.pairB set): the small-window kernels when the window leaves one of their 32 contraction
-// columns unused, the stride-1 3x3 kernel, the transpose-read kernel and the generic fp32 kernel.
-// `per_image`: layers whose images the per-image LDS kernel could take (few channels under a wide window) leave the bias
-// to the caller at the entry point, whatever kernel runs them; the networks pass true and have it taken along.
+// columns unused, in bf16 the stride-1 3x3 kernel and the transpose-read kernel, in fp32 the strips, the fully connected
+// and the generic kernel.
+// `per_image`: layers that the per-image LDS kernel could take (few channels under a wide window) have always left the bias
+// to the caller of the entry point, which reports so; the strips, which run most of them by now, could take it, and do for
+// the networks, which pass true.
 bool wgrad_takes_bias(int dtype, int replicas, const ConvGeom &g, const WgradIO &io, bool per_image);
 hipError_t launch_wgrad_small_f32(hipStream_t st, int replicas, const ConvGeom &g, const WgradIO &io);
 // Backward-data of stride-2 3x3 pad-1 layers, four parity classes per workgroup (igemm_dgrad2.hip).

@@ -269,7 +269,7 @@ hipError_t launch_dgrad_window(hipStream_t st, int n, int B, int H, int W, int C
 
 // ---------------------------------------------------------------------------------------------
 // Backward-weight of the same kind of layer (fp32, stride 1, images of at most 64 output pixels) with fewer than 12 input
-// channels (with more, the register kernel of igemm_f32_wgrad.hip takes it), the window gather done in LDS:
+// channels or a 2 x 2 window (the register kernel of igemm_f32_wgrad.hip takes the others), the window gather done in LDS:
 //   dW[n][(r, s, ci)] = sum over images and output pixels m of dy[m][n] * x[m + (r, s)][ci].
 // A workgroup takes a few images one after the other; per image the input patch (12 x 12 x 8 floats, say) and the dy
 // tile lie in LDS, and both MFMA operands are read from there element by element: the (tap, channel) column of a lane

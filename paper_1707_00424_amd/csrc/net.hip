@@ -366,10 +366,11 @@ bool build_plan(Net &N, std::string &err) {
             return !(e && atoi(e) == 0);
           }();
           // Else two kernels with the products in memory between them, on fp32 matrix instructions, or the direct kernel:
-          // 32 columns per input pixel at 6/16 of that cost against Cin per output pixel and the trip through memory.
-          // Step times, two kernels / direct: 3 x 3 padded, 3 x 128 images of 32 channels 1155 / 758 us, 2 x 64 of 16
-          // channels 388 / 332; unpadded 4 x 4 of 20 channels (the product is 1.1 times the other side of the rule)
-          // 391 / 372, 5 x 5 of 28 (1.2) 206 / 217, of 32 (1.4) 188 / 177, of 20 (0.9) 194 / 214.
+          // 32 columns per input pixel at 6/16 of that cost (12) against Cin per output pixel and the trip through memory
+          // (worth two columns: 10).  Step times, two kernels / direct: 3 x 3 padded, 3 x 128 images of 32 channels 1155 /
+          // 758 us, 2 x 64 of 16 channels 388 / 332; unpadded, where neither is far ahead, in order of the ratio of the two
+          // sides: 5 x 5 of 20 channels (0.9) 194 / 214, 4 x 4 of 20 (1.1) 391 / 372, 5 x 5 of 28 (1.2) 206 / 217, of 32 (1.4)
+          // 188 / 177.  Between 0.9 and 1.4 the rule is right to about 5 % of a step either way.
           GemmIO dio{};
           dio.in_bytes = (int64_t)N.B * op.Ho * op.Wo * op.Cout * 4, dio.ldc = op.Cin;
           const ConvGeom gb = conv_bwd_geom(ConvShape{N.B, op.Hin, op.Win, op.Cin, op.Cout, op.R, op.stride, op.pad});

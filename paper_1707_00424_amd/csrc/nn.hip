@@ -95,7 +95,8 @@ __device__ __forceinline__ float as_stored<bf16_t>(float v) {
   return bf16_to_f32(f32_to_bf16(v));
 }
 
-// The softmax of one image by one wavefront.  `v` holds each lane's part of the C <= kHeadClasses logits (zero beyond C).  A
+// The softmax of one image by one wavefront.  `v` holds each lane's part of the C <= kHeadClasses logits; what it holds beyond
+// C only reaches lanes whose class does not exist, and those are left out.  A
 // reduce-scatter tree adds them up: at each of four steps a lane passes half of its values on and keeps the other half, so
 // 15 shuffles (and two more over the last four lanes) do what 6 x C do when every lane ends up with every sum, and lane l
 // holds the logit of class head_class(l): one exponential per lane instead of C per lane.  `scale`, `bias`: logit = sum *
