@@ -17,6 +17,8 @@
 // thread.  Six replicas of 128 x 800 x 500, forward + input gradient + weight gradient: 80 -> 50 us (the three kernels 21 +
 // 36 with its weight transpose + 19 -> 13.5 + 17.5 + 14); three of 128 x 784 x 128 forward 14.7 -> 4.6 us, weight
 // gradient 10.7 -> 4.6 us.
+#include <algorithm>
+
 #include "igemm_dev.h"
 
 namespace {
@@ -303,11 +305,16 @@ hipError_t launch_fc_f32(hipStream_t st, int replicas, const ConvGeom &g, const 
 // 6.4 / 11.9, 7.9 / 16.5, 16 / 53; 64 rows 6.4 / 4.3, 7.0 / 5.7, 11.5 / 12.5, 14.0 / 17.7, 39 / 59; 128 rows 10.1 / 4.4,
 // 10.8 / 7.5, 18.2 / 17.3, 22.3 / 23.6, 68 / 83; 256 rows 13.4 / 5.4, 19.7 / 10.8, 30.8 / 28.6, 39.3 / 37.4, 127 / 132; at
 // 512 rows this one leads at every size (245 / 233).  So the number of tiles it takes grows with the rows.
+// Rows of no whole vectors are loaded and stored value by value here, which the generic kernel does with either, so it is
+// ahead earlier: 304 tiles (5 x 175 x 307) at 32 rows 4.7 / 5.7, 65 7.3 / 6.6, 128 10.1 / 7.7, 300 15.4 / 12.8, 500 17.9 /
+// 19.1; 560 (8 x 241 x 263) 4.8 / 6.6, 7.6 / 9.7, 10.4 / 11.7, 19.4 / 22.2, 22.7 / 32.6; 3700 (8 x 900 x 502) at 200 rows 32 / 47.
 bool wgrad_fc_f32_applicable(int dtype, int replicas, const ConvGeom &g) {
   if (dtype != 0 || !plain_product(g) || g.M > 1024 || (g.N + 15) / 16 > 65535) return false;
   const long long lim = 1LL << 31;
   if ((long long)g.M * g.K * 4 >= lim || (long long)g.M * g.N * 4 >= lim || (long long)g.N * g.K * 4 >= lim) return false;
-  return g.M >= 512 || fc_tiles(g.N, g.K, 32) * replicas <= (g.M > 16 ? 24LL * (g.M - 8) : 192LL);
+  const long long tiles = fc_tiles(g.N, g.K, 32) * replicas;
+  if (g.N % 4 != 0 || g.K % 4 != 0) return tiles <= (g.M > 400 ? 200 : std::min(400, std::max(150, 6 * (g.M - 12))));
+  return g.M >= 512 || tiles <= std::max(192, 24 * (g.M - 8));
 }
 
 hipError_t launch_wgrad_fc_f32(hipStream_t st, int replicas, const ConvGeom &g, const WgradIO &io) {
