@@ -490,10 +490,26 @@ bool short_contraction(const ConvGeom &g, const HaloGeom &hg, int replicas) {
 }
 }  // namespace
 
+namespace {
+// Stride 2 on images that do not cut into full tiles: of the sizes the uniform-tap gather kernel takes as well, it keeps those
+// where the patch kernel's wider workgroups are no gain.  Patch / gather time on 28 x 28, 14 x 14, 24 x 24, 12 x 12 and 7 x 7
+// images: 96 and 128 outputs 1.02 to 1.2 (320 -> 128, 200 workgroups; 0.98 at best); 160 to 256 outputs 0.67 to 0.77 up to 200
+// workgroups, 1.0 to 1.05 around 400, 1.06 to 1.24 at 600 to 700; 64 outputs 0.9 at 100, 1.06 at 300 (15 x 15: 1.28 at 250);
+// 320 outputs 0.68 to 0.99 throughout.
+bool gather_keeps_s2(const ConvGeom &g, const HaloGeom &hg, int replicas) {
+  const int pq = g.P * g.Q;
+  const bool full = 2 * g.P == g.Hin && 2 * g.Q == g.Win && 128 % g.Q == 0 && (pq % 128 == 0 || 128 % pq == 0);
+  if (g.sp != 2 || g.Cc % 32 != 0 || full || g.N > 256) return false;
+  const long long groups = (long long)((hg.rows + hg.TH - 1) / hg.TH) * replicas * (g.N > 128 ? 2 : 1);
+  return (g.N > 64 && g.N <= 128) || groups > (g.N > 64 ? 256 : 128);
+}
+}  // namespace
+
 bool conv_halo_applicable(int dtype, int replicas, const ConvGeom &g, const GemmIO &io, bool out_f32) {
   HaloGeom hg;
   if (dtype != 1 || out_f32 || g.R * g.S < 2 || g.Cc < 16 || g.M < 256 || !make_halo_geom(g, hg)) return false;
   if (halo_wide(g, io) && !halo_vector(g, io) && short_contraction(g, hg, replicas)) return false;
+  if (gather_keeps_s2(g, hg, replicas)) return false;
   // rows of an even number of channels start on a dword wherever the tensors do
   const bool narrow_ok = g.sp == 1 && (g.Cc % 2 == 1 || (aligned_to(io.in, 4) && aligned_to(io.w, 4) && io.in_rs % 2 == 0 && io.w_rs % 2 == 0));
   return (halo_vector(g, io) || narrow_ok) && io.in_bytes > 0 && io.in_bytes < (1LL << 31) &&
