@@ -346,7 +346,17 @@ bool plan_f32(const ConvGeom &g, int replicas, F32Plan &best) {
   // the gather kernel with twice as many workgroups is shorter.  us, gather kernel / here: 64 -> 128 channels on 32 x 32, 128
   // workgroups 20.1 / 23.4, 256 29.7 / 25.5; 128 -> 256 on 16 x 16, 128 34.1 / 42.4, 256 51.9 / 45.0; 96 -> 96 on 28 x 28, 100
   // 26.0 / 33.2, 200 38.7 / 34.4; 32 -> 32 on 32 x 32, 128 12.3 / 13.8, 256 17.9 / 15.1.
-  if (g.sp == 2 && (long long)fg.tiles * fg.nb * replicas < 160) return false;
+  // A long contraction (over 1000) takes a full tile to every compute unit: 128 -> 320 on 28 x 28, 250 workgroups at 126 of 128
+  // pixels 51.6 / 56.6; 256 -> 256 on 14 x 14, 264 at 119 pixels 96 / 112.
+  const long long groups = (long long)fg.tiles * fg.nb * replicas;
+  if (g.sp == 2 && groups * fg.TH * g.Q < (g.K > 1000 ? 250 : 156) * 128) return false;
+  // Short contractions are mostly staging and epilogue, the latter value by value where the output channels are no multiple
+  // of 4.  Time here over the gather kernel's, 3 x 3 windows, by input channels: 10 to 50 outputs (no multiple of 4) in large
+  // launches, 14 x 14 / 32 x 32 images, 8 1.7 / 1.5, 12 1.4 / 1.2, 16 1.2 / 1.0, 20 1.24 / 1.05, 24 1.15 / 0.95, 32 0.95 /
+  // 0.8; 85 outputs 16 1.38; but 151 outputs from 12 up 1.0 / 0.96; 151 outputs in 256 to 512 workgroups 12 1.25, 20 1.16,
+  // 24 1.04; small launches 8 1.15, 12 0.93 to 1.0; 16 and 20 outputs in large ones 8 1.15 / 0.98, 12 0.93 / 0.8.
+  if (g.sp == 1 && g.N % 4 != 0 && g.K < (groups <= 128 || (groups > 512 && g.N > 128) ? 100 : g.N > 32 ? 240 : 216)) return false;
+  if (g.sp == 1 && g.K < 100 && g.N <= 32 && groups > 256) return false;
   fg.PRI = g.sp * (g.P - 1) + g.R;
   const int last_h = g.off + (g.R - 1) * g.sr, last_w = g.off + (g.S - 1) * g.sr;
   fg.omin_h = g.off < last_h ? g.off : last_h, fg.omin_w = g.off < last_w ? g.off : last_w;
