@@ -36,7 +36,7 @@ constexpr int kDxDyPitch = kWinMaxCout + 4;  // of the dy tile, which lies there
 struct WinGeom {
   int B, H, W, Cin, Cout, R, pad, P, Q;  // dx [B][H][W][Cin], dy [B][P][Q][Cout]
   int NC;                                // R*R*Cin: columns of col
-  int vec;                               // Cin % 4 == 0: the gather runs on 16-byte vectors
+  int vec;                               // channels the gather takes at a time: 4, 2 or 1
   FastDiv dCin, dW, dCv, dR;             // no integer division on the device (dCv: vectors of a pixel)
 };
 
@@ -63,7 +63,7 @@ __device__ __forceinline__ void plain_dx(const WinGeom &g, const float *dy, cons
     }
 }
 
-// V: consecutive channels a thread gathers at a time (4 or 1)
+// V: consecutive channels a thread gathers at a time (4, 2 or 1)
 template <int V>
 __global__ __launch_bounds__(kWinThreads, 4) void k_dgrad_window(const WinGeom g, const float *__restrict__ dy, long long dy_rs,
                                                              const float *__restrict__ w, long long w_rs,
@@ -171,7 +171,7 @@ __global__ __launch_bounds__(kWinThreads, 4) void k_dgrad_window(const WinGeom g
 
     // gather over the taps of these columns, in order
     for (int i = tid; i < total / V; i += kWinThreads) {
-      const int pix = (int)fdiv((uint32_t)i, V == 4 ? g.dCv : g.dCin), c = i * V - pix * g.Cin;
+      const int pix = (int)fdiv((uint32_t)i, g.dCv), c = i * V - pix * g.Cin;
       const int hh = (int)fdiv((uint32_t)pix, g.dW), ww = pix - hh * g.W;
       const int t0 = (int)fdiv((uint32_t)max(c0 - c + g.Cin - 1, 0), g.dCin);
       const int t1 = min(taps, (int)fdiv((uint32_t)max(c0 + kDxCols - c + g.Cin - 1, 0), g.dCin));
@@ -229,16 +229,21 @@ bool make_win_geom(int B, int H, int W, int Cin, int Cout, int R, int pad, WinGe
   if (g.P < 1 || g.Q < 1 || g.P * g.Q > kWinMaxPix || Cout > kWinMaxCout || Cout < 1) return false;
   if ((long long)B * H * W * Cin >= (1LL << 31) || (long long)R * R * Cin > kWinLdsBytes / 4) return false;
   g.NC = R * R * Cin;
-  g.vec = Cin % 4 == 0;
+  g.vec = Cin % 4 == 0 ? 4 : Cin % 2 == 0 ? 2 : 1;
   g.dCin = make_fastdiv(Cin), g.dW = make_fastdiv(W), g.dR = make_fastdiv(R);
-  g.dCv = make_fastdiv(g.vec ? Cin / 4 : 1);
-  const long long col = ((long long)kWinMaxPix * ((Cout + 7) / 8 * 8 + 4) + (long long)g.P * g.Q * (g.NC + (g.vec ? 4 : 1))) * 4;
+  g.dCv = make_fastdiv(Cin / g.vec);
+  const long long col = ((long long)kWinMaxPix * ((Cout + 7) / 8 * 8 + 4) + (long long)g.P * g.Q * (g.NC + (g.vec == 4 ? 4 : 1))) * 4;
   return col <= kWinLdsBytes && dx_lds_bytes(g) <= kWinLdsBytes;
 }
 
 }  // namespace
 
 bool dgrad_window_applicable(int dtype, int B, int H, int W, int Cin, int Cout, int R, int stride, int pad) {
+  // A tap of 56 channels or more under a 3 x 3 window leaves two taps to a chunk of columns, and with few output channels the
+  // products are short beside what the gather spends on each chunk: the row kernel of igemm_f32.hip is ahead.  us, this / row
+  // kernel with its weight transpose, 7 x 7: 64 -> 16 channels, 16 images 12.6 / 9.5, 1000 32 / 17.9; 64 -> 32 14.7 / 13.0 and
+  // 40 / 24; but 64 -> 50 18.5 / 21.5, 32 -> 32 8.3 / 12.9.
+  if (R == 3 && Cin >= 56 && Cout >= 8 && Cout <= 32) return false;
   WinGeom g;
   return dtype == 0 && stride == 1 && R > 1 && B >= 1 && B <= 65535 && make_win_geom(B, H, W, Cin, Cout, R, pad, g);
 }
@@ -252,18 +257,15 @@ hipError_t launch_dgrad_window(hipStream_t st, int n, int B, int H, int W, int C
   const size_t lds = dx_lds_bytes(g);
   static bool raised = false;   // more than 64 KB of dynamic LDS has to be asked for once
   if (!raised) {
-    for (const void *f : {(const void *)k_dgrad_window<4>, (const void *)k_dgrad_window<1>}) {
+    for (const void *f : {(const void *)k_dgrad_window<4>, (const void *)k_dgrad_window<2>, (const void *)k_dgrad_window<1>}) {
       const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kWinLdsBytes);
       if (e != hipSuccess) return e;
     }
     raised = true;
   }
-  if (g.vec)
-    hipLaunchKernelGGL(k_dgrad_window<4>, dim3(B, n), dim3(kWinThreads), lds, st, g, dy, dy_rs, w, w_rs, mask, mask_rs,
-                       accumulate, dx, dx_rs);
-  else
-    hipLaunchKernelGGL(k_dgrad_window<1>, dim3(B, n), dim3(kWinThreads), lds, st, g, dy, dy_rs, w, w_rs, mask, mask_rs,
-                       accumulate, dx, dx_rs);
+  const auto kernel = g.vec == 4 ? k_dgrad_window<4> : g.vec == 2 ? k_dgrad_window<2> : k_dgrad_window<1>;
+  hipLaunchKernelGGL(kernel, dim3(B, n), dim3(kWinThreads), lds, st, g, dy, dy_rs, w, w_rs, mask, mask_rs, accumulate, dx,
+                     dx_rs);
   return hipGetLastError();
 }
 

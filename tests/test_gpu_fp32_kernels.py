@@ -66,6 +66,11 @@ WINDOW_CASES = [
     (1, 3, 3, 11, 15, 20, 3, 1, 1),      # 33
     (3, 2, 10, 10, 7, 50, 7, 1, 2),      # 7 x 7
     (1, 1, 12, 12, 4, 3, 5, 1, 0),       # a single vector per pixel
+    (2, 2, 8, 8, 50, 40, 3, 1, 1),       # even counts: two channels at a time, four chunks, taps across every seam
+    (1, 2, 6, 6, 2, 17, 2, 1, 0),        # ... a single pair
+    (1, 2, 5, 12, 130, 33, 2, 1, 0),     # ... a tap wider than a chunk
+    (2, 2, 7, 7, 54, 9, 3, 1, 1),        # the widest tap of a 3 x 3 window with few outputs
+    (2, 2, 7, 7, 56, 32, 3, 1, 1),       # ... and the first that takes the row kernel
 ]
 
 

@@ -95,6 +95,8 @@ SPLIT = [
     (16, 24, 14, 14, 50, 20, 3, 2, 1),   # stride 2, which takes 160 workgroups
     (1, 2, 12, 12, 20, 50, 5, 1, 0),     # input gradient with an image per workgroup
     (1, 2, 7, 7, 28, 48, 3, 1, 1),
+    (1, 2, 7, 7, 30, 48, 3, 1, 1),       # ... two channels at a time
+    (1, 2, 7, 7, 27, 48, 3, 1, 1),       # ... one
 ]
 
 
