@@ -346,16 +346,19 @@ bool plan_f32(const ConvGeom &g, int replicas, F32Plan &best) {
   // the gather kernel with twice as many workgroups is shorter.  us, gather kernel / here: 64 -> 128 channels on 32 x 32, 128
   // workgroups 20.1 / 23.4, 256 29.7 / 25.5; 128 -> 256 on 16 x 16, 128 34.1 / 42.4, 256 51.9 / 45.0; 96 -> 96 on 28 x 28, 100
   // 26.0 / 33.2, 200 38.7 / 34.4; 32 -> 32 on 32 x 32, 128 12.3 / 13.8, 256 17.9 / 15.1.
-  // A long contraction (over 1000) takes a full tile to every compute unit: 128 -> 320 on 28 x 28, 250 workgroups at 126 of 128
-  // pixels 51.6 / 56.6; 256 -> 256 on 14 x 14, 264 at 119 pixels 96 / 112.
+  // A long contraction (over 1000) into four or more column blocks, which fetch their weights each, takes a full tile to every
+  // compute unit: 128 -> 320 on 28 x 28, 250 workgroups at 126 of 128 pixels 51.6 / 56.6; 256 -> 256 on 14 x 14, 264 at 119 pixels
+  // 96 / 112; but 256 -> 50 on 28 x 28, 165 129 / 92.  Odd channel counts are gathered value by value, which a long
+  // contraction makes slower than anything here: 65 -> 32 under 5 x 5, 27 workgroups 111 / 66.
   const long long groups = (long long)fg.tiles * fg.nb * replicas;
-  if (g.sp == 2 && groups * fg.TH * g.Q < (g.K > 1000 ? 250 : 156) * 128) return false;
+  if (g.sp == 2 && (g.Cc % 2 == 0 || g.K < 400) && groups * fg.TH * g.Q < (g.K > 1000 && fg.nb > 3 ? 250 : 156) * 128) return false;
   // Short contractions are mostly staging and epilogue, the latter value by value where the output channels are no multiple
-  // of 4.  Time here over the gather kernel's, 3 x 3 windows, by input channels: 10 to 50 outputs (no multiple of 4) in large
-  // launches, 14 x 14 / 32 x 32 images, 8 1.7 / 1.5, 12 1.4 / 1.2, 16 1.2 / 1.0, 20 1.24 / 1.05, 24 1.15 / 0.95, 32 0.95 /
-  // 0.8; 85 outputs 16 1.38; but 151 outputs from 12 up 1.0 / 0.96; 151 outputs in 256 to 512 workgroups 12 1.25, 20 1.16,
-  // 24 1.04; small launches 8 1.15, 12 0.93 to 1.0; 16 and 20 outputs in large ones 8 1.15 / 0.98, 12 0.93 / 0.8.
-  if (g.sp == 1 && g.N % 4 != 0 && g.K < (groups <= 128 || (groups > 512 && g.N > 128) ? 100 : g.N > 32 ? 240 : 216)) return false;
+  // of 4.  Time here over the gather kernel's, 3 x 3 windows, by (even) input channels: 10 to 50 outputs (no multiple of 4) in
+  // large launches, 14 x 14 / 32 x 32 images, 8 1.7 / 1.5, 12 1.4 / 1.2, 16 1.2 / 1.0, 20 1.24 / 0.9 to 1.05, 24 1.15 / 0.95, 32
+  // 0.95 / 0.8; 85 outputs 16 1.38; but 151 outputs from 12 up 1.0 / 0.96; 151 outputs in 256 to 512 workgroups 12 1.25, 20
+  // 1.16, 24 1.04; small launches 8 1.15, 12 0.93 to 1.0; 16 and 20 outputs in large ones 8 1.15 / 0.98, 12 0.93 / 0.8.
+  const int short_k = groups <= 128 || (groups > 512 && g.N > 128) ? 100 : g.Q >= 24 ? 150 : g.N > 32 ? 240 : 216;
+  if (g.sp == 1 && g.N % 4 != 0 && g.Cc % 2 == 0 && g.K < short_k) return false;
   if (g.sp == 1 && g.K < 100 && g.N <= 32 && groups > 256) return false;
   fg.PRI = g.sp * (g.P - 1) + g.R;
   const int last_h = g.off + (g.R - 1) * g.sr, last_w = g.off + (g.S - 1) * g.sr;
