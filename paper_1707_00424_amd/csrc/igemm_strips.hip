@@ -149,6 +149,9 @@ bool make_strips(const ConvGeom &g, int replicas, StripGeom &wg) {
 bool generic_is_shorter(const ConvGeom &g, int replicas, StripGeom &wg) {
   if (strips_pair(g) != 2) return false;
   const int tn = g.N <= 32 ? 32 : g.N <= 64 ? 64 : g.N % 96 == 0 || g.N <= 96 ? 96 : 128;
+  // 128 x 128 tiles are no shorter at stride 1 (32 -> 250 on 8 x 8, 3 x 29 images, 25.2 / 19.2), nor several of them (50 -> 320 on
+  // 12 x 12 with stride 2, 31.3 / 26.1; 250 -> 130 on 7 x 7 with stride 2, 16 images, 19.0 / 22.0)
+  if (tn > 64 && (g.sp == 1 || g.N > 256)) return false;
   const GenericSplit s = generic_split(g, replicas, tn, 128);
   if (s.steps > 5 || s.groups > (tn == 32 ? 512 : 256)) return false;
   split_strips(g, replicas, strips_slots(g), 260, wg);

@@ -53,7 +53,7 @@ def exhaustive(dtype, n, B, H, W, cin, cout, k, stride, pad):
             other = 2500 + chunk * (2500 if tiles * generic > 256 else 1600) + (4500 + generic * partial if generic > 1 else 0)
             if other < cost + 4500 + splits * partial:
                 return generic
-    elif pair and chunk <= 5 and tiles * generic <= (512 if tn == 32 else 256) and pps * rows >= 8:
+    elif pair and (tn <= 64 or stride == 2 and cout <= 256) and chunk <= 5 and tiles * generic <= (512 if tn == 32 else 256) and pps * rows >= 8:
         return generic
     return splits
 
