@@ -313,7 +313,7 @@ bool wgrad_fc_f32_applicable(int dtype, int replicas, const ConvGeom &g) {
   const long long lim = 1LL << 31;
   if ((long long)g.M * g.K * 4 >= lim || (long long)g.M * g.N * 4 >= lim || (long long)g.N * g.K * 4 >= lim) return false;
   const long long tiles = fc_tiles(g.N, g.K, 32) * replicas;
-  if (g.N % 4 != 0 || g.K % 4 != 0) return tiles <= (g.M > 400 ? 200 : std::min(400, std::max(150, 6 * (g.M - 12))));
+  if (g.N % 4 != 0 || g.K % 4 != 0) return tiles <= (g.M > 400 ? 200 : std::min(400, std::max(150, 4 * g.M + 70)));
   return g.M >= 512 || tiles <= std::max(192, 24 * (g.M - 8));
 }
 
