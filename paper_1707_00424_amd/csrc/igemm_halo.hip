@@ -19,7 +19,7 @@
 // from memory reads 64-byte pieces 2 pixels apart, nine times over, and is bound by that.
 #include <stdlib.h>
 
-#include "igemm_dev.h"
+#include "igemm_halo.h"
 
 namespace {
 
@@ -29,19 +29,6 @@ constexpr uint32_t kOob = 0x80000000u;
 constexpr int kHaloSlots = 400;    // LDS patch capacity in pixels (32 KB at 32 channels + padding)
 constexpr int kHaloSlotsHalf = 304;  // 128 output pixels at stride 1, 24 KB
 constexpr int kHaloSlotsS2 = 592;  // stride 2: 17 x 33 (16 output columns) or 2 x 17 x 17 (two 8 x 8 outputs), 47 KB
-
-// A tile is a number of whole output rows, counted through all images (row b*P + p), as many as BM pixels hold: 8 rows of
-// 32, four images of 8 x 8, 9 rows of 28.  An image that ends inside a tile adds its own halo rows to the patch.
-struct HaloGeom {
-  int TH;              // output rows per tile
-  int HC;              // patch columns = sp*(Q - 1) + S
-  int PRI;             // patch rows of a whole image = sp*(P - 1) + R
-  int slots;           // pixels of the largest patch
-  int rows;            // output rows of all images
-  int omin_h, omin_w;  // smallest tap offset (input row = sp * output row + offset)
-  FastDiv dP, dHC, dPRI;  // no integer division on the device
-  int tiles, nb, bn;   // pixel tiles, column blocks and their width in channels (set with the grid)
-};
 
 // LDS of a workgroup with TN column tiles: patch + a ring of three weight tiles; the epilogue reuses the same
 // bytes as its staging strips
@@ -306,16 +293,6 @@ __device__ __forceinline__ void conv_halo_body(const ConvGeom &g, const GemmIO &
   if (STAT) write_tile_sums<BN, 4>(g, io, rep, hg.tiles, tile, n0, tid, wsums);
 }
 
-// Workgroups are handed to the eight XCDs in turn, so ids that differ by 8 share an L2: the column blocks
-// of one pixel tile get such ids.  They run at the same time on the same XCD, the patch is fetched into
-// that L2 once, and their partial output rows meet there before they are written back.
-__device__ __forceinline__ bool halo_block(const HaloGeom &hg, int &tile, int &col) {
-  const int per_group = 8 * hg.nb;
-  const int group = blockIdx.x / per_group, within = blockIdx.x - group * per_group;
-  tile = group * 8 + (within & 7), col = within >> 3;
-  return tile < hg.tiles;  // the grid is padded to whole groups
-}
-
 // Column blocks 0 .. nb-2 are TN tiles wide, the last one TL <= TN tiles (160 channels = 96 + 64,
 // 320 = 128 + 128 + 64): a narrower last block multiplies no padding.
 template <int TN, int TL, bool STAT>
@@ -438,7 +415,9 @@ hipError_t run_halo(hipStream_t st, int replicas, const ConvGeom &g, const GemmI
   return hipGetLastError();
 }
 
-bool make_halo_geom(const ConvGeom &g, HaloGeom &hg, bool half = false) {
+}  // namespace
+
+bool make_halo_geom(const ConvGeom &g, HaloGeom &hg, bool half) {
   const bool s2 = g.sp == 2;
   const int BM = s2 || half ? 128 : 256;
   if (g.dshift != 0 || g.R < g.sp || g.S < g.sp) return false;
@@ -470,8 +449,6 @@ bool make_halo_geom(const ConvGeom &g, HaloGeom &hg, bool half = false) {
   hg.omin_h = g.off < o_last ? g.off : o_last, hg.omin_w = g.off < w_last ? g.off : w_last;
   return true;
 }
-
-}  // namespace
 
 namespace {
 // Layers of whole-vector input whose output channels are no multiple of 4: the kernel that gathers per tap loads vectors as
@@ -507,7 +484,7 @@ bool gather_keeps_s2(const ConvGeom &g, const HaloGeom &hg, int replicas) {
 
 bool conv_halo_applicable(int dtype, int replicas, const ConvGeom &g, const GemmIO &io, bool out_f32) {
   HaloGeom hg;
-  if (dtype != 1 || out_f32 || g.R * g.S < 2 || g.Cc < 16 || g.M < 256 || !make_halo_geom(g, hg)) return false;
+  if (dtype != 1 || out_f32 || g.R * g.S < 2 || g.Cc < 16 || g.M < 256 || !make_halo_geom(g, hg, false)) return false;
   if (halo_wide(g, io) && !halo_vector(g, io) && short_contraction(g, hg, replicas)) return false;
   if (gather_keeps_s2(g, hg, replicas)) return false;
   // rows of an even number of channels start on a dword wherever the tensors do
@@ -555,7 +532,7 @@ HaloVariant halo_variant(const ConvGeom &g, const HaloGeom &hg, int replicas) {
 // -0.7 % for the other layers of the same network).
 int conv_halo_stat_splits(const ConvGeom &g, const GemmIO &io, int replicas) {
   HaloGeom hg;
-  if (!halo_vector(g, io) || !make_halo_geom(g, hg)) return 0;
+  if (!halo_vector(g, io) || !make_halo_geom(g, hg, false)) return 0;
   const HaloVariant v = halo_variant(g, hg, replicas);
   if (v == kHalo96 || v == kHaloHalf96) return 0;
   if (v == kHaloHalf128) make_halo_geom(g, hg, true);
@@ -563,8 +540,9 @@ int conv_halo_stat_splits(const ConvGeom &g, const GemmIO &io, int replicas) {
 }
 
 hipError_t launch_conv_halo(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io) {
+  if (conv_patch_applicable(replicas, g, io)) return launch_conv_patch(st, replicas, g, io);
   HaloGeom hg;
-  if (!make_halo_geom(g, hg)) return hipErrorInvalidValue;
+  if (!make_halo_geom(g, hg, false)) return hipErrorInvalidValue;
   const int n = g.N;
   if (!halo_vector(g, io)) {
     if (io.stat) return hipErrorInvalidValue;

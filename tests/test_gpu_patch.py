@@ -1,0 +1,83 @@
+"""The stride-1 3x3 bf16 kernel with operands loaded straight into LDS: each of its tile shapes, one tile and several per
+workgroup, ragged channel chunks and column blocks, images that end inside a tile, and every form of the epilogue, against
+plain products in 64 bits."""
+import pytest
+
+import test_gpu_kernels as tk
+
+pytestmark = pytest.mark.gpu
+gpu = tk.gpu
+
+CASES = [
+    # n, B, H, W, Cin, Cout: tile shape (pixels x channels, last column block) of the forward pass
+    (2, 3, 16, 16, 24, 40),     # 128 x 64, half of the columns padding, one ragged chunk of channels
+    (1, 200, 32, 32, 16, 64),   # 128 x 64, 1600 tiles on 768 workgroups
+    (1, 100, 28, 28, 40, 96),   # 128 x 96, rows of 28, tiles across images
+    (1, 53, 32, 32, 16, 160),   # 128 x 96 and 64
+    (1, 256, 32, 32, 40, 64),   # 256 x 64, two tiles each
+    (1, 160, 32, 32, 72, 96),   # 256 x 96, 640 tiles on 512 workgroups, three chunks
+    (3, 14, 24, 24, 16, 160),   # 256 x 96 and 64
+    (1, 64, 32, 32, 32, 128),   # 256 x 128
+    (1, 1023, 8, 8, 16, 120),   # same, four images per tile and a shorter ring of weight tiles, ragged everywhere
+    (1, 25, 32, 32, 64, 320),   # 256 x 128 and 64
+    (1, 100, 32, 32, 16, 320),  # same, both widths several tiles per workgroup
+    (1, 399, 8, 8, 32, 304),    # same with four images per tile, the narrow block ragged
+]
+
+
+def _products64(torch, x, w, transpose):
+    """``[B, H, W, C]`` with ``[Cout, 3, 3, Cin]``; transposed: the input gradient."""
+    B, H, W, _ = x.shape
+    xp = torch.nn.functional.pad(x.double(), (0, 0, 1, 1, 1, 1))
+    out = 0
+    for r in range(3):
+        for c in range(3):
+            tap = xp[:, r:r + H, c:c + W].reshape(B * H * W, -1)
+            m = w[:, 2 - r, 2 - c] if transpose else w[:, r, c].t()
+            out = out + tap @ m.double().contiguous()
+    return out.reshape(B, H, W, -1)
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_shapes_and_epilogues(gpu, case):
+    torch, pb = gpu
+    n, B, H, W, Cin, Cout = case
+    gen = torch.Generator(device="cuda").manual_seed(sum(case))
+
+    def normal(*shape, std=1.0, dtype=torch.bfloat16):
+        return (torch.randn(shape, generator=gen, device="cuda") * std).to(dtype)
+
+    x, dy, resid, mask, prev = (normal(n, B, H, W, c) for c in (Cin, Cout, Cout, Cin, Cin))
+    w = normal(n, Cout, 3, 3, Cin, std=(9 * Cin) ** -0.5)
+    bias = normal(n, Cout, dtype=torch.float32)
+    desc = pb.parle_conv_desc(1, n, B, H, W, Cin, Cout, 3, 1, 1)
+    wt = torch.empty_like(w)
+
+    def forward(bias, resid, relu):
+        y = torch.full_like(dy, float("nan"))
+        pb.parle_k_conv_forward(desc, x, w, bias, resid, relu, y)
+        return y
+
+    def backward(mask, onto):
+        g = torch.full_like(x, float("nan")) if onto is None else onto.clone()
+        pb.parle_k_conv_backward_data(desc, dy, w, mask, int(onto is not None), wt, g)
+        return g
+
+    def near(name, got, ref):
+        # half a bf16 ulp (2^-9) on the store and room for the order of the sums
+        bound = 2.0 ** -8 * ref.abs() + 2e-5 * ref.abs().max()
+        worst = ((got.double() - ref).abs() - bound).max().item()
+        assert worst <= 0, f"{name}: {worst:.3e} outside tolerance"
+
+    for a in range(n):
+        y = _products64(torch, x[a], w[a], False)
+        g = _products64(torch, dy[a], w[a], True)
+        b, r, m = bias[a].double(), resid[a].double(), mask[a] > 0
+        near("plain", forward(None, None, 0)[a], y)
+        near("bias, ReLU", forward(bias, None, 1)[a], (y + b).relu())
+        near("bias, residual", forward(bias, resid, 0)[a], y + b + r)
+        near("residual, ReLU", forward(None, resid, 1)[a], (y + r).relu())
+        near("gradient", backward(None, None)[a], g)
+        near("gradient, mask", backward(mask, None)[a], g * m)
+        near("gradient, added", backward(None, prev)[a], g + prev[a].double())
+        near("gradient, mask, added", backward(mask, prev)[a], g * m + prev[a].double())
