@@ -36,32 +36,6 @@ using namespace igemm_dev;
 constexpr uint32_t kOob = 0x80000000u;
 constexpr int kPix = 64;  // bytes of a patch pixel or weight row in LDS: 32 channels
 
-__device__ __forceinline__ u4 buffer_desc(const void *p, uint32_t bytes) {
-  const uint64_t a = (uint64_t)p;
-  u4 r;
-  r.x = __builtin_amdgcn_readfirstlane((uint32_t)a);
-  r.y = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32) & 0xffffu);
-  r.z = __builtin_amdgcn_readfirstlane(bytes);
-  r.w = 0x00020000u;
-  return r;
-}
-
-// 64 lanes x 16 bytes straight into LDS at `lds` + 16 * lane; a lane whose offset lies beyond the buffer writes zeros.
-// The waits in front cover an operand that the vector unit has just written to a scalar register.
-__device__ __forceinline__ void dma16(uint32_t lds, const u4 &rsrc, uint32_t voff, uint32_t soff) {
-  asm volatile("s_nop 3\n\ts_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff)
-               : "memory");
-}
-// ... and 64 lanes x 4 bytes at `lds` + 4 * lane
-__device__ __forceinline__ void dma4(uint32_t lds, const u4 &rsrc, uint32_t voff) {
-  asm volatile("s_nop 3\n\ts_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc) : "memory");
-}
-// The counter takes the compiler's own loads and stores along, which only makes a wait longer.
-template <int N>
-__device__ __forceinline__ void wait_loads() {
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
 __device__ __forceinline__ void swap32(uint32_t &a, uint32_t &b) {
   const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
   a = r[0], b = r[1];

@@ -17,12 +17,21 @@
 // Images 8 pixels wide take sub-steps of two rows of 8 pixels: the fragment of the row pair that
 // starts at x row t serves tap row r of the dy pair that starts at row t + 1 - r, pairs start at
 // even dy rows, so one of three fragment sets is reused and two enter per sub-step.
-// A workgroup is NT wavefronts (NT dy tiles sharing one x tile).  It walks blocks of 128 pixels
-// (8 rows x 16 columns, or two 8 x 8 images) of the images of its split; the operands of the next block travel from memory to
-// registers while the current block is multiplied, LDS is single-buffered.  Partial sums of the
-// splits go to per-split buffers that a second kernel adds in a fixed order (no float atomics).
-// BIAS: the workgroups of the first x tile also sum the dy vectors they stage (a thread keeps the same eight
-// channels for the whole kernel) and write the layer's bias gradient, the column sums of dy, behind the weights.
+// A workgroup is NTN x NTC wavefronts, dy tiles by x tiles.  It walks blocks of 128 pixels (8 rows x 16 columns, or two
+// 8 x 8 images) of the images of its split.  Operands go from memory to LDS directly (buffer loads with the LDS bit; halo
+// pixels outside the image write zeros), one block ahead in a second buffer, with one barrier per block: the form before
+// took them through registers into a single buffer, two barriers and the LDS stores between a wavefront's last product of a
+// block and its first of the next, with one wavefront per SIMD and nothing else to run (0.66 in the mean, matrix units 27 %
+// busy).  Sixteen pixels of a tile are 64 bytes each, one behind the other, as the loads write them; a transpose read takes
+// four consecutive pixels of 32 channels = 256 bytes per half wavefront, every bank once, without padding.
+// us, weight gradient with its reduction, before -> now, 3 x 128 images: 96 channels 32 x 32 102 -> 87, 320 on 16 x 16
+// 191 -> 162, 64 on 32 x 32 50 -> 41, 128 on 16 x 16 52 -> 41, 256 on 8 x 8 50 -> 41, 192 on 16 x 16 94 -> 69, 160 on 32 x 32
+// 219 -> 193.  Three or five dy tiles (96, 160 channels) load the SIMDs unevenly: 75 and 63 % of the matrix units at best.
+// Partial sums of the splits go to per-split buffers that a second kernel adds in a fixed order (no float atomics).
+// BIAS: the wavefronts of the first x tile multiply their dy fragments by ones as well, a tenth product beside the nine, and
+// write the layer's bias gradient, the column sums of dy, behind the weights.
+#include <stdlib.h>
+
 #include "igemm_dev.h"
 
 namespace {
@@ -32,7 +41,6 @@ typedef short s4v __attribute__((ext_vector_type(4)));
 
 constexpr int kBlockPixels = 128;                // 8 rows x 16 columns, or two images of 8 x 8
 constexpr int kSub = 8;                          // contraction sub-steps (16 pixels) per block
-constexpr int kXS = 96;                          // bytes per patch pixel: 32 channels + padding
 // patch of a block: one halo pixel around each image part
 template <int KC>
 struct Patch {
@@ -64,104 +72,82 @@ __device__ __forceinline__ u4 tr_frag(const bf16_t *tile, int ld, int krow, int 
   return r;
 }
 
-template <int NT, int KC, bool BIAS>
-__global__ __launch_bounds__(NT * 64) __attribute__((amdgpu_waves_per_eu(2))) void k_wgrad9(const Wg9Geom wg, const WgradIO io) {
+template <int NTN, int NTC, int KC, bool BIAS>
+__global__ __launch_bounds__(NTN * NTC * 64) __attribute__((amdgpu_waves_per_eu(2))) void k_wgrad9(const Wg9Geom wg, const WgradIO io) {
   typedef Patch<KC> PT;
-  constexpr int kSlots = PT::SLOTS, kPC = PT::PC;
-  constexpr int T = NT * 64;
-  constexpr int DS = NT * 64 + 32;                        // bytes per dy pixel row in LDS
-  constexpr int X_IT = (kSlots * 4 + T - 1) / T;          // 16-byte vectors of the patch per thread
-  constexpr int D_IT = kSub;                              // dy: 16 pixels per iteration
-  __shared__ __attribute__((aligned(16))) char xs[kSlots * kXS];
-  __shared__ __attribute__((aligned(16))) char ds[kBlockPixels * DS];
+  constexpr int kPC = PT::PC, W = NTN * NTC;
+  constexpr int XG = (PT::SLOTS + 15) / 16;               // loads of 16 pixels: one x tile, one dy tile (8)
+  constexpr int PIECES = NTC * XG + NTN * 8;
+  constexpr int IT = (PIECES + W - 1) / W;                // loads of a block per wavefront
+  constexpr int BUF = PIECES * 1024;
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int ct = blockIdx.x, ng = blockIdx.y;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wn = wave % NTN, wc = wave / NTN;             // this wavefront's dy tile and x tile
+  const int cg = blockIdx.x, ng = blockIdx.y;
   const int rep = blockIdx.z / wg.splits, split = blockIdx.z - rep * wg.splits;
   const int blk_begin = split * wg.bps, blk_end = min(wg.total_blocks, blk_begin + wg.bps);
-  const long long x_bytes = (long long)wg.B * wg.H * wg.W * wg.Cin * 2, dy_bytes = (long long)wg.B * wg.H * wg.W * wg.N * 2;
-  const __amdgpu_buffer_rsrc_t x_rsrc =
-      __builtin_amdgcn_make_buffer_rsrc((void *)((const bf16_t *)io.x + rep * io.x_rs), 0, (int)x_bytes, 0x00020000);
-  const __amdgpu_buffer_rsrc_t d_rsrc =
-      __builtin_amdgcn_make_buffer_rsrc((void *)((const bf16_t *)io.dy + rep * io.dy_rs), 0, (int)dy_bytes, 0x00020000);
+  const u4 x_rsrc = buffer_desc((const bf16_t *)io.x + rep * io.x_rs, (uint32_t)((long long)wg.B * wg.H * wg.W * wg.Cin * 2));
+  const u4 d_rsrc = buffer_desc((const bf16_t *)io.dy + rep * io.dy_rs, (uint32_t)((long long)wg.B * wg.H * wg.W * wg.N * 2));
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
 
-  // patch loader: vector id = it*T + tid covers patch slot id/4 = (image part, row, column), channels 8*(id%4) .. +7
-  int x_rel[X_IT], x_prow[X_IT], x_pcol[X_IT], x_img[X_IT];
+  // Piece q = it * W + wave: sixteen pixels of an x tile (q < NTC * XG) or of a dy tile.  `rel`: offset of this lane's pixel
+  // and channels from the block's first pixel; `pos`: patch row and column of an x pixel, to tell what lies inside the image.
+  int rel[IT], pos[IT];
 #pragma unroll
-  for (int it = 0; it < X_IT; ++it) {
-    const int id = it * T + tid, slot = id >> 2;
-    const int img = slot / (PT::PRI * kPC), rem = slot - img * (PT::PRI * kPC);
-    const int prow = rem / kPC, pcol = rem - prow * kPC;
-    x_prow[it] = slot < kSlots ? prow : -1000;   // never a valid image row
-    x_pcol[it] = pcol;
-    x_img[it] = img;
-    x_rel[it] = (((img * wg.H + prow - 1) * wg.W + (pcol - 1)) * wg.Cin + (id & 3) * 8) * 2;
+  for (int it = 0; it < IT; ++it) {
+    const int q = it * W + wave, px = lane >> 2, ch = (lane & 3) * 8;
+    if (q < NTC * XG) {
+      const int t = q / XG, slot = (q - t * XG) * 16 + px;
+      const int img = slot / (PT::PRI * kPC), rem = slot - img * (PT::PRI * kPC);
+      const int prow = rem / kPC, pcol = rem - prow * kPC;
+      rel[it] = (((img * wg.H + prow - 1) * wg.W + (pcol - 1)) * wg.Cin + (cg * NTC + t) * 32 + ch) * 2;
+      pos[it] = slot < PT::SLOTS ? prow | pcol << 8 | img << 16 : 0x4000;  // column 64 and beyond: never inside
+    } else {
+      const int d = q - NTC * XG, t = d >> 3, p = (d & 7) * 16 + px;  // pixel of the block
+      const int row = p / KC, col = p - row * KC;                      // two 8 x 8 images lie one behind the other
+      rel[it] = ((row * wg.W + col) * wg.N + (ng * NTN + t) * 32 + ch) * 2;
+      pos[it] = 0;
+    }
   }
-  // dy loader: iteration `it` covers 16 pixels of the block (one row of 16, or two rows of 8, which
-  // are consecutive in memory); this thread's pixel inside them and its channel vector are fixed
-  const int d_vec = tid % (NT * 4), d_pcol = tid / (NT * 4);
-  const int d_rel = (d_pcol * wg.N + (ng * NT * 32 + d_vec * 8)) * 2;
-  const int d_pitch = (KC == 16 ? wg.W : 16) * wg.N * 2;
-
-  u4 xreg[X_IT], dreg[D_IT];
-  const bool tally = BIAS && ct == 0;
-  float bsum[BIAS ? 8 : 1];
-  if (BIAS) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) bsum[e] = 0.f;
-  }
-  auto load_block = [&](int blk) {
-    const bool live = blk < blk_end;
+  auto load_block = [&](int blk, int buf) {
     int b, row0, col0;
     if (KC == 16) {
-      b = (int)fdiv((uint32_t)(live ? blk : 0), wg.dBpi);
-      const int rem = (live ? blk : 0) - b * wg.bpi;
+      b = (int)fdiv((uint32_t)blk, wg.dBpi);
+      const int rem = blk - b * wg.bpi;
       const int rb = (int)fdiv((uint32_t)rem, wg.dCbn), cb = rem - rb * wg.cbn;
       row0 = rb * 8, col0 = cb * 16;
     } else {
-      b = 2 * (live ? blk : 0), row0 = 0, col0 = 0;
+      b = 2 * blk, row0 = 0, col0 = 0;
     }
-    const int xbase = (((b * wg.H + row0) * wg.W + col0) * wg.Cin + ct * 32) * 2;
+    const int pix = (b * wg.H + row0) * wg.W + col0;
 #pragma unroll
-    for (int it = 0; it < X_IT; ++it) {
-      const int row = row0 + x_prow[it] - 1, col = col0 + x_pcol[it] - 1;
-      const bool ok = live && (unsigned)row < (unsigned)wg.H && (unsigned)col < (unsigned)wg.W && b + x_img[it] < wg.B;
-      xreg[it] = __builtin_amdgcn_raw_buffer_load_b128(x_rsrc, ok ? (uint32_t)(xbase + x_rel[it]) : kOobOffset, 0, 0);
-    }
-    // an image beyond the batch (odd batch, second 8 x 8 image of the last block) lies beyond the buffer: zeros
-    const int dbase = ((b * wg.H + row0) * wg.W + col0) * wg.N * 2;
-#pragma unroll
-    for (int it = 0; it < D_IT; ++it)
-      dreg[it] = __builtin_amdgcn_raw_buffer_load_b128(d_rsrc, live ? (uint32_t)(dbase + it * d_pitch + d_rel) : kOobOffset, 0, 0);
-  };
-  auto store_block = [&]() {
-#pragma unroll
-    for (int it = 0; it < X_IT; ++it) {
-      const int id = it * T + tid;
-      if (kSlots * 4 % T == 0 || id < kSlots * 4) *(u4 *)&xs[(id >> 2) * kXS + (id & 3) * 16] = xreg[it];
-    }
-#pragma unroll
-    for (int it = 0; it < D_IT; ++it) *(u4 *)&ds[(it * 16 + d_pcol) * DS + d_vec * 16] = dreg[it];
-    if (BIAS && tally) {
-#pragma unroll
-      for (int it = 0; it < D_IT; ++it) {
-        const uint32_t w[4] = {dreg[it].x, dreg[it].y, dreg[it].z, dreg[it].w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          bsum[2 * e] += __uint_as_float(w[e] << 16);
-          bsum[2 * e + 1] += __uint_as_float(w[e] & 0xffff0000u);
-        }
+    for (int it = 0; it < IT; ++it) {
+      const int q = it * W + wave;
+      if (PIECES % W != 0 && it == IT - 1 && q >= PIECES) break;
+      const uint32_t dst = lds0 + (uint32_t)(buf * BUF + q * 1024);
+      if (q < NTC * XG) {
+        const int row = row0 + (pos[it] & 0xff) - 1, col = col0 + (pos[it] >> 8 & 0xff) - 1;
+        const bool ok = (unsigned)row < (unsigned)wg.H && (unsigned)col < (unsigned)wg.W && b + (pos[it] >> 16) < wg.B;
+        dma16(dst, x_rsrc, ok ? (uint32_t)(pix * wg.Cin * 2 + rel[it]) : kOobOffset, 0);
+      } else {
+        // an image beyond the batch (odd batch, second 8 x 8 image of the last block) lies beyond the buffer: zeros
+        dma16(dst, d_rsrc, (uint32_t)(pix * wg.N * 2 + rel[it]), 0);
       }
     }
   };
 
-  f16v acc[3][3];
+  f16v acc[3][3], accb;
 #pragma unroll
-  for (int r = 0; r < 3; ++r)
+  for (int v = 0; v < 16; ++v) {
 #pragma unroll
-    for (int c = 0; c < 3; ++c)
+    for (int r = 0; r < 3; ++r)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[r][c][v] = 0.f;
+      for (int c = 0; c < 3; ++c) acc[r][c][v] = 0.f;
+    accb[v] = 0.f;
+  }
+  const bool tally = BIAS && cg == 0 && wc == 0;
+  const u4 ones = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
 
   // fragment addressing of the transpose read: 16-lane group gq covers columns 16*(gq%2) .. +15 and
   // contraction half gq/2
@@ -170,28 +156,32 @@ __global__ __launch_bounds__(NT * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
   // contraction index e of the sub-step -> patch slot: one row of 16, or two rows of 8 (e / 8 is the
   // lane's contraction half gq / 2; the transpose read adds 4 slots for its second part)
   const int frag_x = KC == 16 ? frag_k : (gq >> 1) * kPC + (j >> 2);
-  const bf16_t *xt = (const bf16_t *)xs, *dt = (const bf16_t *)ds + wave * 32;
+  const char *xt, *dt;
   // x fragments of the sub-step whose first pixel is patch row `prow`, at the three column shifts;
   // dy fragment of sub-step p
   auto read_x = [&](int prow, u4 (&f)[3]) {
 #pragma unroll
-    for (int s = 0; s < 3; ++s) f[s] = tr_frag(xt + (prow * kPC + s) * (kXS / 2), kXS / 2, frag_x, frag_c);
+    for (int s = 0; s < 3; ++s) f[s] = tr_frag((const bf16_t *)xt + (prow * kPC + s) * 32, 32, 0, 0);
   };
-  auto read_d = [&](int p) { return tr_frag(dt + p * 16 * (DS / 2), DS / 2, frag_k, frag_c); };
+  auto read_d = [&](int p) { return tr_frag((const bf16_t *)dt + p * 16 * 32, 32, 0, 0); };
 
-  load_block(blk_begin);
+  load_block(blk_begin, 0);
+  int buf = 0;
   for (int blk = blk_begin; blk < blk_end; ++blk) {
-    __syncthreads();  // every wavefront has read the fragments of the previous block
-    store_block();
-    __syncthreads();
-    load_block(blk + 1);
+    wait_loads<0>();
+    __syncthreads();  // the block has arrived, and every wavefront is done with the one before it
+    asm volatile("" ::: "memory");
+    if (blk + 1 < blk_end) load_block(blk + 1, buf ^ 1);
+    xt = smem + buf * BUF + wc * XG * 1024 + (frag_x * 32 + frag_c) * 2;
+    dt = smem + buf * BUF + (NTC * XG + wn * 8) * 1024 + (frag_k * 32 + frag_c) * 2;
+    buf ^= 1;
     u4 window[3][3], dfrag[2];
     if (KC == 16) {
       // x rows p-1, p, p+1 live in window[(p + 0, 1, 2) % 3]; patch row index = image row + 1
       read_x(0, window[0]);
+      dfrag[0] = read_d(0);
       read_x(1, window[1]);
       read_x(2, window[2]);
-      dfrag[0] = read_d(0);
 #pragma unroll
       for (int p = 0; p < kSub; ++p) {
         const int w0 = p % 3, w1 = (p + 1) % 3, w2 = (p + 2) % 3;
@@ -202,6 +192,7 @@ __global__ __launch_bounds__(NT * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
         if (p + 1 < kSub) dfrag[(p + 1) & 1] = read_d(p + 1);
         u4 incoming[3];
         if (p + 2 < kSub + 1) read_x(p + 3, incoming);
+        if (BIAS && tally) mma<bf16_t>(d, ones, accb);
 #pragma unroll
         for (int s = 0; s < 3; ++s) mma<bf16_t>(d, window[w1][s], acc[1][s]);
 #pragma unroll
@@ -218,9 +209,9 @@ __global__ __launch_bounds__(NT * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
       for (int img = 0; img < 2; ++img) {
         const int pr0 = img * PT::PRI;
         read_x(pr0 + 0, window[0]);
+        dfrag[0] = read_d(img * 4);
         read_x(pr0 + 1, window[1]);
         read_x(pr0 + 2, window[2]);
-        dfrag[0] = read_d(img * 4);
 #pragma unroll
         for (int mu = 0; mu < 4; ++mu) {
           const int w0 = (2 * mu) % 3, w1 = (2 * mu + 1) % 3, w2 = (2 * mu + 2) % 3;
@@ -230,6 +221,7 @@ __global__ __launch_bounds__(NT * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
           if (mu + 1 < 4) dfrag[(mu + 1) & 1] = read_d(img * 4 + mu + 1);
           u4 in0[3], in1[3];
           if (mu + 1 < 4) read_x(pr0 + 2 * mu + 3, in0);
+          if (BIAS && tally) mma<bf16_t>(d, ones, accb);
 #pragma unroll
           for (int s = 0; s < 3; ++s) mma<bf16_t>(d, window[w1][s], acc[1][s]);
           if (mu + 1 < 4) read_x(pr0 + 2 * mu + 4, in1);
@@ -246,7 +238,7 @@ __global__ __launch_bounds__(NT * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
 
   // acc[r][s]: lane holds column c = lane % 32 and rows n = 8*(v/4) + 4*(lane/32) + v%4
   float *out = io.out + rep * io.out_rs + split * io.split_stride;
-  const int c = ct * 32 + (lane & 31), h = lane >> 5;
+  const int c = (cg * NTC + wc) * 32 + (lane & 31), h = lane >> 5;
   const int K = 9 * wg.Cin;
 #pragma unroll
   for (int r = 0; r < 3; ++r)
@@ -254,32 +246,28 @@ __global__ __launch_bounds__(NT * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
     for (int s = 0; s < 3; ++s)
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const int n = (ng * NT + wave) * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
+        const int n = (ng * NTN + wn) * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
         out[(long long)n * K + (r * 3 + s) * wg.Cin + c] = acc[r][s][v];
       }
-  if (BIAS && tally) {
-    // the sixteen threads that share a channel vector (one per pixel column of a sub-step) are added in a fixed order
-    float *bs = (float *)ds;  // [16][NT * 32]
-    __syncthreads();          // the last block's fragments have been read
+  if (BIAS && tally && (lane & 31) == 0) {  // all columns hold the same sums
 #pragma unroll
-    for (int e = 0; e < 8; ++e) bs[d_pcol * (NT * 32) + d_vec * 8 + e] = bsum[e];
-    __syncthreads();
-    if (tid < NT * 32) {
-      float t = 0.f;
-#pragma unroll
-      for (int q = 0; q < 16; ++q) t += bs[q * (NT * 32) + tid];
-      out[(long long)wg.N * K + ng * NT * 32 + tid] = t;
-    }
+    for (int v = 0; v < 16; ++v) out[(long long)wg.N * K + (ng * NTN + wn) * 32 + 8 * (v >> 2) + 4 * h + (v & 3)] = accb[v];
   }
 }
 
-int wg9_tiles(int nt32) {  // dy tiles per workgroup for N/32 tiles in all
-  // four first: two workgroups of four wavefronts fill a compute unit's eight wavefront slots (two per SIMD at
-  // this kernel's register count), one of five leaves three of them empty
-  static const int order[4] = {4, 5, 3, 2};
+// Tiles per workgroup, dy x x.
+struct Wg9Tiles {
+  int n, c;
+};
+Wg9Tiles wg9_tiles(int nt32, int ct32) {
+  // 2 x 2: an x tile and a dy tile each serve two wavefronts, and two workgroups put two wavefronts on every SIMD; three or
+  // five dy tiles leave SIMDs with one beside others with two.  2 x 1 loads half as much again per product (192 channels on
+  // 16 x 16, 3 x 128 images: 2 x 2 69.6 us, 3 x 1 69.9, 4 x 1 70.1, 2 x 1 92).
+  if (nt32 % 2 == 0 && ct32 % 2 == 0) return {2, 2};
+  static const int order[4] = {3, 4, 5, 2};
   for (int nt : order)
-    if (nt32 % nt == 0) return nt;
-  return nt32 == 1 ? 1 : 0;
+    if (nt32 % nt == 0) return {nt, 1};
+  return {nt32 == 1 ? 1 : 0, 1};
 }
 
 bool make_wg9_geom(const ConvGeom &g, int batch_hint, Wg9Geom &wg) {
@@ -298,13 +286,24 @@ bool make_wg9_geom(const ConvGeom &g, int batch_hint, Wg9Geom &wg) {
   return true;
 }
 
+template <int NTN, int NTC, int KC, bool BIAS>
+hipError_t run_wgrad9(hipStream_t st, int replicas, const ConvGeom &g, const Wg9Geom &wg, const WgradIO &io) {
+  constexpr int lds = 2 * (NTC * ((Patch<KC>::SLOTS + 15) / 16) + NTN * 8) * 1024;
+  static const hipError_t lds_ok =
+      hipFuncSetAttribute((const void *)k_wgrad9<NTN, NTC, KC, BIAS>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  if (lds_ok != hipSuccess) return lds_ok;
+  dim3 grid(g.Cc / 32 / NTC, g.N / 32 / NTN, replicas * io.splits);
+  hipLaunchKernelGGL((k_wgrad9<NTN, NTC, KC, BIAS>), grid, dim3(NTN * NTC * 64), lds, st, wg, io);
+  return hipGetLastError();
+}
+
 }  // namespace
 
 bool wgrad9_applicable(int dtype, const ConvGeom &g) {
   if (dtype != 1 || g.R != 3 || g.S != 3 || g.sp != 1 || g.dshift != 0 || g.sr != 1 || g.off != -1) return false;
   if (g.P != g.Hin || g.Q != g.Win) return false;
   if (!((g.Win % 16 == 0 && g.Hin % 8 == 0) || (g.Win == 8 && g.Hin == 8))) return false;
-  if (g.Cc % 32 != 0 || g.N % 32 != 0 || wg9_tiles(g.N / 32) < 2) return false;
+  if (g.Cc % 32 != 0 || g.N % 32 != 0 || wg9_tiles(g.N / 32, g.Cc / 32).n < 2) return false;
   const long long in_bytes = (long long)g.M * g.Cc * 2, dy_bytes = (long long)g.M * g.N * 2;
   return in_bytes < (1LL << 31) && dy_bytes < (1LL << 31) && g.M % (g.P * g.Q) == 0;
 }
@@ -314,18 +313,39 @@ bool wgrad9_applicable(int dtype, const ConvGeom &g) {
 int wgrad9_plan(int replicas, const ConvGeom &g, int *chunk_out) {
   Wg9Geom wg;
   make_wg9_geom(g, 0, wg);
-  const int nt = wg9_tiles(g.N / 32);
-  const long long tiles = (long long)(g.Cc / 32) * (g.N / 32 / nt) * replicas;
-  // about 1024 wavefronts in flight (one per SIMD; more splits cost more in partial sums than they gain), never
-  // fewer than 4 blocks per split
+  const Wg9Tiles t = wg9_tiles(g.N / 32, g.Cc / 32);
+  const long long tiles = (long long)(g.Cc / 32 / t.c) * (g.N / 32 / t.n) * replicas;
+  // One or two workgroups per compute unit, never a few stragglers in another round, whichever ends sooner: the second
+  // fills gaps of the first (8 %), and doubles the partial sums, which are written and read once more.  us with 256 / 512
+  // workgroups at 3 x 128 images: 64 channels on 32 x 32 39.6 / 44.2, 128 on 16 x 16 39.5 / 43.9, 256 on 8 x 8 40 / 51, 320 on
+  // 16 x 16 173 / 160.  A network that has its leaves run beside a longer chain asks for fewer.
+  // PARLE_WG9_WAVES: wavefronts in flight instead.
   static const int waves = [] {
     const char *e = getenv("PARLE_WG9_WAVES");
-    const int v = e ? atoi(e) : 0;
-    return v > 0 ? v : 1024;
+    return e ? atoi(e) : 0;
   }();
+  constexpr int kCus = 256;
   const int target = g.leaf_waves > 0 ? g.leaf_waves : waves;
-  long long want = (target / nt + tiles - 1) / tiles;
-  if (want > wg.total_blocks / 4) want = wg.total_blocks / 4;
+  long long want;
+  if (target > 0) {
+    want = target / (t.n * t.c) / tiles;
+  } else {
+    const double product = 2.0 * g.M * g.N * (double)g.K * replicas / 1.45e9;           // us at what the chip sustains
+    const double partial = 8.0 * g.N * (double)g.K * replicas / 8e6;                    // us per split
+    const int per_cu = t.n * t.c == 5 || t.n == 4 ? 1 : 2;                              // by LDS
+    double least = 0.;
+    want = 1;
+    for (int k = 1; k <= per_cu; ++k) {
+      const long long splits = k * kCus / tiles;
+      if (splits < 1) continue;
+      const double us = product / ((double)splits * tiles / (k * kCus) * (k == 1 ? .92 : 1.)) + splits * partial;
+      if (least == 0. || us < least) least = us, want = splits;
+    }
+  }
+  // never fewer than 4 blocks per split
+  // Four blocks per split at least, two where that leaves most of the chip idle (16 images of 8 x 8 x 128: 14.1 -> 11.8 us).
+  const int blocks = wg.total_blocks / 4 * tiles < 96 ? 2 : 4;
+  if (want > wg.total_blocks / blocks) want = wg.total_blocks / blocks;
   if (want < 1) want = 1;
   const long long cap = 65535 / replicas;
   if (want > cap) want = cap;
@@ -341,30 +361,19 @@ hipError_t launch_wgrad9(hipStream_t st, int replicas, const ConvGeom &g, const 
   wg.bps = io.chunk / kBlockPixels;
   wg.splits = io.splits;
   if (wg.bps < 1 || (long long)wg.bps * io.splits < wg.total_blocks) return hipErrorInvalidValue;
-  const int nt = wg9_tiles(g.N / 32);
-  dim3 grid(g.Cc / 32, g.N / 32 / nt, replicas * io.splits);
-#define WG9_LAUNCH(NTV, KCV)                                                                  \
-  do {                                                                                        \
-    if (io.with_bias)                                                                         \
-      hipLaunchKernelGGL((k_wgrad9<NTV, KCV, true>), grid, dim3(NTV * 64), 0, st, wg, io);    \
-    else                                                                                      \
-      hipLaunchKernelGGL((k_wgrad9<NTV, KCV, false>), grid, dim3(NTV * 64), 0, st, wg, io);   \
-  } while (0)
-#define WG9_CASE(NTV)          \
-  case NTV:                    \
-    if (wg.W == 8)             \
-      WG9_LAUNCH(NTV, 8);      \
-    else                       \
-      WG9_LAUNCH(NTV, 16);     \
-    break
-  switch (nt) {
-    WG9_CASE(2);
-    WG9_CASE(3);
-    WG9_CASE(4);
-    WG9_CASE(5);
-    default: return hipErrorInvalidValue;
-  }
+  const Wg9Tiles t = wg9_tiles(g.N / 32, g.Cc / 32);
+  const bool narrow = wg.W == 8;
+#define WG9_CASE(NV, CV)                                                                                                      \
+  if (t.n == NV && t.c == CV)                                                                                                 \
+    return io.with_bias ? narrow ? run_wgrad9<NV, CV, 8, true>(st, replicas, g, wg, io)                                       \
+                                 : run_wgrad9<NV, CV, 16, true>(st, replicas, g, wg, io)                                      \
+                        : narrow ? run_wgrad9<NV, CV, 8, false>(st, replicas, g, wg, io)                                      \
+                                 : run_wgrad9<NV, CV, 16, false>(st, replicas, g, wg, io)
+  WG9_CASE(2, 2);
+  WG9_CASE(2, 1);
+  WG9_CASE(3, 1);
+  WG9_CASE(4, 1);
+  WG9_CASE(5, 1);
 #undef WG9_CASE
-#undef WG9_LAUNCH
-  return hipGetLastError();
+  return hipErrorInvalidValue;
 }
