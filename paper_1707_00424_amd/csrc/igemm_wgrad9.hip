@@ -255,11 +255,171 @@ __global__ __launch_bounds__(NTN * NTC * 64) __attribute__((amdgpu_waves_per_eu(
   }
 }
 
+// Stride 2, padding 1, even input sizes (dy [H][W], x [2H][2W]):
+//   dW[n][r][s][c] = sum over pixels (b, p, q) of dy[b, p, q, n] * x[b, 2p + r - 1, 2q + s - 1, c]
+// The same walk in blocks of 64 pixels (4 rows x 16 columns, or one 8 x 8 image).  A patch row holds its odd input columns,
+// -1, 1, 3, ..., and behind them the even ones: the pixels that a tap pairs with consecutive dy pixels are consecutive again.
+// In blocks of 16 columns the x row of tap row 2 is that of tap row 0 for the next dy row and stays in registers: 1 + 6
+// fragment reads per nine products, in pairs of 8-pixel rows 1 + 9.  Gathering each tap for itself (k_wgrad_tr) reads x nine
+// times from L2 in pieces of 64 bytes two pixels apart.  us with the reduction, before -> now, 3 x 128 images: 64 -> 128
+// channels 32 x 32 48 -> 36, 96 -> 96 50 -> 41, 160 -> 320 201 -> 127; 128 -> 256 on 16 x 16 44 -> 35, 192 -> 192 43 -> 42.
+template <int KC>
+struct Patch2 {
+  static constexpr int QC = KC == 16 ? 16 : 8, ROWS = 64 / QC;  // dy columns and rows of a block
+  static constexpr int PC = 2 * QC + 1;                         // QC + 1 odd columns, QC even ones
+  static constexpr int PR = 2 * ROWS + 1;
+  static constexpr int SLOTS = PR * PC;                         // 297 / 289
+};
+
+template <int NTN, int KC, bool BIAS>
+__global__ __launch_bounds__(NTN * 64) __attribute__((amdgpu_waves_per_eu(2))) void k_wgrad9_s2(const Wg9Geom wg, const WgradIO io) {
+  typedef Patch2<KC> PT;
+  constexpr int kPC = PT::PC, W = NTN, QC = PT::QC;
+  constexpr int XG = (PT::SLOTS + 15) / 16;               // loads of 16 pixels: the x tile, one dy tile (4)
+  constexpr int PIECES = XG + NTN * 4;
+  constexpr int IT = (PIECES + W - 1) / W;
+  constexpr int BUF = PIECES * 1024;
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ct = blockIdx.x, ng = blockIdx.y;
+  const int rep = blockIdx.z / wg.splits, split = blockIdx.z - rep * wg.splits;
+  const int blk_begin = split * wg.bps, blk_end = min(wg.total_blocks, blk_begin + wg.bps);
+  const int Hx = 2 * wg.H, Wx = 2 * wg.W;
+  const u4 x_rsrc = buffer_desc((const bf16_t *)io.x + rep * io.x_rs, (uint32_t)((long long)wg.B * Hx * Wx * wg.Cin * 2));
+  const u4 d_rsrc = buffer_desc((const bf16_t *)io.dy + rep * io.dy_rs, (uint32_t)((long long)wg.B * wg.H * wg.W * wg.N * 2));
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
+
+  // rel: offset of this lane's pixel and channels from the block's first pixel; pos: what lies outside the image, bit 0 where
+  // the block is in the first column, bit 1 in the first row, bit 2 always (beyond the patch)
+  int rel[IT], pos[IT];
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const int q = it * W + wave, px = lane >> 2, ch = (lane & 3) * 8;
+    if (q < XG) {
+      const int slot = q * 16 + px, prow = slot / kPC, i = slot - prow * kPC;
+      const int col = i <= QC ? 2 * i - 1 : 2 * (i - QC - 1), row = prow - 1;
+      rel[it] = ((row * Wx + col) * wg.Cin + ct * 32 + ch) * 2;
+      pos[it] = (col < 0 ? 1 : 0) | (row < 0 ? 2 : 0) | (slot < PT::SLOTS ? 0 : 4);
+    } else {
+      const int d = q - XG, t = d >> 2, p = (d & 3) * 16 + px;
+      const int row = p / QC, col = p - row * QC;
+      rel[it] = ((row * wg.W + col) * wg.N + (ng * NTN + t) * 32 + ch) * 2;
+      pos[it] = 0;
+    }
+  }
+  auto load_block = [&](int blk, int buf) {
+    const int b = (int)fdiv((uint32_t)blk, wg.dBpi);
+    const int rem = blk - b * wg.bpi;
+    const int rb = (int)fdiv((uint32_t)rem, wg.dCbn), cb = rem - rb * wg.cbn;
+    const int row0 = rb * PT::ROWS, col0 = cb * QC;
+    const int xbase = ((b * Hx + 2 * row0) * Wx + 2 * col0) * wg.Cin * 2, dbase = ((b * wg.H + row0) * wg.W + col0) * wg.N * 2;
+    const int outside = 4 | (cb == 0 ? 1 : 0) | (rb == 0 ? 2 : 0);
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const int q = it * W + wave;
+      if (PIECES % W != 0 && it == IT - 1 && q >= PIECES) break;
+      const uint32_t dst = lds0 + (uint32_t)(buf * BUF + q * 1024);
+      if (q < XG)
+        dma16(dst, x_rsrc, pos[it] & outside ? kOobOffset : (uint32_t)(xbase + rel[it]), 0);
+      else
+        dma16(dst, d_rsrc, (uint32_t)(dbase + rel[it]), 0);
+    }
+  };
+
+  f16v acc[3][3], accb;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) acc[r][c][v] = 0.f;
+    accb[v] = 0.f;
+  }
+  const bool tally = BIAS && ct == 0;
+  const u4 ones = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+  const int gq = lane >> 4, j = lane & 15;
+  const int frag_k = 8 * (gq >> 1) + (j >> 2), frag_c = 16 * (gq & 1) + 4 * (j & 3);
+  // a sub-step is a row of 16, or two rows of 8, two patch rows apart
+  const int frag_x = KC == 16 ? frag_k : (gq >> 1) * 2 * kPC + (j >> 2);
+  const char *xt, *dt;
+  // x fragments of patch row `prow` at column shifts -1, 0, 1: odd columns from 0, even ones, odd ones from 1
+  auto read_x = [&](int prow, u4 (&f)[3]) {
+    const bf16_t *row = (const bf16_t *)xt + prow * kPC * 32;
+    f[0] = tr_frag(row, 32, 0, 0);
+    f[1] = tr_frag(row + (QC + 1) * 32, 32, 0, 0);
+    f[2] = tr_frag(row + 32, 32, 0, 0);
+  };
+  auto read_d = [&](int p) { return tr_frag((const bf16_t *)dt + p * 16 * 32, 32, 0, 0); };
+
+  load_block(blk_begin, 0);
+  int buf = 0;
+  for (int blk = blk_begin; blk < blk_end; ++blk) {
+    wait_loads<0>();
+    __syncthreads();  // the block has arrived, and every wavefront is done with the one before it
+    asm volatile("" ::: "memory");
+    if (blk + 1 < blk_end) load_block(blk + 1, buf ^ 1);
+    xt = smem + buf * BUF + (frag_x * 32 + frag_c) * 2;
+    dt = smem + buf * BUF + (XG + wave * 4) * 1024 + (frag_k * 32 + frag_c) * 2;
+    buf ^= 1;
+    constexpr int STEP = KC == 16 ? 2 : 4;  // patch rows from one sub-step to the next
+    u4 top[3], mid[3], bot[3], d = read_d(0);
+    read_x(0, top);
+    read_x(1, mid);
+    read_x(2, bot);
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      const u4 dn = p < 3 ? read_d(p + 1) : d;
+#pragma unroll
+      for (int s = 0; s < 3; ++s) mma<bf16_t>(d, top[s], acc[0][s]);
+      if (p < 3 && KC == 8) read_x((p + 1) * STEP, top);
+#pragma unroll
+      for (int s = 0; s < 3; ++s) mma<bf16_t>(d, mid[s], acc[1][s]);
+      if (p < 3) read_x((p + 1) * STEP + 1, mid);
+      if (BIAS && tally) mma<bf16_t>(d, ones, accb);
+#pragma unroll
+      for (int s = 0; s < 3; ++s) mma<bf16_t>(d, bot[s], acc[2][s]);
+      if (p < 3) {
+        if (KC == 16) {
+#pragma unroll
+          for (int s = 0; s < 3; ++s) top[s] = bot[s];
+        }
+        read_x((p + 1) * STEP + 2, bot);
+      }
+      d = dn;
+    }
+  }
+
+  float *out = io.out + rep * io.out_rs + split * io.split_stride;
+  const int c = ct * 32 + (lane & 31), h = lane >> 5;
+  const int K = 9 * wg.Cin;
+#pragma unroll
+  for (int r = 0; r < 3; ++r)
+#pragma unroll
+    for (int s = 0; s < 3; ++s)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int n = (ng * NTN + wave) * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
+        out[(long long)n * K + (r * 3 + s) * wg.Cin + c] = acc[r][s][v];
+      }
+  if (BIAS && tally && (lane & 31) == 0) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) out[(long long)wg.N * K + (ng * NTN + wave) * 32 + 8 * (v >> 2) + 4 * h + (v & 3)] = accb[v];
+  }
+}
+
 // Tiles per workgroup, dy x x.
 struct Wg9Tiles {
   int n, c;
 };
-Wg9Tiles wg9_tiles(int nt32, int ct32) {
+Wg9Tiles wg9_tiles(const ConvGeom &g) {
+  const int nt32 = g.N / 32, ct32 = g.Cc / 32;
+  if (g.sp == 2) {  // four, three or five dy tiles over one x tile: the patch is the larger load
+    static const int order2[4] = {4, 3, 5, 2};
+    for (int nt : order2)
+      if (nt32 % nt == 0) return {nt, 1};
+    return {0, 1};
+  }
   // 2 x 2: an x tile and a dy tile each serve two wavefronts, and two workgroups put two wavefronts on every SIMD; three or
   // five dy tiles leave SIMDs with one beside others with two.  2 x 1 loads half as much again per product (192 channels on
   // 16 x 16, 3 x 128 images: 2 x 2 69.6 us, 3 x 1 69.9, 4 x 1 70.1, 2 x 1 92).
@@ -270,20 +430,20 @@ Wg9Tiles wg9_tiles(int nt32, int ct32) {
   return {nt32 == 1 ? 1 : 0, 1};
 }
 
-bool make_wg9_geom(const ConvGeom &g, int batch_hint, Wg9Geom &wg) {
-  (void)batch_hint;
-  wg.H = g.Hin, wg.W = g.Win, wg.Cin = g.Cc, wg.N = g.N;
+int block_pixels(const ConvGeom &g) { return g.sp == 2 ? 64 : kBlockPixels; }
+
+void make_wg9_geom(const ConvGeom &g, Wg9Geom &wg) {
+  wg.H = g.P, wg.W = g.Q, wg.Cin = g.Cc, wg.N = g.N;
   wg.B = g.M / (g.P * g.Q);
-  if (wg.W == 8) {  // two whole images per block
+  if (wg.W == 8) {  // two whole images per block, one at stride 2
     wg.cbn = 1, wg.bpi = 1;
-    wg.total_blocks = (wg.B + 1) / 2;
+    wg.total_blocks = g.sp == 2 ? wg.B : (wg.B + 1) / 2;
   } else {
     wg.cbn = wg.W / 16;
-    wg.bpi = (wg.H / 8) * wg.cbn;
+    wg.bpi = (wg.H / (block_pixels(g) / 16)) * wg.cbn;
     wg.total_blocks = wg.B * wg.bpi;
   }
   wg.dBpi = make_fastdiv(wg.bpi), wg.dCbn = make_fastdiv(wg.cbn);
-  return true;
 }
 
 template <int NTN, int NTC, int KC, bool BIAS>
@@ -297,23 +457,34 @@ hipError_t run_wgrad9(hipStream_t st, int replicas, const ConvGeom &g, const Wg9
   return hipGetLastError();
 }
 
+template <int NTN, int KC, bool BIAS>
+hipError_t run_wgrad9_s2(hipStream_t st, int replicas, const ConvGeom &g, const Wg9Geom &wg, const WgradIO &io) {
+  constexpr int lds = 2 * ((Patch2<KC>::SLOTS + 15) / 16 + NTN * 4) * 1024;
+  static const hipError_t lds_ok =
+      hipFuncSetAttribute((const void *)k_wgrad9_s2<NTN, KC, BIAS>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  if (lds_ok != hipSuccess) return lds_ok;
+  dim3 grid(g.Cc / 32, g.N / 32 / NTN, replicas * io.splits);
+  hipLaunchKernelGGL((k_wgrad9_s2<NTN, KC, BIAS>), grid, dim3(NTN * 64), lds, st, wg, io);
+  return hipGetLastError();
+}
+
 }  // namespace
 
 bool wgrad9_applicable(int dtype, const ConvGeom &g) {
-  if (dtype != 1 || g.R != 3 || g.S != 3 || g.sp != 1 || g.dshift != 0 || g.sr != 1 || g.off != -1) return false;
-  if (g.P != g.Hin || g.Q != g.Win) return false;
-  if (!((g.Win % 16 == 0 && g.Hin % 8 == 0) || (g.Win == 8 && g.Hin == 8))) return false;
-  if (g.Cc % 32 != 0 || g.N % 32 != 0 || wg9_tiles(g.N / 32, g.Cc / 32).n < 2) return false;
-  const long long in_bytes = (long long)g.M * g.Cc * 2, dy_bytes = (long long)g.M * g.N * 2;
+  if (dtype != 1 || g.R != 3 || g.S != 3 || (g.sp != 1 && g.sp != 2) || g.dshift != 0 || g.sr != 1 || g.off != -1) return false;
+  if (g.sp * g.P != g.Hin || g.sp * g.Q != g.Win) return false;
+  if (!((g.Q % 16 == 0 && g.P % (g.sp == 2 ? 4 : 8) == 0) || (g.Q == 8 && g.P == 8))) return false;
+  if (g.Cc % 32 != 0 || g.N % 32 != 0 || wg9_tiles(g).n < 2) return false;
+  const long long in_bytes = (long long)g.M * g.sp * g.sp * g.Cc * 2, dy_bytes = (long long)g.M * g.N * 2;
   return in_bytes < (1LL << 31) && dy_bytes < (1LL << 31) && g.M % (g.P * g.Q) == 0;
 }
 
-// Blocks of 128 pixels per split so that the launch fills the chip; returns the split count and the
+// Blocks of 128 pixels (64 at stride 2) per split so that the launch fills the chip; returns the split count and the
 // pixels per split in *chunk_out.
 int wgrad9_plan(int replicas, const ConvGeom &g, int *chunk_out) {
   Wg9Geom wg;
-  make_wg9_geom(g, 0, wg);
-  const Wg9Tiles t = wg9_tiles(g.N / 32, g.Cc / 32);
+  make_wg9_geom(g, wg);
+  const Wg9Tiles t = wg9_tiles(g);
   const long long tiles = (long long)(g.Cc / 32 / t.c) * (g.N / 32 / t.n) * replicas;
   // One or two workgroups per compute unit, never a few stragglers in another round, whichever ends sooner: the second
   // fills gaps of the first (8 %), and doubles the partial sums, which are written and read once more.  us with 256 / 512
@@ -332,7 +503,7 @@ int wgrad9_plan(int replicas, const ConvGeom &g, int *chunk_out) {
   } else {
     const double product = 2.0 * g.M * g.N * (double)g.K * replicas / 1.45e9;           // us at what the chip sustains
     const double partial = 8.0 * g.N * (double)g.K * replicas / 8e6;                    // us per split
-    const int per_cu = t.n * t.c == 5 || t.n == 4 ? 1 : 2;                              // by LDS
+    const int per_cu = t.n == 5 || (t.n == 4 && g.sp == 1) ? 1 : 2;                           // by LDS
     double least = 0.;
     want = 1;
     for (int k = 1; k <= per_cu; ++k) {
@@ -342,7 +513,6 @@ int wgrad9_plan(int replicas, const ConvGeom &g, int *chunk_out) {
       if (least == 0. || us < least) least = us, want = splits;
     }
   }
-  // never fewer than 4 blocks per split
   // Four blocks per split at least, two where that leaves most of the chip idle (16 images of 8 x 8 x 128: 14.1 -> 11.8 us).
   const int blocks = wg.total_blocks / 4 * tiles < 96 ? 2 : 4;
   if (want > wg.total_blocks / blocks) want = wg.total_blocks / blocks;
@@ -351,18 +521,32 @@ int wgrad9_plan(int replicas, const ConvGeom &g, int *chunk_out) {
   if (want > cap) want = cap;
   const int bps = (int)((wg.total_blocks + want - 1) / want);
   const int splits = (wg.total_blocks + bps - 1) / bps;
-  if (chunk_out) *chunk_out = bps * kBlockPixels;
+  if (chunk_out) *chunk_out = bps * block_pixels(g);
   return splits;
 }
 
 hipError_t launch_wgrad9(hipStream_t st, int replicas, const ConvGeom &g, const WgradIO &io) {
   Wg9Geom wg;
-  make_wg9_geom(g, 0, wg);
-  wg.bps = io.chunk / kBlockPixels;
+  make_wg9_geom(g, wg);
+  wg.bps = io.chunk / block_pixels(g);
   wg.splits = io.splits;
   if (wg.bps < 1 || (long long)wg.bps * io.splits < wg.total_blocks) return hipErrorInvalidValue;
-  const Wg9Tiles t = wg9_tiles(g.N / 32, g.Cc / 32);
+  const Wg9Tiles t = wg9_tiles(g);
   const bool narrow = wg.W == 8;
+#define WG9_S2(NV)                                                                                                            \
+  if (t.n == NV)                                                                                                              \
+    return io.with_bias ? narrow ? run_wgrad9_s2<NV, 8, true>(st, replicas, g, wg, io)                                        \
+                                 : run_wgrad9_s2<NV, 16, true>(st, replicas, g, wg, io)                                       \
+                        : narrow ? run_wgrad9_s2<NV, 8, false>(st, replicas, g, wg, io)                                       \
+                                 : run_wgrad9_s2<NV, 16, false>(st, replicas, g, wg, io)
+  if (g.sp == 2) {
+    WG9_S2(2);
+    WG9_S2(3);
+    WG9_S2(4);
+    WG9_S2(5);
+    return hipErrorInvalidValue;
+  }
+#undef WG9_S2
 #define WG9_CASE(NV, CV)                                                                                                      \
   if (t.n == NV && t.c == CV)                                                                                                 \
     return io.with_bias ? narrow ? run_wgrad9<NV, CV, 8, true>(st, replicas, g, wg, io)                                       \
