@@ -1,4 +1,4 @@
-// Backward-weight of stride-1 "same" 3x3 convolutions (bf16) with the input patch staged ONCE in LDS
+// Backward-weight of "same" 3x3 convolutions (bf16) with the input patch staged ONCE in LDS
 // and each output-gradient fragment reused by all nine window taps.
 //
 //   dW[n][r][s][c] = sum over pixels (b, p, q) of dy[b, p, q, n] * x[b, p + r - 1, q + s - 1, c]
@@ -72,7 +72,9 @@ __device__ __forceinline__ u4 tr_frag(const bf16_t *tile, int ld, int krow, int 
   return r;
 }
 
-template <int NTN, int NTC, int KC, bool BIAS>
+// RAG: images that do not cut into blocks.  Loads beyond the image are zeros on both sides; x pixels that meet a dy pixel
+// beyond its row are blanked as well, since they may be infinite, and rows beyond the image are left out.
+template <int NTN, int NTC, int KC, bool BIAS, bool RAG>
 __global__ __launch_bounds__(NTN * NTC * 64) __attribute__((amdgpu_waves_per_eu(2))) void k_wgrad9(const Wg9Geom wg, const WgradIO io) {
   typedef Patch<KC> PT;
   constexpr int kPC = PT::PC, W = NTN * NTC;
@@ -105,9 +107,9 @@ __global__ __launch_bounds__(NTN * NTC * 64) __attribute__((amdgpu_waves_per_eu(
       pos[it] = slot < PT::SLOTS ? prow | pcol << 8 | img << 16 : 0x4000;  // column 64 and beyond: never inside
     } else {
       const int d = q - NTC * XG, t = d >> 3, p = (d & 7) * 16 + px;  // pixel of the block
-      const int row = p / KC, col = p - row * KC;                      // two 8 x 8 images lie one behind the other
-      rel[it] = ((row * wg.W + col) * wg.N + (ng * NTN + t) * 32 + ch) * 2;
-      pos[it] = 0;
+      const int img = p / (kBlockPixels / PT::IMG), r = p - img * (kBlockPixels / PT::IMG), row = r / KC, col = r - row * KC;
+      rel[it] = (((img * wg.H + row) * wg.W + col) * wg.N + (ng * NTN + t) * 32 + ch) * 2;
+      pos[it] = row | col << 8;
     }
   }
   auto load_block = [&](int blk, int buf) {
@@ -132,7 +134,8 @@ __global__ __launch_bounds__(NTN * NTC * 64) __attribute__((amdgpu_waves_per_eu(
         dma16(dst, x_rsrc, ok ? (uint32_t)(pix * wg.Cin * 2 + rel[it]) : kOobOffset, 0);
       } else {
         // an image beyond the batch (odd batch, second 8 x 8 image of the last block) lies beyond the buffer: zeros
-        dma16(dst, d_rsrc, (uint32_t)(pix * wg.N * 2 + rel[it]), 0);
+        const bool ok = !RAG || (row0 + (pos[it] & 0xff) < wg.H && col0 + (pos[it] >> 8) < wg.W);
+        dma16(dst, d_rsrc, ok ? (uint32_t)(pix * wg.N * 2 + rel[it]) : kOobOffset, 0);
       }
     }
   };
@@ -159,10 +162,22 @@ __global__ __launch_bounds__(NTN * NTC * 64) __attribute__((amdgpu_waves_per_eu(
   const char *xt, *dt;
   // x fragments of the sub-step whose first pixel is patch row `prow`, at the three column shifts;
   // dy fragment of sub-step p
+  u4 inside;  // RAG: the contraction indexes of this lane that are pixels of the row
   auto read_x = [&](int prow, u4 (&f)[3]) {
 #pragma unroll
-    for (int s = 0; s < 3; ++s) f[s] = tr_frag((const bf16_t *)xt + (prow * kPC + s) * 32, 32, 0, 0);
+    for (int s = 0; s < 3; ++s) {
+      f[s] = tr_frag((const bf16_t *)xt + (prow * kPC + s) * 32, 32, 0, 0);
+      if (RAG) f[s] &= inside;
+    }
   };
+  // of contraction indexes k .. k + 7 those below `lim`
+  auto below = [&](int k, int lim) {
+    u4 m;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) m[e] = (k + 2 * e < lim ? 0xffffu : 0u) | (k + 2 * e + 1 < lim ? 0xffff0000u : 0u);
+    return m;
+  };
+  if (RAG && KC == 8) inside = below(0, wg.W);
   auto read_d = [&](int p) { return tr_frag((const bf16_t *)dt + p * 16 * 32, 32, 0, 0); };
 
   load_block(blk_begin, 0);
@@ -175,6 +190,12 @@ __global__ __launch_bounds__(NTN * NTC * 64) __attribute__((amdgpu_waves_per_eu(
     xt = smem + buf * BUF + wc * XG * 1024 + (frag_x * 32 + frag_c) * 2;
     dt = smem + buf * BUF + (NTC * XG + wn * 8) * 1024 + (frag_k * 32 + frag_c) * 2;
     buf ^= 1;
+    int rows = kSub;
+    if (RAG && KC == 16) {
+      const int rem = blk - (int)fdiv((uint32_t)blk, wg.dBpi) * wg.bpi, rb = (int)fdiv((uint32_t)rem, wg.dCbn);
+      rows = min(kSub, wg.H - rb * kSub);
+      inside = below(8 * (gq >> 1), wg.W - (rem - rb * wg.cbn) * 16);
+    }
     u4 window[3][3], dfrag[2];
     if (KC == 16) {
       // x rows p-1, p, p+1 live in window[(p + 0, 1, 2) % 3]; patch row index = image row + 1
@@ -184,6 +205,7 @@ __global__ __launch_bounds__(NTN * NTC * 64) __attribute__((amdgpu_waves_per_eu(
       read_x(2, window[2]);
 #pragma unroll
       for (int p = 0; p < kSub; ++p) {
+        if (RAG && p >= rows) break;
         const int w0 = p % 3, w1 = (p + 1) % 3, w2 = (p + 2) % 3;
         const u4 d = dfrag[p & 1];
         // taps of window row r = 0 use x row p-1; its registers then take x row p+2 for the next rows
@@ -214,6 +236,11 @@ __global__ __launch_bounds__(NTN * NTC * 64) __attribute__((amdgpu_waves_per_eu(
         read_x(pr0 + 2, window[2]);
 #pragma unroll
         for (int mu = 0; mu < 4; ++mu) {
+          if (RAG && 2 * mu >= wg.H) break;
+          if (RAG && 2 * mu + 1 >= wg.H && (gq >> 1)) {  // the pair's second row lies beyond the image
+#pragma unroll
+            for (int i = 0; i < 9; ++i) window[i / 3][i % 3] = u4{0, 0, 0, 0};
+          }
           const int w0 = (2 * mu) % 3, w1 = (2 * mu + 1) % 3, w2 = (2 * mu + 2) % 3;
           const u4 d = dfrag[mu & 1];
 #pragma unroll
@@ -430,30 +457,33 @@ Wg9Tiles wg9_tiles(const ConvGeom &g) {
   return {nt32 == 1 ? 1 : 0, 1};
 }
 
+bool small_images(const ConvGeom &g) { return g.Q <= 8 && g.P <= 8; }
+bool whole_blocks(const ConvGeom &g) { return g.Q % 16 == 0 ? g.P % (g.sp == 2 ? 4 : 8) == 0 : g.Q == 8 && g.P == 8; }
 int block_pixels(const ConvGeom &g) { return g.sp == 2 ? 64 : kBlockPixels; }
 
 void make_wg9_geom(const ConvGeom &g, Wg9Geom &wg) {
   wg.H = g.P, wg.W = g.Q, wg.Cin = g.Cc, wg.N = g.N;
   wg.B = g.M / (g.P * g.Q);
-  if (wg.W == 8) {  // two whole images per block, one at stride 2
+  if (small_images(g)) {  // two whole images per block, one at stride 2
     wg.cbn = 1, wg.bpi = 1;
     wg.total_blocks = g.sp == 2 ? wg.B : (wg.B + 1) / 2;
   } else {
-    wg.cbn = wg.W / 16;
-    wg.bpi = (wg.H / (block_pixels(g) / 16)) * wg.cbn;
+    const int rows = block_pixels(g) / 16;
+    wg.cbn = (wg.W + 15) / 16;
+    wg.bpi = (wg.H + rows - 1) / rows * wg.cbn;
     wg.total_blocks = wg.B * wg.bpi;
   }
   wg.dBpi = make_fastdiv(wg.bpi), wg.dCbn = make_fastdiv(wg.cbn);
 }
 
-template <int NTN, int NTC, int KC, bool BIAS>
+template <int NTN, int NTC, int KC, bool BIAS, bool RAG>
 hipError_t run_wgrad9(hipStream_t st, int replicas, const ConvGeom &g, const Wg9Geom &wg, const WgradIO &io) {
   constexpr int lds = 2 * (NTC * ((Patch<KC>::SLOTS + 15) / 16) + NTN * 8) * 1024;
   static const hipError_t lds_ok =
-      hipFuncSetAttribute((const void *)k_wgrad9<NTN, NTC, KC, BIAS>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+      hipFuncSetAttribute((const void *)k_wgrad9<NTN, NTC, KC, BIAS, RAG>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (lds_ok != hipSuccess) return lds_ok;
   dim3 grid(g.Cc / 32 / NTC, g.N / 32 / NTN, replicas * io.splits);
-  hipLaunchKernelGGL((k_wgrad9<NTN, NTC, KC, BIAS>), grid, dim3(NTN * NTC * 64), lds, st, wg, io);
+  hipLaunchKernelGGL((k_wgrad9<NTN, NTC, KC, BIAS, RAG>), grid, dim3(NTN * NTC * 64), lds, st, wg, io);
   return hipGetLastError();
 }
 
@@ -473,7 +503,15 @@ hipError_t run_wgrad9_s2(hipStream_t st, int replicas, const ConvGeom &g, const 
 bool wgrad9_applicable(int dtype, const ConvGeom &g) {
   if (dtype != 1 || g.R != 3 || g.S != 3 || (g.sp != 1 && g.sp != 2) || g.dshift != 0 || g.sr != 1 || g.off != -1) return false;
   if (g.sp * g.P != g.Hin || g.sp * g.Q != g.Win) return false;
-  if (!((g.Q % 16 == 0 && g.P % (g.sp == 2 ? 4 : 8) == 0) || (g.Q == 8 && g.P == 8))) return false;
+  if (!whole_blocks(g)) {
+    // Share of the products that are no padding.  us, this kernel / the transpose-read kernel: 28 x 28 (0.88) 96 channels, 100
+    // images 35 / 46; 14 x 14 (0.88) 256 channels 48 / 61; 15 x 15 (0.94) 320 channels 44 / 69; 24 x 24 (0.75) 37 / 54;
+    // 12 x 12 (0.75) 320 channels 44 / 61; 10 x 10 and 20 x 20 (0.63) 32.9 / 32.2 and 29.4 / 29.4; 9 x 9 32 / 29.  Images of
+    // at most 8 x 8 come two to a block whatever their size: 7 x 7 256 channels, 4 x 64 images 39 / 44, but 16 images 13.4 /
+    // 11.2; 6 x 6 24 / 19.
+    if (g.sp == 2) return false;
+    if (small_images(g) ? g.P * g.Q < 49 || g.M < 64 * 49 : g.Q * 10 < 16 * ((g.Q + 15) / 16) * 7) return false;
+  }
   if (g.Cc % 32 != 0 || g.N % 32 != 0 || wg9_tiles(g).n < 2) return false;
   const long long in_bytes = (long long)g.M * g.sp * g.sp * g.Cc * 2, dy_bytes = (long long)g.M * g.N * 2;
   return in_bytes < (1LL << 31) && dy_bytes < (1LL << 31) && g.M % (g.P * g.Q) == 0;
@@ -501,7 +539,7 @@ int wgrad9_plan(int replicas, const ConvGeom &g, int *chunk_out) {
   if (target > 0) {
     want = target / (t.n * t.c) / tiles;
   } else {
-    const double product = 2.0 * g.M * g.N * (double)g.K * replicas / 1.45e9;           // us at what the chip sustains
+    const double product = 2.0 * wg.total_blocks * block_pixels(g) * g.N * (double)g.K * replicas / 1.45e9;  // us at what the chip sustains
     const double partial = 8.0 * g.N * (double)g.K * replicas / 8e6;                    // us per split
     const int per_cu = t.n == 5 || (t.n == 4 && g.sp == 1) ? 1 : 2;                           // by LDS
     double least = 0.;
@@ -532,7 +570,7 @@ hipError_t launch_wgrad9(hipStream_t st, int replicas, const ConvGeom &g, const 
   wg.splits = io.splits;
   if (wg.bps < 1 || (long long)wg.bps * io.splits < wg.total_blocks) return hipErrorInvalidValue;
   const Wg9Tiles t = wg9_tiles(g);
-  const bool narrow = wg.W == 8;
+  const bool narrow = small_images(g);
 #define WG9_S2(NV)                                                                                                            \
   if (t.n == NV)                                                                                                              \
     return io.with_bias ? narrow ? run_wgrad9_s2<NV, 8, true>(st, replicas, g, wg, io)                                        \
@@ -547,17 +585,24 @@ hipError_t launch_wgrad9(hipStream_t st, int replicas, const ConvGeom &g, const 
     return hipErrorInvalidValue;
   }
 #undef WG9_S2
-#define WG9_CASE(NV, CV)                                                                                                      \
-  if (t.n == NV && t.c == CV)                                                                                                 \
-    return io.with_bias ? narrow ? run_wgrad9<NV, CV, 8, true>(st, replicas, g, wg, io)                                       \
-                                 : run_wgrad9<NV, CV, 16, true>(st, replicas, g, wg, io)                                      \
-                        : narrow ? run_wgrad9<NV, CV, 8, false>(st, replicas, g, wg, io)                                      \
-                                 : run_wgrad9<NV, CV, 16, false>(st, replicas, g, wg, io)
+  const bool rag = !whole_blocks(g);
+#define WG9_RUN(NV, CV, KCV, RAGV)                                                \
+  return io.with_bias ? run_wgrad9<NV, CV, KCV, true, RAGV>(st, replicas, g, wg, io) \
+                      : run_wgrad9<NV, CV, KCV, false, RAGV>(st, replicas, g, wg, io)
+#define WG9_CASE(NV, CV)                 \
+  if (t.n == NV && t.c == CV) {          \
+    if (narrow && rag)                   \
+      WG9_RUN(NV, CV, 8, true);          \
+    if (narrow) WG9_RUN(NV, CV, 8, false); \
+    if (rag) WG9_RUN(NV, CV, 16, true);  \
+    WG9_RUN(NV, CV, 16, false);          \
+  }
   WG9_CASE(2, 2);
   WG9_CASE(2, 1);
   WG9_CASE(3, 1);
   WG9_CASE(4, 1);
   WG9_CASE(5, 1);
 #undef WG9_CASE
+#undef WG9_RUN
   return hipErrorInvalidValue;
 }
