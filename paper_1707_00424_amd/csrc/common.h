@@ -15,6 +15,8 @@ typedef unsigned short bf16_t;  // raw bfloat16 bits
 
 #define PARLE_WAVE 64
 
+constexpr float kBnEps = 1e-5f;
+
 // fp32 -> bf16, round to nearest even; NaN stays a quiet NaN.  gfx950 converts in hardware
 // (v_cvt_pk_bf16_f32, two values per instruction).
 typedef __bf16 bf16x2_hw __attribute__((ext_vector_type(2)));

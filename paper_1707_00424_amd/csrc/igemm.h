@@ -71,6 +71,12 @@ struct GemmIO {
   // set it; kernels that do not produce the sums ignore it and launch_igemm reports S = 0.
   double *stat;
   int stat_capacity;  // partial rows per replica the buffer has room for
+  // Evaluation, one replica: the batch-norm + ReLU that reads the result, from its running statistics (means, then variances,
+  // N each), is written to bn_out as well, of the result as it is stored; bn_only: nothing else reads the result, which is
+  // then not stored.  Only for layers that conv_takes_bn names.
+  void *bn_out;
+  const float *bn_gamma, *bn_beta, *bn_running;
+  int bn_only;
 };
 
 struct WgradIO {
@@ -129,6 +135,8 @@ int igemm_fast_stat_splits(int dtype, bool out_f32, const ConvGeom &g, const Gem
 // Stride-1 'same' convolutions with the input patch staged once in LDS (igemm_halo.hip).
 bool conv_halo_applicable(int dtype, int replicas, const ConvGeom &g, const GemmIO &io, bool out_f32);
 hipError_t launch_conv_halo(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io);
+// True when launch_igemm would honour io.bn_out for this layer (everything but bn_out's own fields set).
+bool conv_takes_bn(int dtype, int replicas, const ConvGeom &g, const GemmIO &io, bool out_f32);
 int conv_halo_stat_splits(const ConvGeom &g, const GemmIO &io, int replicas);
 // fp32 backward-data of a stride-1 layer with few input channels under a wide window, the per-tap products of one
 // image held in LDS (igemm_dgrad_win.hip).  w: the layer's weights as they lie, [Cout][R][R][Cin].

@@ -408,6 +408,7 @@ hipError_t launch_igemm(hipStream_t st, int dtype, bool out_f32, int replicas, c
   if (stat_splits) *stat_splits = 0;
   if (io_in.w_kn && !fc_f32_applicable(dtype, replicas, g)) return hipErrorInvalidValue;
   if (fc_f32_applicable(dtype, replicas, g)) return launch_fc_f32(st, replicas, g, io_in);
+  if (io_in.bn_out && !conv_takes_bn(dtype, replicas, g, io_in, out_f32)) return hipErrorInvalidValue;
   if (io_in.stat && stat_splits) {
     // the same order of choices as below, for the kernels whose epilogue can take the sums
     int S = 0;

@@ -75,8 +75,8 @@ __device__ __forceinline__ uint32_t fdivc(uint32_t n, __attribute__((address_spa
 }
 
 // TM: 32-pixel tiles per wavefront (four wavefronts: 128 or 256 pixels); TN: 32-channel tiles; D: weight tiles in flight;
-// LAST: this workgroup's column blocks are args->last.
-template <int TM, int TN, int D, bool LAST>
+// LAST: this workgroup's column blocks are args->last; NORM: io.bn_out.
+template <int TM, int TN, int D, bool LAST, bool NORM>
 __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int first) {
   typedef bf16_t T;
   constexpr int BN = TN * 32, NB = D + 1, RS = 9;
@@ -91,7 +91,7 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
   const int cv = (lane & 3) ^ ((lane >> 4) & 3);  // channel vector this lane loads
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
   const int pbytes = (args->hg.slots + 15) / 16 * 16 * kPix;
-  const int wring = 2 * pbytes, lbias = wring + NB * TB, ldump = lbias + 1024;
+  const int wring = 2 * pbytes, lbias = wring + NB * TB, ldump = lbias + 1024, lnorm = ldump + 1024;
   const int Cc = args->g.Cc, chunks = (Cc + 31) >> 5;
   const int b_l = (lane & 31) * kPix + ((h ^ ((lane >> 2) & 3)) << 4);
   int n0;  // all items of a workgroup have the same columns
@@ -277,12 +277,35 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
 #pragma unroll
       for (int j = 0; j < 2; ++j) ex[tm][j][tn] = __builtin_amdgcn_raw_buffer_load_b128(r, off(N, tm, j, tn), 0, 0);
   };
+  // stores eight channels of a pixel; NORM: and what the batch-norm + ReLU behind the layer makes of them
+  auto put = [&](CArgs *a, int rep, const u4 &o, uint32_t at, int tn, __amdgpu_buffer_rsrc_t o_rsrc, __amdgpu_buffer_rsrc_t n_rsrc) {
+    if (!NORM || !a->io.bn_only) __builtin_amdgcn_raw_buffer_store_b128(o, o_rsrc, at, 0, 0);
+    if constexpr (NORM) {
+      const char *p = smem + lnorm + (tn * 32 + chan) * 4;  // means, 1/sigma, gamma, beta of the column block
+      u4 r;
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const f4 mu = *(const f4 *)(p + q * 16), rs = *(const f4 *)(p + BN * 4 + q * 16), gm = *(const f4 *)(p + BN * 8 + q * 16),
+                 bt = *(const f4 *)(p + BN * 12 + q * 16);
+        float v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float x = __uint_as_float(e & 1 ? o[2 * q + (e >> 1)] & 0xffff0000u : o[2 * q + (e >> 1)] << 16);
+          const float t = (x - mu[e]) * rs[e] * gm[e] + bt[e];
+          v[e] = t > 0.f ? t : 0.f;
+        }
+        r[2 * q] = f32x2_to_bf16x2(v[0], v[1]), r[2 * q + 1] = f32x2_to_bf16x2(v[2], v[3]);
+      }
+      __builtin_amdgcn_raw_buffer_store_b128(r, n_rsrc, at, 0, 0);
+    }
+  };
   auto half_of = [](uint32_t w, int e) { return __uint_as_float(e ? w & 0xffff0000u : w << 16); };
   auto store_item = [&](CArgs *a, int rep, int tile) {
     const bool relu = a->io.relu, mask = a->io.mask, resid = a->io.resid, accumulate = a->io.accumulate;
     const __amdgpu_buffer_rsrc_t o_rsrc = out_like(a, a->io.out, a->io.out_rs, rep);
     const bool more_than_one = mask ? resid || accumulate : resid && accumulate;
     const int N = a->g.N;
+    const __amdgpu_buffer_rsrc_t n_rsrc = out_like(a, NORM ? a->io.bn_out : nullptr, a->io.out_rs, rep);
 #pragma unroll
     for (int tm = kEarly ? TM : 0; tm < TM; ++tm) load_extra(a, rep, tm);
 #pragma unroll
@@ -323,7 +346,7 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
                 o[j][k] &= __builtin_bit_cast(uint32_t, t);
               }
             }
-            __builtin_amdgcn_raw_buffer_store_b128(o[j], o_rsrc, off(N, tm, j, tn), 0, 0);
+            put(a, rep, o[j], off(N, tm, j, tn), tn, o_rsrc, n_rsrc);
           }
         }
       } else {
@@ -364,7 +387,7 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
               }
               o[k] = f32x2_to_bf16x2(v[0], v[1]);
             }
-            __builtin_amdgcn_raw_buffer_store_b128(o, o_rsrc, off(N, tm, j, tn), 0, 0);
+            put(a, rep, o, off(N, tm, j, tn), tn, o_rsrc, n_rsrc);
           }
         }
       }
@@ -387,6 +410,12 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
     for (int it = 0; it < H_IT; ++it) load_piece(it, 0, 0, live);
 #pragma unroll
     for (int i = 0; i < D; ++i) load_w(i * TB, (uint32_t)(i * Cc * 2), live);
+  }
+  if (NORM && tid < BN) {
+    const int n = min(n0 + tid, args->g.N - 1);
+    float *p = (float *)(smem + lnorm) + tid;
+    p[0] = args->io.bn_running[n], p[BN] = 1.0f / sqrtf(args->io.bn_running[args->g.N + n] + kBnEps);
+    p[2 * BN] = args->io.bn_gamma[n], p[3 * BN] = args->io.bn_beta[n];
   }
   wait_tiles(false);
   meet();
@@ -460,21 +489,21 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
   wait_loads<0>();  // nothing may land in LDS after the workgroup has ended
 }
 
-template <int TM, int TN, int TL, int D>
+template <int TM, int TN, int TL, int D, bool NORM>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TM == 1 ? 3 : 2))) void k_conv_patch(const PatchArgs) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   CArgs *args = (CArgs *)__builtin_amdgcn_kernarg_segment_ptr();
   const int groups = args->wide.groups;
   if ((int)blockIdx.x < groups)
-    conv_patch_body<TM, TN, D, false>(args, smem, blockIdx.x);
+    conv_patch_body<TM, TN, D, false, NORM>(args, smem, blockIdx.x);
   else if (TL != TN)
-    conv_patch_body<TM, TL, D, true>(args, smem, blockIdx.x - groups);
+    conv_patch_body<TM, TL, D, true, NORM>(args, smem, blockIdx.x - groups);
 }
 
-template <int TM, int TN, int TL, int D>
-hipError_t run_patch(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io, HaloGeom hg) {
+template <int TM, int TN, int TL, int D, bool NORM>
+hipError_t run_patch_as(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io, HaloGeom hg) {
   constexpr int kCus = 256, kLdsOfCu = 160 * 1024;
-  const int lds = 2 * ((hg.slots + 15) / 16 * 16) * kPix + (D + 1) * TN * 32 * kPix + 2048;
+  const int lds = 2 * ((hg.slots + 15) / 16 * 16) * kPix + (D + 1) * TN * 32 * kPix + 2048 + (NORM ? TN * 32 * 16 : 0);
   // workgroups that the chip holds at once: by registers, by LDS
   const int resident = kCus * (kLdsOfCu / lds < (TM == 1 ? 3 : 2) ? kLdsOfCu / lds : (TM == 1 ? 3 : 2));
   hg.tiles = (hg.rows + hg.TH - 1) / hg.TH;
@@ -506,10 +535,15 @@ hipError_t run_patch(hipStream_t st, int replicas, const ConvGeom &g, const Gemm
     }
   }
   static const hipError_t lds_ok =
-      hipFuncSetAttribute((const void *)k_conv_patch<TM, TN, TL, D>, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsOfCu);
+      hipFuncSetAttribute((const void *)k_conv_patch<TM, TN, TL, D, NORM>, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsOfCu);
   if (lds_ok != hipSuccess) return lds_ok;
-  hipLaunchKernelGGL((k_conv_patch<TM, TN, TL, D>), dim3(wide.groups + last.groups), dim3(kThreads), lds, st, pa);
+  hipLaunchKernelGGL((k_conv_patch<TM, TN, TL, D, NORM>), dim3(wide.groups + last.groups), dim3(kThreads), lds, st, pa);
   return hipGetLastError();
+}
+
+template <int TM, int TN, int TL, int D>
+hipError_t run_patch(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io, const HaloGeom &hg) {
+  return io.bn_out ? run_patch_as<TM, TN, TL, D, true>(st, replicas, g, io, hg) : run_patch_as<TM, TN, TL, D, false>(st, replicas, g, io, hg);
 }
 
 // us per step of a workgroup that has its compute unit to itself, and what every further workgroup of it adds (measured over
@@ -547,7 +581,7 @@ bool conv_patch_applicable(int replicas, const ConvGeom &g, const GemmIO &io) {
   HaloGeom hg;
   return g.R == 3 && g.S == 3 && g.sp == 1 && g.dshift == 0 && g.Cc % 8 == 0 && io.vecA && io.vecB && g.N % 8 == 0 && io.ldc % 8 == 0 &&
          !io.stat && aligned_to(io.out, 16) && io.out_rs % 8 == 0 && aligned_to(io.resid, 16) && io.resid_rs % 8 == 0 &&
-         aligned_to(io.mask, 16) && io.mask_rs % 8 == 0 && choose_shape(replicas, g, s, hg);
+         aligned_to(io.mask, 16) && io.mask_rs % 8 == 0 && aligned_to(io.bn_out, 16) && choose_shape(replicas, g, s, hg);
 }
 
 hipError_t launch_conv_patch(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io) {
@@ -565,4 +599,9 @@ hipError_t launch_conv_patch(hipStream_t st, int replicas, const ConvGeom &g, co
   // two workgroups in the LDS of a compute unit: one weight tile less beside the larger patches
   if (hg.slots > 352) return narrow ? run_patch<2, 4, 2, 2>(st, replicas, g, io, hg) : run_patch<2, 4, 4, 2>(st, replicas, g, io, hg);
   return narrow ? run_patch<2, 4, 2, 3>(st, replicas, g, io, hg) : run_patch<2, 4, 4, 3>(st, replicas, g, io, hg);
+}
+
+bool conv_takes_bn(int dtype, int replicas, const ConvGeom &g, const GemmIO &io, bool out_f32) {
+  return replicas == 1 && !conv_smallk_applicable(dtype, g, io) && conv_halo_applicable(dtype, replicas, g, io, out_f32) &&
+         conv_patch_applicable(replicas, g, io);
 }

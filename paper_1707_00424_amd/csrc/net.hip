@@ -531,6 +531,20 @@ hipError_t forward(const Run &r, bool train, float *bn_stats, const float *bn_ev
     if (r.images_direct && op.in == N.t_images) io.in_f32 = 1, io.vecA = 0, io.in_bytes = io.in_rs * 4;
     return io;
   };
+  // Evaluation: batch-norms that the convolution before them can apply in its epilogue, where the running statistics are known
+  // beforehand (WRN-16-4, 384 images: ten of thirteen, 787 -> 673 us).  A result that only its batch-norm reads is not stored then.
+  std::vector<int> bn_of(N.ops.size(), -1);
+  std::vector<char> bn_done(N.ops.size(), 0), bn_only(N.ops.size(), 0);
+  if (!train)
+    for (size_t b = 0; b < N.ops.size(); ++b) {
+      if (N.ops[b].type != OP_BNRELU) continue;
+      for (size_t c = 0; c < b; ++c) {
+        if (N.ops[c].type != OP_CONV || N.ops[c].out != N.ops[b].in) continue;
+        bn_of[c] = (int)b, bn_only[c] = 1;
+        for (size_t o = 0; o < N.ops.size(); ++o)
+          if (o != b && (N.ops[o].in == N.ops[b].in || N.ops[o].resid == N.ops[b].in)) bn_only[c] = 0;
+      }
+    }
   auto launch_pending = [&]() -> hipError_t {
     if (pending < 0) return hipSuccess;
     const int pi = pending;
@@ -560,6 +574,13 @@ hipError_t forward(const Run &r, bool train, float *bn_stats, const float *bn_ev
         GemmIO io = conv_io(op, g);
         // the sums go where the batch-norm's own reduction would put them (room for 1024 partial rows per replica)
         if (wants_stat[oi]) io.stat = (double *)(r.ws + N.off_colpartial), io.stat_capacity = 1024;
+        if (bn_of[oi] >= 0) {
+          const Op &b = N.ops[bn_of[oi]];
+          io.bn_out = r.tptr(b.out), io.bn_only = bn_only[oi];
+          io.bn_gamma = r.fptr(b.gseg), io.bn_beta = r.fptr(b.betaseg), io.bn_running = bn_eval_row + b.run_off;
+          bn_done[bn_of[oi]] = conv_takes_bn(N.dtype, r.n, g, io, N.tensors[op.out].f32);
+          if (!bn_done[bn_of[oi]]) io.bn_out = nullptr;
+        }
         HIP_TRY(launch_igemm(r.st, N.dtype, N.tensors[op.out].f32, r.n, g, io, &stat_S[oi]));
         HIP_TRY(launch_pending());
         break;
@@ -587,6 +608,7 @@ hipError_t forward(const Run &r, bool train, float *bn_stats, const float *bn_ev
         break;
       }
       case OP_BNRELU: {
+        if (bn_done[oi]) break;
         const Tensor &ti = N.tensors[op.in];
         const int M = r.B * ti.H * ti.W;
         float *saved = (float *)(r.ws + op.saved_off);

@@ -6,7 +6,6 @@
 namespace {
 
 constexpr int kThreads = 256;
-constexpr float kBnEps = 1e-5f;
 constexpr float kBnMomentum = 0.1f;
 
 template <typename T>
