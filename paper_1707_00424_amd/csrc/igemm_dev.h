@@ -471,6 +471,64 @@ __device__ __forceinline__ void write_tile_sums(const ConvGeom &g, const GemmIO 
   }
 }
 
+// Exchanges between the halves of a wavefront and between its rows of 16 lanes: the upper half (the odd rows) of `a` with the
+// lower half (the even rows) of `b`.
+__device__ __forceinline__ void swap32(uint32_t &a, uint32_t &b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  a = r[0], b = r[1];
+}
+__device__ __forceinline__ void swap16(uint32_t &a, uint32_t &b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+  a = r[0], b = r[1];
+}
+
+// Epilogue for transposed accumulator tiles of bf16 results with bias and ReLU only, without LDS: lanes exchange registers
+// until each holds eight channels of a pixel, and a store writes 64 bytes of sixteen pixels.  Requires natural row order,
+// N % 8 == 0, ldc % 8 == 0 and 16-byte aligned rows.
+template <int TM, int TN>
+__device__ __forceinline__ void store_tile_regs(const ConvGeom &g, const GemmIO &io, int rep, int mrow0, int ncol0, int lane,
+                                                f16v (&acc)[TM][TN]) {
+  const int h = lane >> 5, chan = 16 * ((lane >> 4) & 1) + 8 * h;
+  const __amdgpu_buffer_rsrc_t o_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+      (void *)((bf16_t *)io.out + rep * io.out_rs), 0, (int)((uint32_t)g.M * (uint32_t)io.ldc * 2u), 0x00020000);
+#pragma unroll
+  for (int tn = 0; tn < TN; ++tn) {
+    f4 bias[4];
+#pragma unroll
+    for (int vg = 0; vg < 4; ++vg) {
+      const int n = ncol0 + tn * 32 + 8 * vg + 4 * h;
+      bias[vg] = f4{0.f, 0.f, 0.f, 0.f};
+      if (io.bias && n < g.N) {
+        const float *bp = io.bias + rep * io.bias_rs + n;  // segment offsets need not be 16-byte aligned
+        bias[vg] = f4{bp[0], bp[1], bp[2], bp[3]};
+      }
+    }
+#pragma unroll
+    for (int tm = 0; tm < TM; ++tm) {
+      uint32_t d[4][2];
+#pragma unroll
+      for (int vg = 0; vg < 4; ++vg) {
+        f4 v = f4{acc[tm][tn][4 * vg], acc[tm][tn][4 * vg + 1], acc[tm][tn][4 * vg + 2], acc[tm][tn][4 * vg + 3]} + bias[vg];
+        if (io.relu) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.f ? v[e] : 0.f;
+        }
+        d[vg][0] = f32x2_to_bf16x2(v.x, v.y), d[vg][1] = f32x2_to_bf16x2(v.z, v.w);
+      }
+#pragma unroll
+      for (int k = 0; k < 2; ++k) swap32(d[0][k], d[1][k]), swap32(d[2][k], d[3][k]);
+#pragma unroll
+      for (int k = 0; k < 2; ++k) swap16(d[0][k], d[2][k]), swap16(d[1][k], d[3][k]);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int m = mrow0 + tm * 32 + j * 16 + (lane & 15), n = ncol0 + tn * 32 + chan;
+        const uint32_t at = m < g.M && n < g.N ? ((uint32_t)m * (uint32_t)io.ldc + (uint32_t)n) * 2u : kOobOffset;
+        __builtin_amdgcn_raw_buffer_store_b128(u4{d[2 * j][0], d[2 * j][1], d[2 * j + 1][0], d[2 * j + 1][1]}, o_rsrc, at, 0, 0);
+      }
+    }
+  }
+}
+
 // Writes a wavefront's TM x TN accumulator tiles: bias, residual, ReLU, mask, accumulate, convert.
 template <typename T, int TM, int TN, bool OUT_F32>
 __device__ __forceinline__ void store_tile(const ConvGeom &g, const GemmIO &io, int rep, int mrow0, int ncol0, int lane,

@@ -36,15 +36,6 @@ using namespace igemm_dev;
 constexpr uint32_t kOob = 0x80000000u;
 constexpr int kPix = 64;  // bytes of a patch pixel or weight row in LDS: 32 channels
 
-__device__ __forceinline__ void swap32(uint32_t &a, uint32_t &b) {
-  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
-  a = r[0], b = r[1];
-}
-__device__ __forceinline__ void swap16(uint32_t &a, uint32_t &b) {
-  const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
-  a = r[0], b = r[1];
-}
-
 // The tiles of the column blocks of one width.  Items are numbered replica, eight pixel tiles, column block, tile: ids that
 // differ by 8 share an XCD (see halo_block), and a workgroup's items are `groups` apart, a multiple of 8 * nb, so that all
 // of them have the same columns and the column blocks of a pixel tile run on one XCD.

@@ -32,8 +32,12 @@ __device__ __forceinline__ float buffer_load_elem<float>(__amdgpu_buffer_rsrc_t 
 // row per workgroup.  (The 64-wide bf16 variant came out at 172 registers, four over the budget of three wavefronts
 // per SIMD: it is held to that budget.)
 // IN_F32 (bf16 layers): the gathered tensor is fp32 in memory, rounded to bf16 as it is gathered.
-template <typename T, int TN, bool OUT_F32, bool STAT, bool IN_F32 = false>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 2 && TN == 2 && !OUT_F32 ? 3 : 1))) void k_conv_smallk(const ConvGeom g, const GemmIO io) {
+// REGS (bf16, channels in multiples of 8, bias and ReLU at most): epilogue in registers.  A workgroup is a chain of latencies,
+// gather, barrier, a few products, stores, and the strips of the other epilogue (51 KB at 96 columns) hold a compute unit to
+// three of them; without them five or six hide each other's.  us, before -> now, 3 x 128 images of 32 x 32 x 3 to 96 channels
+// with bias and ReLU 43 -> 37, 384 images of 16 channels 1 x 1 to 64 26 -> 24, and 17 with whole vectors loaded.
+template <typename T, int TN, bool OUT_F32, bool STAT, bool IN_F32 = false, bool REGS = false>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(REGS ? (TN == 3 ? 3 : 4) : sizeof(T) == 2 && TN == 2 && !OUT_F32 ? 3 : 1))) void k_conv_smallk(const ConvGeom g, const GemmIO io) {
   static_assert(!IN_F32 || sizeof(T) == 2, "fp32 layers read fp32 as it is");
   constexpr int VW = 16 / sizeof(T);
   constexpr int BK = 4 * VW;               // one contraction step of the MFMA helper: 32 bf16 / 16 fp32
@@ -41,7 +45,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(sizeof
   constexpr int LK = BK + VW;
   constexpr int TM = 2, BM = 256, BN = TN * 32;
   constexpr int kTileBytes = STEPS * (BM + BN) * LK * (int)sizeof(T);
-  constexpr int kStageBytes = (4 * kStageFloats<TN> + (STAT ? 4 * 2 * BN : 0)) * (int)sizeof(float);
+  constexpr int kStageBytes = REGS ? 0 : (4 * kStageFloats<TN> + (STAT ? 4 * 2 * BN : 0)) * (int)sizeof(float);
   __shared__ __attribute__((aligned(16))) char smem[kTileBytes > kStageBytes ? kTileBytes : kStageBytes];
   T *As = reinterpret_cast<T *>(smem);                                   // [STEPS][BM][LK]
   T *Bs = reinterpret_cast<T *>(smem) + STEPS * BM * LK;                 // [STEPS][BN][LK]
@@ -65,7 +69,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(sizeof
 
   // gather: value k = (r, s, c) sits at base + (r*Win + s)*Cc + c when the tap is inside the image
   T vals[kKP];
-  {
+  // 1 x 1 windows of whole vectors: the pixel's channels as they lie, 16 bytes at a time
+  const bool vec = REGS && !IN_F32 && g.R * g.S == 1 && io.vecA;
+  if (vec) {
+#pragma unroll
+    for (int v = 0; v < kKP / VW; ++v) {
+      const u4 t = __builtin_amdgcn_raw_buffer_load_b128(a_rsrc, m_ok && v * VW < g.K ? (uint32_t)((base + v * VW) * (int)sizeof(T)) : kOobOffset, 0, 0);
+      __builtin_memcpy(&vals[v * VW], &t, 16);
+    }
+  } else {
     int r = 0, s = 0, c = 0;  // wavefront-uniform
 #pragma unroll
     for (int k = 0; k < kKP; ++k) {
@@ -111,6 +123,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(sizeof
 #pragma unroll
   for (int st = 0; st < STEPS; ++st)
     mma_tile_t<T, TM, TN, LK, VW>(As + st * BM * LK, Bs + st * BN * LK, wave * TM * 32, 0, lane, acc);
+  if constexpr (REGS) {
+    store_tile_regs<TM, TN>(g, io, rep, m0 + wave * TM * 32, n0, lane, acc);
+    return;
+  }
   __syncthreads();  // operand tiles are dead: their LDS becomes the staging strips
   float *wsums = reinterpret_cast<float *>(smem) + 4 * kStageFloats<TN>;
   store_tile_lds<T, TM, TN, OUT_F32, STAT>(g, io, rep, m0 + wave * TM * 32, n0, lane, acc,
@@ -266,6 +282,16 @@ __global__ __launch_bounds__(kThreads) void k_wgrad_smallk(const ConvGeom g, con
 template <typename T, int TN>
 hipError_t run_smallk(hipStream_t st, bool out_f32, int replicas, const ConvGeom &g, const GemmIO &io) {
   dim3 grid((g.M + 255) / 256, (g.N + TN * 32 - 1) / (TN * 32), replicas);
+  if constexpr (sizeof(T) == 2) {
+    if (!out_f32 && !io.stat && !io.resid && !io.mask && !io.accumulate && g.plq == 0 && g.N % 8 == 0 && io.ldc % 8 == 0 &&
+        aligned_to(io.out, 16) && io.out_rs % 8 == 0) {
+      if (io.in_f32)
+        hipLaunchKernelGGL((k_conv_smallk<T, TN, false, false, true, true>), grid, dim3(kThreads), 0, st, g, io);
+      else
+        hipLaunchKernelGGL((k_conv_smallk<T, TN, false, false, false, true>), grid, dim3(kThreads), 0, st, g, io);
+      return hipGetLastError();
+    }
+  }
   if (io.in_f32) {  // a bf16 layer over fp32 memory
     if constexpr (sizeof(T) == 2) {
       if (out_f32 || (io.stat && TN > 2)) return hipErrorInvalidValue;

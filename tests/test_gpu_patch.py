@@ -81,3 +81,33 @@ def test_shapes_and_epilogues(gpu, case):
         near("gradient, mask", backward(mask, None)[a], g * m)
         near("gradient, added", backward(None, prev)[a], g + prev[a].double())
         near("gradient, mask, added", backward(mask, prev)[a], g * m + prev[a].double())
+
+
+@pytest.mark.parametrize("case", [
+    # n, B, H, W, Cin, Cout, k, stride: layers whose whole contraction is one tile, epilogue in registers
+    (2, 3, 32, 32, 3, 96, 3, 1),
+    (1, 5, 15, 13, 3, 16, 3, 1),     # a ragged last tile, half of the columns padding
+    (1, 2, 16, 16, 3, 136, 3, 1),    # two column blocks, the second ragged
+    (2, 3, 16, 16, 16, 64, 1, 1),    # whole vectors
+    (1, 3, 9, 7, 24, 40, 1, 2),      # same, stride 2, a contraction of three vectors
+    (1, 2, 11, 11, 5, 24, 1, 1),     # 1 x 1 gathered value by value
+])
+def test_small_contractions(gpu, case):
+    torch, pb = gpu
+    n, B, H, W, Cin, Cout, k, stride = case
+    gen = torch.Generator(device="cuda").manual_seed(sum(case))
+    x = torch.randn((n, B, H, W, Cin), generator=gen, device="cuda").bfloat16()
+    w = (torch.randn((n, Cout, k, k, Cin), generator=gen, device="cuda") * (k * k * Cin) ** -0.5).bfloat16()
+    bias = torch.randn((n, Cout), generator=gen, device="cuda")
+    P, Q = (H - 1) // stride + 1, (W - 1) // stride + 1
+    desc = pb.parle_conv_desc(1, n, B, H, W, Cin, Cout, k, stride, k // 2)
+    for relu in (0, 1):
+        y = torch.full((n, B, P, Q, Cout), float("nan"), dtype=torch.bfloat16, device="cuda")
+        pb.parle_k_conv_forward(desc, x, w, bias, None, relu, y)
+        for a in range(n):
+            xp = torch.nn.functional.pad(x[a].double(), (0, 0) + (k // 2,) * 4)
+            ref = bias[a].double() + sum(xp[:, r:r + H:stride, c:c + W:stride].reshape(-1, Cin) @ w[a][:, r, c].double().t().contiguous()
+                                         for r in range(k) for c in range(k)).reshape(B, P, Q, Cout)
+            ref = ref.relu() if relu else ref
+            # half a bf16 ulp on the store and room for the order of the sums
+            assert ((y[a].double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 2e-5 * ref.abs().max()).all()
