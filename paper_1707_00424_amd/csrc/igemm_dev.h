@@ -62,7 +62,8 @@ __device__ __forceinline__ u4 buffer_desc(const void *p, uint32_t bytes) {
 }
 
 // 64 lanes x 16 bytes straight into LDS at `lds` + 16 * lane; a lane whose offset lies beyond the buffer writes zeros.
-// The waits in front cover an operand that the vector unit has just written to a scalar register.
+// The waits in front cover an operand that the vector unit has just written to a scalar register.  m0 is no register that
+// the compiler keeps values in: it writes it in front of every use of its own.
 __device__ __forceinline__ void dma16(uint32_t lds, const u4 &rsrc, uint32_t voff, uint32_t soff) {
   asm volatile("s_nop 3\n\ts_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff)
                : "memory");

@@ -1,4 +1,4 @@
-// Stride-1 3x3 convolutions in bf16 (forward, and backward-data of such a layer), channel counts in multiples of 8: the
+// Stride-1 3x3 and 5x5 convolutions in bf16 (forward, and backward-data of such a layer), channel counts in multiples of 8: the
 // input patch of a tile staged in LDS as in igemm_halo.hip, with nothing on its way through registers.
 //
 // What bounds them, from stamps in the kernel before this one (96 -> 96 channels, 32 x 32, batch 3 x 128: 512 of 1536
@@ -10,11 +10,11 @@
 //   * a workgroup walks several tiles, and the patch, the first weight tiles and the bias of the next one are on their way
 //     while the last channels of the current one are multiplied: only the first tile waits for memory;
 //   * the epilogue exchanges lanes in registers (permlane swaps) until each lane holds eight channels of a pixel and a
-//     store writes 64 bytes of sixteen pixels; LDS has no part in it, the next tile's loads run on beneath it.  The bias is
-//     what the sums start from.
+//     store writes 64 bytes of sixteen pixels; LDS has no part in it, the next tile's loads run on beneath it.
 // What is left is the matrix work at the clock that the power limit allows (1.4 to 1.6 GHz in these loops) and, in launches
 // of one round, the first patch.  us per pass, before -> now: 96 -> 96 32 x 32, 3 x 128 images 93 -> 79; 320 -> 320
 // 16 x 16 195 -> 161; 64 -> 64 32 x 32 47 -> 43; 96 -> 96 28 x 28, 100 images 31 -> 23; 256 -> 256 8 x 8 45 -> 35.
+// 5 x 5: 128 -> 128 on 16 x 16, 64 images 41 -> 31; 32 -> 96 28 x 28, 100 images 42 -> 30; 64 -> 64 32 x 32, 128 images 52 -> 52.
 // (Non-temporal stores took 2 to 5 % off the layer, and put as much on the batch-norm that reads its output next.)
 //
 // LDS: patch pixels and weight rows are 64 bytes (32 channels) without padding, as the direct loads write them; the four
@@ -65,12 +65,12 @@ __device__ __forceinline__ uint32_t fdivc(uint32_t n, __attribute__((address_spa
   return (uint32_t)(((uint64_t)n * f.magic) >> f.shift);
 }
 
-// TM: 32-pixel tiles per wavefront (four wavefronts: 128 or 256 pixels); TN: 32-channel tiles; D: weight tiles in flight;
+// S: window side; TM: 32-pixel tiles per wavefront (four wavefronts: 128 or 256 pixels); TN: 32-channel tiles; D: weight tiles in flight;
 // LAST: this workgroup's column blocks are args->last; NORM: io.bn_out.
-template <int TM, int TN, int D, bool LAST, bool NORM>
+template <int S, int TM, int TN, int D, bool LAST, bool NORM>
 __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int first) {
   typedef bf16_t T;
-  constexpr int BN = TN * 32, NB = D + 1, RS = 9;
+  constexpr int BN = TN * 32, NB = D + 1, RS = S * S;
   constexpr int H_IT = TM == 1 ? 5 : TN == 4 && D == 3 ? 6 : 7;  // wavefront loads of a patch per wavefront, 64 pixels of the workgroup each time
   constexpr int WG = TN * 2;             // wavefront loads of a weight tile, 16 rows each
   constexpr int WI = (WG + 3) / 4;       // per wavefront, at most
@@ -169,7 +169,7 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
 
   f16v acc[TM][TN];
   int a_b[TM];
-  auto begin = [&](CArgs *a, int tile, int bias_buf) {
+  auto begin = [&](CArgs *a, int tile) {
     const int P = a->g.P, Q = a->g.Q, TH = a->hg.TH, HC = a->hg.HC, PRI = a->hg.PRI;
     const int row0 = tile * TH, b0 = (int)fdivc((uint32_t)row0, a->hg.dP), p0 = row0 - b0 * P;
     const int first_rows = P - 1 - p0 + a->g.R;
@@ -184,20 +184,16 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
       a_b[tm] = (pr * HC + q) * kPix + h * 16;
     }
 #pragma unroll
-    for (int tn = 0; tn < TN; ++tn)
+    for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
-      for (int vg = 0; vg < 4; ++vg) {
-        const f4 b = *(const f4 *)(smem + lbias + bias_buf * 512 + (tn * 32 + vg * 8 + h * 4) * 4);
+      for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
-        for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) acc[tm][tn][vg * 4 + e] = b[e];
-      }
+        for (int v = 0; v < 16; ++v) acc[tm][tn][v] = 0.f;
   };
 
-  // tap (r, c) of a forward pass lies r rows and c columns into the patch, of a backward-data pass 2 - r and 2 - c
+  // tap (r, c) of a forward pass lies r rows and c columns into the patch, of a backward-data pass S - 1 - r and S - 1 - c
   const int pix_step = args->g.sr > 0 ? kPix : -kPix, row_step = args->hg.HC * pix_step;
-  const int tap0 = args->g.sr > 0 ? 0 : 2 * (args->hg.HC + 1) * kPix;
+  const int tap0 = args->g.sr > 0 ? 0 : (S - 1) * (args->hg.HC + 1) * kPix;
   int a_ad[TM];
   u4 fa_a[TM], fa_b[TN], fb_a[TM], fb_b[TN];
   auto read0 = [&](int shift, int ring) {
@@ -291,9 +287,10 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
     }
   };
   auto half_of = [](uint32_t w, int e) { return __uint_as_float(e ? w & 0xffff0000u : w << 16); };
-  auto store_item = [&](CArgs *a, int rep, int tile) {
+  auto store_item = [&](CArgs *a, int rep, int tile, int bias_buf) {
     const bool relu = a->io.relu, mask = a->io.mask, resid = a->io.resid, accumulate = a->io.accumulate;
     const __amdgpu_buffer_rsrc_t o_rsrc = out_like(a, a->io.out, a->io.out_rs, rep);
+    auto bias_of = [&](int tn, int vg) { return *(const f4 *)(smem + lbias + bias_buf * 512 + (tn * 32 + vg * 8 + h * 4) * 4); };
     const bool more_than_one = mask ? resid || accumulate : resid && accumulate;
     const int N = a->g.N;
     const __amdgpu_buffer_rsrc_t n_rsrc = out_like(a, NORM ? a->io.bn_out : nullptr, a->io.out_rs, rep);
@@ -307,7 +304,7 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
           uint32_t d[4][2];
 #pragma unroll
           for (int vg = 0; vg < 4; ++vg) {
-            f4 v = {acc[tm][tn][4 * vg], acc[tm][tn][4 * vg + 1], acc[tm][tn][4 * vg + 2], acc[tm][tn][4 * vg + 3]};
+            f4 v = f4{acc[tm][tn][4 * vg], acc[tm][tn][4 * vg + 1], acc[tm][tn][4 * vg + 2], acc[tm][tn][4 * vg + 3]} + bias_of(tn, vg);
             if (relu) {
 #pragma unroll
               for (int e = 0; e < 4; ++e) v[e] = __builtin_amdgcn_fmed3f(v[e], 0.f, __builtin_inff());  // NaN: 0
@@ -354,9 +351,11 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
           }
           uint32_t d[2][2][4];  // [channels 0 .. 15 / 16 .. 31][first / second four of a vector][e]
 #pragma unroll
-          for (int vg = 0; vg < 4; ++vg)
+          for (int vg = 0; vg < 4; ++vg) {
+            const f4 b = bias_of(tn, vg);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) d[vg >> 1][vg & 1][e] = __float_as_uint(acc[tm][tn][4 * vg + e]);
+            for (int e = 0; e < 4; ++e) d[vg >> 1][vg & 1][e] = __float_as_uint(acc[tm][tn][4 * vg + e] + b[e]);
+          }
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             swap32(d[0][0][e], d[0][1][e]), swap32(d[1][0][e], d[1][1][e]);
@@ -414,7 +413,7 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
   const bool has_extra = args->io.mask || args->io.resid || args->io.accumulate;
   bool later = false;  // not the first item: the stores of the one before it are in flight
   for (;;) {
-    begin(fresh(args), tile, bbuf);
+    begin(fresh(args), tile);
     read0(tap0 + pbuf * pbytes, ring);
     int rep1 = rep, tile1 = tile;
     bool more = false;
@@ -462,7 +461,7 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
         interleave();
         wait_tiles((tap < D - 1 && c == 0 && later) || (kEarly && tap + D >= RS && last && has_extra));
         meet();
-        shift += tap % 3 == 2 ? row_step - 2 * pix_step : pix_step;
+        shift += tap % S == S - 1 ? row_step - (S - 1) * pix_step : pix_step;
         if (tap + 1 < RS)
           read0(shift, next);
         else if (!last)
@@ -473,25 +472,25 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
       }
       pbuf ^= 1;
     }
-    store_item(fresh(args), rep, tile);
+    store_item(fresh(args), rep, tile, bbuf);
     if (!more) break;
     rep = rep1, tile = tile1, later = true, bbuf ^= 1;
   }
   wait_loads<0>();  // nothing may land in LDS after the workgroup has ended
 }
 
-template <int TM, int TN, int TL, int D, bool NORM>
+template <int S, int TM, int TN, int TL, int D, bool NORM>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TM == 1 ? 3 : 2))) void k_conv_patch(const PatchArgs) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   CArgs *args = (CArgs *)__builtin_amdgcn_kernarg_segment_ptr();
   const int groups = args->wide.groups;
   if ((int)blockIdx.x < groups)
-    conv_patch_body<TM, TN, D, false, NORM>(args, smem, blockIdx.x);
+    conv_patch_body<S, TM, TN, D, false, NORM>(args, smem, blockIdx.x);
   else if (TL != TN)
-    conv_patch_body<TM, TL, D, true, NORM>(args, smem, blockIdx.x - groups);
+    conv_patch_body<S, TM, TL, D, true, NORM>(args, smem, blockIdx.x - groups);
 }
 
-template <int TM, int TN, int TL, int D, bool NORM>
+template <int S, int TM, int TN, int TL, int D, bool NORM>
 hipError_t run_patch_as(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io, HaloGeom hg) {
   constexpr int kCus = 256, kLdsOfCu = 160 * 1024;
   const int lds = 2 * ((hg.slots + 15) / 16 * 16) * kPix + (D + 1) * TN * 32 * kPix + 2048 + (NORM ? TN * 32 * 16 : 0);
@@ -526,15 +525,17 @@ hipError_t run_patch_as(hipStream_t st, int replicas, const ConvGeom &g, const G
     }
   }
   static const hipError_t lds_ok =
-      hipFuncSetAttribute((const void *)k_conv_patch<TM, TN, TL, D, NORM>, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsOfCu);
+      hipFuncSetAttribute((const void *)k_conv_patch<S, TM, TN, TL, D, NORM>, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsOfCu);
   if (lds_ok != hipSuccess) return lds_ok;
-  hipLaunchKernelGGL((k_conv_patch<TM, TN, TL, D, NORM>), dim3(wide.groups + last.groups), dim3(kThreads), lds, st, pa);
+  hipLaunchKernelGGL((k_conv_patch<S, TM, TN, TL, D, NORM>), dim3(wide.groups + last.groups), dim3(kThreads), lds, st, pa);
   return hipGetLastError();
 }
 
 template <int TM, int TN, int TL, int D>
 hipError_t run_patch(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io, const HaloGeom &hg) {
-  return io.bn_out ? run_patch_as<TM, TN, TL, D, true>(st, replicas, g, io, hg) : run_patch_as<TM, TN, TL, D, false>(st, replicas, g, io, hg);
+  if (g.S == 5) return run_patch_as<5, TM, TN, TL, D, false>(st, replicas, g, io, hg);
+  return io.bn_out ? run_patch_as<3, TM, TN, TL, D, true>(st, replicas, g, io, hg)
+                   : run_patch_as<3, TM, TN, TL, D, false>(st, replicas, g, io, hg);
 }
 
 // us per step of a workgroup that has its compute unit to itself, and what every further workgroup of it adds (measured over
@@ -570,7 +571,7 @@ bool choose_shape(int replicas, const ConvGeom &g, PatchShape &best, HaloGeom &h
 bool conv_patch_applicable(int replicas, const ConvGeom &g, const GemmIO &io) {
   PatchShape s;
   HaloGeom hg;
-  return g.R == 3 && g.S == 3 && g.sp == 1 && g.dshift == 0 && g.Cc % 8 == 0 && io.vecA && io.vecB && g.N % 8 == 0 && io.ldc % 8 == 0 &&
+  return g.R == g.S && (g.S == 3 || (g.S == 5 && !io.bn_out)) && g.sp == 1 && g.dshift == 0 && g.Cc % 8 == 0 && io.vecA && io.vecB && g.N % 8 == 0 && io.ldc % 8 == 0 &&
          !io.stat && aligned_to(io.out, 16) && io.out_rs % 8 == 0 && aligned_to(io.resid, 16) && io.resid_rs % 8 == 0 &&
          aligned_to(io.mask, 16) && io.mask_rs % 8 == 0 && aligned_to(io.bn_out, 16) && choose_shape(replicas, g, s, hg);
 }

@@ -90,8 +90,9 @@ struct Net {
   int images_reader = -1;  // the one convolution that reads the images, or -1
   // Wavefronts a weight-gradient launch of the nine-tap kernel puts in flight.  Where batch-norm passes share
   // the chain of input gradients, that chain is the longer one and the leaves have slack: they take half the
-  // chip's SIMDs and leave the rest to the chain (WRN-16-4 -3 %); without batch-norm the leaves are the longer
-  // side and take all of them (All-CNN-C: +3.7 % with half).
+  // chip's SIMDs and leave the rest to the chain (WRN-16-4, 256 / 512 / 768 / 1024 wavefronts: 2.56 / 2.18 / 2.20 / 2.23 ms);
+  // without batch-norm the leaves are the longer side and take what the kernel's own estimate gives (All-CNN-C: 512
+  // wavefronts 1.10 ms, 768 and more 1.05).
   int leaf_waves = 0;
   // A layer without input gradient (the first one) is the last the backward pass reaches: nothing follows it on
   // the first stream, so its leaves run there, beside whatever the second stream still has queued (own scratch).

@@ -1,4 +1,4 @@
-"""The stride-1 3x3 bf16 kernel with operands loaded straight into LDS: each of its tile shapes, one tile and several per
+"""The stride-1 3x3 and 5x5 bf16 kernel with operands loaded straight into LDS: each of its tile shapes, one tile and several per
 workgroup, ragged channel chunks and column blocks, images that end inside a tile, and every form of the epilogue, against
 plain products in 64 bits."""
 import pytest
@@ -26,20 +26,23 @@ CASES = [
 
 
 def _products64(torch, x, w, transpose):
-    """``[B, H, W, C]`` with ``[Cout, 3, 3, Cin]``; transposed: the input gradient."""
+    """``[B, H, W, C]`` with ``[Cout, k, k, Cin]``; transposed: the input gradient."""
     B, H, W, _ = x.shape
-    xp = torch.nn.functional.pad(x.double(), (0, 0, 1, 1, 1, 1))
+    k = w.shape[1]
+    xp = torch.nn.functional.pad(x.double(), (0, 0) + (k // 2,) * 4)
     out = 0
-    for r in range(3):
-        for c in range(3):
+    for r in range(k):
+        for c in range(k):
             tap = xp[:, r:r + H, c:c + W].reshape(B * H * W, -1)
-            m = w[:, 2 - r, 2 - c] if transpose else w[:, r, c].t()
+            m = w[:, k - 1 - r, k - 1 - c] if transpose else w[:, r, c].t()
             out = out + tap @ m.double().contiguous()
     return out.reshape(B, H, W, -1)
 
 
-@pytest.mark.parametrize("case", CASES)
-def test_shapes_and_epilogues(gpu, case):
+@pytest.mark.parametrize("case,k", [(c, 3) for c in CASES] + [
+    ((2, 3, 16, 16, 24, 40), 5), ((1, 60, 28, 28, 40, 96), 5), ((1, 140, 32, 32, 16, 64), 5), ((3, 14, 24, 24, 16, 160), 5),
+    ((1, 64, 32, 32, 32, 128), 5), ((1, 201, 8, 8, 16, 304), 5), ((1, 65, 7, 7, 72, 64), 5)])
+def test_shapes_and_epilogues(gpu, case, k):
     torch, pb = gpu
     n, B, H, W, Cin, Cout = case
     gen = torch.Generator(device="cuda").manual_seed(sum(case))
@@ -48,9 +51,9 @@ def test_shapes_and_epilogues(gpu, case):
         return (torch.randn(shape, generator=gen, device="cuda") * std).to(dtype)
 
     x, dy, resid, mask, prev = (normal(n, B, H, W, c) for c in (Cin, Cout, Cout, Cin, Cin))
-    w = normal(n, Cout, 3, 3, Cin, std=(9 * Cin) ** -0.5)
+    w = normal(n, Cout, k, k, Cin, std=(k * k * Cin) ** -0.5)
     bias = normal(n, Cout, dtype=torch.float32)
-    desc = pb.parle_conv_desc(1, n, B, H, W, Cin, Cout, 3, 1, 1)
+    desc = pb.parle_conv_desc(1, n, B, H, W, Cin, Cout, k, 1, k // 2)
     wt = torch.empty_like(w)
 
     def forward(bias, resid, relu):
