@@ -537,7 +537,7 @@ int wgrad9_plan(int replicas, const ConvGeom &g, int *chunk_out) {
   const int target = g.leaf_waves > 0 ? g.leaf_waves : waves;
   long long want;
   if (target > 0) {
-    want = target / (t.n * t.c) / tiles;
+    want = (target / (t.n * t.c) + tiles - 1) / tiles;
   } else {
     const double product = 2.0 * wg.total_blocks * block_pixels(g) * g.N * (double)g.K * replicas / 1.45e9;  // us at what the chip sustains
     const double partial = 8.0 * g.N * (double)g.K * replicas / 8e6;                    // us per split

@@ -89,9 +89,9 @@ struct Net {
   // kernels can (the small-window ones); otherwise a bf16 copy is made first.  PARLE_IMAGES_DIRECT=0: always copy.
   int images_reader = -1;  // the one convolution that reads the images, or -1
   // Wavefronts a weight-gradient launch of the nine-tap kernel puts in flight.  Where batch-norm passes share
-  // the chain of input gradients, that chain is the longer one and the leaves have slack: they take half the
-  // chip's SIMDs and leave the rest to the chain (WRN-16-4, 256 / 512 / 768 / 1024 wavefronts: 2.56 / 2.18 / 2.20 / 2.23 ms);
-  // without batch-norm the leaves are the longer side and take what the kernel's own estimate gives (All-CNN-C: 512
+  // the chain of input gradients, that chain is the longer one and the leaves have slack: they take part
+  // of the chip and leave the rest to the chain (512 / 768 / 1024 wavefronts: WRN-16-4 2.18 / 2.19 / 2.26 ms, WRN-28-10
+  // 16.7 / 15.8 / 15.7; with 256 WRN-16-4 takes 2.56); without batch-norm the leaves are the longer side and take what the kernel's own estimate gives (All-CNN-C: 512
   // wavefronts 1.10 ms, 768 and more 1.05).
   int leaf_waves = 0;
   // A layer without input gradient (the first one) is the last the backward pass reaches: nothing follows it on
@@ -337,7 +337,7 @@ bool build_plan(Net &N, std::string &err) {
       if (N.ops[j].type == OP_CONV && N.ops[j].out == N.ops[i].in && !N.ops[j].branch) N.ops[i].stat_src = (int)j;
   }
   // gradients, transposed weights, scratch
-  N.leaf_waves = N.max_bn_c > 0 ? 512 : 0;
+  N.leaf_waves = N.max_bn_c > 0 ? 768 : 0;
   int64_t wpartial = 0, wpartial_main = 0, col_bytes = 0;
   for (Op &op : N.ops) {
     if (op.wseg < 0 && op.type == OP_CONV) {
