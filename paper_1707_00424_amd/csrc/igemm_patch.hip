@@ -427,7 +427,6 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
         if (more) {
           patch_of(a, rep1, tile1);
           bn_base = weights_at(a, rep1);
-          load_bias(a, rep1, bbuf ^ 1);
         } else {
 #pragma unroll
           for (int it = 0; it < H_IT; ++it) h_off[it] = kOob;
@@ -441,6 +440,9 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
       for (int tap = 0; tap < RS; ++tap) {
         const int prev = ring == 0 ? (NB - 1) * TB : ring - TB, next = ring == (NB - 1) * TB ? 0 : ring + TB;
         read1(ring);
+        // The buffer is the one that the item before this one took its bias from, behind its last barrier: with a single chunk
+        // the barrier of tap 0 is the first that all wavefronts reach after it, and replicas differ.
+        if (tap == 1 && last && more) load_bias(fresh(args), rep1, bbuf ^ 1);
         if (tap < H_IT) load_piece(tap, pbuf ^ 1, (uint32_t)(c1 * 64), live1);
         if (tap + D == RS) {
           soff = (uint32_t)(c1 * 64);

@@ -22,6 +22,10 @@ CASES = [
     (1, 25, 32, 32, 64, 320),   # 256 x 128 and 64
     (1, 100, 32, 32, 16, 320),  # same, both widths several tiles per workgroup
     (1, 399, 8, 8, 32, 304),    # same with four images per tile, the narrow block ragged
+    # workgroups that go from one replica to the next under a single chunk of channels: their three tiles lie in three replicas,
+    # and the bias of the third goes where that of the first was
+    (3, 128, 32, 32, 32, 32),   # 256 x 64
+    (5, 43, 32, 32, 16, 64),    # 128 x 64
 ]
 
 
