@@ -36,15 +36,16 @@ using namespace igemm_dev;
 constexpr uint32_t kOob = 0x80000000u;
 constexpr int kPix = 64;  // bytes of a patch pixel or weight row in LDS: 32 channels
 
-// The tiles of the column blocks of one width.  Items are numbered replica, eight pixel tiles, column block, tile: ids that
-// differ by 8 share an XCD (see halo_block), and a workgroup's items are `groups` apart, a multiple of 8 * nb, so that all
-// of them have the same columns and the column blocks of a pixel tile run on one XCD.
+// The tiles of the column blocks of one width.  Items are numbered eight pixel tiles (counted through all replicas), column
+// block, tile: ids that differ by 8 share an XCD (see halo_block), and a workgroup's items are `groups` apart, a multiple of
+// 8 * nb, so that all of them have the same columns and the column blocks of a pixel tile run on one XCD.
 struct PatchPlan {
   int nb;            // column blocks of this kind
   int col0;          // the first of them
-  int items;         // pixel tiles (padded to eights) x column blocks x replicas
+  int items;         // pixel tiles of all replicas (padded to eights once, behind the last) x column blocks
   int groups;        // workgroups that share them
-  FastDiv dRep, dGroup;  // items of a replica; items of eight tiles
+  int tiles;         // pixel tiles of all replicas
+  FastDiv dRep, dGroup;  // tiles of a replica; items of eight tiles
 };
 
 struct PatchArgs {
@@ -87,16 +88,14 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
   const int b_l = (lane & 31) * kPix + ((h ^ ((lane >> 2) & 3)) << 4);
   int n0;  // all items of a workgroup have the same columns
 
-  // the item `idx` or the next one of this workgroup
-  auto item_at = [&](CArgs *a, int &idx, int &rep, int &tile) {
+  // the item `idx`, if there is one
+  auto item_at = [&](CArgs *a, int idx, int &rep, int &tile) {
     const auto *pp = LAST ? &a->last : &a->wide;
-    for (; idx < pp->items; idx += pp->groups) {
-      rep = (int)fdivc((uint32_t)idx, pp->dRep);
-      const int r = idx - rep * (int)pp->dRep.d, group = (int)fdivc((uint32_t)r, pp->dGroup), w = r - group * (int)pp->dGroup.d;
-      tile = group * 8 + (w & 7), n0 = (pp->col0 + (w >> 3)) * a->hg.bn;
-      if (tile < a->hg.tiles) return true;
-    }
-    return false;
+    if (idx >= pp->items) return false;
+    const int group = (int)fdivc((uint32_t)idx, pp->dGroup), w = idx - group * (int)pp->dGroup.d, t = group * 8 + (w & 7);
+    n0 = (pp->col0 + (w >> 3)) * a->hg.bn;
+    rep = (int)fdivc((uint32_t)t, pp->dRep), tile = t - rep * (int)pp->dRep.d;
+    return t < pp->tiles;  // the last item of its workgroup where it is not: those behind it are further on
   };
 
   uint32_t h_off[H_IT], b_off[WI];
@@ -501,16 +500,16 @@ hipError_t run_patch_as(hipStream_t st, int replicas, const ConvGeom &g, const G
   hg.tiles = (hg.rows + hg.TH - 1) / hg.TH;
   hg.bn = TN * 32;
   hg.nb = (g.N + hg.bn - 1) / hg.bn;
-  const int tiles8 = (hg.tiles + 7) / 8 * 8;
+  const int tiles = hg.tiles * replicas;
   auto plan = [&](int nb, int col0) {
     PatchPlan p{};
-    p.nb = nb, p.col0 = col0, p.items = tiles8 * nb * replicas;
-    p.dRep = make_fastdiv(tiles8 * (nb > 0 ? nb : 1)), p.dGroup = make_fastdiv(8 * (nb > 0 ? nb : 1));
+    p.nb = nb, p.col0 = col0, p.tiles = tiles, p.items = (tiles + 7) / 8 * 8 * nb;
+    p.dRep = make_fastdiv(hg.tiles), p.dGroup = make_fastdiv(8 * (nb > 0 ? nb : 1));
     return p;
   };
   PatchArgs pa{g, io, hg, plan(TL == TN ? hg.nb : hg.nb - 1, 0), plan(TL == TN ? 0 : 1, hg.nb - 1)};
   PatchPlan &wide = pa.wide, &last = pa.last;
-  if (wide.items + last.items <= resident) {
+  if ((long long)tiles * hg.nb <= resident) {  // workgroups of the padding end at once
     wide.groups = wide.items, last.groups = last.items;
   } else if (last.items == 0) {
     const int step = 8 * wide.nb;

@@ -26,6 +26,11 @@ CASES = [
     # and the bias of the third goes where that of the first was
     (3, 128, 32, 32, 32, 32),   # 256 x 64
     (5, 43, 32, 32, 16, 64),    # 128 x 64
+    # ... and several chunks, the tiles of a replica no multiple of eight
+    (7, 33, 27, 29, 40, 64),    # 256 x 64, a ragged last tile in each replica
+    (5, 57, 28, 28, 40, 96),    # 256 x 96
+    (3, 86, 28, 28, 40, 160),   # 256 x 96 and 64
+    (3, 31, 32, 32, 40, 304),   # 256 x 128 and 64
 ]
 
 
