@@ -246,22 +246,25 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
     return __builtin_amdgcn_make_buffer_rsrc((void *)((const T *)p + rep * rs), 0, p ? (int)((uint32_t)a->g.M * (uint32_t)a->io.ldc * 2u) : 0,
                                              0x00020000);
   };
-  // The first of mask, residual and old output that there is.  All of it is requested before the tile's first store: a load
-  // behind a store is waited for until the store is done (residual of 64 channels on 32 x 32: 56 us a layer instead of 42).
+  // The first of mask, residual and old output that there is (mask and old output: the second one is `old` below).  All of it
+  // is requested before the tile's first store: a load behind a store is waited for until the store is done (residual of 64
+  // channels on 32 x 32: 56 us a layer instead of 42).  Lanes beyond the layer's channels read what follows: offsets of their
+  // own would be computed in registers that loads of the tile before may still be on their way to, behind a wait for everything.
   constexpr bool kEarly = TN < 4;  // registers for it beside the last fragments
   u4 ex[TM][2][TN];
-  auto load_extra = [&](CArgs *a, int rep, int tm) {
-    const int N = a->g.N;
-    const void *p = a->io.mask;
-    long long rs = a->io.mask_rs;
-    if (!p) p = a->io.resid, rs = a->io.resid_rs;
-    if (!p && a->io.accumulate) p = a->io.out, rs = a->io.out_rs;
-    if (!p) return;
+  auto load_like = [&](CArgs *a, const void *p, long long rs, int rep, int tm, u4 (&to)[2][TN]) {
     const __amdgpu_buffer_rsrc_t r = out_like(a, p, rs, rep);
 #pragma unroll
     for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) ex[tm][j][tn] = __builtin_amdgcn_raw_buffer_load_b128(r, off(N, tm, j, tn), 0, 0);
+      for (int j = 0; j < 2; ++j) to[j][tn] = __builtin_amdgcn_raw_buffer_load_b128(r, row_off[tm][j] + tn * 64u, 0, 0);
+  };
+  auto load_extra = [&](CArgs *a, int rep, int tm) {
+    const void *p = a->io.mask;
+    long long rs = a->io.mask_rs;
+    if (!p) p = a->io.resid, rs = a->io.resid_rs;
+    if (!p && a->io.accumulate) p = a->io.out, rs = a->io.out_rs;
+    if (p) load_like(a, p, rs, rep, tm, ex[tm]);
   };
   // stores eight channels of a pixel; NORM: and what the batch-norm + ReLU behind the layer makes of them
   auto put = [&](CArgs *a, int rep, const u4 &o, uint32_t at, int tn, __amdgpu_buffer_rsrc_t o_rsrc, __amdgpu_buffer_rsrc_t n_rsrc) {
@@ -290,11 +293,18 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
     const bool relu = a->io.relu, mask = a->io.mask, resid = a->io.resid, accumulate = a->io.accumulate;
     const __amdgpu_buffer_rsrc_t o_rsrc = out_like(a, a->io.out, a->io.out_rs, rep);
     auto bias_of = [&](int tn, int vg) { return *(const f4 *)(smem + lbias + bias_buf * 512 + (tn * 32 + vg * 8 + h * 4) * 4); };
-    const bool more_than_one = mask ? resid || accumulate : resid && accumulate;
+    const bool two = mask && accumulate;
     const int N = a->g.N;
     const __amdgpu_buffer_rsrc_t n_rsrc = out_like(a, NORM ? a->io.bn_out : nullptr, a->io.out_rs, rep);
 #pragma unroll
     for (int tm = kEarly ? TM : 0; tm < TM; ++tm) load_extra(a, rep, tm);
+    u4 old[kEarly ? TM : 1][2][TN];
+    if constexpr (kEarly) {
+      if (two) {
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm) load_like(a, a->io.out, a->io.out_rs, rep, tm, old[tm]);
+      }
+    }
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm) {
       if (!resid && !accumulate) {
@@ -339,14 +349,11 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
       } else {
 #pragma unroll
         for (int tn = 0; tn < TN; ++tn) {
-          u4 rv[2] = {ex[tm][0][tn], ex[tm][1][tn]}, ov[2] = {ex[tm][0][tn], ex[tm][1][tn]};
-          if (more_than_one) {
-            const __amdgpu_buffer_rsrc_t r_rsrc = out_like(a, a->io.resid, a->io.resid_rs, rep);
+          u4 ov[2] = {ex[tm][0][tn], ex[tm][1][tn]};
+          if (two) {
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-              if (mask && resid) rv[j] = __builtin_amdgcn_raw_buffer_load_b128(r_rsrc, off(N, tm, j, tn), 0, 0);
-              if (accumulate) ov[j] = __builtin_amdgcn_raw_buffer_load_b128(o_rsrc, off(N, tm, j, tn), 0, 0);
-            }
+            for (int j = 0; j < 2; ++j)
+              ov[j] = kEarly ? old[kEarly ? tm : 0][j][tn] : __builtin_amdgcn_raw_buffer_load_b128(o_rsrc, row_off[tm][j] + tn * 64u, 0, 0);
           }
           uint32_t d[2][2][4];  // [channels 0 .. 15 / 16 .. 31][first / second four of a vector][e]
 #pragma unroll
@@ -369,7 +376,7 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
 #pragma unroll
               for (int e = 0; e < 2; ++e) {
                 v[e] = __uint_as_float(d[j][k >> 1][2 * (k & 1) + e]);
-                if (resid) v[e] += half_of(rv[j][k], e);
+                if (resid) v[e] += half_of(ex[tm][j][tn][k], e);
                 if (relu) v[e] = v[e] > 0.f ? v[e] : 0.f;
                 if (mask) v[e] = half_of(ex[tm][j][tn][k], e) > 0.f ? v[e] : 0.f;
                 if (accumulate) v[e] += half_of(ov[j][k], e);
@@ -540,20 +547,32 @@ hipError_t run_patch(hipStream_t st, int replicas, const ConvGeom &g, const Gemm
 }
 
 // us per step of a workgroup that has its compute unit to itself, and what every further workgroup of it adds (measured over
-// 23 layers of 64 to 320 channels, 7 x 7 to 32 x 32, 16 to 384 images, in each of the five shapes).
+// 23 layers of 64 to 320 channels, 7 x 7 to 32 x 32, 16 to 384 images, in each of the five shapes).  `extra`: us that a mask,
+// residual or old output to read adds to an epilogue, twice that with two of them (fitted to 792 layers of 16 to 640 channels;
+// 96 columns run short of registers for them, and 128 hold them in part only).  In a short contraction, of at most 18 steps
+// (64 channels under 3 x 3), it comes with every workgroup, in a long one with the last: others of the compute unit hide it.
 struct PatchShape {
   int tm, tn;
-  float first, more;
+  float first, more, extra;
 };
-constexpr PatchShape kShapes[] = {{1, 2, .16f, .12f}, {1, 3, .28f, .17f}, {2, 2, .28f, .23f}, {2, 3, .33f, .31f}, {2, 4, .46f, .40f}};
+constexpr PatchShape kShapes[] = {
+    {1, 2, .16f, .12f, 0.f}, {1, 3, .28f, .17f, 0.f}, {2, 2, .28f, .23f, 0.f}, {2, 3, .33f, .31f, 4.f}, {2, 4, .46f, .40f, 8.f}};
 
 // The shape with the shortest estimate.  Within 3 % of the best one on 20 of the 23 layers, 4 to 11 % on the others.  The
 // small ones keep launches of few tiles spread over the chip (16 images of 32 x 32 x 96: 10.1 us at 128 x 64, 15.0 at
-// 256 x 96), the large ones need less of LDS and of the barriers per product (3 x 128 images: 90.7 and 68.8).
-bool choose_shape(int replicas, const ConvGeom &g, PatchShape &best, HaloGeom &hg_best) {
+// 256 x 96), the large ones need less of LDS and of the barriers per product (3 x 128 images: 90.7 and 68.8).  Short
+// contractions with something to read in the epilogue run narrow: 32 -> 128 on 15 x 15, 240 images, residual, 22.4 us at 128
+// columns, 13.8 at 64.
+// False where the kernel through registers is the faster one: a residual, or an old output without a mask, is added in fp32
+// behind twice the exchanges, which a contraction of at most 18 steps (64 channels under 3 x 3) does not hide once workgroups
+// have more than one tile.  Of 73 such layers this kernel takes 0.82 to 1.22 times the other's time, the same in the mean; up
+// to 512 workgroups, and in longer contractions (96 channels, 3 x 128 images of 32 x 32: 82 us, the other 89), it is ahead.
+bool choose_shape(int replicas, const ConvGeom &g, const GemmIO &io, PatchShape &best, HaloGeom &hg_best) {
   HaloGeom geom[2];
   const bool ok[2] = {make_halo_geom(g, geom[0], true), make_halo_geom(g, geom[1], false)};
+  const int steps = (g.Cc + 31) / 32 * g.R * g.S, extras = (io.mask ? 1 : 0) + (io.resid || io.accumulate ? 1 : 0);
   float least = 0.f;
+  double least_groups = 0.;
   for (const PatchShape &s : kShapes) {
     if (!ok[s.tm - 1] || (s.tn > 2 && g.N <= 64)) continue;
     const HaloGeom &hg = geom[s.tm - 1];
@@ -561,9 +580,11 @@ bool choose_shape(int replicas, const ConvGeom &g, PatchShape &best, HaloGeom &h
     const double tiles = (double)((hg.rows + hg.TH - 1) / hg.TH) * replicas;
     double groups = tiles * nb;
     if (groups > 512. && s.tn > 2 && last <= 64) groups = tiles * (nb - 1 + 2. / s.tn);  // a narrow last block takes less
-    const float t = s.first + (float)(ceil(groups / 256.) - 1.) * s.more;
-    if (least == 0.f || t < least) least = t, best = s, hg_best = hg;
+    const float ranks = (float)ceil(groups / 256.);
+    const float t = (s.first + (ranks - 1.f) * s.more) * steps + extras * s.extra * (steps <= 18 ? ranks : 1.f);
+    if (least == 0.f || t < least) least = t, least_groups = groups, best = s, hg_best = hg;
   }
+  if (!io.bn_out && !io.mask && extras && steps <= 18 && least_groups > 512.) return false;
   return least > 0.f;
 }
 
@@ -574,13 +595,13 @@ bool conv_patch_applicable(int replicas, const ConvGeom &g, const GemmIO &io) {
   HaloGeom hg;
   return g.R == g.S && (g.S == 3 || (g.S == 5 && !io.bn_out)) && g.sp == 1 && g.dshift == 0 && g.Cc % 8 == 0 && io.vecA && io.vecB && g.N % 8 == 0 && io.ldc % 8 == 0 &&
          !io.stat && aligned_to(io.out, 16) && io.out_rs % 8 == 0 && aligned_to(io.resid, 16) && io.resid_rs % 8 == 0 &&
-         aligned_to(io.mask, 16) && io.mask_rs % 8 == 0 && aligned_to(io.bn_out, 16) && choose_shape(replicas, g, s, hg);
+         aligned_to(io.mask, 16) && io.mask_rs % 8 == 0 && !(io.resid && (io.mask || io.accumulate)) && aligned_to(io.bn_out, 16) && choose_shape(replicas, g, io, s, hg);
 }
 
 hipError_t launch_conv_patch(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io) {
   PatchShape s;
   HaloGeom hg;
-  if (!choose_shape(replicas, g, s, hg)) return hipErrorInvalidValue;
+  if (!choose_shape(replicas, g, io, s, hg)) return hipErrorInvalidValue;
   const int width = s.tn * 32;
   const bool narrow = g.N - ((g.N + width - 1) / width - 1) * width <= 64;  // the last column block
   if (s.tm == 1) {

@@ -31,6 +31,10 @@ CASES = [
     (5, 57, 28, 28, 40, 96),    # 256 x 96
     (3, 86, 28, 28, 40, 160),   # 256 x 96 and 64
     (3, 31, 32, 32, 40, 304),   # 256 x 128 and 64
+    # contractions long enough that an epilogue with something to read runs on wide tiles
+    (1, 256, 32, 32, 96, 96),   # 256 x 96
+    (1, 384, 16, 16, 320, 320),  # 256 x 128 and 64, several tiles per workgroup
+    (2, 385, 8, 8, 320, 632),   # same, and a shorter ring of weight tiles
 ]
 
 
