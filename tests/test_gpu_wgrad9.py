@@ -27,6 +27,7 @@ CASES = [
     (1, 3, 15, 15, 64, 64, 1),     # a row more than a block, 15 pixels
     (1, 4, 12, 12, 32, 128, 1),    # 4 x 1
     (1, 2, 9, 40, 64, 64, 1),      # three columns of blocks
+    (1, 2, 16, 128, 64, 64, 1),    # eight columns of blocks
     (2, 3, 32, 32, 32, 64, 2),     # stride 2: two dy tiles, rows of 16
     (1, 5, 16, 16, 64, 64, 2),     # 8x8 results, odd batch
     (1, 6, 8, 64, 64, 96, 2),      # three, one row of blocks, two per row
