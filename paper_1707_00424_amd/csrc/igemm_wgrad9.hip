@@ -42,13 +42,16 @@ typedef short s4v __attribute__((ext_vector_type(4)));
 constexpr int kBlockPixels = 128;                // 8 rows x 16 columns, or two images of 8 x 8
 constexpr int kSub = 8;                          // contraction sub-steps (16 pixels) per block
 constexpr int kOutside = 1 << 30;                // a patch slot that belongs to no pixel
-// patch of a block: one halo pixel around each image part
+// Patch of a block: one halo pixel around each image part.  Rows of whole 8 x 8 images have zeros on both sides: the one on the
+// right of a row is the one on the left of the next, and one more lies behind the last row.  That keeps 2 x 2 tiles at 80 KB,
+// two workgroups per compute unit (640 channels, 3 x 128 images, 300 workgroups: 196 us; 244 with columns of their own).
 template <int KC>
 struct Patch {
-  static constexpr int PC = KC + 2;                      // columns
+  static constexpr int PC = KC == 16 ? KC + 2 : KC + 1;  // columns
   static constexpr int IMG = KC == 16 ? 1 : 2;           // image parts per block
   static constexpr int PRI = kBlockPixels / KC / IMG + 2;  // rows per image part
-  static constexpr int SLOTS = IMG * PRI * PC;           // 180 / 200
+  static constexpr int SLOTS = IMG * PRI * PC + (KC == 16 ? 0 : 1);  // 180 / 181
+  static constexpr int LOADS = (SLOTS + 15) / 16;        // of 16 pixels
 };
 
 struct Wg9Geom {
@@ -79,7 +82,7 @@ template <int NTN, int NTC, int KC, bool BIAS, bool RAG>
 __global__ __launch_bounds__(NTN * NTC * 64) __attribute__((amdgpu_waves_per_eu(2))) void k_wgrad9(const Wg9Geom wg, const WgradIO io) {
   typedef Patch<KC> PT;
   constexpr int kPC = PT::PC, W = NTN * NTC;
-  constexpr int XG = (PT::SLOTS + 15) / 16;               // loads of 16 pixels: one x tile, one dy tile (8)
+  constexpr int XG = PT::LOADS;                           // loads of 16 pixels: one x tile, one dy tile (8)
   constexpr int PIECES = NTC * XG + NTN * 8;
   constexpr int IT = (PIECES + W - 1) / W;                // loads of a block per wavefront
   constexpr int BUF = PIECES * 1024;
@@ -105,7 +108,7 @@ __global__ __launch_bounds__(NTN * NTC * 64) __attribute__((amdgpu_waves_per_eu(
       const int img = slot / (PT::PRI * kPC), rem = slot - img * (PT::PRI * kPC);
       const int prow = rem / kPC, pcol = rem - prow * kPC;
       rel[it] = (((img * wg.H + prow - 1) * wg.W + (pcol - 1)) * wg.Cin + (cg * NTC + t) * 32 + ch) * 2;
-      pos[it] = slot < PT::SLOTS ? prow | pcol << 8 | img << 16 : kOutside;
+      pos[it] = slot < PT::IMG * PT::PRI * kPC ? prow | pcol << 8 | img << 16 : kOutside;
     } else {
       const int d = q - NTC * XG, t = d >> 3, p = (d & 7) * 16 + px;  // pixel of the block
       const int img = p / (kBlockPixels / PT::IMG), r = p - img * (kBlockPixels / PT::IMG), row = r / KC, col = r - row * KC;
@@ -297,13 +300,14 @@ struct Patch2 {
   static constexpr int PC = 2 * QC + 1;                         // QC + 1 odd columns, QC even ones
   static constexpr int PR = 2 * ROWS + 1;
   static constexpr int SLOTS = PR * PC;                         // 297 / 289
+  static constexpr int LOADS = (SLOTS + 15) / 16;               // of 16 pixels
 };
 
 template <int NTN, int KC, bool BIAS>
 __global__ __launch_bounds__(NTN * 64) __attribute__((amdgpu_waves_per_eu(2))) void k_wgrad9_s2(const Wg9Geom wg, const WgradIO io) {
   typedef Patch2<KC> PT;
   constexpr int kPC = PT::PC, W = NTN, QC = PT::QC;
-  constexpr int XG = (PT::SLOTS + 15) / 16;               // loads of 16 pixels: the x tile, one dy tile (4)
+  constexpr int XG = PT::LOADS;                           // loads of 16 pixels: the x tile, one dy tile (4)
   constexpr int PIECES = XG + NTN * 4;
   constexpr int IT = (PIECES + W - 1) / W;
   constexpr int BUF = PIECES * 1024;
@@ -462,6 +466,11 @@ bool small_images(const ConvGeom &g) { return g.Q <= 8 && g.P <= 8; }
 bool whole_blocks(const ConvGeom &g) { return g.Q % 16 == 0 ? g.P % (g.sp == 2 ? 4 : 8) == 0 : g.Q == 8 && g.P == 8; }
 int block_pixels(const ConvGeom &g) { return g.sp == 2 ? 64 : kBlockPixels; }
 
+int wg9_lds(const ConvGeom &g, const Wg9Tiles &t) {
+  if (g.sp == 2) return 2 * ((small_images(g) ? Patch2<8>::LOADS : Patch2<16>::LOADS) + t.n * 4) * 1024;
+  return 2 * (t.c * (small_images(g) ? Patch<8>::LOADS : Patch<16>::LOADS) + t.n * 8) * 1024;
+}
+
 void make_wg9_geom(const ConvGeom &g, Wg9Geom &wg) {
   wg.H = g.P, wg.W = g.Q, wg.Cin = g.Cc, wg.N = g.N;
   wg.B = g.M / (g.P * g.Q);
@@ -479,7 +488,7 @@ void make_wg9_geom(const ConvGeom &g, Wg9Geom &wg) {
 
 template <int NTN, int NTC, int KC, bool BIAS, bool RAG>
 hipError_t run_wgrad9(hipStream_t st, int replicas, const ConvGeom &g, const Wg9Geom &wg, const WgradIO &io) {
-  constexpr int lds = 2 * (NTC * ((Patch<KC>::SLOTS + 15) / 16) + NTN * 8) * 1024;
+  const int lds = wg9_lds(g, {NTN, NTC});
   static const hipError_t lds_ok =
       hipFuncSetAttribute((const void *)k_wgrad9<NTN, NTC, KC, BIAS, RAG>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (lds_ok != hipSuccess) return lds_ok;
@@ -490,7 +499,7 @@ hipError_t run_wgrad9(hipStream_t st, int replicas, const ConvGeom &g, const Wg9
 
 template <int NTN, int KC, bool BIAS>
 hipError_t run_wgrad9_s2(hipStream_t st, int replicas, const ConvGeom &g, const Wg9Geom &wg, const WgradIO &io) {
-  constexpr int lds = 2 * ((Patch2<KC>::SLOTS + 15) / 16 + NTN * 4) * 1024;
+  const int lds = wg9_lds(g, {NTN, 1});
   static const hipError_t lds_ok =
       hipFuncSetAttribute((const void *)k_wgrad9_s2<NTN, KC, BIAS>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (lds_ok != hipSuccess) return lds_ok;
@@ -542,13 +551,15 @@ int wgrad9_plan(int replicas, const ConvGeom &g, int *chunk_out) {
   } else {
     const double product = 2.0 * wg.total_blocks * block_pixels(g) * g.N * (double)g.K * replicas / 1.45e9;  // us at what the chip sustains
     const double partial = 8.0 * g.N * (double)g.K * replicas / 8e6;                    // us per split
-    const int per_cu = t.n == 5 || (t.n == 4 && g.sp == 1) ? 1 : 2;                           // by LDS
+    // by LDS, and by two wavefronts of up to 256 registers per SIMD
+    const int waves_of = t.n * t.c, lds = wg9_lds(g, t), per_cu = 160 * 1024 / lds < 8 / waves_of ? 160 * 1024 / lds : 8 / waves_of;
     double least = 0.;
     want = 1;
     for (int k = 1; k <= per_cu; ++k) {
       const long long splits = k * kCus / tiles;
       if (splits < 1) continue;
-      const double us = product / ((double)splits * tiles / (k * kCus) * (k == 1 ? .92 : 1.)) + splits * partial;
+      const double busy = waves_of == 2 ? k / (double)per_cu : k == 1 ? .92 : 1.;  // two wavefronts: half of the SIMDs
+      const double us = product / ((double)splits * tiles / (k * kCus) * busy) + splits * partial;
       if (least == 0. || us < least) least = us, want = splits;
     }
   }

@@ -65,7 +65,7 @@ def test_weight_and_bias_gradient(gpu, case):
         assert ((both[a, wsize:] - d.sum(0)).abs() <= 2e-6 * d.abs().sum(0)).all()
 
 
-@pytest.mark.parametrize("case", [(1, 2, 28, 28, 64, 64), (1, 64, 7, 7, 64, 64), (1, 2, 15, 12, 32, 96)])
+@pytest.mark.parametrize("case", [(1, 2, 28, 28, 64, 64), (1, 64, 7, 7, 64, 64), (1, 2, 15, 12, 32, 96), (1, 3, 8, 8, 64, 64)])
 def test_infinities_at_the_edge_reach_no_other_tap(gpu, case):
     """A wavefront multiplies whole rows of 16 or 8 pixels: what an infinite pixel in the last column or row meets beyond the
     image may not turn a finite result into NaN."""
