@@ -16,3 +16,10 @@ def test_two_wavefronts_get_two_workgroups_per_compute_unit(case):
     would leave half of the SIMDs without work."""
     n, cin = case[0], case[4]
     assert splits(*case) * (cin // 32) * n > 256
+
+
+@pytest.mark.parametrize("case,one", [((4, 9, 8, 8, 224, 288), True), ((4, 8, 8, 8, 160, 256), True), ((1, 9, 8, 8, 288, 640), True),
+                                      ((3, 10, 8, 8, 32, 256), False), ((6, 12, 8, 8, 64, 160), False), ((5, 6, 28, 28, 384, 320), False)])
+def test_few_blocks_are_split_only_where_the_reduction_costs_less(case, one):
+    """Up to seven blocks of pixels: large gradients are written by one split, as they are; small ones are worth a reduction."""
+    assert (splits(*case) == 1) == one
