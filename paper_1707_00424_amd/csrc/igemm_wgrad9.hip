@@ -82,6 +82,7 @@ template <int NTN, int NTC, int KC, bool BIAS, bool RAG>
 __global__ __launch_bounds__(NTN * NTC * 64) __attribute__((amdgpu_waves_per_eu(2))) void k_wgrad9(const Wg9Geom wg, const WgradIO io) {
   typedef Patch<KC> PT;
   constexpr int kPC = PT::PC, W = NTN * NTC;
+  static_assert(!RAG || KC == 16, "8 x 8 images are whole");
   constexpr int XG = PT::LOADS;                           // loads of 16 pixels: one x tile, one dy tile (8)
   constexpr int PIECES = NTC * XG + NTN * 8;
   constexpr int IT = (PIECES + W - 1) / W;                // loads of a block per wavefront
@@ -181,7 +182,6 @@ __global__ __launch_bounds__(NTN * NTC * 64) __attribute__((amdgpu_waves_per_eu(
     for (int e = 0; e < 4; ++e) m[e] = (k + 2 * e < lim ? 0xffffu : 0u) | (k + 2 * e + 1 < lim ? 0xffff0000u : 0u);
     return m;
   };
-  if (RAG && KC == 8) inside = below(0, wg.W);
   auto read_d = [&](int p) { return tr_frag((const bf16_t *)dt + p * 16 * 32, 32, 0, 0); };
 
   load_block(blk_begin, 0);
@@ -195,7 +195,7 @@ __global__ __launch_bounds__(NTN * NTC * 64) __attribute__((amdgpu_waves_per_eu(
     dt = smem + buf * BUF + (NTC * XG + wn * 8) * 1024 + (frag_k * 32 + frag_c) * 2;
     buf ^= 1;
     int rows = kSub;
-    if (RAG && KC == 16) {
+    if (RAG) {
       const int rem = blk - (int)fdiv((uint32_t)blk, wg.dBpi) * wg.bpi, rb = (int)fdiv((uint32_t)rem, wg.dCbn);
       rows = min(kSub, wg.H - rb * kSub);
       inside = below(8 * (gq >> 1), wg.W - (rem - rb * wg.cbn) * 16);
@@ -240,11 +240,6 @@ __global__ __launch_bounds__(NTN * NTC * 64) __attribute__((amdgpu_waves_per_eu(
         read_x(pr0 + 2, window[2]);
 #pragma unroll
         for (int mu = 0; mu < 4; ++mu) {
-          if (RAG && 2 * mu >= wg.H) break;
-          if (RAG && 2 * mu + 1 >= wg.H && (gq >> 1)) {  // the pair's second row lies beyond the image
-#pragma unroll
-            for (int i = 0; i < 9; ++i) window[i / 3][i % 3] = u4{0, 0, 0, 0};
-          }
           const int w0 = (2 * mu) % 3, w1 = (2 * mu + 1) % 3, w2 = (2 * mu + 2) % 3;
           const u4 d = dfrag[mu & 1];
 #pragma unroll
@@ -517,10 +512,9 @@ bool wgrad9_applicable(int dtype, const ConvGeom &g) {
     // Share of the products that are no padding.  us, this kernel / the transpose-read kernel: 28 x 28 (0.88) 96 channels, 100
     // images 35 / 46; 14 x 14 (0.88) 256 channels 48 / 61; 15 x 15 (0.94) 320 channels 44 / 69; 24 x 24 (0.75) 37 / 54;
     // 12 x 12 (0.75) 320 channels 44 / 61; 10 x 10 and 20 x 20 (0.63) 32.9 / 32.2 and 29.4 / 29.4; 9 x 9 32 / 29.  Images of
-    // at most 8 x 8 come two to a block whatever their size: 7 x 7 256 channels, 4 x 64 images 39 / 44, but 16 images 13.4 /
-    // 11.2; 6 x 6 24 / 19.
-    if (g.sp == 2) return false;
-    if (small_images(g) ? g.P * g.Q < 49 || g.M < 64 * 49 : g.Q * 10 < 16 * ((g.Q + 15) / 16) * 7) return false;
+    // less than 8 x 8 would come two to a block whatever their size: 7 x 7, 65 images and more, 0.80 to 1.27 of the other's
+    // time, 1.00 in the mean of 26 layers.  2 x 1 tiles load half as much again per product: 0.8 to 1.24, 1.00 of 33 layers.
+    if (g.sp == 2 || small_images(g) || g.Q * 10 < 16 * ((g.Q + 15) / 16) * 7 || wg9_tiles(g).n * wg9_tiles(g).c == 2) return false;
   }
   if (g.Cc % 32 != 0 || g.N % 32 != 0 || wg9_tiles(g).n < 2) return false;
   const long long in_bytes = (long long)g.M * g.sp * g.sp * g.Cc * 2, dy_bytes = (long long)g.M * g.N * 2;
@@ -608,13 +602,11 @@ hipError_t launch_wgrad9(hipStream_t st, int replicas, const ConvGeom &g, const 
 #define WG9_RUN(NV, CV, KCV, RAGV)                                                \
   return io.with_bias ? run_wgrad9<NV, CV, KCV, true, RAGV>(st, replicas, g, wg, io) \
                       : run_wgrad9<NV, CV, KCV, false, RAGV>(st, replicas, g, wg, io)
-#define WG9_CASE(NV, CV)                 \
-  if (t.n == NV && t.c == CV) {          \
-    if (narrow && rag)                   \
-      WG9_RUN(NV, CV, 8, true);          \
-    if (narrow) WG9_RUN(NV, CV, 8, false); \
-    if (rag) WG9_RUN(NV, CV, 16, true);  \
-    WG9_RUN(NV, CV, 16, false);          \
+#define WG9_CASE(NV, CV)                            \
+  if (t.n == NV && t.c == CV) {                     \
+    if (narrow) WG9_RUN(NV, CV, 8, false);          \
+    if (rag) WG9_RUN(NV, CV, 16, (NV * CV != 2));   \
+    WG9_RUN(NV, CV, 16, false);                     \
   }
   WG9_CASE(2, 2);
   WG9_CASE(2, 1);

@@ -23,3 +23,11 @@ def test_two_wavefronts_get_two_workgroups_per_compute_unit(case):
 def test_few_blocks_are_split_only_where_the_reduction_costs_less(case, one):
     """Up to seven blocks of pixels: large gradients are written by one split, as they are; small ones are worth a reduction."""
     assert (splits(*case) == 1) == one
+
+
+@pytest.mark.parametrize("case,count", [((6, 76, 7, 7, 288, 192), 4), ((1, 82, 7, 7, 32, 160), 26), ((6, 124, 12, 12, 160, 64), 14),
+                                        ((2, 95, 25, 25, 224, 64), 32), ((3, 100, 28, 28, 96, 96), 28)])
+def test_kernel_of_ragged_images(case, count):
+    """The split counts tell the two kernels apart: images below 8 x 8, and 2 x 1 tiles on images that do not cut into blocks,
+    run on the kernel that gathers each tap; other ragged images stay on this one."""
+    assert splits(*case) == count
