@@ -552,7 +552,7 @@ int wgrad9_plan(int replicas, const ConvGeom &g, int *chunk_out) {
     for (int k = 1; k <= per_cu; ++k) {
       const long long splits = k * kCus / tiles;
       if (splits < 1) continue;
-      const double busy = waves_of == 2 ? k / (double)per_cu : k == 1 ? .92 : 1.;  // two wavefronts: half of the SIMDs
+      const double busy = waves_of == 2 && g.sp == 1 ? k / (double)per_cu : k == 1 ? .92 : 1.;  // two wavefronts: half of the SIMDs
       const double us = product / ((double)splits * tiles / (k * kCus) * busy) + splits * partial;
       if (least == 0. || us < least) least = us, want = splits;
     }

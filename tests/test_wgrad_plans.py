@@ -31,3 +31,8 @@ def test_kernel_of_ragged_images(case, count):
     """The split counts tell the two kernels apart: images below 8 x 8, and 2 x 1 tiles on images that do not cut into blocks,
     run on the kernel that gathers each tap; other ragged images stay on this one."""
     assert splits(*case) == count
+
+
+def test_two_wavefronts_at_stride_2_keep_one_workgroup():
+    """64 outputs at stride 2: the patch is the larger load there, and twice the workgroups were no gain."""
+    assert splits(3, 128, 32, 32, 64, 64, 2) * (64 // 32) * 3 <= 256
