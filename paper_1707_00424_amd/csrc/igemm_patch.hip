@@ -246,25 +246,25 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
     return __builtin_amdgcn_make_buffer_rsrc((void *)((const T *)p + rep * rs), 0, p ? (int)((uint32_t)a->g.M * (uint32_t)a->io.ldc * 2u) : 0,
                                              0x00020000);
   };
-  // The first of mask, residual and old output that there is (mask and old output: the second one is `old` below).  All of it
+  // The first of mask, residual and old output that there is (mask and old output: the second one takes its place).  All of it
   // is requested before the tile's first store: a load behind a store is waited for until the store is done (residual of 64
   // channels on 32 x 32: 56 us a layer instead of 42).  Lanes beyond the layer's channels read what follows: offsets of their
   // own would be computed in registers that loads of the tile before may still be on their way to, behind a wait for everything.
   constexpr bool kEarly = TN < 4;  // registers for it beside the last fragments
   u4 ex[TM][2][TN];
-  auto load_like = [&](CArgs *a, const void *p, long long rs, int rep, int tm, u4 (&to)[2][TN]) {
-    const __amdgpu_buffer_rsrc_t r = out_like(a, p, rs, rep);
+  auto load_like = [&](__amdgpu_buffer_rsrc_t r, int tm, int tn) {
 #pragma unroll
-    for (int tn = 0; tn < TN; ++tn)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) to[j][tn] = __builtin_amdgcn_raw_buffer_load_b128(r, row_off[tm][j] + tn * 64u, 0, 0);
+    for (int j = 0; j < 2; ++j) ex[tm][j][tn] = __builtin_amdgcn_raw_buffer_load_b128(r, row_off[tm][j] + tn * 64u, 0, 0);
   };
   auto load_extra = [&](CArgs *a, int rep, int tm) {
     const void *p = a->io.mask;
     long long rs = a->io.mask_rs;
     if (!p) p = a->io.resid, rs = a->io.resid_rs;
     if (!p && a->io.accumulate) p = a->io.out, rs = a->io.out_rs;
-    if (p) load_like(a, p, rs, rep, tm, ex[tm]);
+    if (!p) return;
+    const __amdgpu_buffer_rsrc_t r = out_like(a, p, rs, rep);
+#pragma unroll
+    for (int tn = 0; tn < TN; ++tn) load_like(r, tm, tn);
   };
   // stores eight channels of a pixel; NORM: and what the batch-norm + ReLU behind the layer makes of them
   auto put = [&](CArgs *a, int rep, const u4 &o, uint32_t at, int tn, __amdgpu_buffer_rsrc_t o_rsrc, __amdgpu_buffer_rsrc_t n_rsrc) {
@@ -290,7 +290,7 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
   };
   auto half_of = [](uint32_t w, int e) { return __uint_as_float(e ? w & 0xffff0000u : w << 16); };
   auto store_item = [&](CArgs *a, int rep, int tile, int bias_buf) {
-    const bool relu = a->io.relu, mask = a->io.mask, resid = a->io.resid, accumulate = a->io.accumulate;
+    const bool relu = a->io.relu, mask = !NORM && a->io.mask, resid = a->io.resid, accumulate = !NORM && a->io.accumulate;
     const __amdgpu_buffer_rsrc_t o_rsrc = out_like(a, a->io.out, a->io.out_rs, rep);
     auto bias_of = [&](int tn, int vg) { return *(const f4 *)(smem + lbias + bias_buf * 512 + (tn * 32 + vg * 8 + h * 4) * 4); };
     const bool two = mask && accumulate;
@@ -298,12 +298,50 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
     const __amdgpu_buffer_rsrc_t n_rsrc = out_like(a, NORM ? a->io.bn_out : nullptr, a->io.out_rs, rep);
 #pragma unroll
     for (int tm = kEarly ? TM : 0; tm < TM; ++tm) load_extra(a, rep, tm);
-    u4 old[kEarly ? TM : 1][2][TN];
-    if constexpr (kEarly) {
-      if (two) {
+    // a tile's sums with the bias, exchanged: [channels 0 .. 15 / 16 .. 31][first / second four of a vector][e]
+    auto exchanged = [&](int tm, int tn, uint32_t (&d)[2][2][4]) {
 #pragma unroll
-        for (int tm = 0; tm < TM; ++tm) load_like(a, a->io.out, a->io.out_rs, rep, tm, old[tm]);
+      for (int vg = 0; vg < 4; ++vg) {
+        const f4 b = bias_of(tn, vg);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) d[vg >> 1][vg & 1][e] = __float_as_uint(acc[tm][tn][4 * vg + e] + b[e]);
       }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        swap32(d[0][0][e], d[0][1][e]), swap32(d[1][0][e], d[1][1][e]);
+        swap16(d[0][0][e], d[1][0][e]), swap16(d[0][1][e], d[1][1][e]);
+      }
+    };
+    if (kEarly && two) {  // the masked sums stay where the sums were, the old output comes where the mask was
+#pragma unroll
+      for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn) {
+          uint32_t d[2][2][4];
+          exchanged(tm, tn, d);
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              float v = __uint_as_float(d[j][e >> 2][e & 3]);
+              if (relu) v = v > 0.f ? v : 0.f;
+              acc[tm][tn][j * 8 + e] = half_of(ex[tm][j][tn][e >> 1], e & 1) > 0.f ? v : 0.f;
+            }
+          load_like(o_rsrc, tm, tn);
+        }
+#pragma unroll
+      for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            u4 o;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+              o[k] = f32x2_to_bf16x2(acc[tm][tn][j * 8 + 2 * k] + half_of(ex[tm][j][tn][k], 0), acc[tm][tn][j * 8 + 2 * k + 1] + half_of(ex[tm][j][tn][k], 1));
+            put(a, rep, o, off(N, tm, j, tn), tn, o_rsrc, n_rsrc);
+          }
+      return;
     }
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm) {
@@ -350,23 +388,12 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
 #pragma unroll
         for (int tn = 0; tn < TN; ++tn) {
           u4 ov[2] = {ex[tm][0][tn], ex[tm][1][tn]};
-          if (two) {
+          if (!kEarly && two) {
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
-              ov[j] = kEarly ? old[kEarly ? tm : 0][j][tn] : __builtin_amdgcn_raw_buffer_load_b128(o_rsrc, row_off[tm][j] + tn * 64u, 0, 0);
+            for (int j = 0; j < 2; ++j) ov[j] = __builtin_amdgcn_raw_buffer_load_b128(o_rsrc, row_off[tm][j] + tn * 64u, 0, 0);
           }
-          uint32_t d[2][2][4];  // [channels 0 .. 15 / 16 .. 31][first / second four of a vector][e]
-#pragma unroll
-          for (int vg = 0; vg < 4; ++vg) {
-            const f4 b = bias_of(tn, vg);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) d[vg >> 1][vg & 1][e] = __float_as_uint(acc[tm][tn][4 * vg + e] + b[e]);
-          }
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            swap32(d[0][0][e], d[0][1][e]), swap32(d[1][0][e], d[1][1][e]);
-            swap16(d[0][0][e], d[1][0][e]), swap16(d[0][1][e], d[1][1][e]);
-          }
+          uint32_t d[2][2][4];
+          exchanged(tm, tn, d);
 #pragma unroll
           for (int j = 0; j < 2; ++j) {
             u4 o;
@@ -378,7 +405,7 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
                 v[e] = __uint_as_float(d[j][k >> 1][2 * (k & 1) + e]);
                 if (resid) v[e] += half_of(ex[tm][j][tn][k], e);
                 if (relu) v[e] = v[e] > 0.f ? v[e] : 0.f;
-                if (mask) v[e] = half_of(ex[tm][j][tn][k], e) > 0.f ? v[e] : 0.f;
+                if (!kEarly && mask) v[e] = half_of(ex[tm][j][tn][k], e) > 0.f ? v[e] : 0.f;
                 if (accumulate) v[e] += half_of(ov[j][k], e);
               }
               o[k] = f32x2_to_bf16x2(v[0], v[1]);
@@ -564,9 +591,8 @@ constexpr PatchShape kShapes[] = {
 // contractions with something to read in the epilogue run narrow: 32 -> 128 on 15 x 15, 240 images, residual, 22.4 us at 128
 // columns, 13.8 at 64.
 // False where the kernel through registers is the faster one: a residual, or an old output without a mask, is added in fp32
-// behind twice the exchanges, which a contraction of at most 18 steps (64 channels under 3 x 3) does not hide once workgroups
-// have more than one tile.  Of 73 such layers this kernel takes 0.82 to 1.22 times the other's time, the same in the mean; up
-// to 512 workgroups, and in longer contractions (96 channels, 3 x 128 images of 32 x 32: 82 us, the other 89), it is ahead.
+// behind twice the exchanges, which the 9 steps of a single chunk do not hide once workgroups have more than one tile (16 -> 256
+// channels on 35 x 30, 8 x 66 images 216 us, the other 164; 32 -> 32 on 40 x 40 47 / 42).  Longer ones are 0.8 to 1.13 of it.
 bool choose_shape(int replicas, const ConvGeom &g, const GemmIO &io, PatchShape &best, HaloGeom &hg_best) {
   HaloGeom geom[2];
   const bool ok[2] = {make_halo_geom(g, geom[0], true), make_halo_geom(g, geom[1], false)};
@@ -584,7 +610,7 @@ bool choose_shape(int replicas, const ConvGeom &g, const GemmIO &io, PatchShape 
     const float t = (s.first + (ranks - 1.f) * s.more) * steps + extras * s.extra * (steps <= 18 ? ranks : 1.f);
     if (least == 0.f || t < least) least = t, least_groups = groups, best = s, hg_best = hg;
   }
-  if (!io.bn_out && !io.mask && extras && steps <= 18 && least_groups > 512.) return false;
+  if (!io.bn_out && !io.mask && extras && steps <= 9 && least_groups > 512.) return false;
   return least > 0.f;
 }
 
@@ -595,7 +621,7 @@ bool conv_patch_applicable(int replicas, const ConvGeom &g, const GemmIO &io) {
   HaloGeom hg;
   return g.R == g.S && (g.S == 3 || (g.S == 5 && !io.bn_out)) && g.sp == 1 && g.dshift == 0 && g.Cc % 8 == 0 && io.vecA && io.vecB && g.N % 8 == 0 && io.ldc % 8 == 0 &&
          !io.stat && aligned_to(io.out, 16) && io.out_rs % 8 == 0 && aligned_to(io.resid, 16) && io.resid_rs % 8 == 0 &&
-         aligned_to(io.mask, 16) && io.mask_rs % 8 == 0 && !(io.resid && (io.mask || io.accumulate)) && aligned_to(io.bn_out, 16) && choose_shape(replicas, g, io, s, hg);
+         aligned_to(io.mask, 16) && io.mask_rs % 8 == 0 && !((io.resid || io.bn_out) && (io.mask || io.accumulate)) && aligned_to(io.bn_out, 16) && choose_shape(replicas, g, io, s, hg);
 }
 
 hipError_t launch_conv_patch(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io) {
