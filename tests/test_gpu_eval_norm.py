@@ -22,7 +22,10 @@ def _conv(torch, x, w, stride):
     return out.reshape(B, (H + stride - 1) // stride, (W + stride - 1) // stride, cout)
 
 
-@pytest.mark.parametrize("width,blocks,count", [(4, 1, 5), (4, 2, 70), (2, 2, 130)])
+@pytest.mark.parametrize("width,blocks,count", [
+    (4, 1, 5), (4, 2, 70), (2, 2, 130),
+    # column blocks of 96 (several tiles per workgroup), of 128, of 96 and 64, and of 128 and 64 channels
+    (6, 1, 250), (8, 1, 200), (10, 1, 140), (10, 2, 85)])
 def test_eval_with_running_statistics(gpu, width, blocks, count):
     torch, pb = gpu
     n = 2
