@@ -41,7 +41,6 @@ typedef short s4v __attribute__((ext_vector_type(4)));
 
 constexpr int kBlockPixels = 128;                // 8 rows x 16 columns, or two images of 8 x 8
 constexpr int kSub = 8;                          // contraction sub-steps (16 pixels) per block
-constexpr int kOutside = 1 << 30;                // a patch slot that belongs to no pixel
 // Patch of a block: one halo pixel around each image part.  Rows of whole 8 x 8 images have zeros on both sides: the one on the
 // right of a row is the one on the left of the next, and one more lies behind the last row.  That keeps 2 x 2 tiles at 80 KB,
 // two workgroups per compute unit (640 channels, 3 x 128 images, 300 workgroups: 196 us; 244 with columns of their own).
@@ -109,7 +108,9 @@ __global__ __launch_bounds__(NTN * NTC * 64) __attribute__((amdgpu_waves_per_eu(
       const int img = slot / (PT::PRI * kPC), rem = slot - img * (PT::PRI * kPC);
       const int prow = rem / kPC, pcol = rem - prow * kPC;
       rel[it] = (((img * wg.H + prow - 1) * wg.W + (pcol - 1)) * wg.Cin + (cg * NTC + t) * 32 + ch) * 2;
-      pos[it] = slot < PT::IMG * PT::PRI * kPC ? prow | pcol << 8 | img << 16 : kOutside;
+      pos[it] = prow | pcol << 8 | img << 16;
+      // a slot that belongs to no pixel: beyond the buffer from wherever a block begins
+      if (slot >= PT::IMG * PT::PRI * kPC) rel[it] = (int)kOobOffset, pos[it] = 0;
     } else {
       const int d = q - NTC * XG, t = d >> 3, p = (d & 7) * 16 + px;  // pixel of the block
       const int img = p / (kBlockPixels / PT::IMG), r = p - img * (kBlockPixels / PT::IMG), row = r / KC, col = r - row * KC;
@@ -135,7 +136,7 @@ __global__ __launch_bounds__(NTN * NTC * 64) __attribute__((amdgpu_waves_per_eu(
       const uint32_t dst = lds0 + (uint32_t)(buf * BUF + q * 1024);
       if (q < NTC * XG) {
         const int row = row0 + (pos[it] & 0xff) - 1, col = col0 + (pos[it] >> 8 & 0xff) - 1;
-        const bool ok = !(pos[it] & kOutside) && (unsigned)row < (unsigned)wg.H && (unsigned)col < (unsigned)wg.W && b + (pos[it] >> 16) < wg.B;
+        const bool ok = (unsigned)row < (unsigned)wg.H && (unsigned)col < (unsigned)wg.W && b + (pos[it] >> 16) < wg.B;
         dma16(dst, x_rsrc, ok ? (uint32_t)(pix * wg.Cin * 2 + rel[it]) : kOobOffset, 0);
       } else {
         // an image beyond the batch (odd batch, second 8 x 8 image of the last block) lies beyond the buffer: zeros
