@@ -39,8 +39,8 @@ struct ConvGeom {
   // (row-major over the blocks), parity class, position (i, j) of the 8 x 8 grid inside the block, i.e.
   // pixel (16*bi + 2*i + class/2, 16*bj + 2*j + class%2): a 256-row tile is one block, 64 rows per class.
   int pblk;
-  // Backward-weight only: wavefronts a launch of the nine-tap kernel should put in flight (0 = one per SIMD of
-  // the chip); the contraction is split over workgroups accordingly.
+  // Backward-weight only: wavefronts a launch of the nine-tap kernel should put in flight (0 = one or two workgroups per
+  // compute unit by the kernel's own estimate); the contraction is split over workgroups accordingly.
   int leaf_waves;
 };
 
@@ -157,7 +157,7 @@ hipError_t launch_conv_smallk(hipStream_t st, int dtype, bool out_f32, int repli
 int conv_smallk_stat_splits(const ConvGeom &g, bool out_f32);
 bool wgrad_smallk_applicable(int dtype, const ConvGeom &g);
 hipError_t launch_wgrad_smallk(hipStream_t st, int replicas, const ConvGeom &g, const WgradIO &io);
-// Stride-1 'same' 3x3 backward-weight with the patch staged in LDS and nine taps per wavefront (igemm_wgrad9.hip).
+// 'Same' 3x3 backward-weight, stride 1 and 2, with the patch staged in LDS and nine taps per wavefront (igemm_wgrad9.hip).
 bool wgrad9_applicable(int dtype, const ConvGeom &g);
 int wgrad9_plan(int replicas, const ConvGeom &g, int *chunk_out);
 hipError_t launch_wgrad9(hipStream_t st, int replicas, const ConvGeom &g, const WgradIO &io);

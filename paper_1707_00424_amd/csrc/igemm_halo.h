@@ -29,6 +29,6 @@ __device__ __forceinline__ bool halo_block(const HaloGeom &hg, int &tile, int &c
 
 // The tiles of a layer, 256 pixels or (half, stride 2) 128; false where they would fill less than three quarters (igemm_halo.hip).
 bool make_halo_geom(const ConvGeom &g, HaloGeom &hg, bool half);
-// Stride-1 3x3 layers with operands loaded straight into LDS (igemm_patch.hip).
+// Stride-1 3x3 and 5x5 layers with operands loaded straight into LDS (igemm_patch.hip).
 bool conv_patch_applicable(int replicas, const ConvGeom &g, const GemmIO &io);
 hipError_t launch_conv_patch(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io);

@@ -6,7 +6,7 @@
 // work that the two workgroups of a compute unit share; 7 400 went by until the first patch had come from memory and 4 000
 // in the epilogue.  So
 //   * operands go from memory to LDS directly (buffer loads with the LDS bit; lanes outside the image or the layer write
-//     zeros): no staging registers, no LDS stores, 181 registers instead of 224 for 96 columns;
+//     zeros): no staging registers, no LDS stores;
 //   * a workgroup walks several tiles, and the patch, the first weight tiles and the bias of the next one are on their way
 //     while the last channels of the current one are multiplied: only the first tile waits for memory;
 //   * the epilogue exchanges lanes in registers (permlane swaps) until each lane holds eight channels of a pixel and a
@@ -19,7 +19,9 @@
 //
 // LDS: patch pixels and weight rows are 64 bytes (32 channels) without padding, as the direct loads write them; the four
 // 16-byte vectors of pixel or row i lie at vector ^ (i / 4 % 4), which puts any sixteen consecutive pixels on different
-// banks (no conflicts at 32 x 32; the vector a lane loads is chosen accordingly).  Two patches, a ring of D + 1 weight tiles.
+// banks (the vector a lane loads is chosen accordingly).  Lanes that go on in the next row of an image skip its halo pixels and
+// meet others: SQ_LDS_BANK_CONFLICT is 16 to 20 % of SQ_LDS_IDX_ACTIVE over layers of 32 x 32 and 16 x 16, 39 % on 8 x 8.  Two
+// patches, a ring of D + 1 weight tiles.
 //
 // Step t = (channel chunk, tap): 2 x TM x TN products of 16 channels per wavefront.  While its first half is multiplied the
 // weight tile of step t + D and a piece of the next chunk's patch are requested and the second half is read from LDS; then

@@ -531,8 +531,8 @@ int wgrad9_plan(int replicas, const ConvGeom &g, int *chunk_out) {
   const long long tiles = (long long)(g.Cc / 32 / t.c) * (g.N / 32 / t.n) * replicas;
   // One or two workgroups per compute unit, never a few stragglers in another round, whichever ends sooner: the second
   // fills gaps of the first (8 %), and doubles the partial sums, which are written and read once more.  us with 256 / 512
-  // workgroups at 3 x 128 images: 64 channels on 32 x 32 39.6 / 44.2, 128 on 16 x 16 39.5 / 43.9, 256 on 8 x 8 40 / 51, 320 on
-  // 16 x 16 173 / 160.  A network that has its leaves run beside a longer chain asks for fewer.
+  // workgroups at 3 x 128 images: 64 channels on 32 x 32 39.6 / 44.2, 128 on 16 x 16 39.5 / 43.9, 320 on 16 x 16 173 /
+  // 160.  A network that has its leaves run beside a longer chain asks for fewer.
   // PARLE_WG9_WAVES: wavefronts in flight instead.
   static const int waves = [] {
     const char *e = getenv("PARLE_WG9_WAVES");
