@@ -92,7 +92,7 @@ parle_status parle_k_conv_backward_data(void *hip_stream, const parle_conv_desc 
   }
   const ConvGeom g = conv_bwd_geom(c);
   GemmIO io{};
-  io.w_kn = fc_f32_applicable(desc->dtype, desc->n, g);
+  io.w_kn = dgrad_reads_weights(desc->dtype, desc->n, g, wsize % vw == 0);
   if (!io.w_kn && launch_weight_transpose(st, desc->dtype, desc->n, c.Cout, c.R * c.R, c.Cin, w, wsize, wt_scratch, wsize) !=
                       hipSuccess)
     return PARLE_EHIP;

@@ -59,7 +59,7 @@ struct GemmIO {
   const void *mask;   // [M][ldc]: result multiplied by (mask > 0), or NULL
   long long mask_rs;
   int relu, accumulate;
-  int w_kn;           // `w` lies as [K][N] (a layer's weights read for its input gradient); only launch_fc_f32 takes it
+  int w_kn;           // `w`: a layer's weights as they lie, read for its input gradient; only for layers that dgrad_reads_weights names
   int vecA, vecB;     // 16-byte loads allowed for the gathered operand / the weight matrix
   long long in_bytes; // bytes of one replica's gathered tensor (range of the buffer loads)
   // The gathered tensor lies in memory as fp32 although the layer computes in bf16 (the caller's images in front of a
@@ -194,5 +194,11 @@ hipError_t launch_wgrad_small_f32(hipStream_t st, int replicas, const ConvGeom &
 // Backward-data of stride-2 3x3 pad-1 layers, four parity classes per workgroup (igemm_dgrad2.hip).
 bool dgrad_s2_applicable(int dtype, const ConvGeom &g, const GemmIO &io, bool out_f32);
 hipError_t launch_dgrad_s2(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io);
+// ... and with patch and weights loaded straight into LDS, on any image size; reads the weights as they lie (igemm_dgrad_patch.hip).
+bool dgrad_patch_applicable(int dtype, const ConvGeom &g, bool weights_aligned);
+hipError_t launch_dgrad_patch(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io);
+// True where backward-data (g: its geometry) reads the layer's weights as they lie instead of turned round (GemmIO::w_kn).
+// `weights_aligned`: every replica's weights start on 16 bytes.
+bool dgrad_reads_weights(int dtype, int replicas, const ConvGeom &g, bool weights_aligned);
 // Rows of M per split so that the launch has enough workgroups; returns the split count.
 int wgrad_plan(int dtype, int replicas, const ConvGeom &g, int *chunk_out);

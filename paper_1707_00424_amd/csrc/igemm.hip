@@ -402,12 +402,20 @@ int bf16_ntile(int n) {
 
 }  // namespace
 
+bool dgrad_reads_weights(int dtype, int replicas, const ConvGeom &g, bool weights_aligned) {
+  return fc_f32_applicable(dtype, replicas, g) || dgrad_patch_applicable(dtype, g, weights_aligned);
+}
+
 hipError_t launch_igemm(hipStream_t st, int dtype, bool out_f32, int replicas, const ConvGeom &g, const GemmIO &io_in,
                         int *stat_splits) {
   if (g.M < 1 || g.N < 1 || g.K < 1 || replicas < 1 || replicas > 65535) return hipErrorInvalidValue;
   if (stat_splits) *stat_splits = 0;
-  if (io_in.w_kn && !fc_f32_applicable(dtype, replicas, g)) return hipErrorInvalidValue;
   if (fc_f32_applicable(dtype, replicas, g)) return launch_fc_f32(st, replicas, g, io_in);
+  if (io_in.w_kn) {
+    const bool aligned = aligned_to(io_in.w, 16) && io_in.w_rs % 8 == 0 && aligned_to(io_in.in, 16) && aligned_to(io_in.out, 16) && aligned_to(io_in.mask, 16);
+    if (!dgrad_patch_applicable(dtype, g, aligned) || out_f32 || io_in.resid || io_in.bias || io_in.relu || io_in.ldc != g.N) return hipErrorInvalidValue;
+    return launch_dgrad_patch(st, replicas, g, io_in);
+  }
   if (io_in.bn_out && !conv_takes_bn(dtype, replicas, g, io_in, out_f32)) return hipErrorInvalidValue;
   if (io_in.stat && stat_splits) {
     // the same order of choices as below, for the kernels whose epilogue can take the sums

@@ -44,7 +44,7 @@ struct Op {
   int dx_after = -1;       // index of the shortcut op whose input gradient this op's accumulates onto
   int64_t wt_off = -1;     // transposed weights (bytes)
   int64_t col_off = -1;    // per-tap products of the two-pass backward-data (bytes), -1 = direct kernel
-  bool w_as_is = false;    // backward-data by the fully connected kernel, which reads the weights as they lie
+  bool w_as_is = false;    // backward-data reads the weights as they lie (dgrad_reads_weights)
   bool win = false;        // backward-data through per-tap products held in LDS, one image per workgroup
   // pool
   bool pool_relu_mask = false;
@@ -353,8 +353,8 @@ bool build_plan(Net &N, std::string &err) {
       const int64_t wsize = (int64_t)op.Cout * op.R * op.R * op.Cin;
       if (op.need_dx) {
         N.want_grad(op.in);
-        op.w_as_is = fc_f32_applicable(
-            N.dtype, N.n, conv_bwd_geom(ConvShape{N.B, op.Hin, op.Win, op.Cin, op.Cout, op.R, op.stride, op.pad}));
+        op.w_as_is = dgrad_reads_weights(N.dtype, N.n, conv_bwd_geom(ConvShape{N.B, op.Hin, op.Win, op.Cin, op.Cout, op.R, op.stride, op.pad}),
+                                         N.segs[op.wseg].offset % 8 == 0 && N.n_pad % 8 == 0);
         if (!op.head && !op.w_as_is) op.wt_off = N.alloc((int64_t)N.n * wsize * N.esize);  // the head kernel reads the weights as they lie
         // few input channels under a wide window (LeNet's second convolution: 20 channels, 25 taps): the direct kernel
         // fills 20 of 32 output columns and visits every input pixel; as dy x W (500 columns, contraction 50) plus a
