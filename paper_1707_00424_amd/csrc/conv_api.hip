@@ -92,18 +92,20 @@ parle_status parle_k_conv_backward_data(void *hip_stream, const parle_conv_desc 
   }
   const ConvGeom g = conv_bwd_geom(c);
   GemmIO io{};
-  io.w_kn = dgrad_reads_weights(desc->dtype, desc->n, g, wsize % vw == 0);
-  if (!io.w_kn && launch_weight_transpose(st, desc->dtype, desc->n, c.Cout, c.R * c.R, c.Cin, w, wsize, wt_scratch, wsize) !=
-                      hipSuccess)
-    return PARLE_EHIP;
   io.in = dy, io.in_rs = (long long)c.B * c.Ho() * c.Wo() * c.Cout;
-  io.w = io.w_kn ? w : wt_scratch, io.w_rs = wsize;
+  io.w = w, io.w_rs = wsize;
   io.out = dx, io.out_rs = (long long)g.M * g.N, io.ldc = g.N;
   io.mask = relu_mask, io.mask_rs = io.out_rs;
   io.accumulate = accumulate;
   io.vecA = (c.Cout % vw == 0) && (io.in_rs % vw == 0);
   io.vecB = (g.K % vw == 0) && (wsize % vw == 0);
   io.in_bytes = io.in_rs * es;
+  io.w_kn = dgrad_reads_weights(desc->dtype, desc->n, g, io);
+  if (!io.w_kn) {
+    io.w = wt_scratch;
+    if (launch_weight_transpose(st, desc->dtype, desc->n, c.Cout, c.R * c.R, c.Cin, w, wsize, wt_scratch, wsize) != hipSuccess)
+      return PARLE_EHIP;
+  }
   return launch_igemm(st, desc->dtype, false, desc->n, g, io) == hipSuccess ? PARLE_OK : PARLE_EHIP;
 }
 

@@ -194,11 +194,11 @@ hipError_t launch_wgrad_small_f32(hipStream_t st, int replicas, const ConvGeom &
 // Backward-data of stride-2 3x3 pad-1 layers, four parity classes per workgroup (igemm_dgrad2.hip).
 bool dgrad_s2_applicable(int dtype, const ConvGeom &g, const GemmIO &io, bool out_f32);
 hipError_t launch_dgrad_s2(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io);
-// ... and with patch and weights loaded straight into LDS, on any image size; reads the weights as they lie (igemm_dgrad_patch.hip).
-bool dgrad_patch_applicable(int dtype, const ConvGeom &g, bool weights_aligned);
+// ... and with patch and weights loaded straight into LDS, on any image size, weights as they lie (igemm_dgrad_patch.hip).
+bool dgrad_patch_applicable(int dtype, const ConvGeom &g, const GemmIO &io);
 hipError_t launch_dgrad_patch(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io);
-// True where backward-data (g: its geometry) reads the layer's weights as they lie instead of turned round (GemmIO::w_kn).
-// `weights_aligned`: every replica's weights start on 16 bytes.
-bool dgrad_reads_weights(int dtype, int replicas, const ConvGeom &g, bool weights_aligned);
+// True where backward-data reads the layer's weights as they lie instead of turned round (GemmIO::w_kn).  io: of the launch,
+// but for w_kn; io.w, w_rs and vecB of the weights as they lie.
+bool dgrad_reads_weights(int dtype, int replicas, const ConvGeom &g, const GemmIO &io);
 // Rows of M per split so that the launch has enough workgroups; returns the split count.
 int wgrad_plan(int dtype, int replicas, const ConvGeom &g, int *chunk_out);

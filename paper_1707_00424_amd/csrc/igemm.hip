@@ -15,6 +15,7 @@
 #include <stdlib.h>
 
 #include "igemm_dev.h"
+#include "igemm_halo.h"
 
 namespace {
 
@@ -402,8 +403,10 @@ int bf16_ntile(int n) {
 
 }  // namespace
 
-bool dgrad_reads_weights(int dtype, int replicas, const ConvGeom &g, bool weights_aligned) {
-  return fc_f32_applicable(dtype, replicas, g) || dgrad_patch_applicable(dtype, g, weights_aligned);
+bool dgrad_reads_weights(int dtype, int replicas, const ConvGeom &g, const GemmIO &io) {
+  if (fc_f32_applicable(dtype, replicas, g) || dgrad_patch_applicable(dtype, g, io)) return true;
+  return g.sr == -1 && !conv_smallk_applicable(dtype, g, io) && conv_halo_applicable(dtype, replicas, g, io, false) &&
+         conv_patch_applicable(replicas, g, io) && aligned_to(io.w, 16) && io.w_rs % 8 == 0 && io.ldc == g.N && !io.resid && !io.bias && !io.relu;
 }
 
 hipError_t launch_igemm(hipStream_t st, int dtype, bool out_f32, int replicas, const ConvGeom &g, const GemmIO &io_in,
@@ -412,9 +415,8 @@ hipError_t launch_igemm(hipStream_t st, int dtype, bool out_f32, int replicas, c
   if (stat_splits) *stat_splits = 0;
   if (fc_f32_applicable(dtype, replicas, g)) return launch_fc_f32(st, replicas, g, io_in);
   if (io_in.w_kn) {
-    const bool aligned = aligned_to(io_in.w, 16) && io_in.w_rs % 8 == 0 && aligned_to(io_in.in, 16) && aligned_to(io_in.out, 16) && aligned_to(io_in.mask, 16);
-    if (!dgrad_patch_applicable(dtype, g, aligned) || out_f32 || io_in.resid || io_in.bias || io_in.relu || io_in.ldc != g.N) return hipErrorInvalidValue;
-    return launch_dgrad_patch(st, replicas, g, io_in);
+    if (out_f32 || !dgrad_reads_weights(dtype, replicas, g, io_in)) return hipErrorInvalidValue;
+    return dgrad_patch_applicable(dtype, g, io_in) ? launch_dgrad_patch(st, replicas, g, io_in) : launch_conv_patch(st, replicas, g, io_in);
   }
   if (io_in.bn_out && !conv_takes_bn(dtype, replicas, g, io_in, out_f32)) return hipErrorInvalidValue;
   if (io_in.stat && stat_splits) {

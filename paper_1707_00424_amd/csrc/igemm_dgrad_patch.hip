@@ -402,11 +402,13 @@ hipError_t run_dgrad_patch(hipStream_t st, int replicas, const ConvGeom &g, cons
 }  // namespace
 
 // g: backward-data geometry of a stride-2 layer; io.w: its weights as they lie.
-bool dgrad_patch_applicable(int dtype, const ConvGeom &g, bool weights_aligned) {
+bool dgrad_patch_applicable(int dtype, const ConvGeom &g, const GemmIO &io) {
   PosGeom pg;
   return dtype == 1 && g.dshift == 1 && g.R == 3 && g.S == 3 && g.off == 1 && g.sr == -1 && g.sp == 1 &&
-         g.Hin == (g.P + 1) / 2 && g.Win == (g.Q + 1) / 2 && g.Cc % 8 == 0 && g.N % 8 == 0 && weights_aligned &&
-         (long long)g.M * g.N * 2 < (1LL << 31) && (long long)g.Hin * g.Win * g.Cc * (g.M / (g.P * g.Q)) * 2 < (1LL << 31) &&
+         g.Hin == (g.P + 1) / 2 && g.Win == (g.Q + 1) / 2 && g.Cc % 8 == 0 && g.N % 8 == 0 && io.vecA && io.vecB && aligned_to(io.w, 16) &&
+         io.w_rs % 8 == 0 && aligned_to(io.out, 16) && io.out_rs % 8 == 0 && aligned_to(io.mask, 16) && io.mask_rs % 8 == 0 && io.ldc == g.N &&
+         !io.resid && !io.bias && !io.relu && !io.stat && !io.bn_out &&
+         (long long)g.M * g.N * 2 < (1LL << 31) && io.in_bytes > 0 && io.in_bytes < (1LL << 31) &&
          (long long)g.N * g.K * 2 < (1LL << 31) && make_pos_geom(g, pg);
 }
 

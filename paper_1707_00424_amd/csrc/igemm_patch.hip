@@ -15,6 +15,10 @@
 // of one round, the first patch.  us per pass, before -> now: 96 -> 96 32 x 32, 3 x 128 images 93 -> 79; 320 -> 320
 // 16 x 16 195 -> 161; 64 -> 64 32 x 32 47 -> 43; 96 -> 96 28 x 28, 100 images 31 -> 23; 256 -> 256 8 x 8 45 -> 35.
 // 5 x 5: 128 -> 128 on 16 x 16, 64 images 41 -> 31; 32 -> 96 28 x 28, 100 images 42 -> 30; 64 -> 64 32 x 32, 128 images 52 -> 52.
+// Backward-data reads the layer's weights as they lie, [Cout][k][k][Cin] (KN): a direct load puts rows of 32 input channels into
+// LDS and the transposing read turns them round, in place of a pass over the weights in front of the kernel.  us, with that pass
+// -> without: 96 -> 96 32 x 32, 3 x 128 images 78 -> 74; 320 -> 320 16 x 16 156 -> 146; 256 -> 256 8 x 8 41 -> 33; 96 -> 96
+// 28 x 28, 100 images 25.5 -> 22.4; 3 x 16 images of 128 -> 128 on 16 x 16 16.4 -> 11.2.
 // (Non-temporal stores took 2 to 5 % off the layer, and put as much on the batch-norm that reads its output next.)
 //
 // LDS: patch pixels and weight rows are 64 bytes (32 channels) without padding, as the direct loads write them; the four
@@ -34,6 +38,8 @@
 namespace {
 
 using namespace igemm_dev;
+typedef short s4v __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s4v lds_s4v;
 
 constexpr uint32_t kOob = 0x80000000u;
 constexpr int kPix = 64;  // bytes of a patch pixel or weight row in LDS: 32 channels
@@ -69,8 +75,8 @@ __device__ __forceinline__ uint32_t fdivc(uint32_t n, __attribute__((address_spa
 }
 
 // S: window side; TM: 32-pixel tiles per wavefront (four wavefronts: 128 or 256 pixels); TN: 32-channel tiles; D: weight tiles in flight;
-// LAST: this workgroup's column blocks are args->last; NORM: io.bn_out.
-template <int S, int TM, int TN, int D, bool LAST, bool NORM>
+// LAST: this workgroup's column blocks are args->last; NORM: io.bn_out; KN: io.w_kn.
+template <int S, int TM, int TN, int D, bool LAST, bool NORM, bool KN>
 __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int first) {
   typedef bf16_t T;
   constexpr int BN = TN * 32, NB = D + 1, RS = S * S;
@@ -87,7 +93,14 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
   const int pbytes = (args->hg.slots + 15) / 16 * 16 * kPix;
   const int wring = 2 * pbytes, lbias = wring + NB * TB, ldump = lbias + 1024, lnorm = ldump + 1024;
   const int Cc = args->g.Cc, chunks = (Cc + 31) >> 5;
-  const int b_l = (lane & 31) * kPix + ((h ^ ((lane >> 2) & 3)) << 4);
+  // KN: a weight row of LDS is an output channel of the layer (contraction) with 32 of its input channels (columns), no vectors
+  // exchanged; a transposing read has lane l of sixteen address row l / 4, columns 4 (l % 4) .. + 3 of a 4 x 16 block and gives
+  // it column l.  Four rows are all banks.
+  const int b_l = KN ? (8 * h + ((lane & 15) >> 2)) * kPix + ((lane >> 4) & 1) * 32 + (lane & 3) * 8
+                     : (lane & 31) * kPix + ((h ^ ((lane >> 2) & 3)) << 4);
+  // bytes from one tap, and from one chunk of channels, to the next
+  const uint32_t w_tap = (uint32_t)(KN ? args->g.N : Cc) * 2u, w_chunk = KN ? 32u * RS * w_tap : 64u;
+  const int w_live = KN ? (wave & 1) * 16 + (lane >> 2) : cv * 8;  // this lane loads weights of channel w_live of a chunk
   int n0;  // all items of a workgroup have the same columns
 
   // the item `idx`, if there is one
@@ -195,6 +208,11 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
   // tap (r, c) of a forward pass lies r rows and c columns into the patch, of a backward-data pass S - 1 - r and S - 1 - c
   const int pix_step = args->g.sr > 0 ? kPix : -kPix, row_step = args->hg.HC * pix_step;
   const int tap0 = args->g.sr > 0 ? 0 : (S - 1) * (args->hg.HC + 1) * kPix;
+  auto read_kn = [&](const char *p) {
+    const s4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4v *)p);
+    const s4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4v *)(p + 4 * kPix));
+    return __builtin_bit_cast(u4, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  };
   int a_ad[TM];
   u4 fa_a[TM], fa_b[TN], fb_a[TM], fb_b[TN];
   auto read0 = [&](int shift, int ring) {
@@ -205,13 +223,14 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
       fa_a[tm] = *(const u4 *)(smem + a_ad[tm]);
     }
 #pragma unroll
-    for (int tn = 0; tn < TN; ++tn) fa_b[tn] = *(const u4 *)(smem + (wring + ring + b_l) + tn * 32 * kPix);
+    for (int tn = 0; tn < TN; ++tn) fa_b[tn] = KN ? read_kn(smem + (wring + ring + b_l) + tn * 32 * kPix) : *(const u4 *)(smem + (wring + ring + b_l) + tn * 32 * kPix);
   };
   auto read1 = [&](int ring) {
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm) fb_a[tm] = *(const u4 *)(smem + (a_ad[tm] ^ 32));
 #pragma unroll
-    for (int tn = 0; tn < TN; ++tn) fb_b[tn] = *(const u4 *)(smem + (wring + ring + (b_l ^ 32)) + tn * 32 * kPix);
+    for (int tn = 0; tn < TN; ++tn)
+      fb_b[tn] = KN ? read_kn(smem + (wring + ring + b_l) + (tn * 32 + 16) * kPix) : *(const u4 *)(smem + (wring + ring + (b_l ^ 32)) + tn * 32 * kPix);
   };
   auto mma_sub = [&](const u4 (&af)[TM], const u4 (&bf)[TN]) {
 #pragma unroll
@@ -220,12 +239,20 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
       for (int tn = 0; tn < TN; ++tn) mma<T>(bf[tn], af[tm], acc[tm][tn]);
   };
   auto interleave = [&]() {
+    if constexpr (KN) {
 #pragma unroll
-    for (int i = 0; i < TM + TN; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      for (int i = 0; i < TM * TN; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < TM + TN; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      }
+      __builtin_amdgcn_sched_group_barrier(0x008, TM * TN - TM - TN, 0);
     }
-    __builtin_amdgcn_sched_group_barrier(0x008, TM * TN - TM - TN, 0);
   };
 
   // Outputs: after the exchanges lane l holds channels 16 * (l / 16 % 2) + 8 * (l / 32) .. + 7 of pixel l % 16 (+ 16) of a tile
@@ -425,8 +452,13 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
   b_rsrc = buffer_desc((const void *)weights_at(args, rep), (uint32_t)((long long)args->g.N * args->g.K * sizeof(T)));
 #pragma unroll
   for (int i = 0; i < WI; ++i) {
-    const int nrow = n0 + (wave + 4 * i) * 16 + (lane >> 2);
-    b_off[i] = nrow < args->g.N ? (uint32_t)((nrow * args->g.K + cv * 8) * 2) : kOob;
+    if (KN) {
+      const int n = n0 + ((wave + 4 * i) >> 1) * 32 + (lane & 3) * 8;
+      b_off[i] = n < args->g.N ? (uint32_t)w_live * RS * w_tap + (uint32_t)n * 2u : kOob;
+    } else {
+      const int nrow = n0 + (wave + 4 * i) * 16 + (lane >> 2);
+      b_off[i] = nrow < args->g.N ? (uint32_t)((nrow * args->g.K + cv * 8) * 2) : kOob;
+    }
   }
   {
     const bool live = cv * 8 < Cc;
@@ -434,7 +466,7 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
 #pragma unroll
     for (int it = 0; it < H_IT; ++it) load_piece(it, 0, 0, live);
 #pragma unroll
-    for (int i = 0; i < D; ++i) load_w(i * TB, (uint32_t)(i * Cc * 2), live);
+    for (int i = 0; i < D; ++i) load_w(i * TB, (uint32_t)i * w_tap, w_live < Cc);
   }
   if (NORM && tid < BN) {
     const int n = min(n0 + tid, args->g.N - 1);
@@ -454,7 +486,7 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
     bool more = false;
     for (int c = 0; c < chunks; ++c) {
       const bool last = c + 1 == chunks;
-      const bool live = c * 32 + cv * 8 < Cc;
+      const bool live = c * 32 + w_live < Cc;
       if (last) {
         CArgs *a = fresh(args);
         idx += LAST ? a->last.groups : a->wide.groups;
@@ -468,9 +500,9 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
         }
       }
       const int c1 = last ? 0 : c + 1;
-      const bool live1 = c1 * 32 + cv * 8 < Cc;
+      const bool live1 = c1 * 32 + cv * 8 < Cc, w_live1 = c1 * 32 + w_live < Cc;
       int shift = tap0 + pbuf * pbytes;                 // of the tap after this one
-      uint32_t soff = (uint32_t)((D * Cc + c * 32) * 2);  // of the weight tile that is requested
+      uint32_t soff = D * w_tap + (uint32_t)c * w_chunk;  // of the weight tile that is requested
 #pragma unroll
       for (int tap = 0; tap < RS; ++tap) {
         const int prev = ring == 0 ? (NB - 1) * TB : ring - TB, next = ring == (NB - 1) * TB ? 0 : ring + TB;
@@ -480,11 +512,11 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
         if (tap == 1 && last && more) load_bias(fresh(args), rep1, bbuf ^ 1);
         if (tap < H_IT) load_piece(tap, pbuf ^ 1, (uint32_t)(c1 * 64), live1);
         if (tap + D == RS) {
-          soff = (uint32_t)(c1 * 64);
+          soff = (uint32_t)c1 * w_chunk;
           if (last && more) set_weights(bn_base);
         }
-        load_w(prev, soff, tap + D >= RS ? live1 : live);
-        soff += (uint32_t)(Cc * 2);
+        load_w(prev, soff, tap + D >= RS ? w_live1 : live);
+        soff += w_tap;
         if (tap + D == RS && last) {
           // behind the weight tile that the last wait is for
           CArgs *a = fresh(args);
@@ -516,18 +548,18 @@ __device__ __forceinline__ void conv_patch_body(CArgs *args, char *smem, int fir
   wait_loads<0>();  // nothing may land in LDS after the workgroup has ended
 }
 
-template <int S, int TM, int TN, int TL, int D, bool NORM>
+template <int S, int TM, int TN, int TL, int D, bool NORM, bool KN>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TM == 1 ? 3 : 2))) void k_conv_patch(const PatchArgs) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   CArgs *args = (CArgs *)__builtin_amdgcn_kernarg_segment_ptr();
   const int groups = args->wide.groups;
   if ((int)blockIdx.x < groups)
-    conv_patch_body<S, TM, TN, D, false, NORM>(args, smem, blockIdx.x);
+    conv_patch_body<S, TM, TN, D, false, NORM, KN>(args, smem, blockIdx.x);
   else if (TL != TN)
-    conv_patch_body<S, TM, TL, D, true, NORM>(args, smem, blockIdx.x - groups);
+    conv_patch_body<S, TM, TL, D, true, NORM, KN>(args, smem, blockIdx.x - groups);
 }
 
-template <int S, int TM, int TN, int TL, int D, bool NORM>
+template <int S, int TM, int TN, int TL, int D, bool NORM, bool KN>
 hipError_t run_patch_as(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io, HaloGeom hg) {
   constexpr int kCus = 256, kLdsOfCu = 160 * 1024;
   const int lds = 2 * ((hg.slots + 15) / 16 * 16) * kPix + (D + 1) * TN * 32 * kPix + 2048 + (NORM ? TN * 32 * 16 : 0);
@@ -562,17 +594,20 @@ hipError_t run_patch_as(hipStream_t st, int replicas, const ConvGeom &g, const G
     }
   }
   static const hipError_t lds_ok =
-      hipFuncSetAttribute((const void *)k_conv_patch<S, TM, TN, TL, D, NORM>, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsOfCu);
+      hipFuncSetAttribute((const void *)k_conv_patch<S, TM, TN, TL, D, NORM, KN>, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsOfCu);
   if (lds_ok != hipSuccess) return lds_ok;
-  hipLaunchKernelGGL((k_conv_patch<S, TM, TN, TL, D, NORM>), dim3(wide.groups + last.groups), dim3(kThreads), lds, st, pa);
+  hipLaunchKernelGGL((k_conv_patch<S, TM, TN, TL, D, NORM, KN>), dim3(wide.groups + last.groups), dim3(kThreads), lds, st, pa);
   return hipGetLastError();
 }
 
 template <int TM, int TN, int TL, int D>
 hipError_t run_patch(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io, const HaloGeom &hg) {
-  if (g.S == 5) return run_patch_as<5, TM, TN, TL, D, false>(st, replicas, g, io, hg);
-  return io.bn_out ? run_patch_as<3, TM, TN, TL, D, true>(st, replicas, g, io, hg)
-                   : run_patch_as<3, TM, TN, TL, D, false>(st, replicas, g, io, hg);
+  if (io.w_kn)
+    return g.S == 5 ? run_patch_as<5, TM, TN, TL, D, false, true>(st, replicas, g, io, hg)
+                    : run_patch_as<3, TM, TN, TL, D, false, true>(st, replicas, g, io, hg);
+  if (g.S == 5) return run_patch_as<5, TM, TN, TL, D, false, false>(st, replicas, g, io, hg);
+  return io.bn_out ? run_patch_as<3, TM, TN, TL, D, true, false>(st, replicas, g, io, hg)
+                   : run_patch_as<3, TM, TN, TL, D, false, false>(st, replicas, g, io, hg);
 }
 
 // us per step of a workgroup that has its compute unit to itself, and what every further workgroup of it adds (measured over

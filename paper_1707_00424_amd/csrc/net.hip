@@ -353,8 +353,19 @@ bool build_plan(Net &N, std::string &err) {
       const int64_t wsize = (int64_t)op.Cout * op.R * op.R * op.Cin;
       if (op.need_dx) {
         N.want_grad(op.in);
-        op.w_as_is = dgrad_reads_weights(N.dtype, N.n, conv_bwd_geom(ConvShape{N.B, op.Hin, op.Win, op.Cin, op.Cout, op.R, op.stride, op.pad}),
-                                         N.segs[op.wseg].offset % 8 == 0 && N.n_pad % 8 == 0);
+        {
+          // the launch in backward(), where every tensor starts on 256 bytes and every parameter row on 4096
+          const ConvGeom gb = conv_bwd_geom(ConvShape{N.B, op.Hin, op.Win, op.Cin, op.Cout, op.R, op.stride, op.pad});
+          const int vw = 16 / N.esize;
+          const int64_t in_rs = (int64_t)N.B * op.Ho * op.Wo * op.Cout, out_rs = (int64_t)N.B * op.Hin * op.Win * op.Cin;
+          GemmIO dio{};
+          dio.in_rs = in_rs, dio.out_rs = out_rs, dio.ldc = op.Cin, dio.in_bytes = in_rs * N.esize;
+          dio.w = (const void *)(uintptr_t)(N.segs[op.wseg].offset * N.esize), dio.w_rs = N.n_pad;
+          if (op.mask_in) dio.mask = (const void *)256;
+          dio.mask_rs = out_rs, dio.accumulate = op.dx_accumulate;
+          dio.vecA = op.Cout % vw == 0, dio.vecB = gb.K % vw == 0 && N.segs[op.wseg].offset % vw == 0 && N.n_pad % vw == 0;
+          op.w_as_is = dgrad_reads_weights(N.dtype, N.n, gb, dio);
+        }
         if (!op.head && !op.w_as_is) op.wt_off = N.alloc((int64_t)N.n * wsize * N.esize);  // the head kernel reads the weights as they lie
         // few input channels under a wide window (LeNet's second convolution: 20 channels, 25 taps): the direct kernel
         // fills 20 of 32 output columns and visits every input pixel; as dy x W (500 columns, contraction 50) plus a
