@@ -188,12 +188,17 @@ const float *replica_rows(const parle_ctx *ctx) {
 parle_status enqueue_inner(parle_ctx *ctx, hipStream_t st, const float *images_dev, const int32_t *labels_dev,
                            float *loss_dev) {
   const parle_config &c = ctx->cfg;
+  bool updated = false;
   if (c.model != PARLE_MODEL_FLAT) {
+    const InnerState update{ctx->buf.x, ctx->buf.y, ctx->buf.vy, ctx->buf.z,
+                            {c.eta_inner, c.momentum, c.alpha, c.weight_decay, (float)ctx->g, coupling_dev(ctx)}};
+    const bool plain = c.algorithm != PARLE_ALG_ELASTIC && !c.compute_bf16;
     hipError_t e = net_train_step(ctx->net, st, ctx->buf.y, ctx->buf.y_bf16, ctx->buf.grad, (float *)ctx->buf.bn_stats,
-                                  net_ws(ctx), images_dev, labels_dev, loss_dev, step_dev(ctx));
+                                  net_ws(ctx), images_dev, labels_dev, loss_dev, step_dev(ctx), plain ? &update : nullptr, &updated);
     if (e != hipSuccess) return hip_fail(ctx, e, "forward/backward");
     if (step_dev(ctx) && parle_internal_advance_step(st, step_dev(ctx))) return fail(ctx, PARLE_EHIP, "step counter launch failed");
   }
+  if (updated) return PARLE_OK;
   void *shadow = c.compute_bf16 ? ctx->buf.y_bf16 : nullptr;
   parle_status s;
   if (c.algorithm == PARLE_ALG_ELASTIC)

@@ -47,6 +47,41 @@ __device__ __forceinline__ float wave_sum(float v) {
   for (int off = PARLE_WAVE / 2; off > 0; off >>= 1) v += __shfl_down(v, off, PARLE_WAVE);
   return v;
 }
+// loss_out[rep] = mean of replica rep's B losses, by one workgroup of four wavefronts; `red`: four floats of LDS
+__device__ __forceinline__ void mean_loss(int B, const float *loss_img, float *loss_out, int rep, float *red) {
+  constexpr int kWaves = 4;
+  float s = 0.f;
+  for (int b = threadIdx.x; b < B; b += kWaves * PARLE_WAVE) s += loss_img[(long long)rep * B + b];
+  s = wave_sum(s);
+  if ((threadIdx.x & (PARLE_WAVE - 1)) == 0) red[threadIdx.x / PARLE_WAVE] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    float t = 0.f;
+    for (int w = 0; w < kWaves; ++w) t += red[w];
+    loss_out[rep] = t / (float)B;
+  }
+}
+
+// (8a) with Nesterov momentum, then (8b), of one element or vector: from the gradient, x and the old y, vy and z.
+// (k_inner_update, which streams whole tensors, spells it out: through this function it took 0.2 % longer.)
+struct InnerCoeffs {
+  float eta, mu, alpha, wd, g;
+  const float *coupling;  // see parle_internal_inner_update
+};
+template <typename V>
+__device__ __forceinline__ void inner_update(const InnerCoeffs &c, float g, V grad, V x, V &y, V &v, V &z) {
+  const float one_m_alpha = 1.0f - c.alpha;
+  const V d = grad + c.wd * y + g * (y - x);
+  v = c.mu * v + d;
+  y = y - c.eta * (d + c.mu * v);
+  z = c.alpha * z + one_m_alpha * y;
+}
+// What a step's update reads and writes, rows of n_pad, for a kernel that makes gradients and updates at once.
+struct InnerState {
+  const float *x;
+  float *y, *vy, *z;
+  InnerCoeffs c;
+};
 
 // Text behind parle_last_error(NULL) for entry points that have no context (calling thread only).
 void parle_internal_set_error(const std::string &msg);

@@ -180,6 +180,14 @@ bool fc_f32_applicable(int dtype, int replicas, const ConvGeom &g);
 hipError_t launch_fc_f32(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io);
 bool wgrad_fc_f32_applicable(int dtype, int replicas, const ConvGeom &g);
 hipError_t launch_wgrad_fc_f32(hipStream_t st, int replicas, const ConvGeom &g, const WgradIO &io);
+// ... and the weight gradients of up to kFcGroupMax such layers in one launch, with the mean of each replica's B losses
+// (loss_out: not NULL).  fc_group_takes: layers that launch_wgrad runs on that kernel and that leave compute units empty.
+// `grad`: the first replica's row of gradients, which every io.out points into; with `update` the parameters of these layers
+// (weights, and biases where io.with_bias) are updated as well.
+constexpr int kFcGroupMax = 4;
+bool fc_group_takes(int dtype, int replicas, const ConvGeom &g);
+hipError_t launch_fc_group(hipStream_t st, int replicas, int count, const ConvGeom *g, const WgradIO *io, int B,
+                           const float *loss_img, float *loss_out, const float *grad, const InnerState *update);
 // fp32 backward-weight with at most 32 output channels and a window of at most 32 values (igemm_ksplit.hip).
 bool wgrad_small_f32_applicable(int dtype, const ConvGeom &g);
 // True when launch_wgrad would run a kernel that honours WgradIO::with_bias for this layer and these operands

@@ -36,6 +36,8 @@ struct FcArgs {
   int a_bytes, b_bytes;      // one replica's operand: range of the buffer loads
   int relu, accumulate;
   int vec_a, vec_b, vec_out;  // 16-byte operand loads (rows of whole vectors) / result accesses allowed
+  int small;                  // a part of a group: tiles of 16 x 16
+  long long p_off;            // ... where `out` begins in a parameter row
 };
 
 constexpr int kFcBatch = 32;  // contraction values per batch of loads: 128 bytes of a row
@@ -61,28 +63,36 @@ struct Mfma32<16> {
   static __device__ __forceinline__ int row(int lane, int v) { return 4 * (lane >> 4) + v; }
 };
 
-// TS: tile side.  KS wavefronts split the contraction of a tile, NJ tiles side by side per workgroup.
+// A staged batch: [row][k] of an operand whose k is contiguous, [k][column] of one whose k is the slow index.  Pitches:
+// 16-byte reads of consecutive rows hit distinct banks; dword reads of two groups four rows apart do too.
+template <int TS, bool SLOW>
+constexpr int kFcPitch = SLOW ? TS + 8 : kFcBatch + 4;
+template <int TS, bool SLOW>
+constexpr int kFcStaged = (SLOW ? kFcBatch : TS) * kFcPitch<TS, SLOW>;
+// LDS of a workgroup in floats: a staged batch of both operands per wavefront, sums over k of A
 template <int TS, bool A_SLOW, bool B_SLOW, int KS, int NJ>
-__global__ __launch_bounds__(KS *NJ * 64) void k_fc_f32(const FcArgs g) {
+constexpr int kFcLds = NJ * KS * (kFcStaged<TS, A_SLOW> + kFcStaged<TS, B_SLOW>)+KS * TS;
+
+// TS: tile side.  KS wavefronts split the contraction of a tile, NJ tiles side by side per workgroup, which is number bx of
+// row by of tiles of replica `rep`.
+// UPDATE: the parameters that the result is the gradient of are updated as well.
+template <int TS, bool A_SLOW, bool B_SLOW, int KS, int NJ, bool UPDATE = false>
+__device__ __forceinline__ void fc_tile(const FcArgs &g, float *smem, const int bx, const int by, const int rep, const InnerState *st = nullptr) {
   typedef Mfma32<TS> M;
   constexpr int KG = 64 / TS;        // lanes that share a row hold KG groups of four consecutive k
   constexpr int STEP = 4 * KG;       // contraction values per step (four MFMAs)
   constexpr int U = kFcBatch / STEP;  // steps per batch of loads
   constexpr int V = TS / 8;           // 16-byte vectors per lane, operand and batch
-  // A staged batch: [row][k] of an operand whose k is contiguous, [k][column] of one whose k is the slow index.  Pitches:
-  // 16-byte reads of consecutive rows hit distinct banks; dword reads of two groups four rows apart do too.
-  constexpr int LDC = kFcBatch + 4, LDS = TS + 8;
-  constexpr int LDA = A_SLOW ? LDS : LDC, LDB = B_SLOW ? LDS : LDC;
-  constexpr int kStagedA = (A_SLOW ? kFcBatch : TS) * LDA, kStagedB = (B_SLOW ? kFcBatch : TS) * LDB;
+  constexpr int LDC = kFcPitch<TS, false>, LDS = kFcPitch<TS, true>;
+  constexpr int kStagedA = kFcStaged<TS, A_SLOW>, kStagedB = kFcStaged<TS, B_SLOW>;
   constexpr int LD = TS + 4;          // pitch of a partial tile, which takes the place of the staged operands
   static_assert(kStagedA + kStagedB >= TS * LD, "a partial tile has to fit");
-  __shared__ __attribute__((aligned(16))) float lds[NJ][KS][kStagedA + kStagedB];
-  __shared__ float bpart[KS][TS];
+  float(*lds)[KS][kStagedA + kStagedB] = reinterpret_cast<float(*)[KS][kStagedA + kStagedB]>(smem);
+  float(*bpart)[TS] = reinterpret_cast<float(*)[TS]>(smem + NJ * KS * (kStagedA + kStagedB));
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int kw = wave % KS, jw = wave / KS;
-  const int rep = blockIdx.z;
-  const int i0 = blockIdx.y * TS, j0 = (blockIdx.x * NJ + jw) * TS;
+  const int i0 = by * TS, j0 = (bx * NJ + jw) * TS;
   const int rl = lane % TS, kg = lane / TS;
   const __amdgpu_buffer_rsrc_t a_rsrc =
       __builtin_amdgcn_make_buffer_rsrc((void *)(g.a + rep * g.a_rs), 0, g.a_bytes, 0x00020000);
@@ -135,7 +145,7 @@ __global__ __launch_bounds__(KS *NJ * 64) void k_fc_f32(const FcArgs g) {
 #pragma unroll
   for (int v = 0; v < M::kVals; ++v) acc[v] = 0.f, acc2[v] = 0.f;
   float bsum = 0.f;
-  const bool tally = A_SLOW && g.bias_out && blockIdx.x == 0 && jw == 0;
+  const bool tally = A_SLOW && g.bias_out && bx == 0 && jw == 0;
   float *sa = lds[jw][kw], *sb = sa + kStagedA;  // this wavefront's own: its LDS accesses execute in order
   auto multiply = [&](const u4 (&ar)[V], const u4 (&br)[V]) {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -192,6 +202,13 @@ __global__ __launch_bounds__(KS *NJ * 64) void k_fc_f32(const FcArgs g) {
   }
   __syncthreads();
   float *out = g.out + rep * g.o_rs;
+  const long long p0 = rep * g.o_rs + g.p_off;  // of the row that `out` belongs to
+  const float gp = UPDATE ? (st->c.coupling ? st->c.coupling[0] : st->c.g) : 0.f;
+  auto update1 = [&](long long at, float grad) {
+    float y = st->y[at], v = st->vy[at], z = st->z[at];
+    inner_update(st->c, gp, grad, st->x[at], y, v, z);
+    st->y[at] = y, st->vy[at] = v, st->z[at] = z;
+  };
   const float *bias = g.bias ? g.bias + rep * g.bias_rs : nullptr;
   const float *resid = g.resid ? g.resid + rep * g.resid_rs : nullptr;
   const float *mask = g.mask ? g.mask + rep * g.mask_rs : nullptr;
@@ -219,6 +236,11 @@ __global__ __launch_bounds__(KS *NJ * 64) void k_fc_f32(const FcArgs g) {
       }
       if (g.accumulate) v += *(const f4 *)&out[o];
       *(f4 *)&out[o] = v;
+      if constexpr (UPDATE) {
+        f4 y = *(const f4 *)&st->y[p0 + o], vy = *(const f4 *)&st->vy[p0 + o], z = *(const f4 *)&st->z[p0 + o];
+        inner_update(st->c, gp, v, *(const f4 *)&st->x[p0 + o], y, vy, z);
+        *(f4 *)&st->y[p0 + o] = y, *(f4 *)&st->vy[p0 + o] = vy, *(f4 *)&st->z[p0 + o] = z;
+      }
     } else {
       for (int e = 0; e < lim; ++e) {
         float t1 = v[e];
@@ -227,15 +249,56 @@ __global__ __launch_bounds__(KS *NJ * 64) void k_fc_f32(const FcArgs g) {
         if (mask) t1 = mask[o + e] > 0.f ? t1 : 0.f;
         if (g.accumulate) t1 += out[o + e];
         out[o + e] = t1;
+        if constexpr (UPDATE) update1(p0 + o + e, t1);
       }
     }
   }
-  if (A_SLOW && g.bias_out && blockIdx.x == 0 && tid < TS && i0 + tid < g.I) {
+  if (A_SLOW && g.bias_out && bx == 0 && tid < TS && i0 + tid < g.I) {
     float t = bpart[0][tid];
 #pragma unroll
     for (int w = 1; w < KS; ++w) t += bpart[w][tid];
     g.bias_out[rep * g.bias_out_rs + i0 + tid] = t;
+    if constexpr (UPDATE) update1(p0 + (long long)g.I * g.J + i0 + tid, t);
   }
+}
+
+template <int TS, bool A_SLOW, bool B_SLOW, int KS, int NJ>
+__global__ __launch_bounds__(KS *NJ * 64) void k_fc_f32(const FcArgs g) {
+  __shared__ __attribute__((aligned(16))) float smem[kFcLds<TS, A_SLOW, B_SLOW, KS, NJ>];
+  fc_tile<TS, A_SLOW, B_SLOW, KS, NJ>(g, smem, blockIdx.x, blockIdx.y, blockIdx.z);
+}
+
+// Weight gradients of several layers and the mean loss in one launch.  In a network of a few small layers each of these is a
+// launch of 2 to 6 us that leaves most of the chip empty and waits for nothing but the classifier's gradient.  The MLP's two
+// weight gradients and its loss were three launches of 3.5, 5.7 and 1.8 us: a step of it (three replicas) 30.1 -> 25.8 us; with the
+// update, a fourth one of 4 us, 22.3.
+constexpr int kFcGroup = 4;
+struct FcGroup {
+  FcArgs part[kFcGroup];
+  int end[kFcGroup];  // workgroups of the parts up to this one; those behind the last part take a replica's loss each
+  int count, B;
+  const float *loss_img;
+  float *loss_out;
+  InnerState update;
+};
+// UPDATE: and the step's update, where the parts are all that a network has.
+template <bool UPDATE>
+__global__ __launch_bounds__(kThreads) void k_fc_group(const FcGroup a) {
+  __shared__ __attribute__((aligned(16))) float smem[kFcLds<32, true, true, 4, 1>];
+  int p = 0, first = 0;
+  while (p < a.count && (int)blockIdx.x >= a.end[p]) first = a.end[p++];
+  const int b = blockIdx.x - first;
+  if (p == a.count) {
+    mean_loss(a.B, a.loss_img, a.loss_out, b, smem);
+    return;
+  }
+  const FcArgs &g = a.part[p];
+  const int ts = g.small ? 16 : 32, nx = (g.J + ts - 1) / ts, ny = (g.I + ts - 1) / ts;
+  const int rep = b / (nx * ny), t = b - rep * nx * ny, by = t / nx, bx = t - by * nx;
+  if (g.small)
+    fc_tile<16, true, true, 4, 1, UPDATE>(g, smem, bx, by, rep, &a.update);
+  else
+    fc_tile<32, true, true, 4, 1, UPDATE>(g, smem, bx, by, rep, &a.update);
 }
 
 template <int TS, bool A_SLOW, bool B_SLOW, int KS, int NJ>
@@ -249,6 +312,8 @@ constexpr int kCus = 256;
 
 long long fc_tiles(int I, int J, int ts) { return (long long)((I + ts - 1) / ts) * ((J + ts - 1) / ts); }
 
+bool fc_small_tiles(int replicas, int I, int J, int K) { return fc_tiles(I, J, 32) * replicas < (K > 256 ? 144 : kCus); }
+
 template <bool A_SLOW, bool B_SLOW>
 hipError_t choose_fc(hipStream_t st, int replicas, FcArgs &g) {
   // Measured (us; forward / input gradient / weight gradient), six replicas of 128 x 800 x 500 (384 / 600 / 2400 tiles of
@@ -260,7 +325,7 @@ hipError_t choose_fc(hipStream_t st, int replicas, FcArgs &g) {
   // input gradient) 8.9 / 8.2 and 14.7 / 8.4, at 192 (3 x 128 x 500 x 500) 9.5 / 8.4, at 128 (8 x 32 x 1024 x 512) 7.8 / 7.9;
   // <16, 4, 1> / <32, 4, 1> at 192 (3 x 128 x 256 x 500) 4.9 / 5.5.
   const long long t32 = fc_tiles(g.I, g.J, 32) * replicas;
-  if (t32 < (g.K > 256 ? 144 : kCus)) {
+  if (fc_small_tiles(replicas, g.I, g.J, g.K)) {
     if (g.K > 256) return run_fc<16, A_SLOW, B_SLOW, 8, 1>(st, replicas, g);
     return run_fc<16, A_SLOW, B_SLOW, 4, 1>(st, replicas, g);
   }
@@ -317,8 +382,8 @@ bool wgrad_fc_f32_applicable(int dtype, int replicas, const ConvGeom &g) {
   return g.M >= 512 || tiles <= std::max(192, 24 * (g.M - 8));
 }
 
-hipError_t launch_wgrad_fc_f32(hipStream_t st, int replicas, const ConvGeom &g, const WgradIO &io) {
-  if (io.splits != 1) return hipErrorInvalidValue;
+namespace {
+FcArgs wgrad_fc_args(const ConvGeom &g, const WgradIO &io) {
   FcArgs f{};
   f.a = (const float *)io.dy, f.a_rs = io.dy_rs, f.lda = g.N, f.a_bytes = g.M * g.N * 4;
   f.b = (const float *)io.x, f.b_rs = io.x_rs, f.ldb = g.K, f.b_bytes = g.M * g.K * 4;
@@ -327,5 +392,45 @@ hipError_t launch_wgrad_fc_f32(hipStream_t st, int replicas, const ConvGeom &g, 
   f.vec_a = f.lda % 4 == 0, f.vec_b = f.ldb % 4 == 0;
   f.vec_out = g.K % 4 == 0 && aligned_to(io.out, 16) && io.out_rs % 4 == 0;
   if (io.with_bias) f.bias_out = io.out + (long long)g.N * g.K, f.bias_out_rs = io.out_rs;
+  return f;
+}
+}  // namespace
+
+hipError_t launch_wgrad_fc_f32(hipStream_t st, int replicas, const ConvGeom &g, const WgradIO &io) {
+  if (io.splits != 1) return hipErrorInvalidValue;
+  FcArgs f = wgrad_fc_args(g, io);
   return choose_fc<true, true>(st, replicas, f);
+}
+
+// Layers that choose_fc would give four wavefronts per tile; a launch of more tiles fills the chip by itself.
+bool fc_group_takes(int dtype, int replicas, const ConvGeom &g) {
+  if (wgrad_small_f32_applicable(dtype, g) || !wgrad_fc_f32_applicable(dtype, replicas, g)) return false;
+  return fc_small_tiles(replicas, g.N, g.K, g.M) ? g.M <= 256 : fc_tiles(g.N, g.K, 32) * replicas <= 2 * kCus;
+}
+
+hipError_t launch_fc_group(hipStream_t st, int replicas, int count, const ConvGeom *g, const WgradIO *io, int B,
+                           const float *loss_img, float *loss_out, const float *grad, const InnerState *update) {
+  static_assert(kFcGroup == kFcGroupMax, "the callers' limit");
+  if (count < 0 || count > kFcGroup) return hipErrorInvalidValue;
+  FcGroup a{};
+  a.count = count, a.B = B, a.loss_img = loss_img, a.loss_out = loss_out;
+  int blocks = 0;
+  for (int i = 0; i < count; ++i) {
+    if (io[i].splits != 1) return hipErrorInvalidValue;
+    FcArgs &f = a.part[i];
+    f = wgrad_fc_args(g[i], io[i]);
+    f.small = fc_small_tiles(replicas, f.I, f.J, f.K);
+    f.p_off = f.out - grad;
+    blocks += (int)fc_tiles(f.I, f.J, f.small ? 16 : 32) * replicas;
+    a.end[i] = blocks;
+  }
+  if (loss_out) blocks += replicas;
+  if (blocks == 0) return hipSuccess;
+  if (update) {
+    a.update = *update;
+    hipLaunchKernelGGL(k_fc_group<true>, dim3(blocks), dim3(kThreads), 0, st, a);
+  } else {
+    hipLaunchKernelGGL(k_fc_group<false>, dim3(blocks), dim3(kThreads), 0, st, a);
+  }
+  return hipGetLastError();
 }

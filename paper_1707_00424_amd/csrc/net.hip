@@ -640,7 +640,8 @@ hipError_t forward(const Run &r, bool train, float *bn_stats, const float *bn_ev
   return launch_pending();
 }
 
-hipError_t backward(const Run &r, float *grad) {
+// `update`, `updated`: see net_train_step
+hipError_t backward(const Run &r, float *grad, const InnerState *update, bool *updated) {
   Net &N = *r.N;
   const int vw = 16 / N.esize;
   if (N.side) {
@@ -650,6 +651,13 @@ hipError_t backward(const Run &r, float *grad) {
       HIP_TRY(launch_weight_transpose_all(r.st, N.dtype, r.n, t, r.params_t, r.p_rs, r.ws));
   }
   bool used_side2 = false;
+  // On one stream the weight gradients of small fully connected layers and the mean loss wait for one launch at the end:
+  // nothing overwrites an output gradient or a layer's input before the step is over.
+  ConvGeom group_g[kFcGroupMax];
+  WgradIO group_io[kFcGroupMax];
+  int group = 0;
+  int64_t group_params = 0;
+  bool group_loss = false;
   // input gradient of a convolution (direct kernels) on stream `s`
   auto launch_dgrad = [&](const Op &op, hipStream_t s) -> hipError_t {
     const void *dy = r.gptr(op.dy);
@@ -756,7 +764,10 @@ hipError_t backward(const Run &r, float *grad) {
           const int64_t wsize = N.segs[op.wseg].size + (bias_in_wgrad ? op.Cout : 0);  // values per (replica, split)
           if (S == 1) {
             io.out = grad + N.segs[op.wseg].offset, io.out_rs = r.p_rs, io.split_stride = 0;
-            HIP_TRY(launch_wgrad(lst, N.dtype, r.n, gf, io));
+            if (!N.side && group < kFcGroupMax && fc_group_takes(N.dtype, r.n, gf))
+              group_g[group] = gf, group_io[group++] = io, group_params += wsize;
+            else
+              HIP_TRY(launch_wgrad(lst, N.dtype, r.n, gf, io));
           } else {
             // never launch with more partials than the plan reserved room for
             if ((int64_t)r.n * S * wsize * 4 > wpart_bytes) return hipErrorInvalidValue;
@@ -766,7 +777,9 @@ hipError_t backward(const Run &r, float *grad) {
           }
         }
         // the mean of the per-image losses is nobody's input: it is taken where the leaves run, after them
-        if (op.head && r.loss_out)
+        if (op.head && r.loss_out && !N.side)
+          group_loss = true;
+        else if (op.head && r.loss_out)
           HIP_TRY(launch_loss_mean(lst, r.n, r.B, (const float *)(r.ws + N.off_loss_img), r.loss_out));
         break;
       }
@@ -818,6 +831,13 @@ hipError_t backward(const Run &r, float *grad) {
       }
     }
   }
+  // the group has every parameter there is, and all that reads them has run
+  int64_t params = 0;
+  for (const Segment &s : N.segs) params += s.size;
+  *updated = update && group_params == params;
+  if (group > 0 || group_loss)
+    HIP_TRY(launch_fc_group(r.st, r.n, group, group_g, group_io, r.B, (const float *)(r.ws + N.off_loss_img),
+                            group_loss ? r.loss_out : nullptr, grad, *updated ? update : nullptr));
   if (N.side) {  // join: the update that follows reads every gradient
     HIP_TRY(hipEventRecord(N.side_done, N.side));
     HIP_TRY(hipStreamWaitEvent(r.st, N.side_done, 0));
@@ -908,7 +928,8 @@ int64_t net_forward_flops_per_image(const Net *net) {
 
 hipError_t net_train_step(Net *net, hipStream_t st, const float *params, const void *params_bf16, float *grad,
                           float *bn_stats, void *workspace, const float *images, const int32_t *labels,
-                          float *loss_dev, const long long *step_dev) {
+                          float *loss_dev, const long long *step_dev, const InnerState *update, bool *updated) {
+  *updated = false;
   Net &N = *net;
   if (N.cfg.dropout > 0.f && !step_dev) return hipErrorInvalidValue;
   if (N.overlap && !N.side) HIP_TRY(make_side_stream(N, st));
@@ -948,7 +969,7 @@ hipError_t net_train_step(Net *net, hipStream_t st, const float *params, const v
     HIP_TRY(launch_softmax_xent_train(st, N.dtype, N.n, N.B, tl.C, (const float *)r.tptr(N.t_logits),
                                       r.trs(N.t_logits), labels, loss_dev, r.gptr(N.t_logits), r.trs(N.t_logits)));
   }
-  return backward(r, grad);
+  return backward(r, grad, update, updated);
 }
 
 hipError_t net_eval(Net *net, hipStream_t st, const float *param_row, const float *bn_row, void *workspace,

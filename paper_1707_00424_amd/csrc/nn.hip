@@ -257,17 +257,7 @@ __global__ __launch_bounds__(kThreads) void k_gap_head(int B, int HW, int C, con
 __global__ __launch_bounds__(kThreads) void k_loss_mean(int B, const float *__restrict__ loss_img,
                                                         float *__restrict__ loss_out) {
   __shared__ float red[kThreads / PARLE_WAVE];
-  const int rep = blockIdx.x;
-  float s = 0.f;
-  for (int b = threadIdx.x; b < B; b += kThreads) s += loss_img[(long long)rep * B + b];
-  s = wave_sum(s);
-  if ((threadIdx.x & (PARLE_WAVE - 1)) == 0) red[threadIdx.x / PARLE_WAVE] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    float t = 0.f;
-    for (int w = 0; w < kThreads / PARLE_WAVE; ++w) t += red[w];
-    loss_out[rep] = t / (float)B;
-  }
+  mean_loss(B, loss_img, loss_out, blockIdx.x, red);
 }
 
 __global__ __launch_bounds__(kThreads) void k_softmax_eval(int count, int C, const float *__restrict__ logits,

@@ -1,0 +1,103 @@
+"""Steps of networks small enough for one stream, whose last launches are shared between layers: losses, gradients and updated
+state of the MLP and of a small LeNet over sizes on both sides of the limits that decide what shares a launch."""
+import pytest
+
+import test_gpu_kernels as tk
+
+pytestmark = pytest.mark.gpu
+gpu = tk.gpu
+
+CASES = [
+    # n, batch, hidden
+    (3, 128, 128),   # the small workload
+    (1, 1, 1),
+    (1, 17, 37),     # rows of no whole vectors
+    (2, 100, 256),   # the widest that the one-kernel head takes
+    (6, 64, 260),    # beyond: the loss in a kernel of its own
+    (1, 300, 40),    # more rows than a group's small tiles take
+    (2, 257, 64),
+    (6, 128, 512),   # more tiles than two per compute unit
+]
+
+
+def _config(pb, n, batch, model, arch, **kw):
+    return pb.make_config(model=model, n_replicas=n, batch=batch, in_h=28, in_w=28, in_c=1, n_classes=10, arch=arch, eta_inner=0.05,
+                          eta_outer=0.1, momentum=0.9, alpha=0.75, gamma0=0.3, rho0=1.0, weight_decay=1e-3, **kw)
+
+
+def _run(torch, pb, cfg, n, batch):
+    from paper_1707_00424_amd import synth
+    gen = torch.Generator(device="cuda").manual_seed(7 * n + batch)
+    row = torch.as_tensor(synth.init_params(pb.parle_query_layout(cfg), 3, "uniform")).cuda()
+    x0 = row + 0.02 * torch.randn((n, row.numel()), generator=gen, device="cuda") * row.std()
+    P = pb.Parle(cfg, x0.contiguous())
+    images = torch.randn((n, batch, 28, 28, 1), generator=gen, device="cuda")
+    labels = torch.randint(0, 10, (n, batch), generator=gen, device="cuda").int()
+    return P, images, labels
+
+
+def _segments(pb, cfg, row):
+    return {s["name"]: row[s["offset"]:s["offset"] + s["size"]].reshape(s["shape"]) for s in pb.parle_query_layout(cfg)}
+
+
+def _check_update(P, cfg, before, after, N):
+    """The state after a step from the state before it and the step's gradient, in 64 bits."""
+    y, x, v, z = (before[k][:, :N].double() for k in ("y", "x", "vy", "z"))
+    d = P.grad[:, :N].double() + cfg.weight_decay * y + cfg.gamma0 * (y - x)
+    vn = cfg.momentum * v + d
+    yn = y - cfg.eta_inner * (d + cfg.momentum * vn)
+    zn = cfg.alpha * z + (1 - cfg.alpha) * yn
+    for name, want in (("vy", vn), ("y", yn), ("z", zn)):
+        # a handful of roundings of values no larger than those that enter
+        bound = 8 * 2.0 ** -24 * (want.abs() + y.abs() + d.abs() + v.abs() + z.abs())
+        assert ((after[name][:, :N].double() - want).abs() <= bound).all(), name
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_mlp_steps(gpu, case):
+    torch, pb = gpu
+    n, batch, hidden = case
+    cfg = _config(pb, n, batch, pb.MODEL_MLP, (hidden, 0, 0, 0))
+    P, images, labels = _run(torch, pb, cfg, n, batch)
+    N = P.sizes.n_params
+    loss = torch.full((n,), float("nan"), device="cuda")
+    for _ in range(2):
+        before = {k: getattr(P, k).clone() for k in ("x", "y", "vy", "z")}
+        P.grad[:, :N].fill_(float("nan"))
+        P.parle_inner_step(images, labels, loss)
+        after = {k: getattr(P, k) for k in ("y", "vy", "z")}
+        for a in range(n):
+            seg = {k: t.double().requires_grad_(True) for k, t in _segments(pb, cfg, before["y"][a]).items()}
+            h = (images[a].double().reshape(batch, -1) @ seg["fc1.w"].reshape(hidden, -1).t() + seg["fc1.b"]).relu()
+            logits = h @ seg["fc2.w"].reshape(10, -1).t() + seg["fc2.b"]
+            ref = torch.nn.functional.cross_entropy(logits, labels[a].long())
+            assert abs(loss[a].item() - ref.item()) <= 1e-5 * max(1.0, ref.item())
+            grads = torch.autograd.grad(ref, list(seg.values()))
+            got = _segments(pb, cfg, P.grad[a])
+            for (name, _), g in zip(seg.items(), grads):
+                # sums of up to 784 fp32 products, and the same again behind them
+                assert ((got[name].double() - g).norm() <= 1e-5 * g.norm() + 1e-9), (name, a)
+        _check_update(P, cfg, before, after, N)
+
+
+@pytest.mark.parametrize("model,arch", [("mlp", (64, 0, 0, 0)), ("lenet", (12, 16, 5, 64))])
+def test_recorded_block_equals_single_steps(gpu, model, arch):
+    torch, pb = gpu
+    n, batch, steps = 2, 24, 3
+    kind = pb.MODEL_MLP if model == "mlp" else pb.MODEL_LENET
+    cfgs = [_config(pb, n, batch, kind, arch, graph_block=g) for g in (0, 1)]
+    runs = [_run(torch, pb, c, n, batch) for c in cfgs]
+    images = torch.stack([runs[0][1] * (1 + 0.1 * s) for s in range(steps)]).contiguous()
+    labels = torch.stack([runs[0][2]] * steps).contiguous()
+    losses = [torch.full((steps, n), float("nan"), device="cuda") for _ in cfgs]
+    for _ in range(4):
+        for s in range(steps):
+            runs[0][0].parle_inner_step(images[s], labels[s], losses[0][s])
+        runs[1][0].parle_inner_block(images, labels, losses[1])
+        torch.cuda.synchronize()
+        assert torch.equal(losses[0], losses[1])
+        N = runs[0][0].sizes.n_params
+        for name in ("y", "vy", "z", "grad"):
+            assert torch.equal(getattr(runs[0][0], name)[:, :N], getattr(runs[1][0], name)[:, :N]), name
+        for P, _, _ in runs:
+            P.parle_outer_step()
