@@ -440,6 +440,7 @@ hipError_t launch_igemm(hipStream_t st, int dtype, bool out_f32, int replicas, c
   io.stat = nullptr;
   if (io.in_f32 && !(dtype == 1 && !out_f32 && conv_smallk_applicable(dtype, g, io))) return hipErrorInvalidValue;
   if (conv_smallk_applicable(dtype, g, io)) return launch_conv_smallk(st, dtype, out_f32, replicas, g, io);
+  if (dtype == 1 && !out_f32 && patch_s2_applicable(g, io)) return launch_patch_s2(st, replicas, g, io);
   if (conv_halo_applicable(dtype, replicas, g, io, out_f32)) return launch_conv_halo(st, replicas, g, io);
   if (conv_f32x3_applicable(dtype, replicas, g, io)) return launch_conv_f32x3(st, replicas, g, io);
   if (dgrad_s2_applicable(dtype, g, io, out_f32)) return launch_dgrad_s2(st, replicas, g, io);
