@@ -173,6 +173,15 @@ hipError_t launch_wgrad_strips(hipStream_t st, int replicas, const ConvGeom &g, 
 // bf16 plain products with few output tiles: the contraction split over the wavefronts of a workgroup (igemm_ksplit.hip).
 bool gemm_ksplit_applicable(int dtype, int replicas, const ConvGeom &g, const GemmIO &io);
 hipError_t launch_gemm_ksplit(hipStream_t st, bool out_f32, int replicas, const ConvGeom &g, const GemmIO &io);
+// A first fp32 layer with the ReLU and the 2 x 2 max-pool behind it, and its weight and bias gradient from the pooled gradient
+// (igemm_convpool.hip).  `code`: a byte per pooled value, [replica][image][pooled pixel][channel] as the pooled outputs; NULL where
+// no backward pass follows.  out of the second: [replica][split][weights, then biases].
+bool convpool_applicable(int dtype, const ConvShape &c);
+hipError_t launch_convpool(hipStream_t st, int n, const ConvShape &c, const float *x, long long x_rs, const float *w, long long w_rs, const float *bias,
+                           long long bias_rs, float *out, unsigned char *code);
+int convpool_wgrad_splits(int n, const ConvShape &c);
+hipError_t launch_convpool_wgrad(hipStream_t st, int n, const ConvShape &c, const float *x, long long x_rs, const float *dpooled, const unsigned char *code,
+                                 float *out, long long out_rs, long long split_stride);
 // fp32 convolutions as six products of bf16 parts, at fp32 accuracy (igemm_f32.hip).
 bool conv_f32x3_applicable(int dtype, int replicas, const ConvGeom &g, const GemmIO &io);
 hipError_t launch_conv_f32x3(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io);

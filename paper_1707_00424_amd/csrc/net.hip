@@ -48,6 +48,11 @@ struct Op {
   bool win = false;        // backward-data through per-tap products held in LDS, one image per workgroup
   // pool
   bool pool_relu_mask = false;
+  // a first layer and the pool behind it as one operation (convpool_applicable): the convolution's pool, where the window codes
+  // lie (bytes), and whether this pool is part of the convolution in front of it
+  int pool = -1;
+  int64_t code_off = -1;
+  bool pool_fused = false;
   // bn
   int gseg = -1, betaseg = -1;
   int64_t saved_off = -1, sums_off = -1, run_off = 0;  // run_off in floats inside a replica's BN row
@@ -316,9 +321,10 @@ bool build_plan(Net &N, std::string &err) {
     Op &last = N.ops.back();
     if (fused_head && last.type == OP_CONV && last.out == N.t_logits && N.tensors[last.out].f32 && last.R == 1 &&
         last.Hin == 1 && last.Win == 1 && last.stride == 1 && last.pad == 0 && last.need_dx && last.resid < 0 &&
-        !last.relu && fc_head_applicable(last.Cout, last.Cin) && last.Cin <= 256) {
-      // up to 256 features: MLP (128) -12 %, WRN-16-4 (256) -1.1 % per step; beyond, the one kernel was no gain over
-      // the three it replaces (LeNet, 500 features: +1.9 %; WRN-28-10, 640: +0.9 %)
+        !last.relu && fc_head_applicable(last.Cout, last.Cin) && last.Cin <= 512) {
+      // us per step with it / with the three kernels it replaces: LeNet with six replicas of 128 and 500 features 262 / 266, one
+      // replica of 128 143 / 151; MLP of 512 features 50 / 53, two replicas of 64 and 270 features 33 / 39.  WRN-28-10, 640
+      // features: 0.9 % slower with it.
       last.head = true;
       N.head_op = (int)N.ops.size() - 1;
     }
@@ -329,6 +335,19 @@ bool build_plan(Net &N, std::string &err) {
       N.head_op = (int)N.ops.size() - 1;
     }
     N.off_loss_img = N.alloc((int64_t)N.n * N.B * 4);
+  }
+  for (size_t i = 0; i + 1 < N.ops.size(); ++i) {
+    Op &c = N.ops[i], &p = N.ops[i + 1];
+    if (c.type != OP_CONV || p.type != OP_POOL || p.in != c.out || !p.pool_relu_mask || !c.relu || c.need_dx || c.resid >= 0 || c.bseg < 0 || c.wseg < 0 ||
+        N.segs[c.bseg].offset != N.segs[c.wseg].offset + N.segs[c.wseg].size ||
+        !convpool_applicable(N.dtype, ConvShape{N.B, c.Hin, c.Win, c.Cin, c.Cout, c.R, c.stride, c.pad}))
+      continue;
+    bool other = false;  // reader of the convolution's output
+    for (const Op &o : N.ops) other = other || (&o != &p && (o.in == c.out || o.resid == c.out));
+    if (other) continue;
+    const Tensor &tp = N.tensors[p.out];
+    c.pool = (int)i + 1, p.pool_fused = true;
+    c.code_off = N.alloc((int64_t)N.n * N.B * tp.H * tp.W * tp.C);
   }
   // a batch-norm whose input a convolution of the chain writes can get its column sums from that convolution
   for (size_t i = 0; i < N.ops.size(); ++i) {
@@ -402,6 +421,10 @@ bool build_plan(Net &N, std::string &err) {
       // (+ Cout: a kernel that also takes the bias gradient puts it behind the weight gradient, see backward())
       if (S > 1 && (int64_t)N.n * S * (wsize + op.Cout) * 4 > (op.need_dx ? wpartial : wpartial_main))
         (op.need_dx ? wpartial : wpartial_main) = (int64_t)N.n * S * (wsize + op.Cout) * 4;
+      if (op.pool >= 0) {
+        const int64_t bytes = (int64_t)N.n * convpool_wgrad_splits(N.n, ConvShape{N.B, op.Hin, op.Win, op.Cin, op.Cout, op.R, op.stride, op.pad}) * (wsize + op.Cout) * 4;
+        if (bytes > wpartial_main) wpartial_main = bytes;
+      }
       if ((int64_t)N.B * op.Hin * op.Win * op.Cin >= (1LL << 31) || (int64_t)g.M * op.Cout >= (1LL << 31) ||
           wsize >= (1LL << 31)) {
         err = "a layer exceeds 2^31 elements per replica";
@@ -573,6 +596,11 @@ hipError_t forward(const Run &r, bool train, float *bn_stats, const float *bn_ev
     switch (op.type) {
       case OP_CONV: {
         if (train && op.head) break;  // runs with the loss (net_train_step)
+        if (op.pool >= 0) {
+          HIP_TRY(launch_convpool(r.st, r.n, shape_of(op, r.B), (const float *)r.tptr(op.in), r.trs(op.in), (const float *)r.wptr(op.wseg), r.p_rs,
+                                  r.fptr(op.bseg), r.p_rs, (float *)r.tptr(N.ops[op.pool].out), train ? (unsigned char *)r.ws + op.code_off : nullptr));
+          break;
+        }
         const ConvGeom g = fwd_geom(op, r.B);
         if (branches && op.branch) {
           HIP_TRY(launch_pending());
@@ -599,6 +627,7 @@ hipError_t forward(const Run &r, bool train, float *bn_stats, const float *bn_ev
         break;
       }
       case OP_POOL: {
+        if (op.pool_fused) break;
         const Tensor &ti = N.tensors[op.in];
         HIP_TRY(launch_maxpool_fwd(r.st, N.dtype, r.n, r.B, ti.H, ti.W, ti.C, r.tptr(op.in), r.trs(op.in),
                                    r.tptr(op.out), r.trs(op.out)));
@@ -681,6 +710,17 @@ hipError_t backward(const Run &r, float *grad, const InnerState *update, bool *u
     const Op &op = N.ops[oi];
     switch (op.type) {
       case OP_CONV: {
+        if (op.pool >= 0) {
+          const ConvShape cs = shape_of(op, r.B);
+          const int S = convpool_wgrad_splits(r.n, cs);
+          const int64_t len = N.segs[op.wseg].size + op.Cout;
+          float *row = grad + N.segs[op.wseg].offset, *out = S == 1 ? row : (float *)(r.ws + N.off_wpartial_main);
+          if (S > 1 && (int64_t)r.n * S * len * 4 > N.wpartial_main_bytes) return hipErrorInvalidValue;
+          HIP_TRY(launch_convpool_wgrad(r.st, r.n, cs, (const float *)r.tptr(op.in), r.trs(op.in), (const float *)r.gptr(N.ops[op.pool].out),
+                                        (const unsigned char *)r.ws + op.code_off, out, S == 1 ? r.p_rs : S * len, len));
+          if (S > 1) HIP_TRY(launch_reduce_partials(r.st, r.n, S, len, out, row, r.p_rs));
+          break;
+        }
         const void *dy = r.gptr(op.dy);
         const int64_t dy_rs = r.trs(op.dy);
         ConvGeom gf = fwd_geom(op, r.B);
@@ -785,6 +825,7 @@ hipError_t backward(const Run &r, float *grad, const InnerState *update, bool *u
         break;
       }
       case OP_POOL: {
+        if (op.pool_fused) break;
         const Tensor &ti = N.tensors[op.in];
         HIP_TRY(launch_maxpool_bwd(r.st, N.dtype, r.n, r.B, ti.H, ti.W, ti.C, r.tptr(op.in), r.trs(op.in),
                                    r.gptr(op.out), r.trs(op.out), r.gptr(op.in), r.trs(op.in), op.pool_relu_mask));

@@ -101,3 +101,47 @@ def test_recorded_block_equals_single_steps(gpu, model, arch):
             assert torch.equal(getattr(runs[0][0], name)[:, :N], getattr(runs[1][0], name)[:, :N]), name
         for P, _, _ in runs:
             P.parle_outer_step()
+
+
+@pytest.mark.parametrize("case", [
+    # n, batch, image side, channels, first layer's outputs, window: 24 x 24, ragged tiles of windows, odd sides, whole and partial vectors
+    (2, 5, 28, 1, 20, 5), (1, 3, 15, 1, 12, 4), (3, 2, 17, 3, 32, 3), (1, 1, 14, 2, 4, 3), (2, 400, 17, 1, 16, 5), (1, 33, 32, 3, 28, 3)])
+def test_first_layer_with_its_pool(gpu, case):
+    """Loss and every gradient of a LeNet whose first layer runs as one operation with its pool."""
+    torch, pb = gpu
+    n, batch, side, ch, c1, k = case
+    gen = torch.Generator(device="cuda").manual_seed(sum(case))
+    cfg = pb.make_config(model=pb.MODEL_LENET, n_replicas=n, batch=batch, in_h=side, in_w=side, in_c=ch, n_classes=10, arch=(c1, 12, k, 24),
+                         eta_inner=0.05, eta_outer=0.1, gamma0=0.3, rho0=1.0)
+    layout = pb.parle_query_layout(cfg)
+    from paper_1707_00424_amd import synth
+    x0 = torch.stack([torch.as_tensor(synth.init_params(layout, 3 + a, "uniform")) for a in range(n)]).cuda()
+    x0 += 0.05 * torch.randn(x0.shape, generator=gen, device="cuda")
+    P = pb.Parle(cfg, x0.contiguous())
+    images = torch.randn((n, batch, side, side, ch), generator=gen, device="cuda")
+    labels = torch.randint(0, 10, (n, batch), generator=gen, device="cuda").int()
+    loss = torch.full((n,), float("nan"), device="cuda")
+    P.parle_inner_step(images, labels, loss)
+    eval_loss, _, _ = P.parle_eval(-1, images.reshape(-1, side, side, ch), labels.reshape(-1))
+
+    def logits_of(seg, x):
+        x = x.double().permute(0, 3, 1, 2)
+        for name in ("conv1", "conv2"):
+            x = torch.nn.functional.conv2d(x.cpu(), seg[name + ".w"].permute(0, 3, 1, 2).cpu(), seg[name + ".b"].cpu()).relu()
+            x = torch.nn.functional.max_pool2d(x, 2)
+        h = x.permute(0, 2, 3, 1).reshape(x.shape[0], -1).cuda()
+        h = (h @ seg["fc1.w"].reshape(seg["fc1.b"].numel(), -1).t() + seg["fc1.b"]).relu()
+        return h @ seg["fc2.w"].reshape(10, -1).t() + seg["fc2.b"]
+
+    for a in range(n):
+        seg = {key: t.double().requires_grad_(True) for key, t in _segments(pb, cfg, x0[a]).items()}
+        ref = torch.nn.functional.cross_entropy(logits_of(seg, images[a]), labels[a].long())
+        assert abs(loss[a].item() - ref.item()) <= 1e-5 * max(1.0, ref.item())
+        got = _segments(pb, cfg, P.grad[a])
+        for name, g in zip(seg, torch.autograd.grad(ref, list(seg.values()))):
+            # fp32 sums; an input within rounding of a ReLU's or a pool's decision would show as 1e-3 and more: none at these seeds
+            assert (got[name].double() - g).norm() <= 2e-5 * g.norm() + 1e-9, (name, a, ((got[name].double() - g).norm() / g.norm()).item())
+    with torch.no_grad():
+        mean = {key: t.double() for key, t in _segments(pb, cfg, x0.double().mean(0).float()).items()}
+        ref = torch.nn.functional.cross_entropy(logits_of(mean, images.reshape(-1, side, side, ch)), labels.reshape(-1).long())
+    assert abs(eval_loss - ref.item()) <= 1e-5 * max(1.0, ref.item())
