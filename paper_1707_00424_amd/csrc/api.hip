@@ -455,10 +455,15 @@ parle_status parle_eval(parle_ctx *ctx, int32_t which, const float *images_dev, 
         bn_row = (const float *)ctx->buf.bn_stats + (int64_t)which * per;
       }
     }
-    e = net_eval(ctx->net, ctx->stream, row, bn_row, net_ws(ctx), images_dev, labels_dev, count, d_loss, d_nerr);
+    int partials = 0;
+    if (spread_host)
+      if (parle_status s = parle_internal_spread_partial(ctx->stream, c.n_replicas, ctx->sizes.n_pad, replica_rows(ctx), ctx->buf.x_ref, (double *)hdr, &partials))
+        return fail(ctx, s, "spread launch failed");
+    e = net_eval(ctx->net, ctx->stream, row, bn_row, net_ws(ctx), images_dev, labels_dev, count, d_loss, d_nerr, (const double *)hdr, partials,
+                 spread_host ? d_spread : nullptr);
     if (e != hipSuccess) return hip_fail(ctx, e, "eval forward");
   }
-  if (spread_host) {
+  if (spread_host && flat) {
     parle_status s = parle_k_spread(ctx->stream, c.n_replicas, ctx->sizes.n_pad, replica_rows(ctx), ctx->buf.x_ref,
                                     (double *)hdr, d_spread);
     if (s) return fail(ctx, s, "spread launch failed");

@@ -83,6 +83,22 @@ struct InnerState {
   InnerCoeffs c;
 };
 
+// out[0] = sum of the `count` partial sums of the ensemble spread, by the first four wavefronts of a workgroup; `lds`: four doubles
+__device__ __forceinline__ void spread_sum(const double *partial, int count, float *out, double *lds) {
+  constexpr int kWaves = 4, kLanes = kWaves * PARLE_WAVE;
+  double acc = 0.0;
+  if (threadIdx.x < kLanes)
+    for (int i = threadIdx.x; i < count; i += kLanes) acc += partial[i];
+  acc = wave_sum(acc);
+  if (threadIdx.x < kLanes && (threadIdx.x & (PARLE_WAVE - 1)) == 0) lds[threadIdx.x / PARLE_WAVE] = acc;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double s = 0.0;
+    for (int w = 0; w < kWaves; ++w) s += lds[w];
+    out[0] = (float)s;
+  }
+}
+
 // Text behind parle_last_error(NULL) for entry points that have no context (calling thread only).
 void parle_internal_set_error(const std::string &msg);
 
@@ -95,6 +111,8 @@ parle_status parle_internal_to_bf16(hipStream_t st, const float *src, void *dst,
 // override the by-value multipliers (a captured launch cannot change its arguments).  NULL = use the
 // arguments.
 parle_status parle_internal_set_coupling(hipStream_t st, float *coupling_dev, float g, float r);
+// The first kernel of parle_k_spread: *count partial sums, for spread_sum.
+parle_status parle_internal_spread_partial(hipStream_t st, int32_t n, int64_t n_pad, const float *x, const float *x_ref, double *partial_dev, int *count);
 // The inner-step counter in device memory: set it, add one to it (one-thread kernels).
 parle_status parle_internal_set_step(hipStream_t st, long long *step_dev, long long k);
 parle_status parle_internal_advance_step(hipStream_t st, long long *step_dev);

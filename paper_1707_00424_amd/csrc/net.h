@@ -26,9 +26,10 @@ hipError_t net_train_step(Net *net, hipStream_t st, const float *params, const v
 
 // Enqueues a forward pass of ONE parameter row over `count` images in evaluation mode (BN uses
 // `bn_row`, the statistics of one replica or their average).  Results: loss_sum_dev[0] = sum of
-// the per-sample losses, n_err_dev[0] = misclassified count.
+// the per-sample losses, n_err_dev[0] = misclassified count; with spread_dev, the sum of the spread's partial sums (spread_sum).
 hipError_t net_eval(Net *net, hipStream_t st, const float *param_row, const float *bn_row, void *workspace,
-                    const float *images, const int32_t *labels, int count, float *loss_sum_dev, int32_t *n_err_dev);
+                    const float *images, const int32_t *labels, int count, float *loss_sum_dev, int32_t *n_err_dev,
+                    const double *spread_partial, int spread_count, float *spread_dev);
 
 // Averages the per-replica BN running statistics into out_row (device, bn floats per replica).
 hipError_t net_average_bn(Net *net, hipStream_t st, const float *bn_stats, float *out_row);

@@ -1015,7 +1015,8 @@ hipError_t net_train_step(Net *net, hipStream_t st, const float *params, const v
 }
 
 hipError_t net_eval(Net *net, hipStream_t st, const float *param_row, const float *bn_row, void *workspace,
-                    const float *images, const int32_t *labels, int count, float *loss_sum_dev, int32_t *n_err_dev) {
+                    const float *images, const int32_t *labels, int count, float *loss_sum_dev, int32_t *n_err_dev,
+                    const double *spread_partial, int spread_count, float *spread_dev) {
   Net &N = *net;
   char *ws = (char *)workspace;
   const void *row_t = param_row;
@@ -1031,7 +1032,7 @@ hipError_t net_eval(Net *net, hipStream_t st, const float *param_row, const floa
   }
   HIP_TRY(forward(r, false, nullptr, bn_row));
   const Tensor &tl = N.tensors[N.t_logits];
-  return launch_softmax_xent_eval(st, count, tl.C, (const float *)r.tptr(N.t_logits), labels, loss_sum_dev, n_err_dev);
+  return launch_eval_finish(st, count, tl.C, (const float *)r.tptr(N.t_logits), labels, loss_sum_dev, n_err_dev, spread_partial, spread_count, spread_dev);
 }
 
 hipError_t net_average_bn(Net *net, hipStream_t st, const float *bn_stats, float *out_row) {

@@ -24,8 +24,8 @@ hipError_t launch_gap_head(hipStream_t st, int dtype, int n, int B, int HW, int 
                            const int32_t *labels, float *loss_img, void *dlogits, long long dl_rs, void *dfeat,
                            long long dfeat_rs);
 hipError_t launch_loss_mean(hipStream_t st, int n, int B, const float *loss_img, float *loss_out);
-hipError_t launch_softmax_xent_eval(hipStream_t st, int count, int C, const float *logits, const int32_t *labels,
-                                    float *loss_sum, int32_t *n_err);
+hipError_t launch_eval_finish(hipStream_t st, int count, int C, const float *logits, const int32_t *labels, float *loss_sum, int32_t *n_err,
+                              const double *spread_partial, int spread_count, float *spread);
 
 // 2x2 max-pool, stride 2, floor.  in [n][B,H,W,C] -> out [n][B,H/2,W/2,C].
 hipError_t launch_maxpool_fwd(hipStream_t st, int dtype, int n, int B, int H, int W, int C, const void *in,

@@ -332,16 +332,7 @@ __global__ __launch_bounds__(kThreads) void k_spread_partial(const f4 *__restric
 __global__ __launch_bounds__(kThreads) void k_spread_final(const double *__restrict__ partial, int count,
                                                            float *__restrict__ out) {
   __shared__ double lds[kThreads / PARLE_WAVE];
-  double acc = 0.0;
-  for (int i = threadIdx.x; i < count; i += kThreads) acc += partial[i];
-  acc = wave_sum(acc);
-  if ((threadIdx.x & (PARLE_WAVE - 1)) == 0) lds[threadIdx.x / PARLE_WAVE] = acc;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double s = 0.0;
-    for (int w = 0; w < kThreads / PARLE_WAVE; ++w) s += lds[w];
-    out[0] = (float)s;
-  }
+  spread_sum(partial, count, out, lds);
 }
 
 int num_cus() {
@@ -459,6 +450,19 @@ parle_status parle_internal_inner_update(hipStream_t st, int32_t n, int64_t n_pa
   }
 #undef PICK_INNER
 #undef LAUNCH_INNER
+  return launched();
+}
+
+parle_status parle_internal_spread_partial(hipStream_t st, int32_t n, int64_t n_pad, const float *x, const float *x_ref, double *partial_dev, int *count) {
+  if (parle_status s = check_flat_args(n, n_pad)) return s;
+  if (!x || !x_ref || !partial_dev) return PARLE_EINVAL;
+  if (!aligned_to(x, 16) || !aligned_to(x_ref, 16) || !aligned_to(partial_dev, 8)) return PARLE_EALIGN;
+  const int64_t np4 = n_pad / 4;
+  int64_t blocks = (np4 + kThreads - 1) / kThreads;
+  if (blocks > kSpreadBlocks) blocks = kSpreadBlocks;
+  *count = (int)blocks;
+  hipLaunchKernelGGL(k_spread_partial, dim3((int)blocks), dim3(kThreads), 0, st, (const f4 *)x, (const f4 *)x_ref, n,
+                     np4, partial_dev);
   return launched();
 }
 
@@ -610,15 +614,11 @@ parle_status parle_k_outer_update(void *hip_stream, int32_t n, int64_t n_pad, fl
 parle_status parle_k_spread(void *hip_stream, int32_t n, int64_t n_pad, const float *x, const float *x_ref,
                             double *partial_dev, float *out_dev) {
   if (parle_status s = check_flat_args(n, n_pad)) return s;
-  if (!x || !x_ref || !partial_dev || !out_dev) return PARLE_EINVAL;
-  if (!aligned_to(x, 16) || !aligned_to(x_ref, 16) || !aligned_to(partial_dev, 8)) return PARLE_EALIGN;
-  const int64_t np4 = n_pad / 4;
-  int64_t blocks = (np4 + kThreads - 1) / kThreads;
-  if (blocks > kSpreadBlocks) blocks = kSpreadBlocks;
+  if (!out_dev) return PARLE_EINVAL;
   hipStream_t st = (hipStream_t)hip_stream;
-  hipLaunchKernelGGL(k_spread_partial, dim3((int)blocks), dim3(kThreads), 0, st, (const f4 *)x, (const f4 *)x_ref, n,
-                     np4, partial_dev);
-  hipLaunchKernelGGL(k_spread_final, dim3(1), dim3(kThreads), 0, st, (const double *)partial_dev, (int)blocks, out_dev);
+  int count = 0;
+  if (parle_status s = parle_internal_spread_partial(st, n, n_pad, x, x_ref, partial_dev, &count)) return s;
+  hipLaunchKernelGGL(k_spread_final, dim3(1), dim3(kThreads), 0, st, (const double *)partial_dev, count, out_dev);
   return launched();
 }
 
