@@ -429,8 +429,11 @@ hipError_t launch_igemm(hipStream_t st, int dtype, bool out_f32, int replicas, c
     if (smallk) S = conv_smallk_stat_splits(g, out_f32);
     if (halo) S = conv_halo_stat_splits(g, io_in, replicas);
     if (fast) S = igemm_fast_stat_splits(dtype, out_f32, g, io_in);
+    const bool s2 = S > 0 && !smallk && dtype == 1 && !out_f32 && patch_s2_applicable(g, io_in);
+    if (s2) S = patch_s2_stat_splits(replicas, g, io_in);
     if (S > 0 && S <= io_in.stat_capacity) {
       *stat_splits = S;
+      if (s2) return launch_patch_s2(st, replicas, g, io_in);
       if (smallk) return launch_conv_smallk(st, dtype, out_f32, replicas, g, io_in);
       if (halo) return launch_conv_halo(st, replicas, g, io_in);
       return launch_igemm_fast(st, dtype, out_f32, replicas, g, io_in);

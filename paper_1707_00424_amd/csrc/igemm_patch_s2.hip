@@ -1,4 +1,4 @@
-// Evaluation of a stride-2 3x3 convolution with padding 1 (bf16, channel counts in multiples of 8): operands loaded straight
+// Forward pass of a stride-2 3x3 convolution with padding 1 (bf16, channel counts in multiples of 8): operands loaded straight
 // into LDS, several tiles per workgroup and the epilogue in registers, as in igemm_patch.hip.
 //
 // The input of such a layer is four images, its pixels by the parity of row and column, and the layer is the sum of four
@@ -51,6 +51,12 @@ __device__ __forceinline__ uint32_t fdivc(uint32_t n, __attribute__((address_spa
 constexpr int kTapR[9] = {0, 0, 2, 2, 1, 0, 2, 1, 1}, kTapS[9] = {0, 2, 0, 2, 1, 1, 1, 0, 2};
 constexpr int kTapBuf[9] = {0, 0, 0, 0, 1, 2, 2, 0, 0};  // patch buffer, counted from that of the chunk's first class
 
+// another lane's value: quad permutation, or mirrored within 8 (0x141) or 16 lanes (0x140)
+template <int CTRL>
+__device__ __forceinline__ float row_lane(float v) {
+  return __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), CTRL, 0xf, 0xf, true));
+}
+
 template <int TM, int H_IT>
 struct S2Pieces {  // wavefront loads of patches issued in each step
   static constexpr int kHalf = (H_IT + 1) / 2;
@@ -61,8 +67,8 @@ struct S2Pieces {  // wavefront loads of patches issued in each step
 };
 
 // TM: 32-pixel tiles per wavefront (four wavefronts: 128 or 256 outputs); TN: 32-channel tiles; D: weight tiles in flight;
-// H_IT: wavefront loads of a patch per wavefront; NORM: io.bn_out.
-template <int TM, int TN, int D, int H_IT, bool NORM>
+// H_IT: wavefront loads of a patch per wavefront; NORM: io.bn_out; STAT: io.stat, a partial row per tile.
+template <int TM, int TN, int D, int H_IT, bool NORM, bool STAT>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TM == 1 ? 3 : 2))) void k_patch_s2(const S2Args) {
   typedef bf16_t T;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
@@ -79,7 +85,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TM == 
   const int cv = (lane & 3) ^ ((lane >> 4) & 3);  // channel vector this lane loads
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
   const int pbytes = (args->sg.slots + 15) / 16 * 16 * kPix;
-  const int wring = 3 * pbytes, lbias = wring + NB * TB, ldump = lbias + 1024, lnorm = ldump + 1024;
+  const int wring = 3 * pbytes, lbias = wring + NB * TB, ldump = lbias + 1024, lnorm = ldump + 1024;  // NORM or STAT: from lnorm
   const int Cc = args->g.Cc, chunks = (Cc + 31) >> 5;
   const int b_l = (lane & 31) * kPix + ((h ^ ((lane >> 2) & 3)) << 4);
   int n0;
@@ -236,6 +242,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TM == 
     const bool relu = a->io.relu;
     const int m0 = tile * a->sg.TH * a->g.Q, mend = min(a->g.M, m0 + a->sg.TH * a->g.Q), ldc = a->io.ldc, N = a->g.N;
     const __amdgpu_buffer_rsrc_t o_rsrc = out_like(a, a->io.out, rep), n_rsrc = out_like(a, NORM ? a->io.bn_out : nullptr, rep);
+    float sums[STAT ? TN : 1][2][8] = {};  // of what this lane stores, and of its squares
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
@@ -261,6 +268,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TM == 
           const int m = m0 + wave * (TM * 32) + tm * 32 + j * 16 + (lane & 15), n = n0 + tn * 32 + chan;
           const uint32_t at = m < mend && n < N ? ((uint32_t)m * (uint32_t)ldc + (uint32_t)n) * 2u : kOob;
           if (!NORM || !a->io.bn_only) __builtin_amdgcn_raw_buffer_store_b128(o, o_rsrc, at, 0, 0);
+          if constexpr (STAT) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              const float x = m < mend ? __uint_as_float(e & 1 ? o[e >> 1] & 0xffff0000u : o[e >> 1] << 16) : 0.f;
+              sums[tn][0][e] += x, sums[tn][1][e] += x * x;
+            }
+          }
           if constexpr (NORM) {
             const char *p = smem + lnorm + (tn * 32 + chan) * 4;  // means, 1/sigma, gamma, beta of the column block
             u4 r;
@@ -281,6 +295,28 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TM == 
           }
         }
       }
+    if constexpr (STAT) {
+      // over the sixteen lanes that share channels, then over the wavefronts, in a fixed order
+      float *ws = (float *)(smem + lnorm);  // [wavefront][sums, squares][column]
+#pragma unroll
+      for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            float v = sums[tn][k][e];
+            v += row_lane<0xb1>(v), v += row_lane<0x4e>(v), v += row_lane<0x141>(v), v += row_lane<0x140>(v);
+            if ((lane & 15) == 0) ws[(wave * 2 + k) * BN + tn * 32 + chan + e] = v;
+          }
+      meet();
+      if (tid < 2 * BN) {
+        const int k = tid / BN, n = n0 + tid - k * BN;
+        float v = ws[tid];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) v += ws[w * 2 * BN + tid];
+        if (n < N) a->io.stat[(((long long)rep * a->dRep.d + tile) * 2 + k) * ldc + n] = v;
+      }
+    }
   };
 
   typedef std::integral_constant<int, 0> EE;
@@ -396,10 +432,10 @@ bool make_s2_geom(const ConvGeom &g, int outputs, int max_slots, S2Geom &sg) {
   return true;
 }
 
-template <int TM, int TN, int D, int H_IT, bool NORM>
+template <int TM, int TN, int D, int H_IT, bool NORM, bool STAT>
 hipError_t run_as(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io, const S2Geom &sg) {
   constexpr int kCus = 256, kLdsOfCu = 160 * 1024, kWaves = TM == 1 ? 3 : 2;
-  const int lds = 3 * ((sg.slots + 15) / 16 * 16 * kPix) + (D + 1) * TN * 32 * kPix + 2048 + (NORM ? TN * 32 * 16 : 0);
+  const int lds = 3 * ((sg.slots + 15) / 16 * 16 * kPix) + (D + 1) * TN * 32 * kPix + 2048 + (NORM ? TN * 32 * 16 : STAT ? TN * 32 * 32 : 0);
   const int resident = kCus * (kLdsOfCu / lds < kWaves ? kLdsOfCu / lds : kWaves);
   const int nb = (g.N + TN * 32 - 1) / (TN * 32), rep_tiles = (sg.rows + sg.TH - 1) / sg.TH, tiles = rep_tiles * replicas;
   const long long items = (long long)((tiles + 7) / 8 * 8) * nb;
@@ -408,14 +444,17 @@ hipError_t run_as(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO 
   const int step = 8 * nb;
   if (items > resident && step <= resident) a.groups = resident / step * step;
   static const hipError_t lds_ok =
-      hipFuncSetAttribute((const void *)k_patch_s2<TM, TN, D, H_IT, NORM>, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsOfCu);
+      hipFuncSetAttribute((const void *)k_patch_s2<TM, TN, D, H_IT, NORM, STAT>, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsOfCu);
   if (lds_ok != hipSuccess) return lds_ok;
-  hipLaunchKernelGGL((k_patch_s2<TM, TN, D, H_IT, NORM>), dim3(a.groups), dim3(kThreads), lds, st, a);
+  hipLaunchKernelGGL((k_patch_s2<TM, TN, D, H_IT, NORM, STAT>), dim3(a.groups), dim3(kThreads), lds, st, a);
   return hipGetLastError();
 }
 template <int TM, int TN, int D, int H_IT>
 hipError_t run(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io, const S2Geom &sg) {
-  return io.bn_out ? run_as<TM, TN, D, H_IT, true>(st, replicas, g, io, sg) : run_as<TM, TN, D, H_IT, false>(st, replicas, g, io, sg);
+  if (io.bn_out) return run_as<TM, TN, D, H_IT, true, false>(st, replicas, g, io, sg);
+  if constexpr (TN == 2)
+    if (io.stat) return run_as<TM, TN, D, H_IT, false, true>(st, replicas, g, io, sg);
+  return run_as<TM, TN, D, H_IT, false, false>(st, replicas, g, io, sg);
 }
 
 }  // namespace
@@ -423,25 +462,47 @@ hipError_t run(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io
 bool patch_s2_applicable(const ConvGeom &g, const GemmIO &io) {
   S2Geom sg;
   return g.R == 3 && g.S == 3 && g.sp == 2 && g.off == -1 && g.sr == 1 && g.dshift == 0 && g.P == (g.Hin + 1) / 2 && g.Q == (g.Win + 1) / 2 &&
-         g.Cc % 8 == 0 && g.N % 8 == 0 && io.ldc % 8 == 0 && io.vecA && io.vecB && !io.stat && !io.resid && !io.mask && !io.accumulate && !io.in_f32 && io.any_order &&
+         g.Cc % 8 == 0 && g.N % 8 == 0 && io.ldc % 8 == 0 && io.vecA && io.vecB && !(io.stat && io.bn_out) && !io.resid && !io.mask && !io.accumulate && !io.in_f32 && io.any_order &&
          aligned_to(io.out, 16) && io.out_rs % 8 == 0 && aligned_to(io.bn_out, 16) && io.in_bytes > 0 && io.in_bytes < (1LL << 31) &&
          (long long)g.M * io.ldc * 4 < (1LL << 31) && (long long)g.N * g.K * 2 < (1LL << 31) && make_s2_geom(g, 128, 192, sg);
 }
 
-hipError_t launch_patch_s2(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io) {
-  S2Geom wide, half;
-  if (!make_s2_geom(g, 128, 192, half)) return hipErrorInvalidValue;
-  // 96- or 64-wide column blocks, whichever pad the output channels least.  256 outputs with two workgroups per compute unit, as
-  // far as three patches and the weight tiles fit; 128 with three where the wide ones would leave compute units empty (us, 256 /
-  // 128 outputs, 3 x 128 images: 64 -> 128 on 32 x 32, 768 wide workgroups, 24 / 27; 160 -> 320, 1920, 101 / 126; 192 -> 192 on
-  // 16 x 16, 192, 26.2 / 25.8; 8 x 16 images of 256 -> 256 on 14 x 14, 128, 24 / 21; 5 x 40 of 320 -> 96 on 8 x 8, 15, 35 / 25).
-  const bool tn3 = (g.N + 95) / 96 * 96 <= (g.N + 63) / 64 * 64;
+namespace {
+struct S2Shape {
+  int tm, tn, d;
+  S2Geom sg;
+};
+bool choose_s2(int replicas, const ConvGeom &g, const GemmIO &io, S2Shape &v) {
+  S2Geom wide;
+  if (!make_s2_geom(g, 128, 192, v.sg)) return false;
+  // 96- or 64-wide column blocks, whichever pad the output channels least (64 with column sums).  256 outputs with two workgroups
+  // per compute unit, as far as three patches and the weight tiles fit; 128 with three where the wide ones would leave compute
+  // units empty (us, 256 / 128 outputs, 3 x 128 images: 64 -> 128 on 32 x 32, 768 wide workgroups, 24 / 27; 160 -> 320, 1920, 101 /
+  // 126; 192 -> 192 on 16 x 16, 192, 26.2 / 25.8; 8 x 16 images of 256 -> 256 on 14 x 14, 128, 24 / 21; 5 x 40 of 320 -> 96 on 8 x 8,
+  // 15, 35 / 25).
+  const bool tn3 = !io.stat && (g.N + 95) / 96 * 96 <= (g.N + 63) / 64 * 64;
   auto wide_fits = [&](int max_slots) {
     return make_s2_geom(g, 256, max_slots, wide) &&
            (long long)((wide.rows + wide.TH - 1) / wide.TH) * replicas * ((g.N + (tn3 ? 95 : 63)) / (tn3 ? 96 : 64)) > 256;
   };
-  if (tn3 && wide_fits(320)) return run<2, 3, 2, 5>(st, replicas, g, io, wide);
-  if (!tn3 && wide_fits(304)) return run<2, 2, 3, 5>(st, replicas, g, io, wide);
-  if (!tn3 && wide_fits(336)) return run<2, 2, 2, 6>(st, replicas, g, io, wide);
-  return tn3 ? run<1, 3, 2, 3>(st, replicas, g, io, half) : run<1, 2, 3, 3>(st, replicas, g, io, half);
+  v.tm = 1, v.tn = tn3 ? 3 : 2, v.d = tn3 ? 2 : 3;
+  if (wide_fits(tn3 ? 320 : 304))
+    v.tm = 2, v.sg = wide;
+  else if (!tn3 && wide_fits(336))
+    v.tm = 2, v.d = 2, v.sg = wide;
+  return true;
+}
+}  // namespace
+
+int patch_s2_stat_splits(int replicas, const ConvGeom &g, const GemmIO &io) {
+  S2Shape v;
+  return patch_s2_applicable(g, io) && choose_s2(replicas, g, io, v) ? (v.sg.rows + v.sg.TH - 1) / v.sg.TH : 0;
+}
+
+hipError_t launch_patch_s2(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io) {
+  S2Shape v;
+  if (!choose_s2(replicas, g, io, v)) return hipErrorInvalidValue;
+  if (v.tn == 3) return v.tm == 2 ? run<2, 3, 2, 5>(st, replicas, g, io, v.sg) : run<1, 3, 2, 3>(st, replicas, g, io, v.sg);
+  if (v.tm == 2) return v.d == 3 ? run<2, 2, 3, 5>(st, replicas, g, io, v.sg) : run<2, 2, 2, 6>(st, replicas, g, io, v.sg);
+  return run<1, 2, 3, 3>(st, replicas, g, io, v.sg);
 }
