@@ -7,7 +7,7 @@
 // wavefront takes eight windows of four outputs at a time, and the maximum of a window is taken between the four lanes that
 // hold it.  What is kept for the backward pass is one byte per pooled value: which of the four it was, or that it has no
 // gradient.  A matrix instruction (32 x 32 x 2) reads one value of LDS per lane, weights stay in registers.  us, before -> now:
-// forward 36 -> 18, backward 55 -> 19 (alone), LeNet's step 313 -> 275.  Matrix work is 5 us in each direction; the rest goes on
+// forward 36 -> 18, backward 55 -> 19 (alone), LeNet's step 313 -> 265.  Matrix work is 5 us in each direction; the rest goes on
 // vector work (45 instructions per four windows' maxima and 32 channels' group) and on a workgroup's start and end.
 #include "igemm_dev.h"
 
@@ -17,6 +17,7 @@ using namespace igemm_dev;
 
 constexpr int kTaps = 32;      // window values of a matrix tile
 constexpr int kNoGrad = 4;     // code of a window whose maximum the ReLU cut off
+constexpr int kBatch = 4;      // values per thread requested at a time on their way to LDS
 
 struct PoolGeom {
   int H, W, C, S;   // image, window side
@@ -42,8 +43,23 @@ __global__ __launch_bounds__(kThreads) void k_convpool(const PoolGeom g, const f
   const int b = blockIdx.x, rep = blockIdx.y;
   const float *xp = x + rep * x_rs + (long long)b * g.image;
   float *ws = img + g.image;
-  for (int i = tid; i < g.image; i += kThreads) img[i] = xp[i];
-  for (int i = tid; i < g.N * g.K; i += kThreads) ws[i] = w[rep * w_rs + i];
+  // all loads of a batch are on their way before the first is waited for (a workgroup works for about 3 us, and each round of
+  // requests costs it most of one; LeNet's step, here and in the weight gradient, 269.4 -> 265.0 us against one load at a time)
+  for (int base = tid; base < max(g.image, g.N * g.K); base += kBatch * kThreads) {
+    float xv[kBatch], wv[kBatch];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const int i = base + u * kThreads;
+      xv[u] = i < g.image ? xp[i] : 0.f;
+      wv[u] = i < g.N * g.K ? w[rep * w_rs + i] : 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const int i = base + u * kThreads;
+      if (i < g.image) img[i] = xv[u];
+      if (i < g.N * g.K) ws[i] = wv[u];
+    }
+  }
   const int pos = lane & 3, chan = 8 * pos + 4 * h;
   float bv[4];  // of the channels that this lane stores
 #pragma unroll
@@ -128,8 +144,24 @@ __global__ __launch_bounds__(kThreads) void k_convpool_wgrad(const PoolGeom g, i
     const float *xp = x + rep * x_rs + (long long)b * g.image, *dpp = dp + rep * dp_rs + (long long)b * pooled;
     const unsigned char *cp = code + rep * dp_rs + (long long)b * pooled;
     __syncthreads();  // the image before has been read
-    for (int i = tid; i < g.image; i += kThreads) img[i] = xp[i];
-    for (int i = tid; i < pooled / 4; i += kThreads) ((f4 *)gr)[i] = ((const f4 *)dpp)[i], ((uint32_t *)cd)[i] = ((const uint32_t *)cp)[i];
+    for (int base = tid; base < max(g.image, pooled / 4); base += kBatch * kThreads) {
+      float xv[kBatch];
+      f4 gv[kBatch];
+      uint32_t cv[kBatch];
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) {
+        const int i = base + u * kThreads;
+        xv[u] = i < g.image ? xp[i] : 0.f;
+        gv[u] = i < pooled / 4 ? ((const f4 *)dpp)[i] : f4{0.f, 0.f, 0.f, 0.f};
+        cv[u] = i < pooled / 4 ? ((const uint32_t *)cp)[i] : 0u;
+      }
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) {
+        const int i = base + u * kThreads;
+        if (i < g.image) img[i] = xv[u];
+        if (i < pooled / 4) ((f4 *)gr)[i] = gv[u], ((uint32_t *)cd)[i] = cv[u];
+      }
+    }
     __syncthreads();
     for (int ph = wave; ph < P2; ph += 4) {
       const float *px = img + (2 * ph * g.W + h) * g.C + off, *gp = gr + ph * g.Q2 * g.N + nc;
