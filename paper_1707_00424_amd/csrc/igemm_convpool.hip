@@ -34,6 +34,8 @@ __device__ __forceinline__ float quad(float v) {
 }
 constexpr int kXor1 = 0xb1, kXor2 = 0x4e;  // quad permutations [1 0 3 2] and [2 3 0 1]
 
+constexpr int step_value(int i) { return 8 * (i / 4) + i % 4; }
+
 // One workgroup per image.  out, code: [window][N].
 __global__ __launch_bounds__(kThreads) void k_convpool(const PoolGeom g, const float *__restrict__ x, long long x_rs, const float *__restrict__ w,
                                                        long long w_rs, const float *__restrict__ bias, long long bias_rs,
@@ -65,14 +67,15 @@ __global__ __launch_bounds__(kThreads) void k_convpool(const PoolGeom g, const f
 #pragma unroll
   for (int e = 0; e < 4; ++e) bv[e] = chan < g.N ? bias[rep * bias_rs + chan + e] : 0.f;
   __syncthreads();
-  // step i multiplies window values 2 i + h
+  // Step i multiplies window values step_value(i) + 4 h: the order of sums of the convolution without a pool (k_conv_smallk), so
+  // that the output of a window that is the largest there, be it by the last bit, is the largest here.
   float wr[kTaps / 2];
   int off[kTaps / 2];
 #pragma unroll
   for (int i = 0; i < kTaps / 2; ++i) {
-    const int k = 2 * i + h;
+    const int k = step_value(i) + 4 * h;
     wr[i] = n < g.N && k < g.K ? ws[n * g.K + k] : 0.f;
-    off[i] = h ? g.off[2 * i + 1] : g.off[2 * i];
+    off[i] = h ? g.off[step_value(i) + 4] : g.off[step_value(i)];
   }
   float *op = out + rep * out_rs + (long long)b * g.windows * g.N;
   unsigned char *cp = code ? code + rep * out_rs + (long long)b * g.windows * g.N : nullptr;
@@ -85,9 +88,9 @@ __global__ __launch_bounds__(kThreads) void k_convpool(const PoolGeom g, const f
     for (int v = 0; v < 16; ++v) acc[v] = 0.f;
 #pragma unroll
     for (int i = 0; i < kTaps / 2; ++i)
-      if (2 * i < g.K) {
+      if (step_value(i) < g.K) {
         float t = px[off[i]];
-        if (2 * i + 1 >= g.K) t = h ? 0.f : t;  // half of the last step may lie beyond the window
+        if (step_value(i) + 4 >= g.K) t = h ? 0.f : t;  // that half of the step lies beyond the window
         acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wr[i], t, acc, 0, 0, 0);
       }
     // Lane: one output pixel, channels 8 * (v / 4) + 4 h + v % 4.  The four lanes of a window exchange registers until each has

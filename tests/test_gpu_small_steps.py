@@ -145,3 +145,52 @@ def test_first_layer_with_its_pool(gpu, case):
         mean = {key: t.double() for key, t in _segments(pb, cfg, x0.double().mean(0).float()).items()}
         ref = torch.nn.functional.cross_entropy(logits_of(mean, images.reshape(-1, side, side, ch)), labels.reshape(-1).long())
     assert abs(eval_loss - ref.item()) <= 1e-5 * max(1.0, ref.item())
+
+
+@pytest.mark.parametrize("case", [
+    # n, batch, image side, channels, first layer's outputs, window: LeNet's own, windows of 9, 16 and 27 values
+    (6, 128, 28, 1, 20, 5), (3, 100, 17, 1, 16, 3), (2, 150, 21, 1, 12, 4), (2, 120, 16, 3, 32, 3)])
+def test_first_layer_takes_the_largest_output_of_the_convolution_alone(gpu, case):
+    """Images that repeat themselves after a window's side, and every second output channel with equal weights: the four outputs of
+    such a channel under a pool window are sums of the same products in four orders, and rounding decides which one is the largest.
+    The layer by itself (convolution, bias and ReLU) says which one gets the gradient, in the network as well."""
+    torch, pb = gpu
+    from paper_1707_00424_amd import synth
+    n, batch, side, ch, c1, k = case
+    gen = torch.Generator(device="cuda").manual_seed(sum(case))
+    cfg = pb.make_config(model=pb.MODEL_LENET, n_replicas=n, batch=batch, in_h=side, in_w=side, in_c=ch, n_classes=10, arch=(c1, 12, k, 24),
+                         eta_inner=0.05, eta_outer=0.1, gamma0=0.3, rho0=1.0)
+    layout = pb.parle_query_layout(cfg)
+    x0 = torch.stack([torch.as_tensor(synth.init_params(layout, 3 + a, "uniform")) for a in range(n)]).cuda()
+    for a in range(n):
+        _segments(pb, cfg, x0[a])["conv1.w"].reshape(c1, -1)[::2] = torch.rand((c1 // 2, 1), generator=gen, device="cuda") * 0.1 + 0.05
+    P = pb.Parle(cfg, x0.contiguous())
+    reps = side // k + 1
+    images = torch.rand((n, batch, k, k, ch), generator=gen, device="cuda").repeat(1, 1, reps, reps, 1)[:, :, :side, :side].contiguous()
+    labels = torch.randint(0, 10, (n, batch), generator=gen, device="cuda").int()
+    P.parle_inner_step(images, labels, torch.empty(n, device="cuda"))
+
+    out = side - k + 1
+    w, bias = (torch.stack([_segments(pb, cfg, x0[a])[name] for a in range(n)]).contiguous() for name in ("conv1.w", "conv1.b"))
+    y = torch.empty((n, batch, out, out, c1), device="cuda")
+    pb.parle_k_conv_forward(pb.parle_conv_desc(0, n, batch, side, side, ch, c1, k, 1, 0), images, w, bias, None, 1, y)
+    half = out // 2
+    win = y[:, :, :2 * half, :2 * half].reshape(n, batch, half, 2, half, 2, c1).permute(0, 1, 2, 4, 6, 3, 5).reshape(n, batch, half, half, c1, 4)
+    pooled = win.amax(-1)
+    assert ((win - pooled[..., None]).abs() < 1e-5).sum(-1)[..., ::2].min() == 4 and (win != pooled[..., None]).any()
+    at = (win == pooled[..., None]).int().argmax(-1)  # the first of equals
+    for a in range(n):
+        seg = {key: t.double() for key, t in _segments(pb, cfg, x0[a]).items()}
+        p = pooled[a].double().requires_grad_(True)
+        x = torch.nn.functional.conv2d(p.permute(0, 3, 1, 2).cpu(), seg["conv2.w"].permute(0, 3, 1, 2).cpu(), seg["conv2.b"].cpu()).relu()
+        h = torch.nn.functional.max_pool2d(x, 2).permute(0, 2, 3, 1).reshape(batch, -1).cuda()
+        h = (h @ seg["fc1.w"].reshape(seg["fc1.b"].numel(), -1).t() + seg["fc1.b"]).relu()
+        loss = torch.nn.functional.cross_entropy(h @ seg["fc2.w"].reshape(10, -1).t() + seg["fc2.b"], labels[a].long())
+        dp = torch.autograd.grad(loss, p)[0] * (pooled[a] > 0)
+        dy = torch.zeros(win[a].shape, dtype=torch.float64, device="cuda").scatter_(-1, at[a][..., None], dp[..., None])
+        dy = dy.reshape(batch, half, half, c1, 2, 2).permute(0, 1, 4, 2, 5, 3).reshape(-1, c1)
+        xd = images[a].double()
+        cols = torch.stack([xd[:, r:r + 2 * half, c:c + 2 * half] for r in range(k) for c in range(k)], 3).reshape(dy.shape[0], -1)
+        ref, got = dy.t() @ cols, _segments(pb, cfg, P.grad[a])["conv1.w"].reshape(c1, -1)
+        # fp32 sums; one window's gradient given to another output shows as 1e-4 and more of its channel's
+        assert ((got.double() - ref).norm(dim=1) <= 2e-5 * ref.norm(dim=1) + 1e-9).all().item(), a
