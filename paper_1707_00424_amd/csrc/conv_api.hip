@@ -39,7 +39,6 @@ parle_status parle_k_conv_forward(void *hip_stream, const parle_conv_desc *desc,
   io.bias = bias, io.bias_rs = g.N;
   io.resid = resid, io.resid_rs = io.out_rs;
   io.relu = relu;
-  io.any_order = 1;
   io.vecA = (c.Cin % vw == 0) && (io.in_rs % vw == 0);
   io.vecB = (g.K % vw == 0);
   io.in_bytes = io.in_rs * es;
@@ -65,7 +64,6 @@ parle_status parle_k_conv_forward_colsums(void *hip_stream, const parle_conv_des
   io.vecB = (g.K % vw == 0);
   io.in_bytes = io.in_rs * es;
   io.stat = partial, io.stat_capacity = capacity;
-  io.any_order = 1;
   int S = 0;
   if (launch_igemm((hipStream_t)hip_stream, desc->dtype, false, desc->n, g, io, &S) != hipSuccess) return PARLE_EHIP;
   *splits_host = S;

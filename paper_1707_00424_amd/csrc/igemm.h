@@ -77,10 +77,6 @@ struct GemmIO {
   void *bn_out;
   const float *bn_gamma, *bn_beta, *bn_running;
   int bn_only;
-  // An output's products may be added in another order than by the kernels that a training step runs.  There they may not: 3 in
-  // 100 000 bf16 roundings of a layer turn, which two steps of a network amplify to 2 to 9 % of its gradient (All-CNN, 16 to 128
-  // images), so that runs of the same seed drift apart for 2 % of a step's time.
-  int any_order;
 };
 
 struct WgradIO {

@@ -429,11 +429,8 @@ hipError_t launch_igemm(hipStream_t st, int dtype, bool out_f32, int replicas, c
     if (smallk) S = conv_smallk_stat_splits(g, out_f32);
     if (halo) S = conv_halo_stat_splits(g, io_in, replicas);
     if (fast) S = igemm_fast_stat_splits(dtype, out_f32, g, io_in);
-    const bool s2 = S > 0 && !smallk && dtype == 1 && !out_f32 && patch_s2_applicable(g, io_in);
-    if (s2) S = patch_s2_stat_splits(replicas, g, io_in);
     if (S > 0 && S <= io_in.stat_capacity) {
       *stat_splits = S;
-      if (s2) return launch_patch_s2(st, replicas, g, io_in);
       if (smallk) return launch_conv_smallk(st, dtype, out_f32, replicas, g, io_in);
       if (halo) return launch_conv_halo(st, replicas, g, io_in);
       return launch_igemm_fast(st, dtype, out_f32, replicas, g, io_in);
@@ -443,7 +440,7 @@ hipError_t launch_igemm(hipStream_t st, int dtype, bool out_f32, int replicas, c
   io.stat = nullptr;
   if (io.in_f32 && !(dtype == 1 && !out_f32 && conv_smallk_applicable(dtype, g, io))) return hipErrorInvalidValue;
   if (conv_smallk_applicable(dtype, g, io)) return launch_conv_smallk(st, dtype, out_f32, replicas, g, io);
-  if (dtype == 1 && !out_f32 && patch_s2_applicable(g, io)) return launch_patch_s2(st, replicas, g, io);
+  if (patch_s2_applicable(dtype, replicas, g, io, out_f32)) return launch_patch_s2(st, replicas, g, io);
   if (conv_halo_applicable(dtype, replicas, g, io, out_f32)) return launch_conv_halo(st, replicas, g, io);
   if (conv_f32x3_applicable(dtype, replicas, g, io)) return launch_conv_f32x3(st, replicas, g, io);
   if (dgrad_s2_applicable(dtype, g, io, out_f32)) return launch_dgrad_s2(st, replicas, g, io);

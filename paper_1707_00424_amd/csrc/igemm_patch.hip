@@ -680,6 +680,6 @@ hipError_t launch_conv_patch(hipStream_t st, int replicas, const ConvGeom &g, co
 
 bool conv_takes_bn(int dtype, int replicas, const ConvGeom &g, const GemmIO &io, bool out_f32) {
   if (replicas != 1 || conv_smallk_applicable(dtype, g, io)) return false;
-  if (dtype == 1 && !out_f32 && patch_s2_applicable(g, io)) return true;
+  if (patch_s2_applicable(dtype, replicas, g, io, out_f32)) return true;
   return conv_halo_applicable(dtype, replicas, g, io, out_f32) && conv_patch_applicable(replicas, g, io);
 }

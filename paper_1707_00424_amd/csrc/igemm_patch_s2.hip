@@ -1,17 +1,22 @@
 // Forward pass of a stride-2 3x3 convolution with padding 1 (bf16, channel counts in multiples of 8): operands loaded straight
 // into LDS, several tiles per workgroup and the epilogue in registers, as in igemm_patch.hip.
 //
-// The input of such a layer is four images, its pixels by the parity of row and column, and the layer is the sum of four
-// stride-1 convolutions with windows of 2 x 2 (odd, odd), 1 x 1 (even, even), 2 x 1 (odd, even) and 1 x 2 (even, odd) taps.  A
-// patch is a tile's pixels of one parity class and 32 channels, a step one tap: per chunk of channels 4 + 1 + 2 + 2 steps
-// over four patches.  Three patches are in LDS: one in use, two on their way or arrived.
+// The input of such a layer is four images, its pixels by the parity of row and column.  A patch is a tile's pixels of one
+// parity class and 32 channels, a step one tap; the taps of a chunk of channels are taken row by row, which is the order of
+// sums of k_conv_halo_s2, so that a layer's result does not depend on which of the two runs it (column sums, residuals and
+// odd channel counts stay there).  Window rows 0 and 2 read odd rows, row 1 even rows; of each, columns 0 and 2 read odd columns:
+//   step     0   1   2   3   4   5   6   7   8
+//   class    OO  OE  OO  EO  EE  EO  OO  OE  OO     (row, column: odd or even)
+//   buffer   X   Y   X   Z   Y   Z   X   Y   X      X and Z change places with every chunk
+//   loads    Z       Y           Y   Z   Z   Y
+// Three patches fit where four would leave one workgroup per compute unit less; OE is loaded twice for it, from L2.
 //
-// What bounded the kernels before this one (64 -> 128 channels on 32 x 32, 3 x 128 images, 31 us for 75 MB and 14.5 GFLOP): the
-// one that gathers per tap fetches each pixel 9/4 times and takes every operand through registers, the one that stages
-// whole patches waits for each of them.  us per pass, before -> now, 3 x 128 images: 64 -> 128 on 32 x 32 29 -> 24, 96 -> 96 36 ->
-// 31, 160 -> 320 134 -> 101, 192 -> 192 on 16 x 16 35 -> 26, 128 -> 256 29 -> 22, 320 -> 640 121 -> 111; 96 -> 96 on 28 x 28 32 -> 28.
-// Of 24 us, 7 are matrix work; a step of 8 products asks for 2 to 3 KB per wavefront, and every barrier waits for the last of
-// four.
+// The kernel that runs the other layers of 128 channels and more stages whole patches through registers and waits for each of
+// them, the gather kernels fetch each pixel 9/4 times.  us per pass, before -> now, 3 x 128 images unless said: 192 -> 192 on
+// 16 x 16 36 -> 27, 128 -> 256 29 -> 25, 320 -> 640 123 -> 110, 160 -> 320 on 32 x 32 143 -> 113, 32 -> 64 15.5 -> 12.8, 3 x 64
+// images of 128 -> 64 24 -> 19, 8 x 16 images of 256 -> 256 on 14 x 14 33 -> 22.  A step of 8 products asks for 2 to 3 KB per
+// wavefront, and every barrier waits for the last of four.  (Class after class, four taps of odd-odd pixels first, needs no second
+// load of OE and was 0 to 10 % faster, but is another order of sums.)
 #include "igemm_halo.h"
 #include <type_traits>
 
@@ -47,45 +52,33 @@ __device__ __forceinline__ uint32_t fdivc(uint32_t n, __attribute__((address_spa
   return (uint32_t)(((uint64_t)n * f.magic) >> f.shift);
 }
 
-// Steps of a chunk: window row and column of the tap, and its class as 2 * (odd row) + (odd column).
-constexpr int kTapR[9] = {0, 0, 2, 2, 1, 0, 2, 1, 1}, kTapS[9] = {0, 2, 0, 2, 1, 1, 1, 0, 2};
-constexpr int kTapBuf[9] = {0, 0, 0, 0, 1, 2, 2, 0, 0};  // patch buffer, counted from that of the chunk's first class
+constexpr int tap_class(int t) { return (t / 3 != 1 ? 2 : 0) + (t % 3 != 1 ? 1 : 0); }  // 2 * (odd row) + (odd column)
 
-// another lane's value: quad permutation, or mirrored within 8 (0x141) or 16 lanes (0x140)
-template <int CTRL>
-__device__ __forceinline__ float row_lane(float v) {
-  return __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), CTRL, 0xf, 0xf, true));
+// Wavefront loads of a patch (H_IT of them) that step t issues: odd-odd pixels of the next chunk in two halves, else all at once.
+template <int H_IT>
+constexpr int step_pieces(int t) {
+  return t == 0 || t == 2 || t == 5 || t == 8 ? H_IT : t == 6 ? (H_IT + 1) / 2 : t == 7 ? H_IT / 2 : 0;
 }
 
-template <int TM, int H_IT>
-struct S2Pieces {  // wavefront loads of patches issued in each step
-  static constexpr int kHalf = (H_IT + 1) / 2;
-  static constexpr int of(int t) {
-    t = (t + 9) % 9;
-    return t == 0 || t == 5 || t == 7 ? kHalf : t == 1 || t == 6 || t == 8 ? H_IT - kHalf : t == 4 ? H_IT : 0;
-  }
-};
-
-// TM: 32-pixel tiles per wavefront (four wavefronts: 128 or 256 outputs); TN: 32-channel tiles; D: weight tiles in flight;
-// H_IT: wavefront loads of a patch per wavefront; NORM: io.bn_out; STAT: io.stat, a partial row per tile.
-template <int TM, int TN, int D, int H_IT, bool NORM, bool STAT>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TM == 1 ? 3 : 2))) void k_patch_s2(const S2Args) {
+// TM: 32-pixel tiles per wavefront (four wavefronts: 128 or 256 outputs); TN: 32-channel tiles; H_IT: wavefront loads of a patch
+// per wavefront; NORM: io.bn_out.
+template <int TM, int TN, int H_IT, bool NORM>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TM == 1 && TN == 2 ? 3 : 2))) void k_patch_s2(const S2Args) {
   typedef bf16_t T;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   CArgs *args = (CArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+  constexpr int D = 2;                   // weight tiles in flight
   constexpr int BN = TN * 32, NB = D + 1;
   constexpr int WG = TN * 2;             // wavefront loads of a weight tile, 16 rows each
   constexpr int WI = (WG + 3) / 4;       // per wavefront, at most
   constexpr int STORES = TM * TN * 2;    // stores of a tile per wavefront, at least
   constexpr int TB = BN * kPix;          // bytes of a weight tile
-  typedef S2Pieces<TM, H_IT> Pieces;
-  static_assert(D <= 3, "patches are requested three steps before their first tap");
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = lane >> 5;
   const int cv = (lane & 3) ^ ((lane >> 4) & 3);  // channel vector this lane loads
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
   const int pbytes = (args->sg.slots + 15) / 16 * 16 * kPix;
-  const int wring = 3 * pbytes, lbias = wring + NB * TB, ldump = lbias + 1024, lnorm = ldump + 1024;  // NORM or STAT: from lnorm
+  const int wring = 3 * pbytes, lbias = wring + NB * TB, ldump = lbias + 1024, lnorm = ldump + 1024;
   const int Cc = args->g.Cc, chunks = (Cc + 31) >> 5;
   const int b_l = (lane & 31) * kPix + ((h ^ ((lane >> 2) & 3)) << 4);
   int n0;
@@ -123,6 +116,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TM == 
       const bool ok = slot < slots && b * P < rows && u >= 0 && 2 * u < Hin && v >= 0 && 2 * v < Win;
       h_off[it] = ok ? (uint32_t)((((b * Hin + 2 * u) * Win + 2 * v) * Cc + cv * 8) * 2) : kOob;
       odd_ok |= (uint32_t)(2 * u + 1 < Hin) << it | (uint32_t)(2 * v + 1 < Win) << (16 + it);
+      __builtin_amdgcn_sched_barrier(0);  // one after the other: side by side they need registers that the sums have taken
     }
   };
   // pieces `from` .. `to` - 1 of the patch of class 2 a + c and the chunk at byte `soff` of a pixel
@@ -151,8 +145,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TM == 
       dma4(lds0 + (uint32_t)(lbias + buf * 512 + wave * 256), rsrc, n < a->g.N ? (uint32_t)n * 4u : kOob);
     }
   };
-  // The weight tile of the next step has arrived and what was requested before it; behind it came D - 1 tiles, PIECES of
-  // patches and, with `stores`, those of the tile before.
+  // What the step before this one requested has arrived, the weight tile of the next step last; behind it came a tile, PIECES of
+  // a patch and, with `stores`, those of the tile before.
   auto wait_step = [&](auto pieces, bool stores) {
     constexpr int P = decltype(pieces)::value, FULL = WI * (D - 1) + P, SHORT = (WI - 1) * (D - 1) + P;
     if (WG % 4 != 0 && wave >= WG % 4) {
@@ -201,7 +195,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TM == 
   u4 fa_a[TM], fa_b[TN], fb_a[TM], fb_b[TN];
   const int row_step = args->sg.HC * kPix;
   auto read0 = [&](int t, int buf, int ring) {
-    const int shift = buf + (kTapR[t] ? row_step : 0) + (kTapS[t] ? kPix : 0);
+    const int shift = buf + (t / 3 ? row_step : 0) + (t % 3 ? kPix : 0);
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm) {
       const int a = a_b[tm] + shift;
@@ -242,7 +236,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TM == 
     const bool relu = a->io.relu;
     const int m0 = tile * a->sg.TH * a->g.Q, mend = min(a->g.M, m0 + a->sg.TH * a->g.Q), ldc = a->io.ldc, N = a->g.N;
     const __amdgpu_buffer_rsrc_t o_rsrc = out_like(a, a->io.out, rep), n_rsrc = out_like(a, NORM ? a->io.bn_out : nullptr, rep);
-    float sums[STAT ? TN : 1][2][8] = {};  // of what this lane stores, and of its squares
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
@@ -268,13 +261,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TM == 
           const int m = m0 + wave * (TM * 32) + tm * 32 + j * 16 + (lane & 15), n = n0 + tn * 32 + chan;
           const uint32_t at = m < mend && n < N ? ((uint32_t)m * (uint32_t)ldc + (uint32_t)n) * 2u : kOob;
           if (!NORM || !a->io.bn_only) __builtin_amdgcn_raw_buffer_store_b128(o, o_rsrc, at, 0, 0);
-          if constexpr (STAT) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-              const float x = m < mend ? __uint_as_float(e & 1 ? o[e >> 1] & 0xffff0000u : o[e >> 1] << 16) : 0.f;
-              sums[tn][0][e] += x, sums[tn][1][e] += x * x;
-            }
-          }
           if constexpr (NORM) {
             const char *p = smem + lnorm + (tn * 32 + chan) * 4;  // means, 1/sigma, gamma, beta of the column block
             u4 r;
@@ -295,35 +281,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TM == 
           }
         }
       }
-    if constexpr (STAT) {
-      // over the sixteen lanes that share channels, then over the wavefronts, in a fixed order
-      float *ws = (float *)(smem + lnorm);  // [wavefront][sums, squares][column]
-#pragma unroll
-      for (int tn = 0; tn < TN; ++tn)
-#pragma unroll
-        for (int k = 0; k < 2; ++k)
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            float v = sums[tn][k][e];
-            v += row_lane<0xb1>(v), v += row_lane<0x4e>(v), v += row_lane<0x141>(v), v += row_lane<0x140>(v);
-            if ((lane & 15) == 0) ws[(wave * 2 + k) * BN + tn * 32 + chan + e] = v;
-          }
-      meet();
-      if (tid < 2 * BN) {
-        const int k = tid / BN, n = n0 + tid - k * BN;
-        float v = ws[tid];
-#pragma unroll
-        for (int w = 1; w < 4; ++w) v += ws[w * 2 * BN + tid];
-        if (n < N) a->io.stat[(((long long)rep * a->dRep.d + tile) * 2 + k) * ldc + n] = v;
-      }
-    }
   };
 
-  typedef std::integral_constant<int, 0> EE;
-  typedef std::integral_constant<int, 1> EO;
-  typedef std::integral_constant<int, 2> OE;
-  typedef std::integral_constant<int, 3> OO;
-  constexpr int HALF = Pieces::kHalf;
+  constexpr int HALF = (H_IT + 1) / 2;
   int idx = blockIdx.x, rep, tile;
   if (!item_at(args, idx, rep, tile)) return;
   patch_of(args, rep, tile);
@@ -336,10 +296,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TM == 
   {
     const bool live = cv * 8 < Cc;
     load_bias(args, rep, 0);
-    load_pieces(OO{}, 0, H_IT, 0, 0, live);
-    load_pieces(EE{}, 0, H_IT, pbytes, 0, live);
+    load_pieces(std::integral_constant<int, tap_class(0)>{}, 0, H_IT, 0, 0, live);
+    load_pieces(std::integral_constant<int, tap_class(1)>{}, 0, H_IT, pbytes, 0, live);
 #pragma unroll
-    for (int i = 0; i < D; ++i) load_w(i * TB, (uint32_t)((kTapR[i] * 3 + kTapS[i]) * Cc * 2), live);
+    for (int i = 0; i < D; ++i) load_w(i * TB, (uint32_t)i * col_b, live);
   }
   if (NORM && tid < BN) {
     const int n = min(n0 + tid, args->g.N - 1);
@@ -349,7 +309,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TM == 
   }
   wait_step(std::integral_constant<int, 0>{}, false);
   meet();
-  int ring = 0, base = 0, bbuf = 0;  // base: the patch buffer of the chunk's first class
+  int ring = 0, base = 0, bbuf = 0;  // base: buffer X of the chunk
   bool later = false;                // not the first item: the stores of the one before it are in flight
   for (;;) {
     begin(fresh(args), tile);
@@ -361,15 +321,16 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TM == 
       const bool live = c * 32 + cv * 8 < Cc;
       const int c1 = last ? 0 : c + 1;
       bool live1 = c1 * 32 + cv * 8 < Cc;
-      const int b1 = base + pbytes == 3 * pbytes ? 0 : base + pbytes, b2 = b1 + pbytes == 3 * pbytes ? 0 : b1 + pbytes;
+      const int other = 2 * pbytes - base;  // buffer Z
       auto step = [&](auto tc) {
         constexpr int t = decltype(tc)::value;
         const int prev = ring == 0 ? (NB - 1) * TB : ring - TB, next = ring == (NB - 1) * TB ? 0 : ring + TB;
         read1(ring);
-        if (t == 0) load_pieces(OE{}, 0, HALF, b2, (uint32_t)(c * 64), live);
-        if (t == 1) load_pieces(OE{}, HALF, H_IT, b2, (uint32_t)(c * 64), live);
-        if (t == 4) load_pieces(EO{}, 0, H_IT, base, (uint32_t)(c * 64), live);
-        if (t == 5) {
+        // a buffer is loaded again one step or more behind the last tap that reads it, and two or more before its next tap
+        if (t == 0) load_pieces(std::integral_constant<int, tap_class(3)>{}, 0, H_IT, other, (uint32_t)(c * 64), live);
+        if (t == 2) load_pieces(std::integral_constant<int, tap_class(4)>{}, 0, H_IT, pbytes, (uint32_t)(c * 64), live);
+        if (t == 5) load_pieces(std::integral_constant<int, tap_class(7)>{}, 0, H_IT, pbytes, (uint32_t)(c * 64), live);
+        if (t == 6) {
           if (last) {
             CArgs *a = fresh(args);
             idx += a->groups;
@@ -381,26 +342,25 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TM == 
             }
             live1 = live1 && more;
           }
-          load_pieces(OO{}, 0, HALF, b1, (uint32_t)(c1 * 64), live1);
+          load_pieces(std::integral_constant<int, tap_class(0)>{}, 0, HALF, other, (uint32_t)(c1 * 64), live1);
         }
-        if (t == 6) load_pieces(OO{}, HALF, H_IT, b1, (uint32_t)(c1 * 64), live1);
-        if (t == 7) load_pieces(EE{}, 0, HALF, b2, (uint32_t)(c1 * 64), live1);
-        if (t == 8) load_pieces(EE{}, HALF, H_IT, b2, (uint32_t)(c1 * 64), live1);
+        if (t == 7) load_pieces(std::integral_constant<int, tap_class(0)>{}, HALF, H_IT, other, (uint32_t)(c1 * 64), live1);
+        if (t == 8) load_pieces(std::integral_constant<int, tap_class(1)>{}, 0, H_IT, pbytes, (uint32_t)(c1 * 64), live1);
         constexpr int tw = (t + D) % 9;
         if (t + D == 9 && last && more) {
           b_rsrc.x = __builtin_amdgcn_readfirstlane((uint32_t)bn_base);
           b_rsrc.y = __builtin_amdgcn_readfirstlane((uint32_t)(bn_base >> 32) & 0xffffu);
         }
-        load_w(prev, (uint32_t)((kTapR[tw] * 3 + kTapS[tw]) * Cc * 2 + (t + D >= 9 ? c1 : c) * 64), t + D >= 9 ? live1 : live);
+        load_w(prev, (uint32_t)tw * col_b + (uint32_t)((t + D >= 9 ? c1 : c) * 64), t + D >= 9 ? live1 : live);
         mma_sub(fa_a, fa_b);
         interleave();
-        constexpr int pieces = Pieces::of(t) + (D > 2 ? Pieces::of(t - 1) : 0);
-        wait_step(std::integral_constant<int, pieces>{}, t < D - 1 && c == 0 && later);
+        wait_step(std::integral_constant<int, step_pieces<H_IT>(t)>{}, t == 0 && c == 0 && later);
         meet();
+        constexpr int t1 = (t + 1) % 9;
         if (t < 8)
-          read0((t + 1) % 9, kTapBuf[(t + 1) % 9] == 0 ? base : kTapBuf[(t + 1) % 9] == 1 ? b1 : b2, next);
+          read0(t1, t1 == 3 || t1 == 5 ? other : t1 % 3 == 1 ? pbytes : base, next);
         else if (!last)
-          read0(0, b1, next);
+          read0(0, other, next);
         mma_sub(fb_a, fb_b);
         if (t < 8) interleave();
         ring = next;
@@ -408,7 +368,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TM == 
       step(std::integral_constant<int, 0>{}), step(std::integral_constant<int, 1>{}), step(std::integral_constant<int, 2>{});
       step(std::integral_constant<int, 3>{}), step(std::integral_constant<int, 4>{}), step(std::integral_constant<int, 5>{});
       step(std::integral_constant<int, 6>{}), step(std::integral_constant<int, 7>{}), step(std::integral_constant<int, 8>{});
-      base = b1;
+      base = other;
     }
     store_item(fresh(args), rep, tile, bbuf);
     if (!more) break;
@@ -432,10 +392,10 @@ bool make_s2_geom(const ConvGeom &g, int outputs, int max_slots, S2Geom &sg) {
   return true;
 }
 
-template <int TM, int TN, int D, int H_IT, bool NORM, bool STAT>
+template <int TM, int TN, int H_IT, bool NORM>
 hipError_t run_as(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io, const S2Geom &sg) {
-  constexpr int kCus = 256, kLdsOfCu = 160 * 1024, kWaves = TM == 1 ? 3 : 2;
-  const int lds = 3 * ((sg.slots + 15) / 16 * 16 * kPix) + (D + 1) * TN * 32 * kPix + 2048 + (NORM ? TN * 32 * 16 : STAT ? TN * 32 * 32 : 0);
+  constexpr int kCus = 256, kLdsOfCu = 160 * 1024, kWaves = TM == 1 && TN == 2 ? 3 : 2;
+  const int lds = 3 * ((sg.slots + 15) / 16 * 16 * kPix) + 3 * TN * 32 * kPix + 2048 + (NORM ? TN * 32 * 16 : 0);
   const int resident = kCus * (kLdsOfCu / lds < kWaves ? kLdsOfCu / lds : kWaves);
   const int nb = (g.N + TN * 32 - 1) / (TN * 32), rep_tiles = (sg.rows + sg.TH - 1) / sg.TH, tiles = rep_tiles * replicas;
   const long long items = (long long)((tiles + 7) / 8 * 8) * nb;
@@ -444,65 +404,39 @@ hipError_t run_as(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO 
   const int step = 8 * nb;
   if (items > resident && step <= resident) a.groups = resident / step * step;
   static const hipError_t lds_ok =
-      hipFuncSetAttribute((const void *)k_patch_s2<TM, TN, D, H_IT, NORM, STAT>, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsOfCu);
+      hipFuncSetAttribute((const void *)k_patch_s2<TM, TN, H_IT, NORM>, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsOfCu);
   if (lds_ok != hipSuccess) return lds_ok;
-  hipLaunchKernelGGL((k_patch_s2<TM, TN, D, H_IT, NORM, STAT>), dim3(a.groups), dim3(kThreads), lds, st, a);
+  hipLaunchKernelGGL((k_patch_s2<TM, TN, H_IT, NORM>), dim3(a.groups), dim3(kThreads), lds, st, a);
   return hipGetLastError();
 }
-template <int TM, int TN, int D, int H_IT>
+template <int TM, int TN, int H_IT>
 hipError_t run(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io, const S2Geom &sg) {
-  if (io.bn_out) return run_as<TM, TN, D, H_IT, true, false>(st, replicas, g, io, sg);
-  if constexpr (TN == 2)
-    if (io.stat) return run_as<TM, TN, D, H_IT, false, true>(st, replicas, g, io, sg);
-  return run_as<TM, TN, D, H_IT, false, false>(st, replicas, g, io, sg);
+  return io.bn_out ? run_as<TM, TN, H_IT, true>(st, replicas, g, io, sg) : run_as<TM, TN, H_IT, false>(st, replicas, g, io, sg);
 }
 
 }  // namespace
 
-bool patch_s2_applicable(const ConvGeom &g, const GemmIO &io) {
+bool patch_s2_applicable(int dtype, int replicas, const ConvGeom &g, const GemmIO &io, bool out_f32) {
   S2Geom sg;
-  return g.R == 3 && g.S == 3 && g.sp == 2 && g.off == -1 && g.sr == 1 && g.dshift == 0 && g.P == (g.Hin + 1) / 2 && g.Q == (g.Win + 1) / 2 &&
-         g.Cc % 8 == 0 && g.N % 8 == 0 && io.ldc % 8 == 0 && io.vecA && io.vecB && !(io.stat && io.bn_out) && !io.resid && !io.mask && !io.accumulate && !io.in_f32 && io.any_order &&
-         aligned_to(io.out, 16) && io.out_rs % 8 == 0 && aligned_to(io.bn_out, 16) && io.in_bytes > 0 && io.in_bytes < (1LL << 31) &&
-         (long long)g.M * io.ldc * 4 < (1LL << 31) && (long long)g.N * g.K * 2 < (1LL << 31) && make_s2_geom(g, 128, 192, sg);
-}
-
-namespace {
-struct S2Shape {
-  int tm, tn, d;
-  S2Geom sg;
-};
-bool choose_s2(int replicas, const ConvGeom &g, const GemmIO &io, S2Shape &v) {
-  S2Geom wide;
-  if (!make_s2_geom(g, 128, 192, v.sg)) return false;
-  // 96- or 64-wide column blocks, whichever pad the output channels least (64 with column sums).  256 outputs with two workgroups
-  // per compute unit, as far as three patches and the weight tiles fit; 128 with three where the wide ones would leave compute
-  // units empty (us, 256 / 128 outputs, 3 x 128 images: 64 -> 128 on 32 x 32, 768 wide workgroups, 24 / 27; 160 -> 320, 1920, 101 /
-  // 126; 192 -> 192 on 16 x 16, 192, 26.2 / 25.8; 8 x 16 images of 256 -> 256 on 14 x 14, 128, 24 / 21; 5 x 40 of 320 -> 96 on 8 x 8,
-  // 15, 35 / 25).
-  const bool tn3 = !io.stat && (g.N + 95) / 96 * 96 <= (g.N + 63) / 64 * 64;
-  auto wide_fits = [&](int max_slots) {
-    return make_s2_geom(g, 256, max_slots, wide) &&
-           (long long)((wide.rows + wide.TH - 1) / wide.TH) * replicas * ((g.N + (tn3 ? 95 : 63)) / (tn3 ? 96 : 64)) > 256;
-  };
-  v.tm = 1, v.tn = tn3 ? 3 : 2, v.d = tn3 ? 2 : 3;
-  if (wide_fits(tn3 ? 320 : 304))
-    v.tm = 2, v.sg = wide;
-  else if (!tn3 && wide_fits(336))
-    v.tm = 2, v.d = 2, v.sg = wide;
-  return true;
-}
-}  // namespace
-
-int patch_s2_stat_splits(int replicas, const ConvGeom &g, const GemmIO &io) {
-  S2Shape v;
-  return patch_s2_applicable(g, io) && choose_s2(replicas, g, io, v) ? (v.sg.rows + v.sg.TH - 1) / v.sg.TH : 0;
+  if (dtype != 1 || out_f32 || g.R != 3 || g.S != 3 || g.sp != 2 || g.off != -1 || g.sr != 1 || g.dshift != 0 || g.P != (g.Hin + 1) / 2 || g.Q != (g.Win + 1) / 2)
+    return false;
+  if (g.Cc % 8 != 0 || g.N % 8 != 0 || io.ldc % 8 != 0 || !io.vecA || !io.vecB || io.stat || io.resid || io.mask || io.accumulate || io.in_f32) return false;
+  if (!aligned_to(io.out, 16) || io.out_rs % 8 != 0 || !aligned_to(io.bn_out, 16) || io.in_bytes <= 0 || io.in_bytes >= (1LL << 31)) return false;
+  if ((long long)g.M * io.ldc * 4 >= (1LL << 31) || (long long)g.N * g.K * 2 >= (1LL << 31) || !make_s2_geom(g, 128, 192, sg)) return false;
+  // Layers of several chunks that the gather kernels run add all channels of a tap before the next tap: they stay there.  A
+  // single chunk is the same order in either.
+  return g.Cc <= 32 || conv_halo_applicable(dtype, replicas, g, io, out_f32);
 }
 
 hipError_t launch_patch_s2(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io) {
-  S2Shape v;
-  if (!choose_s2(replicas, g, io, v)) return hipErrorInvalidValue;
-  if (v.tn == 3) return v.tm == 2 ? run<2, 3, 2, 5>(st, replicas, g, io, v.sg) : run<1, 3, 2, 3>(st, replicas, g, io, v.sg);
-  if (v.tm == 2) return v.d == 3 ? run<2, 2, 3, 5>(st, replicas, g, io, v.sg) : run<2, 2, 2, 6>(st, replicas, g, io, v.sg);
-  return run<1, 2, 3, 3>(st, replicas, g, io, v.sg);
+  // 96- or 64-wide column blocks, whichever pad the output channels least.  256 outputs with two workgroups per compute unit, as
+  // far as three patches, the weight tiles and a batch-norm's constants fit in half of its LDS; 128 with three where the wide
+  // ones would leave compute units empty.
+  const bool tn3 = (g.N + 95) / 96 * 96 <= (g.N + 63) / 64 * 64;
+  S2Geom sg;
+  if (make_s2_geom(g, 256, tn3 ? (io.bn_out ? 304 : 320) : 336, sg) &&
+      (long long)((sg.rows + sg.TH - 1) / sg.TH) * replicas * ((g.N + (tn3 ? 95 : 63)) / (tn3 ? 96 : 64)) > 256)
+    return tn3 ? run<2, 3, 5>(st, replicas, g, io, sg) : run<2, 2, 6>(st, replicas, g, io, sg);
+  if (!make_s2_geom(g, 128, 192, sg)) return hipErrorInvalidValue;
+  return tn3 ? run<1, 3, 3>(st, replicas, g, io, sg) : run<1, 2, 3>(st, replicas, g, io, sg);
 }

@@ -557,7 +557,6 @@ hipError_t forward(const Run &r, bool train, float *bn_stats, const float *bn_ev
     io.bias = op.bseg >= 0 ? r.fptr(op.bseg) : nullptr, io.bias_rs = r.p_rs;
     io.resid = op.resid >= 0 ? r.tptr(op.resid) : nullptr, io.resid_rs = op.resid >= 0 ? r.trs(op.resid) : 0;
     io.relu = op.relu;
-    io.any_order = !train;
     io.vecA = (op.Cin % vw == 0) && aligned_to(io.in, 16);
     // 16-byte loads of weight rows.  Global and buffer loads need 4-byte alignment only, which fp32 rows
     // always have; bf16 rows must start on a 16-byte boundary (two-byte offsets would misalign them).
