@@ -217,5 +217,7 @@ hipError_t launch_dgrad_patch(hipStream_t st, int replicas, const ConvGeom &g, c
 // True where backward-data reads the layer's weights as they lie instead of turned round (GemmIO::w_kn).  io: of the launch,
 // but for w_kn; io.w, w_rs and vecB of the weights as they lie.
 bool dgrad_reads_weights(int dtype, int replicas, const ConvGeom &g, const GemmIO &io);
+// ... but the kernel by itself is faster with weights that have been turned round (igemm_patch.hip).
+bool dgrad_turned_is_faster(int dtype, int replicas, const ConvGeom &g, const GemmIO &io);
 // Rows of M per split so that the launch has enough workgroups; returns the split count.
 int wgrad_plan(int dtype, int replicas, const ConvGeom &g, int *chunk_out);

@@ -661,6 +661,17 @@ bool conv_patch_applicable(int replicas, const ConvGeom &g, const GemmIO &io) {
          aligned_to(io.mask, 16) && io.mask_rs % 8 == 0 && !((io.resid || io.bn_out) && (io.mask || io.accumulate)) && aligned_to(io.bn_out, 16) && choose_shape(replicas, g, io, s, hg);
 }
 
+// In column blocks of 64 every product needs one transposing read or more beside its other operand.  us of the kernel, as they lie /
+// turned round, 3 x 128 images: 64 -> 64 on 32 x 32 (256 x 64 tiles) 43.2 / 41.4, 128 -> 128 on 16 x 16 (128 x 64) 36.7 / 37.5, with
+// the reads of a weight gradient beside it; in blocks of 96 192 -> 192 on 16 x 16 59 / 63.  A step with blocks of 64 either way:
+// WRN-16-4 (three replicas of 128) 2.232 / 2.207 ms, one replica 1.202 / 1.187, All-CNN of 64 and 128 channels 0.657 / 0.650;
+// with those of 96 turned round as well, All-CNN of 96 and 192 1.008 / 1.030.
+bool dgrad_turned_is_faster(int dtype, int replicas, const ConvGeom &g, const GemmIO &io) {
+  PatchShape s;
+  HaloGeom hg;
+  return dtype == 1 && g.dshift == 0 && conv_patch_applicable(replicas, g, io) && choose_shape(replicas, g, io, s, hg) && s.tn == 2;
+}
+
 hipError_t launch_conv_patch(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io) {
   PatchShape s;
   HaloGeom hg;

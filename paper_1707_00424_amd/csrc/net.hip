@@ -313,6 +313,12 @@ bool build_plan(Net &N, std::string &err) {
       err = "model has no network";
       return false;
   }
+  // A network whose whole forward pass is less than half a GFLOP is bound by the host's launches: a second stream hides
+  // a few microseconds of kernels and costs ten event calls per step.  One stream against two, us per step: MLP with
+  // three replicas (0.08 GFLOP) 33 / 74, LeNet with one replica of 16 (0.07) 140 / 155, of 64 (0.28) 153 / 155, of 128
+  // (0.56) 175 / 170, six of 128 (3.4) 376 / 344.
+  N.overlap = net_forward_flops_per_image(&N) * N.n * N.B >= 500000000LL;
+  if (const char *e = getenv("PARLE_OVERLAP_WGRAD")) N.overlap = atoi(e) != 0;
   {
     static const bool fused_head = [] {
       const char *e = getenv("PARLE_FUSED_HEAD");
@@ -383,7 +389,8 @@ bool build_plan(Net &N, std::string &err) {
           if (op.mask_in) dio.mask = (const void *)256;
           dio.mask_rs = out_rs, dio.accumulate = op.dx_accumulate;
           dio.vecA = op.Cout % vw == 0, dio.vecB = gb.K % vw == 0 && N.segs[op.wseg].offset % vw == 0 && N.n_pad % vw == 0;
-          op.w_as_is = dgrad_reads_weights(N.dtype, N.n, gb, dio);
+          // where the weights are turned round beside the forward pass, that costs the step nothing
+          op.w_as_is = dgrad_reads_weights(N.dtype, N.n, gb, dio) && !(N.overlap && dgrad_turned_is_faster(N.dtype, N.n, gb, dio));
         }
         if (!op.head && !op.w_as_is) op.wt_off = N.alloc((int64_t)N.n * wsize * N.esize);  // the head kernel reads the weights as they lie
         // few input channels under a wide window (LeNet's second convolution: 20 channels, 25 taps): the direct kernel
@@ -948,12 +955,6 @@ Net *net_create(const parle_config &cfg, const Arch &a, const std::vector<Segmen
     delete N;
     return nullptr;
   }
-  // A network whose whole forward pass is less than half a GFLOP is bound by the host's launches: a second stream hides
-  // a few microseconds of kernels and costs ten event calls per step.  One stream against two, us per step: MLP with
-  // three replicas (0.08 GFLOP) 33 / 74, LeNet with one replica of 16 (0.07) 140 / 155, of 64 (0.28) 153 / 155, of 128
-  // (0.56) 175 / 170, six of 128 (3.4) 376 / 344.
-  N->overlap = net_forward_flops_per_image(N) * N->n * N->B >= 500000000LL;
-  if (const char *e = getenv("PARLE_OVERLAP_WGRAD")) N->overlap = atoi(e) != 0;
   return N;
 }
 
