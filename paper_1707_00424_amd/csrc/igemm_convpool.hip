@@ -24,6 +24,7 @@ struct PoolGeom {
   int N, K;         // output channels, window values
   int Q2, windows;  // pooled columns, pooled outputs of an image
   int image;        // values of an image
+  int parts;        // workgroups that share an image: gridDim.z
   FastDiv dQ2;
   int off[kTaps];   // of a window value from the window's first pixel; 0 beyond the last
 };
@@ -36,7 +37,7 @@ constexpr int kXor1 = 0xb1, kXor2 = 0x4e;  // quad permutations [1 0 3 2] and [2
 
 constexpr int step_value(int i) { return 8 * (i / 4) + i % 4; }
 
-// One workgroup per image.  out, code: [window][N].
+// One workgroup per image, or several (blockIdx.z) that share its windows.  out, code: [window][N].
 __global__ __launch_bounds__(kThreads) void k_convpool(const PoolGeom g, const float *__restrict__ x, long long x_rs, const float *__restrict__ w,
                                                        long long w_rs, const float *__restrict__ bias, long long bias_rs,
                                                        float *__restrict__ out, long long out_rs, unsigned char *__restrict__ code) {
@@ -79,7 +80,7 @@ __global__ __launch_bounds__(kThreads) void k_convpool(const PoolGeom g, const f
   }
   float *op = out + rep * out_rs + (long long)b * g.windows * g.N;
   unsigned char *cp = code ? code + rep * out_rs + (long long)b * g.windows * g.N : nullptr;
-  for (int first = wave * 8; first < g.windows; first += 4 * 8) {
+  for (int first = (blockIdx.z * 4 + wave) * 8; first < g.windows; first += g.parts * 4 * 8) {
     const int win = first + (n >> 2), wc = min(win, g.windows - 1);
     const int ph = (int)fdiv((uint32_t)wc, g.dQ2), qw = wc - ph * g.Q2;
     const float *px = img + ((2 * ph + (pos >> 1)) * g.W + 2 * qw + (pos & 1)) * g.C;
@@ -125,14 +126,15 @@ __global__ __launch_bounds__(kThreads) void k_convpool(const PoolGeom g, const f
 }
 
 // Weight gradient, and the bias gradient behind it: dy is the gradient of the pooled output where it came from, zero elsewhere.
-// A workgroup takes `per` images of a replica, its wavefronts every fourth row of windows; a matrix instruction contracts two of a
-// window's four pixels.  The window value behind the last is 1: its column is the sum of dy.
+// A workgroup takes `per` images of a replica, its wavefronts every fourth row of windows, or several (blockIdx.z) share the rows
+// of one image; a matrix instruction contracts two of a window's four pixels.  The window value behind the last is 1: its column is
+// the sum of dy.
 __global__ __launch_bounds__(kThreads) void k_convpool_wgrad(const PoolGeom g, int B, int per, const float *__restrict__ x, long long x_rs,
                                                              const float *__restrict__ dp, long long dp_rs, const unsigned char *__restrict__ code,
                                                              float *__restrict__ out, long long out_rs, long long split_stride) {
   extern __shared__ __attribute__((aligned(16))) float img[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, n = lane & 31;
-  const int split = blockIdx.x, rep = blockIdx.y;
+  const int rep = blockIdx.y, first = blockIdx.x * per;
   const int pooled = g.windows * g.N;
   float *gr = img + (g.image + 3) / 4 * 4;
   unsigned char *cd = (unsigned char *)(gr + pooled);
@@ -142,8 +144,8 @@ __global__ __launch_bounds__(kThreads) void k_convpool_wgrad(const PoolGeom g, i
   f16v acc, acc2;
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = 0.f, acc2[v] = 0.f;
-  const int b1 = min(B, (split + 1) * per);
-  for (int b = split * per; b < b1; ++b) {
+  const int b1 = min(B, first + per);
+  for (int b = first; b < b1; ++b) {
     const float *xp = x + rep * x_rs + (long long)b * g.image, *dpp = dp + rep * dp_rs + (long long)b * pooled;
     const unsigned char *cp = code + rep * dp_rs + (long long)b * pooled;
     __syncthreads();  // the image before has been read
@@ -166,7 +168,7 @@ __global__ __launch_bounds__(kThreads) void k_convpool_wgrad(const PoolGeom g, i
       }
     }
     __syncthreads();
-    for (int ph = wave; ph < P2; ph += 4) {
+    for (int ph = blockIdx.z * 4 + wave; ph < P2; ph += g.parts * 4) {
       const float *px = img + (2 * ph * g.W + h) * g.C + off, *gp = gr + ph * g.Q2 * g.N + nc;
       const unsigned char *kp = cd + ph * g.Q2 * g.N + nc;
 #pragma unroll 4
@@ -183,10 +185,10 @@ __global__ __launch_bounds__(kThreads) void k_convpool_wgrad(const PoolGeom g, i
   for (int v = 0; v < 16; ++v) acc[v] += acc2[v];
   // the wavefronts' sums are added in their order
   __syncthreads();
-  float *part = img;  // [3][64][16]
+  float *sums = img;  // [3][64][16]
   if (wave) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) *(f4 *)&part[((wave - 1) * 64 + lane) * 16 + q * 4] = f4{acc[q * 4], acc[q * 4 + 1], acc[q * 4 + 2], acc[q * 4 + 3]};
+    for (int q = 0; q < 4; ++q) *(f4 *)&sums[((wave - 1) * 64 + lane) * 16 + q * 4] = f4{acc[q * 4], acc[q * 4 + 1], acc[q * 4 + 2], acc[q * 4 + 3]};
   }
   __syncthreads();
   if (wave) return;
@@ -194,10 +196,10 @@ __global__ __launch_bounds__(kThreads) void k_convpool_wgrad(const PoolGeom g, i
   for (int w = 0; w < 3; ++w)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const f4 t = *(const f4 *)&part[(w * 64 + lane) * 16 + q * 4];
+      const f4 t = *(const f4 *)&sums[(w * 64 + lane) * 16 + q * 4];
       acc[q * 4] += t.x, acc[q * 4 + 1] += t.y, acc[q * 4 + 2] += t.z, acc[q * 4 + 3] += t.w;
     }
-  float *o = out + rep * out_rs + split * split_stride;
+  float *o = out + rep * out_rs + (blockIdx.x * g.parts + blockIdx.z) * split_stride;
 #pragma unroll
   for (int v = 0; v < 16; ++v) {
     const int c = 8 * (v >> 2) + 4 * h + (v & 3);
@@ -234,24 +236,43 @@ bool convpool_applicable(int dtype, const ConvShape &c) {
   return g.windows >= 8 && c.B <= 65535 * 16 && wgrad_lds(g) <= 48 * 1024;
 }
 
+namespace {
+constexpr int kResident = 768;  // three workgroups per compute unit
+
+// Workgroups per image, where images alone are too few to fill the chip; the four wavefronts of one keep at least six of the
+// `units` (groups of windows, rows) that they share.  us per LeNet step, one workgroup per image / this / three separate kernels:
+// 32 images of 28 x 28, 5 x 5 window, 98 / 94 / 108; 4 images of 48 x 48, 3 x 3, 108 / 83 / 93; 32 of 64 x 64, 5 x 5, 179 / 117 / 136; 128 of
+// 56 x 56, 231 / 200 / 222; an evaluation of 16 of 64 x 64 112 / 78 / 80.
+int image_parts(int n, const ConvShape &c, int units) {
+  const long long room = kResident / ((long long)n * c.B);
+  const int most = units / 6;
+  return (int)(room < 1 || most < 1 ? 1 : room < most ? room : most);
+}
+struct WgradSplits {
+  int per, parts, splits;
+};
+WgradSplits wgrad_splits(int n, const ConvShape &c) {
+  const int per = (int)(((long long)n * c.B + kResident - 1) / kResident), parts = per > 1 ? 1 : image_parts(n, c, c.Ho() / 2);
+  return {per, parts, (c.B + per - 1) / per * parts};
+}
+}  // namespace
+
 hipError_t launch_convpool(hipStream_t st, int n, const ConvShape &c, const float *x, long long x_rs, const float *w, long long w_rs, const float *bias,
                            long long bias_rs, float *out, unsigned char *code) {
-  const PoolGeom g = pool_geom(c);
-  hipLaunchKernelGGL(k_convpool, dim3(c.B, n), dim3(kThreads), (size_t)(g.image + g.N * g.K) * 4, st, g, x, x_rs, w, w_rs, bias, bias_rs, out,
+  PoolGeom g = pool_geom(c);
+  g.parts = image_parts(n, c, (g.windows + 7) / 8);
+  hipLaunchKernelGGL(k_convpool, dim3(c.B, n, g.parts), dim3(kThreads), (size_t)(g.image + g.N * g.K) * 4, st, g, x, x_rs, w, w_rs, bias, bias_rs, out,
                      (long long)c.B * g.windows * g.N, code);
   return hipGetLastError();
 }
 
-// One image per workgroup up to three workgroups per compute unit.
-int convpool_wgrad_splits(int n, const ConvShape &c) {
-  const int per = (int)(((long long)n * c.B + 767) / 768);
-  return (c.B + per - 1) / per;
-}
+int convpool_wgrad_splits(int n, const ConvShape &c) { return wgrad_splits(n, c).splits; }
 hipError_t launch_convpool_wgrad(hipStream_t st, int n, const ConvShape &c, const float *x, long long x_rs, const float *dpooled, const unsigned char *code,
                                  float *out, long long out_rs, long long split_stride) {
-  const PoolGeom g = pool_geom(c);
-  const int S = convpool_wgrad_splits(n, c), per = (c.B + S - 1) / S;
-  hipLaunchKernelGGL(k_convpool_wgrad, dim3(S, n), dim3(kThreads), wgrad_lds(g), st, g, c.B, per, x, x_rs, dpooled,
+  PoolGeom g = pool_geom(c);
+  const WgradSplits s = wgrad_splits(n, c);
+  g.parts = s.parts;
+  hipLaunchKernelGGL(k_convpool_wgrad, dim3(s.splits / s.parts, n, s.parts), dim3(kThreads), wgrad_lds(g), st, g, c.B, s.per, x, x_rs, dpooled,
                      (long long)c.B * g.windows * g.N, code, out, out_rs, split_stride);
   return hipGetLastError();
 }

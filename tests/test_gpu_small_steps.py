@@ -105,7 +105,9 @@ def test_recorded_block_equals_single_steps(gpu, model, arch):
 
 @pytest.mark.parametrize("case", [
     # n, batch, image side, channels, first layer's outputs, window: 24 x 24, ragged tiles of windows, odd sides, whole and partial vectors
-    (2, 5, 28, 1, 20, 5), (1, 3, 15, 1, 12, 4), (3, 2, 17, 3, 32, 3), (1, 1, 14, 2, 4, 3), (2, 400, 17, 1, 16, 5), (1, 33, 32, 3, 28, 3)])
+    (2, 5, 28, 1, 20, 5), (1, 3, 15, 1, 12, 4), (3, 2, 17, 3, 32, 3), (1, 1, 14, 2, 4, 3), (2, 400, 17, 1, 16, 5), (1, 33, 32, 3, 28, 3),
+    # several workgroups per image: eleven for the forward pass of 23 x 23 windows and three for their gradient, ragged shares; 18 and five
+    (1, 2, 48, 1, 8, 3), (2, 3, 64, 1, 4, 5)])
 def test_first_layer_with_its_pool(gpu, case):
     """Loss and every gradient of a LeNet whose first layer runs as one operation with its pool."""
     torch, pb = gpu
