@@ -19,7 +19,7 @@ struct Tensor {
   int H = 0, W = 0, C = 0;
   bool f32 = false;       // fp32 storage regardless of the activation dtype (logits)
   bool external = false;  // the caller's image buffer (fp32 mode): no workspace slot
-  int64_t off = -1;       // byte offset in the workspace
+  int64_t off = -1;       // byte offset in the workspace, -1 = nothing stores it
   int64_t goff = -1;      // byte offset of its gradient (activation dtype), -1 = none
 };
 
@@ -135,7 +135,6 @@ struct Net {
   int add_tensor(int H, int W, int C, bool f32 = false, bool external = false) {
     Tensor t;
     t.H = H, t.W = W, t.C = C, t.f32 = f32, t.external = external;
-    if (!external) t.off = alloc((int64_t)n * B * H * W * C * (f32 ? 4 : esize));
     tensors.push_back(t);
     return (int)tensors.size() - 1;
   }
@@ -355,6 +354,15 @@ bool build_plan(Net &N, std::string &err) {
     c.pool = (int)i + 1, p.pool_fused = true;
     c.code_off = N.alloc((int64_t)N.n * N.B * tp.H * tp.W * tp.C);
   }
+  {
+    std::vector<char> stored(N.tensors.size(), 1);
+    for (const Op &op : N.ops)
+      if (op.type == OP_CONV && op.pool >= 0) stored[op.out] = 0;
+    for (size_t t = 0; t < N.tensors.size(); ++t) {
+      Tensor &T = N.tensors[t];
+      if (!T.external && stored[t]) T.off = N.alloc((int64_t)N.n * N.B * T.H * T.W * T.C * (T.f32 ? 4 : N.esize));
+    }
+  }
   // a batch-norm whose input a convolution of the chain writes can get its column sums from that convolution
   for (size_t i = 0; i < N.ops.size(); ++i) {
     if (N.ops[i].type != OP_BNRELU) continue;
@@ -373,7 +381,7 @@ bool build_plan(Net &N, std::string &err) {
       err = "internal: stride must be 1 or 2";
       return false;
     }
-    N.want_grad(op.out);
+    if (op.pool < 0) N.want_grad(op.out);
     if (op.type == OP_CONV) {
       const int64_t wsize = (int64_t)op.Cout * op.R * op.R * op.Cin;
       if (op.need_dx) {
@@ -437,7 +445,7 @@ bool build_plan(Net &N, std::string &err) {
         err = "a layer exceeds 2^31 elements per replica";
         return false;
       }
-    } else {
+    } else if (!op.pool_fused) {
       N.want_grad(op.in);
     }
   }

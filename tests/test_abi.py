@@ -172,3 +172,14 @@ def test_struct_layouts_match_the_header(tmp_path):
         assert int(out[name]) == C.sizeof(st), name
         for field, _ in st._fields_:
             assert int(out[f"{name}.{field}"]) == getattr(st, field).offset, (name, field)
+
+
+def test_first_layer_that_runs_with_its_pool_has_no_slots_for_its_outputs():
+    """20 outputs run as one operation with the pool, which keeps a byte per pooled value; 21 store outputs and their gradients."""
+    n, batch, out = 6, 128, 24 * 24
+    sizes = [pb.parle_query_sizes(pb.make_config(model=pb.MODEL_LENET, n_replicas=n, batch=batch, in_h=28, in_w=28, in_c=1, n_classes=10,
+                                                 arch=(c, 50, 5, 500))).workspace_bytes for c in (20, 21)]
+    stored = 2 * n * batch * out * 21 * 4
+    pooled = n * batch * (out // 4) * 20
+    # one channel more or less: pooled values and their gradients, a column of the second layer's per-tap products, partial sums
+    assert sizes[1] - sizes[0] > stored - 2 * pooled, (sizes, stored)
