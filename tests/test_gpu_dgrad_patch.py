@@ -24,6 +24,14 @@ CASES = [
     (1, 4, 16, 16, 1024, 32),   # 32 column blocks
 ]
 
+# bf16 layers of this kind that k_dgrad_s2 keeps: images whose sides are powers of two and output channels in multiples of 32, with
+OTHERS = [
+    (2, 3, 32, 32, 36, 64),     # input channels in multiples of 4 only
+    (1, 5, 16, 16, 100, 32),    # same, the second column block ragged
+    (1, 2, 128, 128, 32, 32),   # rows of 64 positions, which fill no tile of 128 with their patch
+    (1, 1, 16, 128, 64, 96),
+]
+
 
 def _gradient64(torch, dy, w, H, W):
     """``dy`` [B, P, Q, Cout], ``w`` [Cout, 3, 3, Cin]."""
@@ -35,7 +43,7 @@ def _gradient64(torch, dy, w, H, W):
     return out[:, 1:1 + H, 1:1 + W]
 
 
-@pytest.mark.parametrize("case", CASES)
+@pytest.mark.parametrize("case", CASES + OTHERS)
 def test_sizes_and_epilogues(gpu, case):
     torch, pb = gpu
     n, B, H, W, Cin, Cout = case

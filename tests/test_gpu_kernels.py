@@ -98,8 +98,8 @@ CASES = [
     (2, 5, 8, 8, 64, 96, 3, 1, 1),      # four images per tile, last tile ragged
     (1, 2, 32, 32, 32, 20, 3, 1, 1),    # four tiles per image, narrow output
     (2, 2, 16, 16, 64, 64, 3, 1, 1),    # both directions on the patch path
-    (2, 4, 16, 16, 32, 64, 3, 2, 1),    # stride 2, power-of-two image: backward-data rows grouped by parity class
-    (1, 3, 8, 8, 32, 32, 3, 2, 1),      # same, tiles spanning several classes and images
+    (2, 4, 16, 16, 32, 64, 3, 2, 1),    # stride 2, a single chunk of channels: parity classes of patches in both directions
+    (1, 3, 8, 8, 32, 32, 3, 2, 1),      # same, images of 4 x 4 positions
     (2, 3, 16, 8, 16, 32, 1, 2, 0),     # strided 1x1: three of four parity classes reach no tap
     (1, 2, 32, 32, 32, 128, 3, 1, 1),   # backward-weight with nine taps per wavefront: two column blocks, 4 dy tiles
     (1, 3, 16, 16, 64, 160, 3, 1, 1),   # same, 5 dy tiles per workgroup
@@ -112,16 +112,16 @@ CASES = [
     (2, 4, 12, 12, 20, 50, 5, 1, 0),    # LeNet's second conv: backward-data over 50 channels (8-byte gathers in fp32)
     (1, 3, 8, 8, 6, 40, 3, 1, 1),       # forward over 6 channels: 8-byte gathers, 64-wide tile with a ragged edge
     (1, 2, 16, 16, 160, 320, 3, 1, 1),  # WRN-28-10 widths: 320 outputs = 2 x 128 + 64, 160 (backward-data) = 96 + 64
-    (2, 2, 32, 32, 64, 96, 3, 2, 1),    # stride-2 backward-data, four parity classes per workgroup: 2 x 2 blocks per image
-    (1, 3, 16, 32, 96, 64, 3, 2, 1),    # same, image not square, 96-wide column block
-    (1, 2, 16, 16, 160, 32, 3, 2, 1),   # same, 160 channels = 96 + a ragged second block
+    (2, 2, 32, 32, 64, 96, 3, 2, 1),    # stride-2 backward-data, four parity classes per wavefront: two tiles per image
+    (1, 3, 16, 32, 96, 64, 3, 2, 1),    # same, image not square, three column blocks
+    (1, 2, 16, 16, 160, 32, 3, 2, 1),   # same, 160 channels: five column blocks
     (2, 2, 16, 16, 16, 64, 3, 1, 1),    # patch path with half a channel chunk (the first block of the residual networks)
     (1, 2, 16, 16, 40, 48, 3, 1, 1),    # same, one full chunk and a ragged one, in both directions
     (2, 3, 6, 7, 8, 12, 5, 1, 2),       # padded 5x5 window on 6 x 7 pixels, 8 channels
     (1, 2, 8, 8, 32, 10, 2, 1, 0),      # 2x2 window, no padding
     (2, 5, 12, 12, 20, 50, 5, 1, 0),    # LeNet's second convolution: fp32 backward-data with the per-tap products in LDS
     (1, 3, 7, 9, 6, 13, 3, 1, 1),       # same path, padded 3x3 window, odd sizes (63 output pixels, 13 output channels)
-    (2, 3, 16, 16, 128, 96, 3, 2, 1),   # stride-2 forward with the input patch in LDS (128 channels or more): two 8 x 8 outputs per tile, odd batch
+    (2, 3, 16, 16, 128, 96, 3, 2, 1),   # stride-2 forward of 128 channels or more, by patches of parity classes; with a residual, the whole patch: two 8 x 8 outputs per tile, odd batch
     (1, 4, 32, 32, 136, 128, 3, 2, 1),  # same, 16 output columns (half an image per tile), a ragged channel chunk
     (1, 2, 32, 32, 128, 320, 3, 2, 1),  # same, 320 outputs = 128 + 128 + 64
     (3, 128, 1, 1, 784, 128, 1, 1, 0),  # the MLP's first layer: contraction split over the wavefronts of a workgroup

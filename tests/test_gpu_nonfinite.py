@@ -157,3 +157,64 @@ def test_small_operands_keep_their_bits(gpu, case, scale):
         for i, (name, got, ref) in enumerate(zip(names, three_products(torch, pb, case, *operands), refs)):
             err = np.linalg.norm(got - ref) / np.linalg.norm(ref)
             assert err < 1e-6, f"{name}, operand {turn} small: {err:.1e}"
+
+
+BF16 = [
+    # bf16 layers with patches loaded straight into LDS; input gradients read the weights as they lie
+    (2, 3, 16, 16, 32, 64, 3, 2, 1),     # stride 2: parity classes in both directions, one chunk forward
+    (1, 3, 15, 14, 136, 40, 3, 2, 1),    # ragged chunks, an odd side
+    (1, 2, 28, 28, 128, 96, 3, 2, 1),    # rows of 14
+    (2, 3, 16, 16, 32, 64, 3, 1, 1),
+    (1, 4, 9, 14, 40, 72, 3, 1, 1),      # images that end inside a tile
+    (1, 3, 16, 16, 32, 96, 5, 1, 2),
+]
+
+
+@pytest.mark.parametrize("case", BF16)
+def test_infinities_reach_the_pixels_that_a_window_covers(gpu, case):
+    torch, pb = gpu
+    stride, pad = case[7:]
+    xs, ws, ys = shapes(case)
+    rng = np.random.default_rng(9)
+    x, w, dy = (tk.to_bf16_grid(rng.standard_normal(s)) for s in (xs, ws, ys))
+    w /= 16
+    for a in (x, dy):  # corners of the first and last image, an odd and an even place between
+        a[0, 0, 0, 0, 1], a[0, 0, -1, -1, 2], a[0, -1, 3, 4, 5], a[0, -1, -1, 0, 7] = np.inf, -np.inf, np.nan, np.inf
+    with np.errstate(invalid="ignore"):
+        ref, rdx, _ = tk.oracle_conv(x[0], w[0], None, None, False, stride, pad, dy[0])
+    desc = pb.parle_conv_desc(1, *case)
+    dx_, dw_, ddy = (tk.upload(torch, a, 1) for a in (x, w, dy))
+    y, gx = (torch.zeros(s, dtype=torch.bfloat16, device="cuda") for s in (ys, xs))
+    pb.parle_k_conv_forward(desc, dx_, dw_, None, None, 0, y)
+    pb.parle_k_conv_backward_data(desc, ddy, dw_, None, 0, torch.zeros_like(dw_), gx)
+    for name, got, want in (("forward", tk.download(y[0]), ref), ("input gradient", tk.download(gx[0]), rdx)):
+        fin = np.isfinite(want)
+        assert fin.any() and not fin.all() and (np.isfinite(got) == fin).all(), f"{name}: {np.sum(np.isfinite(got) != fin)} differ in kind"
+        inf = np.isinf(want)
+        assert (got[inf] == want[inf]).all() and np.isnan(got[np.isnan(want)]).all(), name
+        tk.assert_near(name, got[fin], want[fin], *tk.tolerances(1, want[fin]))
+
+
+@pytest.mark.parametrize("side,place,taps", [(28, (0, 0), [0]), (28, (27, 27), [24]), (17, (0, 3), [0, 1, 2, 3]), (28, (27, 1), [20, 21])])
+def test_nan_in_an_image_of_a_first_layer_with_its_pool(gpu, side, place, taps):
+    """A ReLU makes zeros of the outputs that a NaN reaches; the weight gradient has NaN at the taps that read it (0 * NaN) and nowhere
+    else."""
+    torch, pb = gpu
+    from paper_1707_00424_amd import synth
+    cfg = pb.make_config(model=pb.MODEL_LENET, n_replicas=2, batch=9, in_h=side, in_w=side, in_c=1, n_classes=10, arch=(16, 12, 5 if side > 17 else 4, 24),
+                         eta_inner=0.05, eta_outer=0.1, gamma0=0.3, rho0=1.0)
+    layout = pb.parle_query_layout(cfg)
+    P = pb.Parle(cfg, np.stack([synth.init_params(layout, 3 + a, "uniform") for a in range(2)]))
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    images = torch.randn((2, 9, side, side, 1), generator=gen, device="cuda")
+    images[0, 4, place[0], place[1], 0] = float("nan")
+    labels = torch.randint(0, 10, (2, 9), generator=gen, device="cuda").int()
+    loss = torch.zeros(2, device="cuda")
+    P.parle_inner_step(images, labels, loss)
+    assert loss.isfinite().all()
+    seg = {s["name"]: P.grad[:, s["offset"]:s["offset"] + s["size"]] for s in layout}
+    nan = seg["conv1.w"].reshape(2, 16, -1).isnan()
+    want = torch.zeros_like(nan)
+    want[0, :, taps] = True
+    assert torch.equal(nan, want)
+    assert all(g.isfinite().all() for name, g in seg.items() if name != "conv1.w")

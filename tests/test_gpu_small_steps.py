@@ -12,11 +12,14 @@ CASES = [
     (3, 128, 128),   # the small workload
     (1, 1, 1),
     (1, 17, 37),     # rows of no whole vectors
-    (2, 100, 256),   # the widest that the one-kernel head takes
-    (6, 64, 260),    # beyond: the loss in a kernel of its own
+    (2, 100, 256),   # 256 features in the one-kernel head
+    (6, 64, 260),
     (1, 300, 40),    # more rows than a group's small tiles take
     (2, 257, 64),
-    (6, 128, 512),   # more tiles than two per compute unit
+    (6, 128, 512),   # the widest that the one-kernel head takes; more tiles than two per compute unit
+    (1, 64, 520),    # beyond: the loss with the softmax, both weight gradients and the update in one launch without it
+    (1, 33, 517),    # ... rows of no whole vectors
+    (3, 100, 600),   # ... the first layer's weight gradient by itself
 ]
 
 
