@@ -81,6 +81,11 @@ __global__ __launch_bounds__(kThreads) void k_softmax_train(int B, int C, const 
 //   dfeat[d] = sum_c dlogits[c] * W[c][d]   (zero where MASK and feat[d] <= 0: the ReLU in front of the layer).
 // The per-image losses go to loss_img; k_loss_mean averages them (off the chain).
 constexpr int kHeadClasses = 16;
+// fp32 heads of more features take probabilities as exp(l - max) / sum in place of exp(l - log of the sum), which rounds its argument
+// twice at the size of the logits.  Behind sums this long the one kernel was otherwise further from 64 bits than the three it
+// replaces: error of the whole gradient against theirs, logarithm / quotient, 16 MLPs of 257 to 512 features 1.019 / 0.912, 18
+// networks of LeNet's kind 1.019 / 0.716; a LeNet step takes 264 us with either.  Up to this width nothing moved.
+constexpr int kHeadLogarithm = 256;
 constexpr int kHeadThreads = 512;  // eight wavefronts = eight images share one copy of the weights in LDS
 
 template <typename T>
@@ -98,7 +103,7 @@ __device__ __forceinline__ float as_stored<bf16_t>(float v) {
 // C only reaches lanes whose class does not exist, and those are left out.  A
 // reduce-scatter tree adds them up: at each of four steps a lane passes half of its values on and keeps the other half, so
 // 15 shuffles (and two more over the last four lanes) do what 6 x C do when every lane ends up with every sum, and lane l
-// holds the logit of class head_class(l): one exponential per lane instead of C per lane.  `scale`, `bias`: logit = sum *
+// holds the logit of class head_class(l): one exponential per lane (two without QUOTIENT) instead of C per lane.  `scale`, `bias`: logit = sum *
 // scale + bias of the lane's class.  Returns the lane's class's dlogits as stored in T; loss and all else as in
 // k_softmax_train.  The chain of one image's shuffles and exponentials bounds the kernel (48 workgroups at 3 x 128 images):
 // k_fc_head with 128 features and 10 classes 11.5 -> 9.8 microseconds, the MLP step 32.4 -> 30.1.
@@ -106,7 +111,7 @@ __device__ __forceinline__ float as_stored<bf16_t>(float v) {
 __device__ __forceinline__ int head_class(int lane) { return lane >> 2; }
 __device__ __forceinline__ int head_lane(int c) { return (c & (kHeadClasses - 1)) << 2; }
 
-template <typename T>
+template <typename T, bool QUOTIENT = false>
 __device__ __forceinline__ float head_softmax(float (&v)[kHeadClasses], int C, float scale, float bias, int y, float invB,
                                               int lane, float &loss) {
 #pragma unroll
@@ -129,17 +134,18 @@ __device__ __forceinline__ float head_softmax(float (&v)[kHeadClasses], int C, f
   float mx = live ? l : -INFINITY;
 #pragma unroll
   for (int off = 4; off < PARLE_WAVE; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off, PARLE_WAVE));
-  float se = live ? expf(l - mx) : 0.f;
+  const float ex = live ? expf(l - mx) : 0.f;
+  float se = ex;
 #pragma unroll
   for (int off = 4; off < PARLE_WAVE; off <<= 1) se += __shfl_xor(se, off, PARLE_WAVE);
   const float lse = logf(se) + mx;
   const float ly = __shfl(l, head_lane(y), PARLE_WAVE);
   loss = lse - ((unsigned)y < (unsigned)C ? ly : 0.f);  // a label that names no class has no logit to take off
-  const float p = expf(l - lse);
+  const float p = QUOTIENT ? ex / se : expf(l - lse);
   return live ? as_stored<T>((p - (cls == y ? 1.f : 0.f)) * invB) : 0.f;
 }
 
-template <typename T, bool MASK>
+template <typename T, bool MASK, bool QUOTIENT>
 __global__ __launch_bounds__(kHeadThreads) void k_fc_head(int B, int D, int C, const T *__restrict__ feat, long long feat_rs,
                                                       const T *__restrict__ w, long long w_rs,
                                                       const float *__restrict__ bias, long long bias_rs,
@@ -192,7 +198,7 @@ __global__ __launch_bounds__(kHeadThreads) void k_fc_head(int B, int D, int C, c
     }
   }
   float loss;
-  const float g = head_softmax<T>(lg, C, 1.f, bv, y, 1.0f / (float)B, lane, loss);
+  const float g = head_softmax<T, QUOTIENT>(lg, C, 1.f, bv, y, 1.0f / (float)B, lane, loss);
   if ((lane & 3) == 0 && cls < C) stf<T>(dl + rep * dl_rs, (long long)b * C + cls, g);
   if (lane == 0) loss_img[(long long)rep * B + b] = loss;
   float gc[kHeadClasses];  // every class's dlogits, the same in all lanes
@@ -1217,13 +1223,15 @@ hipError_t launch_fc_head(hipStream_t st, int dtype, int n, int B, int D, int C,
   if (!fc_head_applicable(C, D) || B < 1) return hipErrorInvalidValue;
   const dim3 grid((B + kHeadThreads / PARLE_WAVE - 1) / (kHeadThreads / PARLE_WAVE), n);
   const size_t lds = (size_t)(C + kHeadThreads / PARLE_WAVE) * D * sizeof(float);
-#define HEAD(T, MASK)                                                                                                  \
-  hipLaunchKernelGGL((k_fc_head<T, MASK>), grid, dim3(kHeadThreads), lds, st, B, D, C, (const T *)feat, feat_rs, (const T *)w, \
+#define HEAD(T, MASK, QUOTIENT)                                                                                        \
+  hipLaunchKernelGGL((k_fc_head<T, MASK, QUOTIENT>), grid, dim3(kHeadThreads), lds, st, B, D, C, (const T *)feat, feat_rs, (const T *)w, \
                      w_rs, bias, bias_rs, labels, loss_img, (T *)dlogits, dl_rs, (T *)dfeat, dfeat_rs)
-  if (dtype == 0) {
-    if (mask) HEAD(float, true); else HEAD(float, false);
+  if (dtype == 0 && D > kHeadLogarithm) {
+    if (mask) HEAD(float, true, true); else HEAD(float, false, true);
+  } else if (dtype == 0) {
+    if (mask) HEAD(float, true, false); else HEAD(float, false, false);
   } else {
-    if (mask) HEAD(bf16_t, true); else HEAD(bf16_t, false);
+    if (mask) HEAD(bf16_t, true, false); else HEAD(bf16_t, false, false);
   }
 #undef HEAD
   return hipGetLastError();

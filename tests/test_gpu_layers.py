@@ -297,6 +297,34 @@ def test_classifier_head(gpu, n, B, D, C, mask, dtype):
         near("dfeat", down(df[r]), pre2.g, dtype)
 
 
+@pytest.mark.parametrize("D,C,mask", [(257, 10, 1), (320, 2, 0), (500, 10, 1), (512, 16, 0)])
+def test_wide_head_far_from_zero(gpu, D, C, mask):
+    """Logits that are sums without rounding (one feature per image, weights in steps of 1/8) and all about 64: what is left is the
+    softmax, whose probabilities do not depend on where the logits lie."""
+    torch, pb = gpu
+    n, B = 2, 64
+    rng = np.random.default_rng(D + C)
+    feat = np.zeros((n, B, D), np.float32)
+    at = rng.integers(0, D, (n, B))
+    for r in range(n):
+        feat[r, np.arange(B), at[r]] = 1
+    w = (rng.integers(-32, 33, (n, C, D)) / 8).astype(np.float32)
+    labels = rng.integers(0, C, (n, B)).astype(np.int32)
+    loss_img, loss = torch.zeros((n, B), device="cuda"), torch.zeros(n, device="cuda")
+    dl, df = torch.zeros((n, B, C), device="cuda"), torch.zeros((n, B, D), device="cuda")
+    pb.parle_k_fc_head(0, up(torch, feat, 0), up(torch, w, 0), torch.full((n, C), 64.0, device="cuda"),
+                       torch.as_tensor(labels).cuda(), mask, loss_img, loss, dl, df)
+    for r in range(n):
+        logits = w[r][:, at[r]].T.astype(np.float64)
+        p = np.exp(logits - logits.max(1, keepdims=True))
+        p /= p.sum(1, keepdims=True)
+        want = p - (np.arange(C) == labels[r][:, None])
+        # two exponentials' worth of 2 ulp (the term and the sum), four additions in a tree, a division and the difference; B is a
+        # power of two.  The logarithm of the sum, rounded at 64, alone moves p by 2^-18 = 64 of these units
+        worst = (np.abs(down(dl[r]) * B - want) - 2.0 ** -24 * (16 * p + np.abs(want))).max()
+        assert worst <= 0, worst
+
+
 @pytest.mark.parametrize("n,B,H,W,C", [(1, 1, 1, 1, 2), (3, 128, 8, 8, 10), (2, 9, 5, 3, 7), (2, 6, 12, 11, 16)])
 @pytest.mark.parametrize("dtype", [0, 1])
 def test_pooling_head(gpu, n, B, H, W, C, dtype):
