@@ -334,7 +334,8 @@ parle_status parle_k_conv_forward_colsums(void *hip_stream, const parle_conv_des
                                           const void *resid, void *y, double *partial, int32_t capacity,
                                           int32_t *splits_host);
 /* dx (+)= conv^T(dy, w), multiplied by (relu_mask > 0) when relu_mask (like x) is given.
- * wt_scratch: n*cout*k*k*cin elements of the tensor dtype (receives the transposed weights). */
+ * wt_scratch: n*cout*k*k*cin elements of the tensor dtype.  It receives the transposed weights where the layer's kernel
+ * reads them; most bf16 3x3 and 5x5 layers and fp32 fully connected ones read w as it lies and leave it unwritten. */
 parle_status parle_k_conv_backward_data(void *hip_stream, const parle_conv_desc *desc, const void *dy, const void *w,
                                         const void *relu_mask, int32_t accumulate, void *wt_scratch, void *dx);
 /* dw [n][cout, k, k, cin] fp32 = sum over batch and positions of dy (x) x.  The sum is split over

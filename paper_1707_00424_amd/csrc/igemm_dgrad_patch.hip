@@ -24,7 +24,9 @@
 //
 // LDS: patch pixels of 64 bytes (32 channels), their four vectors exchanged by the pixel's position as in igemm_patch.hip;
 // weight rows (tap, output channel) of 32 input channels, 64 bytes: a transposing read takes 4 rows x 64 bytes, all banks.
-// The order of an output's sums (channel chunk, window row, window column) is that of the kernel before.
+// The order of an output's sums (channel chunk, window row, window column) is that of igemm_dgrad2.hip.  A gather kernel, which ran
+// the other sizes, takes all channels of a tap before the next tap: there 3 to 11 in 100 000 bf16 results round the other way
+// than with it; the error against 64 bits is the same to six digits.
 #include "igemm_halo.h"
 #include <type_traits>
 
