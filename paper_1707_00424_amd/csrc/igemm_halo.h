@@ -32,6 +32,6 @@ bool make_halo_geom(const ConvGeom &g, HaloGeom &hg, bool half);
 // Stride-1 3x3 and 5x5 layers with operands loaded straight into LDS (igemm_patch.hip).
 bool conv_patch_applicable(int replicas, const ConvGeom &g, const GemmIO &io);
 hipError_t launch_conv_patch(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io);
-// Stride-2 3x3 layers likewise (igemm_patch_s2.hip): same results, bit for bit, as the kernels that run the other ones.
+// Stride-2 3x3 layers likewise (igemm_patch_s2.hip): same results, bit for bit, as the kernels that run them with a residual or column sums.
 bool patch_s2_applicable(int dtype, int replicas, const ConvGeom &g, const GemmIO &io, bool out_f32);
 hipError_t launch_patch_s2(hipStream_t st, int replicas, const ConvGeom &g, const GemmIO &io);

@@ -164,6 +164,7 @@ BF16 = [
     (2, 3, 16, 16, 32, 64, 3, 2, 1),     # stride 2: parity classes in both directions, one chunk forward
     (1, 3, 15, 14, 136, 40, 3, 2, 1),    # ragged chunks, an odd side
     (1, 2, 28, 28, 128, 96, 3, 2, 1),    # rows of 14
+    (1, 3, 15, 14, 40, 24, 3, 2, 1),     # forward tap by tap, a last step of 8 values
     (2, 3, 16, 16, 32, 64, 3, 1, 1),
     (1, 4, 9, 14, 40, 72, 3, 1, 1),      # images that end inside a tile
     (1, 3, 16, 16, 32, 96, 5, 1, 2),

@@ -1,5 +1,5 @@
-"""Stride-2 3x3 layers with patches of parity classes in LDS: every tile shape of that kernel, one tile and several per
-workgroup, ragged channel chunks and column blocks, odd image sides, images that end inside a tile, against plain products in 64
+"""Stride-2 3x3 layers loaded straight into LDS, by patches of parity classes and tap by tap: every tile shape of both kernels, one tile
+and several per workgroup, ragged channel chunks and column blocks, odd image sides, images that end inside a tile, against plain products in 64
 bits and, bit for bit, against the kernels that run these layers with a residual or with column sums; and whole evaluations against
 the same network in 64 bits with every stored value rounded."""
 import pytest
@@ -11,11 +11,11 @@ pytestmark = pytest.mark.gpu
 gpu = te.gpu
 
 CASES = [
-    # widths of the two groups, image sides, images: tile shapes (outputs x channels) of the two stride-2 layers where they are the
-    # kernel's (inputs of at most 32 channels, or of 128 and more)
-    (64, 128, 32, 32, 3),     # the second: 128 x 64
-    (24, 40, 32, 32, 21),     # the first: ragged chunks and column blocks
-    (96, 192, 32, 32, 300),   # the second: 128 x 96, two images per tile
+    # widths of the two groups, image sides, images: tile shapes (outputs x channels) of the two stride-2 layers; inputs of 33 to 127
+    # channels tap by tap
+    (64, 128, 32, 32, 3),     # tap by tap; 128 x 64
+    (24, 40, 32, 32, 21),     # ragged chunks and column blocks; tap by tap, steps across taps
+    (96, 192, 32, 32, 300),   # tap by tap, 128 x 96; 128 x 96, two images per tile
     (160, 32, 32, 32, 300),   # 256 x 64 with several tiles in some workgroups; 128 x 64
     (16, 640, 32, 32, 130),   # 128 x 64; 256 x 64 on small images, four per tile
     (136, 72, 28, 28, 700),   # 256 x 64 on rows of 14, images across tiles
@@ -76,7 +76,19 @@ LAYERS = [
     (1, 600, 28, 28, 136, 96),  # 256 x 96, rows of 14
     (7, 21, 24, 40, 128, 192),  # 256 x 96, two column blocks
     (2, 20, 16, 16, 256, 160),  # 128 x 64, eight chunks
-    (2, 20, 32, 32, 96, 96),    # not the kernel's: three chunks, which a gather kernel adds tap by tap
+    # tap by tap
+    (2, 20, 32, 32, 96, 96),    # 128 x 64, 80 tiles in two column blocks
+    (1, 1, 1, 1, 40, 8),        # one output, one tap inside the image
+    (3, 2, 2, 3, 48, 24),       # windows wider than the image; ragged everything
+    (2, 7, 7, 9, 40, 136),      # steps that span two taps, 8 values in the last one
+    (2, 5, 15, 12, 120, 72),    # ... 24 values
+    (2, 33, 7, 7, 256, 136),    # channels beyond 127 on a size of no full patches
+    (1, 3, 130, 6, 64, 32),     # rows wider and columns narrower than a tile
+    (3, 67, 32, 32, 48, 96),    # 128 x 96
+    (2, 130, 16, 16, 104, 256), # 128 x 128, two column blocks
+    (2, 1001, 15, 15, 40, 64),  # 256 x 64, the last tile of a replica a quarter full
+    (3, 131, 32, 32, 40, 136),  # 256 x 96, two column blocks, the second ragged
+    (5, 103, 32, 32, 64, 128),  # 256 x 128
 ]
 
 
