@@ -17,7 +17,7 @@
 // 16 x 16 36 -> 27, 128 -> 256 29 -> 25, 320 -> 640 123 -> 110, 160 -> 320 on 32 x 32 143 -> 113, 32 -> 64 15.5 -> 12.8, 3 x 64
 // images of 128 -> 64 24 -> 19.  A step of 8 products asks for 2 to 3 KB per
 // wavefront, and every barrier waits for the last of four.  (Class after class, four taps of odd-odd pixels first, needs no second
-// load of OE and was 0 to 10 % faster, but is another order of sums.)
+// load of OE and was 0 to 15 % faster, but is another order of sums.)
 #include "igemm_halo.h"
 #include <type_traits>
 
